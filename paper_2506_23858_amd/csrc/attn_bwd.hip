@@ -90,158 +90,6 @@ __global__ __launch_bounds__(VMOBA_MAX_BLOCKS) void key_run_order_kernel(const i
     }
 }
 
-__device__ __forceinline__ float load_elem(const char* p, int d) { return reinterpret_cast<const float*>(p)[d]; }
-
-// ---------------------------------------------------------------------------------------------
-// Plain FMA dQ tile kernel (float32 tensors): one wavefront per 64 gathered queries of one key block, lane = query.
-template <int D>
-__global__ __launch_bounds__(64) void attn_bwd_dq_simple_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
-    const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int4* __restrict__ tile_desc, int tiles_per_head, float* __restrict__ dQpart, int Hh, int S, int nb, long long cap, float scale_log2,
-    const int* __restrict__ kv_rows) {
-    constexpr int KC = 32;
-    constexpr int ES = 4;
-    __shared__ float sK[KC][D];
-    __shared__ float sV[KC][D];
-    const int bh = blockIdx.y, b = bh / Hh, h = bh % Hh;
-    TileCoord tc;
-    if (!find_tile(tile_desc, tiles_per_head, bh, blockIdx.x, tc)) return;
-    const int lane = threadIdx.x;
-    const long long seg = (long long)bh * cap;
-    const int e = min(lane, tc.count - 1);
-    const int q = q_idx[seg + tc.list0 + tc.t0 + e];
-    float qr[D], dor[D], dq[D];
-    {
-        const char* sq = Q.ptr + ((long long)b * Q.stride_b + (long long)q * Q.stride_s + (long long)h * Q.stride_h) * ES;
-        const char* sd = dO.ptr + ((long long)b * dO.stride_b + (long long)q * dO.stride_s + (long long)h * dO.stride_h) * ES;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            qr[d] = load_elem(sq, d);
-            dor[d] = load_elem(sd, d);
-            dq[d] = 0.f;
-        }
-    }
-    const float lse2 = LSE[(long long)bh * S + q] * LOG2E;
-    const float dl = delta[(long long)bh * S + q];
-    const char* kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * ES;
-    const char* vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * ES;
-    for (int c0 = 0; c0 < tc.L; c0 += KC) {
-        const int kc = min(KC, tc.L - c0);
-        __syncthreads();
-        for (int i = lane; i < kc * D; i += 64) {
-            const int r = i / D, d = i % D;
-            const int pos = tc.k0 + c0 + r;
-            const long long row = kv_rows ? kv_rows[pos] : pos;       // key position -> row of K and V
-            sK[r][d] = load_elem(kbase + row * K.stride_s * ES, d);
-            sV[r][d] = load_elem(vbase + row * V.stride_s * ES, d);
-        }
-        __syncthreads();
-        for (int r = 0; r < kc; ++r) {
-            float s = 0.f, dp = 0.f;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                s = fmaf(qr[d], sK[r][d], s);
-                dp = fmaf(dor[d], sV[r][d], dp);
-            }
-            const float p = exp2f(s * scale_log2 - lse2);
-            const float ds = p * (dp - dl);
-#pragma unroll
-            for (int d = 0; d < D; ++d) dq[d] = fmaf(ds, sK[r][d], dq[d]);
-        }
-    }
-    if (lane < tc.count) {
-        float* dst = dQpart + (seg + tc.list0 + tc.t0 + lane) * D;
-#pragma unroll
-        for (int d = 0; d < D; ++d) dst[d] = dq[d];
-    }
-}
-
-// Plain FMA dK/dV kernel (float32 tensors): one wavefront per run of 64 keys of one block, lane = key;
-// walks the block's whole query list through LDS.
-template <int D>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_simple_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
-    const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int* __restrict__ kb_start, const int* __restrict__ kb_order, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int nb, long long cap,
-    float scale_log2, float scale, const int* __restrict__ kv_rows) {
-    constexpr int KPW = 64, QC = 16;
-    constexpr int ES = 4;
-    __shared__ float sQ[QC][D];
-    __shared__ float sdO[QC][D];
-    __shared__ float sL[QC], sDl[QC];
-    const int bh = blockIdx.y, b = bh / Hh, h = bh % Hh;
-    const int* ks = kb_start + (long long)bh * (nb + 1);
-    if ((int)blockIdx.x >= ks[nb]) return;
-    int lo = 0, hi = nb;
-    while (hi - lo > 1) { int mid = (lo + hi) >> 1; if (ks[mid] <= (int)blockIdx.x) lo = mid; else hi = mid; }
-    const int j = kb_order[(long long)bh * nb + lo];
-    const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
-    const int kk0 = ((int)blockIdx.x - ks[lo]) * KPW;            // first key of this run inside the block
-    const int lane = threadIdx.x;
-    const bool live = kk0 + lane < L;
-    const int krow = k0 + min(kk0 + lane, L - 1);
-    const long long seg = (long long)bh * cap;
-    const int list0 = blk_ptr[(long long)bh * (nb + 1) + j];
-    const int cnt = blk_ptr[(long long)bh * (nb + 1) + j + 1] - list0;
-    float kr[D], vr[D], dk[D], dv[D];
-    {
-        const long long kin = kv_rows ? kv_rows[krow] : krow;         // row of K and V that holds this key
-        const char* sk = K.ptr + ((long long)b * K.stride_b + kin * K.stride_s + (long long)h * K.stride_h) * ES;
-        const char* sv = V.ptr + ((long long)b * V.stride_b + kin * V.stride_s + (long long)h * V.stride_h) * ES;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            kr[d] = load_elem(sk, d);
-            vr[d] = load_elem(sv, d);
-            dk[d] = 0.f;
-            dv[d] = 0.f;
-        }
-    }
-    const char* qbase = Q.ptr + ((long long)b * Q.stride_b + (long long)h * Q.stride_h) * ES;
-    const char* dobase = dO.ptr + ((long long)b * dO.stride_b + (long long)h * dO.stride_h) * ES;
-    for (int c0 = 0; c0 < cnt; c0 += QC) {
-        const int qc = min(QC, cnt - c0);
-        __syncthreads();
-        for (int i = lane; i < qc * D; i += 64) {
-            const int r = i / D, d = i % D;
-            const long long q = q_idx[seg + list0 + c0 + r];
-            sQ[r][d] = load_elem(qbase + q * Q.stride_s * ES, d);
-            sdO[r][d] = load_elem(dobase + q * dO.stride_s * ES, d);
-        }
-        if (lane < qc) {
-            const long long q = q_idx[seg + list0 + c0 + lane];
-            sL[lane] = LSE[(long long)bh * S + q] * LOG2E;
-            sDl[lane] = delta[(long long)bh * S + q];
-        }
-        __syncthreads();
-        for (int r = 0; r < qc; ++r) {
-            float s = 0.f, dp = 0.f;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                s = fmaf(sQ[r][d], kr[d], s);
-                dp = fmaf(sdO[r][d], vr[d], dp);
-            }
-            const float p = exp2f(s * scale_log2 - sL[r]);
-            const float ds = p * (dp - sDl[r]);
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                dv[d] = fmaf(p, sdO[r][d], dv[d]);
-                dk[d] = fmaf(ds, sQ[r][d], dk[d]);
-            }
-        }
-    }
-    if (live) {
-        const int kout = rows ? rows[krow] : krow;
-        char* pk = dK.ptr + ((long long)b * dK.stride_b + (long long)kout * dK.stride_s + (long long)h * dK.stride_h) * ES;
-        char* pv = dV.ptr + ((long long)b * dV.stride_b + (long long)kout * dV.stride_s + (long long)h * dV.stride_h) * ES;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            reinterpret_cast<float*>(pk)[d] = dk[d] * scale;
-            reinterpret_cast<float*>(pv)[d] = dv[d];
-        }
-    }
-}
-
 // Load through a wave-uniform base and a 32-bit byte offset per lane (the address needs no 64-bit vector arithmetic).
 template <typename T>
 __device__ __forceinline__ T load_at(const void* base, uint32_t byte_off) {
@@ -1148,7 +996,7 @@ struct BwdWs {
     float* dQpart;     // [BH * cap][D], in the tensors' type
     float* delta;      // [BH][S]
     int* tile_start;   // [BH][257]
-    int4* tile_desc;   // [BH][tiles_per_head], or the flat list of all heads' tiles
+    int4* tile_desc;   // the flat list of all heads' tiles
     int* head_base;    // [BH + 1]
     int* kb_start;     // [BH][257]
     int* kb_order;     // [BH][256]
@@ -1209,9 +1057,8 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     const TensorView dQv = make_view(dQ), dKv = make_view(dK), dVv = make_view(dV);
     TensorView dOv = make_view(dO);
     const float scale_log2 = softmax_scale * LOG2E;
-    const bool simple = !bf16;              // float32 tensors take the plain FMA kernels
-    // the tile kernels form the byte offset of a row of Q', K', V' or dO with one 24-bit multiply and 32-bit adds
-    if (!simple) {
+    // the bfloat16 kernels form the byte offset of a row of Q', K', V' or dO with one 24-bit multiply and 32-bit adds
+    if (bf16) {
         const int64_t do_stride = rows ? D : dO->stride_s;          // dO is read from its block-order copy when `rows` is given
         const int64_t strides[4] = {Qp->stride_s, Kp->stride_s, Vp->stride_s, do_stride};
         if (S >= (1 << 24)) return VMOBA_ERR_UNSUPPORTED;
@@ -1236,29 +1083,20 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         dOv.stride_s = D;
     }
     // ---- dQ
-    const int TM = simple ? 64 : 128;
+    const int TM = 128;
     tile_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(blk_ptr, ws.tile_start, ws.head_base, BH, n_blocks, TM);
     VMOBA_CHECK_LAUNCH();
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
-    if (simple) {
-        tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-            ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
-    } else {
-        flat_tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-            ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
-    }
+    flat_tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
+        ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
     VMOBA_CHECK_LAUNCH();
     {
         VMOBA_PROFILE_BEGIN(1, st);
-        if (simple) {
-            dim3 grid((unsigned)max_tiles, (unsigned)BH);
-#define DQ_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, (int)max_tiles, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
-            if (D == 128) attn_bwd_dq_simple_kernel<128><<<grid, dim3(64), 0, st>>>(DQ_ARGS);
-            else attn_bwd_dq_simple_kernel<64><<<grid, dim3(64), 0, st>>>(DQ_ARGS);
-#undef DQ_ARGS
+        const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);     // one workgroup per tile
+        if (!bf16) {
+            launch_dq_tiles_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, q_idx, ws.tile_desc, ws.head_base, BH, ws.dQpart, Hh, (int)S,
+                                (long long)nnz_capacity, scale_log2, kv_rows);
         } else {
-            // one workgroup per entry of the flat tile list; the bound on the list length is a multiple of 8
-            const dim3 grid((unsigned)std::min<int64_t>((int64_t)BH * max_tiles, ((nnz_capacity / TM + n_blocks) * (int64_t)BH + 15) / 8 * 8));
 #define DQ_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, ws.head_base, BH, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
             if (D == 128) attn_bwd_dq_mfma_kernel<128><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
             else attn_bwd_dq_mfma_kernel<64><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
@@ -1266,7 +1104,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         }
         VMOBA_PROFILE_END(1, st);
         VMOBA_CHECK_LAUNCH();
-        const int qpw = 256 / (D / (bf16 ? 8 : 4));     // partials: bfloat16 from the MFMA tile kernel, float32 otherwise
+        const int qpw = 256 / (D / (bf16 ? 8 : 4));     // partials in the tensors' type
         dim3 mgrid((unsigned)ceil_div64(S, qpw), (unsigned)BH);
 #define MG_ARGS ws.dQpart, row_ptr, pair_pos, dQv, rows, Hh, (int)S, (long long)nnz_capacity, softmax_scale
         if (bf16 && D == 128) dq_merge_kernel<true, 128><<<mgrid, dim3(256), 0, st>>>(MG_ARGS);
@@ -1278,11 +1116,11 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     }
     // ---- dK, dV
     {
-        const int KPW = simple ? 64 : 128;      // keys per workgroup
-        key_run_order_kernel<<<dim3(BH), dim3(VMOBA_MAX_BLOCKS), 0, st>>>(blk_off, blk_ptr, ws.kb_start, ws.kb_order, n_blocks, KPW, simple ? 0 : 32);
+        const int KPW = bf16 ? 128 : 64;        // keys per workgroup
+        key_run_order_kernel<<<dim3(BH), dim3(VMOBA_MAX_BLOCKS), 0, st>>>(blk_off, blk_ptr, ws.kb_start, ws.kb_order, n_blocks, KPW, bf16 ? 32 : 0);
         VMOBA_CHECK_LAUNCH();
         // a multiple of 8 so that (workgroup id % 8) is the same for every head; + 8 for the per-XCD rounding
-        dim3 grid((unsigned)((S / KPW + n_blocks + 7) / 8 * 8 + 8 + (simple ? 0 : n_blocks)), (unsigned)BH);
+        dim3 grid((unsigned)((S / KPW + n_blocks + 7) / 8 * 8 + 8 + (bf16 ? n_blocks : 0)), (unsigned)BH);
         // slots of the matrix-core kernel in groups of one block's runs (the usual block: S / n_blocks keys, a last run of at
         // most 32 keys goes to the tail workgroups)
         const int64_t usual = S / n_blocks;
@@ -1291,9 +1129,8 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         VMOBA_PROFILE_BEGIN(2, st);
         const int32_t* krows = key_rows ? key_rows : rows;      // row map of dK and dV
 #define DKV_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
-        if (simple) {
-            if (D == 128) attn_bwd_dkv_simple_kernel<128><<<grid, dim3(64), 0, st>>>(DKV_ARGS);
-            else attn_bwd_dkv_simple_kernel<64><<<grid, dim3(64), 0, st>>>(DKV_ARGS);
+        if (!bf16) {
+            launch_dkv_f32(D, grid, st, DKV_ARGS);
         } else {
             const dim3 hgrid((unsigned)(ceil_div64((int64_t)BH * slots, 8) * 8 + 7 * group));   // see the kernel
             if (D == 128) attn_bwd_dkv_kernel<128><<<hgrid, dim3(256), 0, st>>>(DKV_ARGS, BH, slots, group);

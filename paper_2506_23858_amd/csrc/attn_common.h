@@ -72,29 +72,10 @@ struct TileCoord {
     int k0, L;    // first key position and number of keys of the tile's key block
 };
 
-// Tile descriptors: one int4 {first list entry, count, k0, L} per (head, tile), written by
-// tile_desc_kernel so that a tile kernel learns its work with a single 16-byte load instead of a
-// binary search over dependent loads.  count = 0 marks a tile that does not exist.
-__device__ __forceinline__ bool find_tile(const int4* __restrict__ tile_desc, int tiles_per_head, int bh, int tile,
-                                          TileCoord& tc) {
-    const int4 d = tile_desc[(long long)bh * tiles_per_head + tile];
-    if (d.y <= 0) return false;
-    tc.list0 = d.x;
-    tc.t0 = 0;
-    tc.count = d.y;
-    tc.k0 = d.z;
-    tc.L = d.w;
-    return true;
-}
-
 // Tile plan (defined in attn_fwd.hip): tile_start[bh][j] = tiles of all (head, block) pairs before (bh, j) in the call's
 // flat list, tile_start[bh][nb] = first tile of the next head, head_base[bh] = tile_start[bh][0], head_base[BH] = total.
 __global__ __launch_bounds__(1024) void tile_plan_kernel(const int* __restrict__ blk_ptr, int* __restrict__ tile_start,
                                                          int* __restrict__ head_base, int BH, int nb, int TM);
-// Descriptor of every tile id below tiles_per_head of a head (one thread per id; ids past the head's last tile get count 0).
-__global__ __launch_bounds__(256) void tile_desc_kernel(const int* __restrict__ tile_start, const int* __restrict__ blk_ptr,
-                                                        const int* __restrict__ blk_off, int4* __restrict__ tile_desc,
-                                                        int nb, int TM, int tiles_per_head);
 
 inline __device__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -102,6 +83,22 @@ inline __device__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 __global__ __launch_bounds__(256) void flat_tile_desc_kernel(const int* __restrict__ tile_start, const int* __restrict__ blk_ptr,
                                                              const int* __restrict__ blk_off, int4* __restrict__ flat_desc,
                                                              int nb, int TM, int tiles_per_head);
+// Grid of a kernel with one workgroup per entry of the flat list: a bound on its length, a multiple of 8.
+static inline dim3 flat_tile_grid(int BH, int64_t max_tiles, int64_t cap, int TM, int nb) {
+    const int64_t a = (int64_t)BH * max_tiles, b = ((cap / TM + nb) * (int64_t)BH + 15) / 8 * 8;
+    return dim3((unsigned)(a < b ? a : b));
+}
+// float32 tile kernels (attn_f32.hip)
+void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
+                          const int4* flat_desc, const int* head_base, int BH, float* Opart, float* lse_part, int Hh, long long cap,
+                          float scale_log2, const int* kv_rows);
+void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* head_base, int BH,
+                         float* dQpart, int Hh, int S, long long cap, float scale_log2, const int* kv_rows);
+void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+                    const float* LSE, const float* delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,
+                    const int* kb_order, const TensorView& dK, const TensorView& dV, const int* rows, int Hh, int S, int nb, long long cap,
+                    float scale_log2, float scale, const int* kv_rows);
 // Compute units of the current device (queried once).
 int vmoba_num_cus();
 

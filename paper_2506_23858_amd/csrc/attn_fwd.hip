@@ -5,8 +5,8 @@
 // block j and runs flash-attention (online soft-max) over the L_j keys of that block alone,
 // writing a normalised partial output and its log-sum-exp per (query, block) pair.  (2) Merge
 // kernel, query-major: the partials of a query's selected blocks are combined with weights
-// exp(lse_pair - LSE).  bfloat16 inputs use the 32x32x16 bf16 MFMA; float32 inputs use a plain
-// FMA kernel of the same structure.
+// exp(lse_pair - LSE).  bfloat16 inputs use the 32x32x16 bf16 MFMA; the tile kernel for float32
+// inputs is in attn_f32.hip.
 #include "attn_common.h"
 
 #include <algorithm>
@@ -61,32 +61,6 @@ __global__ __launch_bounds__(1024) void tile_plan_kernel(const int* __restrict__
     }
 }
 
-// Per-head tile descriptors of the float32 path (grid: tile id x head; ids past the head's last tile get count 0).
-__global__ __launch_bounds__(256) void tile_desc_kernel(const int* __restrict__ tile_start, const int* __restrict__ blk_ptr,
-                                                        const int* __restrict__ blk_off, int4* __restrict__ tile_desc,
-                                                        int nb, int TM, int tiles_per_head) {
-    const int bh = blockIdx.y;
-    const int tile = blockIdx.x * 256 + threadIdx.x;
-    if (tile >= tiles_per_head) return;
-    const int* ts = tile_start + (long long)bh * (nb + 1);
-    const int first = ts[0];
-    int4 d = {0, 0, 0, 0};
-    if (tile < ts[nb] - first) {
-        int lo = 0, hi = nb;           // largest j with ts[j] - first <= tile
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (ts[mid] - first <= tile) lo = mid; else hi = mid;
-        }
-        const int* bp = blk_ptr + (long long)bh * (nb + 1);
-        const int t0 = (tile - (ts[lo] - first)) * TM;
-        d.x = bp[lo] + t0;
-        d.y = min(TM, bp[lo + 1] - bp[lo] - t0);
-        d.z = blk_off[lo];
-        d.w = blk_off[lo + 1] - blk_off[lo];
-    }
-    tile_desc[(long long)bh * tiles_per_head + tile] = d;
-}
-
 // Flat tile list over all heads for the MFMA tile kernels: flat_desc[tile_start[bh][0] + tile] = {first list entry,
 // count | bh << 10, first key, block length}; one thread per (head, tile id below tiles_per_head).
 __global__ __launch_bounds__(256) void flat_tile_desc_kernel(const int* __restrict__ tile_start, const int* __restrict__ blk_ptr,
@@ -116,74 +90,6 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
-
-// ---------------------------------------------------------------------------------------------
-// Plain FMA tile kernel for float32 inputs.  One wavefront per tile of 64 gathered queries,
-// lane = query.  Keys and values of the block pass through LDS in chunks of KC rows.
-template <int D>
-__global__ __launch_bounds__(64) void attn_fwd_tile_simple_kernel(
-    TensorView Q, TensorView K, TensorView V, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr,
-    const int* __restrict__ q_idx, const int4* __restrict__ tile_desc, int tiles_per_head, float* __restrict__ Opart,
-    float* __restrict__ lse_part, int Hh, int nb, long long cap, float scale_log2, const int* __restrict__ kv_rows) {
-    constexpr int KC = 32;
-    constexpr int ES = 4;
-    __shared__ float sK[KC][D];
-    __shared__ float sV[KC][D];
-    const int bh = blockIdx.y, b = bh / Hh, h = bh % Hh;
-    TileCoord tc;
-    if (!find_tile(tile_desc, tiles_per_head, bh, blockIdx.x, tc)) return;
-    const int lane = threadIdx.x;
-    const long long seg = (long long)bh * cap;
-    const int e = min(lane, tc.count - 1);
-    const int q = q_idx[seg + tc.list0 + tc.t0 + e];
-    float qr[D], o[D];
-    {
-        const char* src = Q.ptr + ((long long)b * Q.stride_b + (long long)q * Q.stride_s + (long long)h * Q.stride_h) * ES;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            qr[d] = reinterpret_cast<const float*>(src)[d];
-            o[d] = 0.f;
-        }
-    }
-    float m = -INFINITY, l = 0.f;
-    const char* kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * ES;
-    const char* vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * ES;
-    for (int c0 = 0; c0 < tc.L; c0 += KC) {
-        const int kc = min(KC, tc.L - c0);
-        __syncthreads();
-        for (int i = lane; i < kc * D; i += 64) {
-            const int r = i / D, d = i % D;
-            const int pos = tc.k0 + c0 + r;
-            const long long row = kv_rows ? kv_rows[pos] : pos;       // key position -> row of K and V
-            const char* ks = kbase + row * K.stride_s * ES;
-            const char* vs = vbase + row * V.stride_s * ES;
-            sK[r][d] = reinterpret_cast<const float*>(ks)[d];
-            sV[r][d] = reinterpret_cast<const float*>(vs)[d];
-        }
-        __syncthreads();
-        for (int r = 0; r < kc; ++r) {
-            float a = 0.f;
-#pragma unroll
-            for (int d = 0; d < D; ++d) a = fmaf(qr[d], sK[r][d], a);
-            a *= scale_log2;
-            const float mc = fmaxf(m, a);
-            const float alpha = exp2f(m - mc);
-            const float p = exp2f(a - mc);
-            l = l * alpha + p;
-#pragma unroll
-            for (int d = 0; d < D; ++d) o[d] = fmaf(p, sV[r][d], o[d] * alpha);
-            m = mc;
-        }
-    }
-    if (lane < tc.count) {
-        const long long pair = seg + tc.list0 + tc.t0 + lane;
-        const float inv = 1.f / l;
-        float* dst = Opart + pair * D;
-#pragma unroll
-        for (int d = 0; d < D; ++d) dst[d] = o[d] * inv;
-        lse_part[pair] = (m + log2f(l)) * LN2;
-    }
-}
 
 // ---------------------------------------------------------------------------------------------
 // bf16 MFMA tile kernel.  NW wavefronts; wavefront w owns 32 gathered queries (a tile is 32 * NW list
@@ -611,7 +517,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
 // ---------------------------------------------------------------------------------------------
 // Merge: O[q] = sum_pairs exp(lse_pair - LSE[q]) * Opart[pair], LSE[q] = logsumexp(lse_pair).
 // A group of lanes per query, each owning CH consecutive channels (one 16-byte load per partial).
-// Partials have the tensors' type: bfloat16 from the MFMA tile kernel, float32 from the FMA one.
+// Partials have the tensors' type.
 // A head whose selection did not fit the lists (row_ptr[S] > cap, see vmoba_select) counts as having selected nothing.
 template <bool BF16, int D>
 __global__ __launch_bounds__(256) void attn_fwd_merge_kernel(const float* __restrict__ Opart, const float* __restrict__ lse_part,
@@ -699,7 +605,7 @@ struct FwdWs {
     float* Opart;      // [BH * cap][D], in the tensors' type
     float* lse_part;   // [BH * cap]
     int* tile_start;   // [BH][nb + 1]
-    int4* tile_desc;   // [BH][tiles_per_head], or the flat list of all heads' tiles
+    int4* tile_desc;   // the flat list of all heads' tiles
     int* head_base;    // [BH + 1]
     size_t total;
 };
@@ -766,37 +672,29 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     const bool bf16 = dt == VMOBA_BF16;
     const TensorView Qv = make_view(Qp), Kv = make_view(Kp), Vv = make_view(Vp), Ov = make_view(O);
     const float scale_log2 = softmax_scale * LOG2E;
-    const bool simple = !bf16;              // float32 tensors take the plain FMA kernels
-    // the MFMA kernel addresses the rows of one (batch, head) slice of K and V with 32-bit byte offsets
-    if (!simple && (Kp->stride_s <= 0 || Vp->stride_s <= 0 ||
-                    (uint64_t)(S + 256) * (uint64_t)Kp->stride_s * 2 >= ((uint64_t)1 << 32) ||
-                    (uint64_t)(S + 256) * (uint64_t)Vp->stride_s * 2 >= ((uint64_t)1 << 32)))
+    // the bfloat16 kernel addresses the rows of one (batch, head) slice of K and V with 32-bit byte offsets
+    if (bf16 && (Kp->stride_s <= 0 || Vp->stride_s <= 0 ||
+                 (uint64_t)(S + 256) * (uint64_t)Kp->stride_s * 2 >= ((uint64_t)1 << 32) ||
+                 (uint64_t)(S + 256) * (uint64_t)Vp->stride_s * 2 >= ((uint64_t)1 << 32)))
         return VMOBA_ERR_UNSUPPORTED;
     // with keys in place a row's byte offset is one 24-bit multiply of its row number and the row stride
-    if (!simple && kv_rows && (S >= (1 << 24) || Kp->stride_s * 2 >= (1 << 24) || Vp->stride_s * 2 >= (1 << 24)))
+    if (bf16 && kv_rows && (S >= (1 << 24) || Kp->stride_s * 2 >= (1 << 24) || Vp->stride_s * 2 >= (1 << 24)))
         return VMOBA_ERR_UNSUPPORTED;
     // bf16, D = 128: 256-query tiles, one persistent workgroup of 8 wavefronts per compute unit (a tile's K and V
-    // rows are fetched once per 256 queries); D = 64: 128-query tiles, two workgroups of 4 wavefronts per compute unit
-    const bool wide = !simple && D == 128;
-    const int TM = simple ? 64 : (wide ? 256 : 128);
+    // rows are fetched once per 256 queries); D = 64: 128-query tiles, two workgroups of 4 wavefronts per compute unit;
+    // float32: one workgroup per tile of 128 queries
+    const bool wide = bf16 && D == 128;
+    const int TM = wide ? 256 : 128;
     tile_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(blk_ptr, ws.tile_start, ws.head_base, BH, n_blocks, TM);
     VMOBA_CHECK_LAUNCH();
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
-    if (simple) {
-        tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-            ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
-    } else {
-        flat_tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-            ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
-    }
+    flat_tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
+        ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
     VMOBA_CHECK_LAUNCH();
     VMOBA_PROFILE_BEGIN(0, st);
-    if (simple) {
-        dim3 grid((unsigned)max_tiles, (unsigned)BH);
-#define TILE_ARGS Qv, Kv, Vv, blk_off, blk_ptr, q_idx, ws.tile_desc, (int)max_tiles, ws.Opart, ws.lse_part, Hh, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
-        if (D == 128) attn_fwd_tile_simple_kernel<128><<<grid, dim3(64), 0, st>>>(TILE_ARGS);
-        else attn_fwd_tile_simple_kernel<64><<<grid, dim3(64), 0, st>>>(TILE_ARGS);
-#undef TILE_ARGS
+    if (!bf16) {
+        launch_fwd_tiles_f32(D, flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks), st, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.head_base, BH,
+                             ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows);
     } else {
         const dim3 pgrid((unsigned)std::min<int64_t>((wide ? 1 : 2) * (int64_t)vmoba_num_cus(), (int64_t)BH * max_tiles));
 #define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.head_base, BH, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows
@@ -808,7 +706,7 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     }
     VMOBA_PROFILE_END(0, st);
     VMOBA_CHECK_LAUNCH();
-    const int qpw = 256 / (D / (bf16 ? 8 : 4));     // partials: bfloat16 from the MFMA tile kernel, float32 otherwise
+    const int qpw = 256 / (D / (bf16 ? 8 : 4));     // partials in the tensors' type
     dim3 mgrid((unsigned)ceil_div64(S, qpw), (unsigned)BH);
 #define MERGE_ARGS ws.Opart, ws.lse_part, row_ptr, pair_pos, Ov, LSE, out_rows, Hh, (int)S, (long long)nnz_capacity
     if (bf16 && D == 128) attn_fwd_merge_kernel<true, 128><<<mgrid, dim3(256), 0, st>>>(MERGE_ARGS);

@@ -1,0 +1,21 @@
+"""Sizes at which the tile kernels and the selection kernels can go wrong: edges of tiles, remainders, the smallest of a
+range.  Every case runs a whole layer against the CPU oracle (bounds: tests/gpu_util.py)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_23858_amd import synth
+from tests.test_gpu_parity import compare_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [2, 32, 33, 64, 65, 97, 199])
+def test_f32_matrix_kernels_at_tile_edges(chunk, D):
+    """Blocks of one key (199 + 1), of two, of one 32-key chunk, one key more, one and two 64-key runs, and lists that end inside and at the
+    end of a 64-query chunk and of a 128-query tile (200 queries, thresholds that keep a part or all of them)."""
+    grid, S = (1, 8, 25), 200
+    Q, K, V, dO = (synth.iid_normal(900 + i, (1, S, 2, D)) for i in range(4))
+    for tau, kv_in_place in ((0.6, False), (1.0, True)):
+        compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, f"f32-edges-{chunk}", kv_in_place=kv_in_place)
