@@ -1,7 +1,8 @@
 // vmoba_partition: token -> key-block rearrangement of Sec. 3.2, Eq. 1 (and its inverse).
-// Two kernels: an index kernel that writes perm / inv_perm / blk_off from the grid
-// description in closed form, and a row-copy kernel that moves 16-byte pieces of the
-// (token, head) rows between the caller's order and block order.
+// One kernel: a workgroup takes a run of block-order positions, finds their tokens -- from the grid
+// description in closed form (and then also writes its part of perm / inv_perm / blk_off), or from
+// perm -- and moves 16-byte pieces of the (token, head) rows between the caller's order and block
+// order.  (With the index arrays in a launch of their own a small call spent a third of its time there.)
 #include "common.h"
 #include <algorithm>
 
@@ -10,37 +11,33 @@ namespace {
 struct GridDesc {
     int T, H, W, bt, bh, bw;
     long long chunk;
-    int nT, nH, nW;
+    int nH, nW;
     int S, n_blocks;
 };
 
-__global__ __launch_bounds__(256) void partition_index_kernel(GridDesc g, int* __restrict__ perm,
-                                                              int* __restrict__ inv_perm,
-                                                              int* __restrict__ blk_off) {
-    int n = blockIdx.x * 256 + threadIdx.x;
-    if (n == 0) blk_off[g.n_blocks] = g.S;
-    if (n >= g.S) return;
-    int pos, j, rank;
+// Block-order position -> token (row-major index of the grid), block and rank inside the block.
+struct Place { int token, block, rank; };
+__device__ __forceinline__ Place place_of(const GridDesc& g, int p) {
+    Place r;
     if (g.chunk > 0) {
-        pos = n;
-        j = (int)(n / g.chunk);
-        rank = (int)(n - (long long)j * g.chunk);
-    } else {
-        int w = n % g.W;
-        int h = (n / g.W) % g.H;
-        int t = n / (g.W * g.H);
-        int it = t / g.bt, ih = h / g.bh, iw = w / g.bw;
-        int t0 = it * g.bt, h0 = ih * g.bh, w0 = iw * g.bw;
-        int et = min(g.bt, g.T - t0), eh = min(g.bh, g.H - h0), ew = min(g.bw, g.W - w0);
-        // tokens in all blocks that precede (it, ih, iw) in row-major block order
-        int off = t0 * g.H * g.W + et * (h0 * g.W) + et * eh * w0;
-        rank = ((t - t0) * eh + (h - h0)) * ew + (w - w0);
-        j = (it * g.nH + ih) * g.nW + iw;
-        pos = off + rank;
+        r.token = p;
+        r.block = (int)(p / g.chunk);
+        r.rank = (int)(p - (long long)r.block * g.chunk);
+        return r;
     }
-    perm[pos] = n;
-    inv_perm[n] = pos;
-    if (rank == 0) blk_off[j] = pos;
+    // positions count the slabs along T, inside a slab the strips along H, inside a strip the boxes along W; only the
+    // last of each can be thinner than the rest
+    const int it = p / (g.bt * g.H * g.W), t0 = it * g.bt, et = min(g.bt, g.T - t0);
+    p -= t0 * g.H * g.W;
+    const int ih = p / (et * g.bh * g.W), h0 = ih * g.bh, eh = min(g.bh, g.H - h0);
+    p -= et * h0 * g.W;
+    const int iw = p / (et * eh * g.bw), w0 = iw * g.bw, ew = min(g.bw, g.W - w0);
+    p -= et * eh * w0;
+    const int t = p / (eh * ew), q = p - t * (eh * ew), h = q / ew, w = q - h * ew;
+    r.token = ((t0 + t) * g.H + h0 + h) * g.W + w0 + w;
+    r.block = (it * g.nH + ih) * g.nW + iw;
+    r.rank = p;
+    return r;
 }
 
 struct CopyDesc {
@@ -49,42 +46,70 @@ struct CopyDesc {
     int n_tensors;
 };
 
-// One work item = one 16-byte piece of the INPUT row of (b, position/token, head).
-// Items are ordered (position, head, piece) with the piece fastest, so a wavefront reads
-// whole rows and, in the caller's layout, the heads of one token that lie next to each other.
-template <bool INVERSE>
-__global__ __launch_bounds__(256) void permute_rows_kernel(CopyDesc d, const int* __restrict__ perm,
-                                                           int S, int Hh, int D) {
-    const int t = blockIdx.z;
-    const int b = blockIdx.y;
+// Work items of a workgroup's positions are ordered (position, head, piece) with the 16-byte piece of the INPUT row
+// fastest, so a wavefront reads whole rows and, in the caller's layout, the heads of one token that lie next to each other.
+// BUILD: perm, inv_perm and blk_off are written (by the workgroups of the first batch element and tensor) instead of perm
+// being read.
+constexpr int MAX_POS = 256;       // positions per workgroup
+template <bool INVERSE, bool BUILD>
+__global__ __launch_bounds__(256) void permute_rows_kernel(GridDesc g, CopyDesc d, int* __restrict__ perm, int* __restrict__ inv_perm,
+                                                           int* __restrict__ blk_off, int n_pos, int Hh, int D) {
+    __shared__ int sTok[MAX_POS];
+    const int t = blockIdx.z, b = blockIdx.y, tid = threadIdx.x;
+    const int p0 = blockIdx.x * n_pos, np = min(n_pos, g.S - p0);
+    if (tid < np) {
+        const int p = p0 + tid;
+        if constexpr (BUILD) {
+            const Place pl = place_of(g, p);
+            sTok[tid] = pl.token;
+            if (b == 0 && t == 0) {
+                perm[p] = pl.token;
+                inv_perm[pl.token] = p;
+                if (pl.rank == 0) blk_off[pl.block] = p;
+                if (p == 0) blk_off[g.n_blocks] = g.S;
+            }
+        } else {
+            sTok[tid] = perm[p];
+        }
+    }
+    if (t >= d.n_tensors) return;                      // only the index arrays are wanted
+    __syncthreads();
     const int in_es = d.in_bf16[t] ? 2 : 4;
-    const int pieces = D * in_es / 16;                 // 16-byte pieces per input row
-    const long long total = (long long)S * Hh * pieces;
+    const int pieces = D * in_es / 16;                 // 16-byte pieces per input row: 8, 16 or 32
+    const int sh = __builtin_ctz(pieces);
+    const int n_items = np * Hh << sh;
     const TensorView in = d.in[t], out = d.out[t];
     const bool cvt = (!d.in_bf16[t]) && d.out_bf16[t];
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total;
-         i += (long long)gridDim.x * 256) {
-        int piece = (int)(i % pieces);
-        long long r = i / pieces;
-        int h = (int)(r % Hh);
-        int p = (int)(r / Hh);
-        int tok = perm[p];
-        int s_in = INVERSE ? p : tok;
-        int s_out = INVERSE ? tok : p;
-        const char* src = in.ptr + ((long long)b * in.stride_b + (long long)s_in * in.stride_s +
-                                    (long long)h * in.stride_h) * in_es + piece * 16;
-        u32x4_t v = *reinterpret_cast<const u32x4_t*>(src);
-        if (!cvt) {
-            char* dst = out.ptr + ((long long)b * out.stride_b + (long long)s_out * out.stride_s +
-                                   (long long)h * out.stride_h) * in_es + piece * 16;
-            *reinterpret_cast<u32x4_t*>(dst) = v;
-        } else {
-            char* dst = out.ptr + ((long long)b * out.stride_b + (long long)s_out * out.stride_s +
-                                   (long long)h * out.stride_h) * 2 + piece * 8;
-            u32x2_t w;
-            w.x = pack_bf16x2(__uint_as_float(v.x), __uint_as_float(v.y));
-            w.y = pack_bf16x2(__uint_as_float(v.z), __uint_as_float(v.w));
-            *reinterpret_cast<u32x2_t*>(dst) = w;
+    const char* in_b = in.ptr + (long long)b * in.stride_b * in_es;
+    char* out_b = out.ptr + (long long)b * out.stride_b * (cvt ? 2 : in_es);
+    const float inv_hh = 1.f / (float)Hh;
+    constexpr int U = 4;                               // loads in flight per thread
+    for (int i0 = tid; i0 < n_items; i0 += 256 * U) {
+        u32x4_t v[U];
+        char* dst[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + 256 * u, n_items - 1);
+            const int piece = i & (pieces - 1), r = i >> sh;
+            int pl = (int)((float)r * inv_hh);         // r / Hh (at most 255), one off at most
+            if (pl * Hh > r) --pl;
+            if ((pl + 1) * Hh <= r) ++pl;
+            const int h = r - pl * Hh;
+            const int tok = sTok[pl], s_in = INVERSE ? p0 + pl : tok, s_out = INVERSE ? tok : p0 + pl;
+            v[u] = *reinterpret_cast<const u32x4_t*>(in_b + ((long long)s_in * in.stride_s + (long long)h * in.stride_h) * in_es + piece * 16);
+            dst[u] = out_b + ((long long)s_out * out.stride_s + (long long)h * out.stride_h) * (cvt ? 2 : in_es) + piece * (cvt ? 8 : 16);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + 256 * u >= n_items) break;
+            if (!cvt) {
+                *reinterpret_cast<u32x4_t*>(dst[u]) = v[u];
+            } else {
+                u32x2_t w;
+                w.x = pack_bf16x2(__uint_as_float(v[u].x), __uint_as_float(v[u].y));
+                w.y = pack_bf16x2(__uint_as_float(v[u].z), __uint_as_float(v[u].w));
+                *reinterpret_cast<u32x2_t*>(dst[u]) = w;
+            }
         }
     }
 }
@@ -142,37 +167,33 @@ extern "C" int vmoba_partition(const vmoba_grid* g, int inverse, int B, int Hh, 
         cd.in_bf16[i] = in[i].dtype == VMOBA_BF16;
         cd.out_bf16[i] = out[i].dtype == VMOBA_BF16;
     }
+    if (!build_index && n_tensors == 0) return VMOBA_OK;
     hipStream_t st = (hipStream_t)stream;
-    if (build_index) {
-        GridDesc gd;
-        gd.T = g->T; gd.H = g->H; gd.W = g->W;
-        gd.bt = g->bt; gd.bh = g->bh; gd.bw = g->bw;
-        gd.chunk = g->chunk;
-        if (g->chunk > 0) {
-            gd.nT = gd.nH = gd.nW = 1;
-            gd.bt = gd.bh = gd.bw = 1;
-        } else {
-            gd.nT = (int)ceil_div64(g->T, g->bt);
-            gd.nH = (int)ceil_div64(g->H, g->bh);
-            gd.nW = (int)ceil_div64(g->W, g->bw);
-        }
-        gd.S = (int)S;
-        gd.n_blocks = nb;
-        partition_index_kernel<<<dim3((unsigned)ceil_div64(S, 256)), dim3(256), 0, st>>>(gd, perm, inv_perm, blk_off);
-        VMOBA_CHECK_LAUNCH();
+    GridDesc gd;
+    gd.T = g->T; gd.H = g->H; gd.W = g->W;
+    gd.bt = g->bt; gd.bh = g->bh; gd.bw = g->bw;
+    gd.chunk = g->chunk;
+    if (g->chunk > 0) {
+        gd.nH = gd.nW = 1;
+        gd.bt = gd.bh = gd.bw = 1;
+    } else {
+        gd.bt = std::min(g->bt, g->T); gd.bh = std::min(g->bh, g->H); gd.bw = std::min(g->bw, g->W);
+        gd.nH = (int)ceil_div64(g->H, g->bh);
+        gd.nW = (int)ceil_div64(g->W, g->bw);
     }
-    if (n_tensors > 0) {
-        int64_t items = S * Hh * (D * 4 / 16);
-        unsigned gx = (unsigned)std::min<int64_t>(ceil_div64(items, 256 * 4), 1 << 20);
-        dim3 grid(gx, (unsigned)B, (unsigned)n_tensors);
-        VMOBA_PROFILE_BEGIN(3, st);
-        if (inverse)
-            permute_rows_kernel<true><<<grid, dim3(256), 0, st>>>(cd, perm, (int)S, Hh, D);
-        else
-            permute_rows_kernel<false><<<grid, dim3(256), 0, st>>>(cd, perm, (int)S, Hh, D);
-        VMOBA_PROFILE_END(3, st);
-        VMOBA_CHECK_LAUNCH();
-    }
+    gd.S = (int)S;
+    gd.n_blocks = nb;
+    // 512 to 2048 16-byte pieces of 16 bit numbers per workgroup: few enough to spread a small call over the chip (1024
+    // workgroups), enough to pay for finding the tokens; the index arrays alone: 256 positions
+    const int64_t per_pos = (int64_t)Hh * (D / 8);
+    const int64_t spread = std::max<int64_t>(S * B * n_tensors / 1024, ceil_div64(512, per_pos));
+    const int n_pos = n_tensors == 0 ? MAX_POS : (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)MAX_POS, 2048 / per_pos, spread}));
+    const dim3 grid((unsigned)ceil_div64(S, n_pos), (unsigned)(n_tensors ? B : 1), (unsigned)std::max(n_tensors, 1));
+    VMOBA_PROFILE_BEGIN(3, st);
+    auto kfn = inverse ? permute_rows_kernel<true, false> : build_index ? permute_rows_kernel<false, true> : permute_rows_kernel<false, false>;
+    kfn<<<grid, dim3(256), 0, st>>>(gd, cd, perm, inv_perm, blk_off, n_pos, Hh, D);
+    VMOBA_PROFILE_END(3, st);
+    VMOBA_CHECK_LAUNCH();
     return VMOBA_OK;
 }
 
