@@ -3,7 +3,7 @@
 //   delta = rowsum(dO * O),  dV = A^T dO,  dP = dO V^T,  dS = A * (dP - delta),
 //   dQ = scale * dS K,       dK = scale * dS^T Q.
 //
-// Three phases.  (1) delta kernel.  (2) dQ: the forward's decomposition (tile of gathered
+// Three phases.  (1) delta (and what the other two need to know about their work).  (2) dQ: the forward's decomposition (tile of gathered
 // queries x one key block), one partial dQ per (query, block) pair, summed query-major by a
 // merge kernel.  (3) dK/dV: a workgroup owns a run of keys of one block and walks the whole
 // query list of that block, so dK and dV of its keys stay in registers and are written once --
@@ -22,14 +22,17 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 
 // ---------------------------------------------------------------------------------------------
+// What a backward call needs before its first large kernel, in one launch: workgroups with blockIdx.x below n_delta compute
+// delta, the next ones write the flat tile list of the dQ kernel (256 tile ids each), the last one of every head the key
+// runs of the dK/dV kernel.  (Four launches before; each of the small ones took about 5 us whatever its size.)
 template <bool BF16, int D>
-__global__ __launch_bounds__(256) void delta_kernel(TensorView O, TensorView dO, float* __restrict__ delta,
-                                                    const int* __restrict__ rows, char* __restrict__ dO_copy, int Hh, int S) {
+__device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView& dO, float* __restrict__ delta, const int* __restrict__ rows,
+                                           char* __restrict__ dO_copy, int bh, int Hh, int S, int slot) {
     constexpr int EPP = BF16 ? 8 : 4;
     constexpr int LPQ = D / EPP;
     constexpr int QPW = 256 / LPQ;
-    const int bh = blockIdx.y, b = bh / Hh, h = bh % Hh;
-    const int q = blockIdx.x * QPW + threadIdx.x / LPQ;
+    const int b = bh / Hh, h = bh % Hh;
+    const int q = slot * QPW + threadIdx.x / LPQ;
     const int part = threadIdx.x % LPQ;
     float acc = 0.f;
     if (q < S) {
@@ -59,35 +62,45 @@ __global__ __launch_bounds__(256) void delta_kernel(TensorView O, TensorView dO,
 // workgroup, and costs time in proportion to the length of the block's query list.  Workgroups are
 // dispatched in index order, so the blocks are numbered longest list first (a longest-processing-time
 // order: the short ones fill the tail of the launch): kb_order[r] = block at rank r,
-// kb_start[r] = number of runs of the blocks at ranks 0..r-1.  One workgroup per head.
-// A last run of at most tail_max keys is not counted: the tail kernel takes those keys.
-__global__ __launch_bounds__(VMOBA_MAX_BLOCKS) void key_run_order_kernel(const int* __restrict__ blk_off, const int* __restrict__ blk_ptr,
-                                                                         int* __restrict__ kb_start, int* __restrict__ kb_order, int nb,
-                                                                         int KPW, int tail_max) {
-    __shared__ int sCnt[VMOBA_MAX_BLOCKS];
-    __shared__ int sRuns[VMOBA_MAX_BLOCKS];
-    const int bh = blockIdx.x, j = threadIdx.x;          // one thread per block
+// kb_start[r] = number of runs of the blocks at ranks 0..r-1.
+// A last run of at most tail_max keys is not counted: the tail body takes those keys.
+struct KeyRunLds { int cnt[VMOBA_MAX_BLOCKS]; int runs[VMOBA_MAX_BLOCKS]; int wave[4]; };
+__device__ __forceinline__ void write_key_runs(KeyRunLds& lds, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr,
+                                               int* __restrict__ kb_start, int* __restrict__ kb_order, int bh, int nb, int KPW, int tail_max) {
+    const int t = threadIdx.x;
     const int* bp = blk_ptr + (long long)bh * (nb + 1);
-    const int cnt = j < nb ? bp[j + 1] - bp[j] : -1;
-    if (j < nb) sCnt[j] = cnt;
+    for (int j = t; j < nb; j += 256) lds.cnt[j] = bp[j + 1] - bp[j];
     __syncthreads();
-    if (j < nb) {
+    for (int j = t; j < nb; j += 256) {
+        const int cnt = lds.cnt[j];
         int rank = 0;
-        for (int i = 0; i < nb; ++i) rank += (sCnt[i] > cnt || (sCnt[i] == cnt && i < j)) ? 1 : 0;
+        for (int i = 0; i < nb; ++i) rank += (lds.cnt[i] > cnt || (lds.cnt[i] == cnt && i < j)) ? 1 : 0;
         kb_order[(long long)bh * nb + rank] = j;
         const int L = blk_off[j + 1] - blk_off[j];
         const int tail = L % KPW;
-        sRuns[rank] = (tail > 0 && tail <= tail_max) ? L / KPW : (L + KPW - 1) / KPW;
+        lds.runs[rank] = (tail > 0 && tail <= tail_max) ? L / KPW : (L + KPW - 1) / KPW;
     }
     __syncthreads();
-    if (j == 0) {
-        int run = 0;
-        for (int r = 0; r < nb; ++r) {
-            kb_start[(long long)bh * (nb + 1) + r] = run;
-            run += sRuns[r];
-        }
-        kb_start[(long long)bh * (nb + 1) + nb] = run;
-    }
+    const int r0 = 2 * t < nb ? lds.runs[2 * t] : 0, r1 = 2 * t + 1 < nb ? lds.runs[2 * t + 1] : 0;
+    int total;
+    const int excl = block_exclusive_sum256(r0 + r1, lds.wave, &total);
+    int* out = kb_start + (long long)bh * (nb + 1);
+    if (2 * t < nb) out[2 * t] = excl;
+    if (2 * t + 1 < nb) out[2 * t + 1] = excl + r0;
+    if (t == 0) out[nb] = total;
+}
+
+template <bool BF16, int D>
+__global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorView dO, float* __restrict__ delta, const int* __restrict__ rows,
+                                                          char* __restrict__ dO_copy, const int* __restrict__ blk_ptr,
+                                                          const int* __restrict__ blk_off, int4* __restrict__ flat_desc, int* __restrict__ n_tiles,
+                                                          int* __restrict__ kb_start, int* __restrict__ kb_order, int BH, int Hh, int S, int nb,
+                                                          int TM, int KPW, int tail_max, int n_delta) {
+    __shared__ union { TileListLds tiles; KeyRunLds runs; } lds;
+    const int bh = blockIdx.y, x = blockIdx.x;
+    if (x < n_delta) delta_rows<BF16, D>(O, dO, delta, rows, dO_copy, bh, Hh, S, x);
+    else if (x + 1 < (int)gridDim.x) write_tile_list(lds.tiles, blk_ptr, blk_off, flat_desc, n_tiles, bh, BH, nb, TM, (x - n_delta) * 256);
+    else write_key_runs(lds.runs, blk_off, blk_ptr, kb_start, kb_order, bh, nb, KPW, tail_max);
 }
 
 // Load through a wave-uniform base and a 32-bit byte offset per lane (the address needs no 64-bit vector arithmetic).
@@ -107,7 +120,7 @@ template <int D>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int4* __restrict__ flat_desc, const int* __restrict__ head_base, int BH, float* __restrict__ dQpart, int Hh, int S, int nb,
+    const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, float* __restrict__ dQpart, int Hh, int S, int nb,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int TM = 128, KC = 64;
     constexpr int STR = D + 8;
@@ -123,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 
     // One workgroup per tile of the flat list (all heads).  Workgroup ids go round the 8 XCDs, so XCD x = id % 8 takes the
     // x-th eighth of the list: a key block's tiles then share one L2 instead of eight (gridDim.x is a multiple of 8).
-    const int total = head_base[BH];
+    const int total = *n_tiles;
     const int per_xcd = (total + 7) >> 3;
     const int slot = (int)(blockIdx.x >> 3);
     const int f = (int)(blockIdx.x & 7) * per_xcd + slot;
@@ -995,11 +1008,10 @@ __global__ __launch_bounds__(256) void dq_merge_kernel(const float* __restrict__
 struct BwdWs {
     float* dQpart;     // [BH * cap][D], in the tensors' type
     float* delta;      // [BH][S]
-    int* tile_start;   // [BH][257]
     int4* tile_desc;   // the flat list of all heads' tiles
-    int* head_base;    // [BH + 1]
-    int* kb_start;     // [BH][257]
-    int* kb_order;     // [BH][256]
+    int* n_tiles;      // its length
+    int* kb_start;     // [BH][nb + 1]
+    int* kb_order;     // [BH][nb]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
     size_t total;
 };
@@ -1010,9 +1022,8 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {
     size_t off = 0;
     w.dQpart = (float*)(p + off);    off += align_up((size_t)BH * cap * D * es, 256);
     w.delta = (float*)(p + off);     off += align_up((size_t)BH * S * 4, 256);
-    w.tile_start = (int*)(p + off);  off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
-    w.head_base = (int*)(p + off);   off += align_up((size_t)(BH + 1) * 4, 256);
+    w.n_tiles = (int*)(p + off);     off += 256;
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
@@ -1066,14 +1077,17 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
             if (ss <= 0 || ss * 2 >= (1 << 24) || (uint64_t)S * (uint64_t)ss * 2 >= ((uint64_t)1 << 32)) return VMOBA_ERR_UNSUPPORTED;
     }
 
-    {   // delta
-        const int epp = bf16 ? 8 : 4;
-        const int qpw = 256 / (D / epp);
-        dim3 grid((unsigned)ceil_div64(S, qpw), (unsigned)BH);
-        if (bf16 && D == 128) delta_kernel<true, 128><<<grid, dim3(256), 0, st>>>(Ov, dOv, ws.delta, rows, ws.dO_copy, Hh, (int)S);
-        else if (bf16) delta_kernel<true, 64><<<grid, dim3(256), 0, st>>>(Ov, dOv, ws.delta, rows, ws.dO_copy, Hh, (int)S);
-        else if (D == 128) delta_kernel<false, 128><<<grid, dim3(256), 0, st>>>(Ov, dOv, ws.delta, rows, ws.dO_copy, Hh, (int)S);
-        else delta_kernel<false, 64><<<grid, dim3(256), 0, st>>>(Ov, dOv, ws.delta, rows, ws.dO_copy, Hh, (int)S);
+    // ---- delta, tile list, key runs
+    const int TM = 128;                     // queries per dQ tile
+    const int KPW = bf16 ? 128 : 64;        // keys per dK/dV workgroup
+    const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
+    {
+        const int n_delta = (int)ceil_div64(S, 256 / (D / (bf16 ? 8 : 4)));
+        const dim3 grid((unsigned)(n_delta + ceil_div64(max_tiles, 256) + 1), (unsigned)BH);
+        auto kfn = bf16 ? (D == 128 ? bwd_prepare_kernel<true, 128> : bwd_prepare_kernel<true, 64>)
+                        : (D == 128 ? bwd_prepare_kernel<false, 128> : bwd_prepare_kernel<false, 64>);
+        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, ws.kb_start, ws.kb_order,
+                                        BH, Hh, (int)S, n_blocks, TM, KPW, bf16 ? 32 : 0, n_delta);
         VMOBA_CHECK_LAUNCH();
     }
     if (rows) {   // from here on dO is the block-order copy [B, Hh, S, D] the delta kernel wrote
@@ -1083,21 +1097,14 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         dOv.stride_s = D;
     }
     // ---- dQ
-    const int TM = 128;
-    tile_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(blk_ptr, ws.tile_start, ws.head_base, BH, n_blocks, TM);
-    VMOBA_CHECK_LAUNCH();
-    const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
-    flat_tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-        ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
-    VMOBA_CHECK_LAUNCH();
     {
         VMOBA_PROFILE_BEGIN(1, st);
         const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);     // one workgroup per tile
         if (!bf16) {
-            launch_dq_tiles_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, q_idx, ws.tile_desc, ws.head_base, BH, ws.dQpart, Hh, (int)S,
+            launch_dq_tiles_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
                                 (long long)nnz_capacity, scale_log2, kv_rows);
         } else {
-#define DQ_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, ws.head_base, BH, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
+#define DQ_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
             if (D == 128) attn_bwd_dq_mfma_kernel<128><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
             else attn_bwd_dq_mfma_kernel<64><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
 #undef DQ_ARGS
@@ -1116,9 +1123,6 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     }
     // ---- dK, dV
     {
-        const int KPW = bf16 ? 128 : 64;        // keys per workgroup
-        key_run_order_kernel<<<dim3(BH), dim3(VMOBA_MAX_BLOCKS), 0, st>>>(blk_off, blk_ptr, ws.kb_start, ws.kb_order, n_blocks, KPW, bf16 ? 32 : 0);
-        VMOBA_CHECK_LAUNCH();
         // a multiple of 8 so that (workgroup id % 8) is the same for every head; + 8 for the per-XCD rounding
         dim3 grid((unsigned)((S / KPW + n_blocks + 7) / 8 * 8 + 8 + (bf16 ? n_blocks : 0)), (unsigned)BH);
         // slots of the matrix-core kernel in groups of one block's runs (the usual block: S / n_blocks keys, a last run of at

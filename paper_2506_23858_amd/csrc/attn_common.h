@@ -3,9 +3,9 @@
 // Work decomposition (both directions).  The selection mask is kept block-major, the
 // orientation M_i in (N_b, s) of Eq. 3: for key block j, q_idx[blk_ptr[j] .. blk_ptr[j+1]) lists
 // the queries that keep it.  A "tile" is TM consecutive entries of one such list, i.e. TM gathered
-// queries that all attend to the same key block.  tile_start[bh][j] = number of tiles before block
-// j of head bh, written on the device from blk_ptr, so the host never learns the data-dependent counts;
-// the grid is sized from nnz_capacity and surplus workgroups leave at once.
+// queries that all attend to the same key block.  The list of all heads' tiles is written on the
+// device from blk_ptr, so the host never learns the data-dependent counts; the grid is sized from
+// nnz_capacity and surplus workgroups leave at once.
 //
 // MFMA operand plumbing (v_mfma_f32_32x32x16_bf16; lane = 32*hf + l32):
 //   A operand: lane holds row l32, 8 consecutive k at 8*hf;   B operand: column l32, same k.
@@ -72,17 +72,72 @@ struct TileCoord {
     int k0, L;    // first key position and number of keys of the tile's key block
 };
 
-// Tile plan (defined in attn_fwd.hip): tile_start[bh][j] = tiles of all (head, block) pairs before (bh, j) in the call's
-// flat list, tile_start[bh][nb] = first tile of the next head, head_base[bh] = tile_start[bh][0], head_base[BH] = total.
-__global__ __launch_bounds__(1024) void tile_plan_kernel(const int* __restrict__ blk_ptr, int* __restrict__ tile_start,
-                                                         int* __restrict__ head_base, int BH, int nb, int TM);
-
 inline __device__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Flat tile list over all heads for the MFMA tile kernels.
-__global__ __launch_bounds__(256) void flat_tile_desc_kernel(const int* __restrict__ tile_start, const int* __restrict__ blk_ptr,
-                                                             const int* __restrict__ blk_off, int4* __restrict__ flat_desc,
-                                                             int nb, int TM, int tiles_per_head);
+// Sum over the workgroup's 256 threads of the values before this thread's (exclusive prefix sum); *total receives the sum
+// of all.  sW: four words of LDS.  Contains two barriers.
+__device__ __forceinline__ int block_exclusive_sum256(int v, int* sW, int* total) {
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    int incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    __syncthreads();
+    if (lane == 63) sW[wv] = incl;
+    __syncthreads();
+    int base = 0, sum = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (w < wv) base += sW[w];
+        sum += sW[w];
+    }
+    *total = sum;
+    return base + incl - v;
+}
+
+// One workgroup's part of the flat tile list over all heads (heads in order, blocks in order): descriptors
+// {first list entry, count | head << 10, first key, block length} of tiles tile0, tile0 + 1, ... tile0 + 255 of head bh, at
+// flat_desc[tiles of the heads before + tile]; the last head's workgroups also write *n_tiles, the length of the list.
+// Every workgroup counts the tiles of the heads before its own and scans its own head's blocks by itself -- at most a few
+// thousand cached loads -- so that the list takes one launch and no workgroup waits for another.
+struct TileListLds { int start[VMOBA_MAX_BLOCKS + 1]; int wave[4]; };
+__device__ __forceinline__ void write_tile_list(TileListLds& lds, const int* __restrict__ blk_ptr, const int* __restrict__ blk_off,
+                                                int4* __restrict__ flat_desc, int* __restrict__ n_tiles, int bh, int BH, int nb, int TM, int tile0) {
+    const int t = threadIdx.x;
+    const int* bp = blk_ptr + (long long)bh * (nb + 1);
+    int mine = 0;
+    for (unsigned i = t; i < (unsigned)bh * nb; i += 256) {
+        const unsigned hh = i / (unsigned)nb, j = i - hh * nb;
+        const int* q = blk_ptr + (size_t)hh * (nb + 1) + j;
+        mine += (q[1] - q[0] + TM - 1) / TM;
+    }
+    int first;
+    (void)block_exclusive_sum256(mine, lds.wave, &first);
+    static_assert(VMOBA_MAX_BLOCKS <= 512, "two blocks per thread");
+    int n0 = 0, n1 = 0, total;
+    if (2 * t < nb) n0 = (bp[2 * t + 1] - bp[2 * t] + TM - 1) / TM;
+    if (2 * t + 1 < nb) n1 = (bp[2 * t + 2] - bp[2 * t + 1] + TM - 1) / TM;
+    const int excl = block_exclusive_sum256(n0 + n1, lds.wave, &total);
+    if (2 * t < nb) lds.start[2 * t] = excl;
+    if (2 * t + 1 < nb) lds.start[2 * t + 1] = excl + n0;
+    if (t == 0) {
+        lds.start[nb] = total;
+        if (bh == BH - 1 && tile0 == 0) *n_tiles = first + total;
+    }
+    __syncthreads();
+    const int tile = tile0 + t;
+    if (tile >= total) return;
+    int lo = 0, hi = nb;           // largest j with start[j] <= tile
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (lds.start[mid] <= tile) lo = mid; else hi = mid;
+    }
+    const int t0 = (tile - lds.start[lo]) * TM;
+    const int e0 = bp[lo] + t0, k0 = blk_off[lo];
+    flat_desc[first + tile] = make_int4(e0, min(TM, bp[lo + 1] - e0) | (bh << 10), k0, blk_off[lo + 1] - k0);
+}
 // Grid of a kernel with one workgroup per entry of the flat list: a bound on its length, a multiple of 8.
 static inline dim3 flat_tile_grid(int BH, int64_t max_tiles, int64_t cap, int TM, int nb) {
     const int64_t a = (int64_t)BH * max_tiles, b = ((cap / TM + nb) * (int64_t)BH + 15) / 8 * 8;
@@ -90,10 +145,10 @@ static inline dim3 flat_tile_grid(int BH, int64_t max_tiles, int64_t cap, int TM
 }
 // float32 tile kernels (attn_f32.hip)
 void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
-                          const int4* flat_desc, const int* head_base, int BH, float* Opart, float* lse_part, int Hh, long long cap,
+                          const int4* flat_desc, const int* n_tiles, float* Opart, float* lse_part, int Hh, long long cap,
                           float scale_log2, const int* kv_rows);
 void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* head_base, int BH,
+                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* n_tiles,
                          float* dQpart, int Hh, int S, long long cap, float scale_log2, const int* kv_rows);
 void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
                     const float* LSE, const float* delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,

@@ -164,9 +164,9 @@ __device__ __forceinline__ void product_over_rows(const TileReads<D>& rd, const 
 }
 
 struct F32Tile { int list0, count, bh, k0, L; };
-// Entry of the flat tile list (see flat_tile_desc_kernel) this workgroup takes, XCD x = id % 8 the x-th eighth of it.
-__device__ __forceinline__ bool take_tile(const int4* __restrict__ flat_desc, const int* __restrict__ head_base, int BH, F32Tile& t) {
-    const int total = head_base[BH];
+// Entry of the flat tile list (see write_tile_list) this workgroup takes, XCD x = id % 8 the x-th eighth of it.
+__device__ __forceinline__ bool take_tile(const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, F32Tile& t) {
+    const int total = *n_tiles;
     const int per_xcd = (total + 7) >> 3;
     const int slot = (int)(blockIdx.x >> 3);
     const int f = (int)(blockIdx.x & 7) * per_xcd + slot;
@@ -189,12 +189,12 @@ __device__ __forceinline__ const char* head_ptr(const TensorView& t, int b, int 
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_fwd_tile_f32_kernel(
     TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
-    const int* __restrict__ head_base, int BH, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
+    const int* __restrict__ n_tiles, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int KC = 32, TILE = KeyRows<D>::TILE, DT = D / 32;
     __shared__ __align__(1024) char sKV[2][2][TILE];              // [buffer][K, V]
     F32Tile t;
-    if (!take_tile(flat_desc, head_base, BH, t)) return;
+    if (!take_tile(flat_desc, n_tiles, t)) return;
     const int b = t.bh / Hh, h = t.bh % Hh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
@@ -278,12 +278,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_tile_f32_kernel(
 template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
     TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
-    const int* __restrict__ q_idx, const int4* __restrict__ flat_desc, const int* __restrict__ head_base, int BH,
+    const int* __restrict__ q_idx, const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles,
     float* __restrict__ dQpart, int Hh, int S, long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int KC = 32, TILE = KeyRows<D>::TILE, DT = D / 32;
     __shared__ __align__(1024) char sKV[2][2][TILE];
     F32Tile t;
-    if (!take_tile(flat_desc, head_base, BH, t)) return;
+    if (!take_tile(flat_desc, n_tiles, t)) return;
     const int b = t.bh / Hh, h = t.bh % Hh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
@@ -491,17 +491,17 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
 }  // namespace
 
 void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
-                          const int4* flat_desc, const int* head_base, int BH, float* Opart, float* lse_part, int Hh, long long cap,
+                          const int4* flat_desc, const int* n_tiles, float* Opart, float* lse_part, int Hh, long long cap,
                           float scale_log2, const int* kv_rows) {
     auto kfn = D == 128 ? attn_fwd_tile_f32_kernel<128> : attn_fwd_tile_f32_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, q_idx, flat_desc, head_base, BH, Opart, lse_part, Hh, cap, scale_log2, kv_rows);
+    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, q_idx, flat_desc, n_tiles, Opart, lse_part, Hh, cap, scale_log2, kv_rows);
 }
 
 void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* head_base, int BH,
+                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* n_tiles,
                          float* dQpart, int Hh, int S, long long cap, float scale_log2, const int* kv_rows) {
     auto kfn = D == 128 ? attn_bwd_dq_f32_kernel<128> : attn_bwd_dq_f32_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, dO, LSE, delta, q_idx, flat_desc, head_base, BH, dQpart, Hh, S, cap, scale_log2, kv_rows);
+    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, dO, LSE, delta, q_idx, flat_desc, n_tiles, dQpart, Hh, S, cap, scale_log2, kv_rows);
 }
 
 void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,

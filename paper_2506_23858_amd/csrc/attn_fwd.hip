@@ -13,83 +13,17 @@
 #include <cmath>
 #include <type_traits>
 
-// Tile plan of a call: tile_start[bh][j] = number of tiles (of TM list entries) in all (head, block) pairs before
-// (bh, j), counted over the whole flat list of the call -- heads in order, blocks in order -- tile_start[bh][nb] = the
-// same for the first pair of the next head, and head_base[bh] = tile_start[bh][0], head_base[BH] = total.  One
-// workgroup; a scan over the BH * nb tile counts in batches of 1024.
-__global__ __launch_bounds__(1024) void tile_plan_kernel(const int* __restrict__ blk_ptr, int* __restrict__ tile_start,
-                                                         int* __restrict__ head_base, int BH, int nb, int TM) {
-    __shared__ int sW[16];
-    __shared__ int sCarry;
-    const int t = threadIdx.x, n = BH * nb;
-    if (t == 0) sCarry = 0;
-    __syncthreads();
-    for (int base = 0; base < n; base += 1024) {
-        const int i = base + t;
-        int v = 0, bh = 0, j = 0;
-        if (i < n) {
-            bh = i / nb;
-            j = i - bh * nb;
-            const int* bp = blk_ptr + (long long)bh * (nb + 1);
-            v = (bp[j + 1] - bp[j] + TM - 1) / TM;
-        }
-        int incl = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if ((t & 63) >= off) incl += o;
-        }
-        if ((t & 63) == 63) sW[t >> 6] = incl;
-        __syncthreads();
-        int wave_base = 0;
-        for (int w = 0; w < (t >> 6); ++w) wave_base += sW[w];
-        const int excl = sCarry + wave_base + incl - v;
-        if (i < n) {
-            tile_start[(long long)bh * (nb + 1) + j] = excl;
-            if (j == 0) {
-                head_base[bh] = excl;
-                if (bh > 0) tile_start[(long long)(bh - 1) * (nb + 1) + nb] = excl;
-            }
-        }
-        __syncthreads();
-        if (t == 1023) sCarry = excl + v;
-        __syncthreads();
-    }
-    if (t == 0) {
-        tile_start[(long long)(BH - 1) * (nb + 1) + nb] = sCarry;
-        head_base[BH] = sCarry;
-    }
-}
-
-// Flat tile list over all heads for the MFMA tile kernels: flat_desc[tile_start[bh][0] + tile] = {first list entry,
-// count | bh << 10, first key, block length}; one thread per (head, tile id below tiles_per_head).
-__global__ __launch_bounds__(256) void flat_tile_desc_kernel(const int* __restrict__ tile_start, const int* __restrict__ blk_ptr,
-                                                             const int* __restrict__ blk_off, int4* __restrict__ flat_desc,
-                                                             int nb, int TM, int tiles_per_head) {
-    const int bh = blockIdx.y;
-    const int tile = blockIdx.x * 256 + threadIdx.x;
-    const int* ts = tile_start + (long long)bh * (nb + 1);
-    const int first = ts[0];
-    if (tile >= tiles_per_head || tile >= ts[nb] - first) return;
-    int lo = 0, hi = nb;           // largest j with ts[j] - first <= tile
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (ts[mid] - first <= tile) lo = mid; else hi = mid;
-    }
-    const int* bp = blk_ptr + (long long)bh * (nb + 1);
-    const int t0 = (tile - (ts[lo] - first)) * TM;
-    int4 d;
-    d.x = bp[lo] + t0;
-    d.y = min(TM, bp[lo + 1] - bp[lo] - t0) | (bh << 10);
-    d.z = blk_off[lo];
-    d.w = blk_off[lo + 1] - blk_off[lo];
-    flat_desc[first + tile] = d;
-}
-
 namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
+
+// The flat tile list of a forward call (see write_tile_list); grid: 256 tile ids x head.
+__global__ __launch_bounds__(256) void tile_list_kernel(const int* __restrict__ blk_ptr, const int* __restrict__ blk_off,
+                                                        int4* __restrict__ flat_desc, int* __restrict__ n_tiles, int BH, int nb, int TM) {
+    __shared__ TileListLds lds;
+    write_tile_list(lds, blk_ptr, blk_off, flat_desc, n_tiles, blockIdx.y, BH, nb, TM, blockIdx.x * 256);
+}
 
 // ---------------------------------------------------------------------------------------------
 // bf16 MFMA tile kernel.  NW wavefronts; wavefront w owns 32 gathered queries (a tile is 32 * NW list
@@ -134,7 +68,7 @@ constexpr float LN2 = 0.6931471805599453f;
 // are first read at the end of step g.
 //
 // Persistence.  A workgroup strides through its XCD's share of the flat tile list (all heads, see
-// flat_tile_desc_kernel) and overlaps the start of its next tile with the end of the current one:
+// write_tile_list) and overlaps the start of its next tile with the end of the current one:
 // the next descriptor and the next tile's query index are fetched at the start of the tile, and its
 // query rows (into the Q^T registers, the first product is done by then) and K(0..3), V(0..1)
 // during the last soft-max step, into slots nobody reads any more (the rings are indexed by
@@ -154,7 +88,7 @@ constexpr float LN2 = 0.6931471805599453f;
 template <int D, int NW, bool KVR>
 __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
-    const int* __restrict__ head_base, int BH, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
+    const int* __restrict__ n_tiles, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int G = 32;                   // keys per group
     constexpr int RB = 2 * D;               // bytes per LDS row
@@ -179,7 +113,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
 
     // Workgroup ids go round the 8 XCDs (each with its own L2), so XCD x = id % 8 takes the x-th eighth of the tile
     // list and its workgroups stride through it: a key block's tiles then share one L2 instead of eight.
-    const int total = head_base[BH];
+    const int total = *n_tiles;
     const bool by_xcd = (gridDim.x & 7) == 0;
     const int xcd = by_xcd ? (int)(blockIdx.x & 7) : 0;
     const int f_step = by_xcd ? (int)(gridDim.x >> 3) : (int)gridDim.x;
@@ -604,9 +538,8 @@ __global__ __launch_bounds__(256) void attn_fwd_merge_kernel(const float* __rest
 struct FwdWs {
     float* Opart;      // [BH * cap][D], in the tensors' type
     float* lse_part;   // [BH * cap]
-    int* tile_start;   // [BH][nb + 1]
     int4* tile_desc;   // the flat list of all heads' tiles
-    int* head_base;    // [BH + 1]
+    int* n_tiles;      // its length
     size_t total;
 };
 
@@ -621,9 +554,8 @@ FwdWs carve_fwd(void* base, int BH, int D, int64_t cap, int es) {       // es: b
     size_t off = 0;
     w.Opart = (float*)(p + off);     off += align_up((size_t)BH * cap * D * es, 256);
     w.lse_part = (float*)(p + off);  off += align_up((size_t)BH * cap * 4, 256);
-    w.tile_start = (int*)(p + off);  off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
-    w.head_base = (int*)(p + off);   off += align_up((size_t)(BH + 1) * 4, 256);
+    w.n_tiles = (int*)(p + off);     off += 256;
     w.total = off;
     return w;
 }
@@ -685,19 +617,17 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     // float32: one workgroup per tile of 128 queries
     const bool wide = bf16 && D == 128;
     const int TM = wide ? 256 : 128;
-    tile_plan_kernel<<<dim3(1), dim3(1024), 0, st>>>(blk_ptr, ws.tile_start, ws.head_base, BH, n_blocks, TM);
-    VMOBA_CHECK_LAUNCH();
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
-    flat_tile_desc_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-        ws.tile_start, blk_ptr, blk_off, ws.tile_desc, n_blocks, TM, (int)max_tiles);
+    tile_list_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
+        blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, BH, n_blocks, TM);
     VMOBA_CHECK_LAUNCH();
     VMOBA_PROFILE_BEGIN(0, st);
     if (!bf16) {
-        launch_fwd_tiles_f32(D, flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks), st, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.head_base, BH,
+        launch_fwd_tiles_f32(D, flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks), st, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles,
                              ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows);
     } else {
         const dim3 pgrid((unsigned)std::min<int64_t>((wide ? 1 : 2) * (int64_t)vmoba_num_cus(), (int64_t)BH * max_tiles));
-#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.head_base, BH, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows
+#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows
         if (wide && kv_rows) attn_fwd_tile_mfma_kernel<128, 8, true><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);
         else if (wide) attn_fwd_tile_mfma_kernel<128, 8, false><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);
         else if (kv_rows) attn_fwd_tile_mfma_kernel<64, 4, true><<<pgrid, dim3(256), 0, st>>>(MFMA_ARGS);
