@@ -15,6 +15,11 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
          "-Wno-unused-command-line-argument",
          "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(HERE, "csrc")]
 
+# attn_bwd: its large kernel names the matrix instructions whose sums belong in accumulator registers and interleaves matrix and
+# vector instructions one by one; results of the others go to ordinary registers, and the vectorizer, which would gather the
+# vector instructions in one place, stays off.
+FILE_FLAGS = {"attn_bwd.hip": ["-fno-slp-vectorize", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
 
 def sources():
     return sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
@@ -28,7 +33,7 @@ def build_lib(verbose: bool = True, extra_flags=()) -> str:
     procs = []
     for src in sources():
         obj = os.path.join(build_dir, os.path.basename(src) + ".o")
-        cmd = [HIPCC] + [f for f in FLAGS if f != "-shared"] + list(extra_flags) + ["-c", src, "-o", obj]
+        cmd = [HIPCC] + [f for f in FLAGS if f != "-shared"] + FILE_FLAGS.get(os.path.basename(src), []) + list(extra_flags) + ["-c", src, "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
     for src, p in procs:

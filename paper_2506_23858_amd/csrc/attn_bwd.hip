@@ -22,12 +22,16 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 
 // ---------------------------------------------------------------------------------------------
+// The bfloat16 kernels read LSE * log2(e) and delta from [head][2][pitch] floats: element S of either is what a row past the
+// end of a query list reads (LSE +inf, i.e. weight 0, and delta 0).  The float32 kernels read delta from [head][S].
+__host__ __device__ constexpr int lse_delta_pitch(int S) { return (S + 64) / 64 * 64; }
+
 // What a backward call needs before its first large kernel, in one launch: workgroups with blockIdx.x below n_delta compute
 // delta, the next ones write the flat tile list of the dQ kernel (256 tile ids each), the last one of every head the key
 // runs of the dK/dV kernel.  (Four launches before; each of the small ones took about 5 us whatever its size.)
 template <bool BF16, int D>
-__device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView& dO, float* __restrict__ delta, const int* __restrict__ rows,
-                                           char* __restrict__ dO_copy, int bh, int Hh, int S, int slot) {
+__device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView& dO, const float* __restrict__ LSE, float* __restrict__ delta,
+                                           const int* __restrict__ rows, char* __restrict__ dO_copy, int bh, int Hh, int S, int slot) {
     constexpr int EPP = BF16 ? 8 : 4;
     constexpr int LPQ = D / EPP;
     constexpr int QPW = 256 / LPQ;
@@ -55,7 +59,15 @@ __device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView
     }
 #pragma unroll
     for (int off = LPQ / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (q < S && part == 0) delta[(long long)bh * S + q] = acc;
+    if (q < S && part == 0) {
+        if constexpr (BF16) {
+            float* d = delta + (long long)bh * 2 * lse_delta_pitch(S) + q;
+            d[0] = LSE[(long long)bh * S + q] * LOG2E;
+            d[lse_delta_pitch(S)] = acc;
+        } else {
+            delta[(long long)bh * S + q] = acc;
+        }
+    }
 }
 
 // Key-run table of one head.  A "run" is KPW consecutive keys of one block, the share of one dK/dV
@@ -91,16 +103,20 @@ __device__ __forceinline__ void write_key_runs(KeyRunLds& lds, const int* __rest
 }
 
 template <bool BF16, int D>
-__global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorView dO, float* __restrict__ delta, const int* __restrict__ rows,
+__global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorView dO, const float* __restrict__ LSE, float* __restrict__ delta, const int* __restrict__ rows,
                                                           char* __restrict__ dO_copy, const int* __restrict__ blk_ptr,
                                                           const int* __restrict__ blk_off, int4* __restrict__ flat_desc, int* __restrict__ n_tiles,
                                                           int* __restrict__ kb_start, int* __restrict__ kb_order, int BH, int Hh, int S, int nb,
                                                           int TM, int KPW, int tail_max, int n_delta) {
     __shared__ union { TileListLds tiles; KeyRunLds runs; } lds;
     const int bh = blockIdx.y, x = blockIdx.x;
-    if (x < n_delta) delta_rows<BF16, D>(O, dO, delta, rows, dO_copy, bh, Hh, S, x);
+    if (x < n_delta) delta_rows<BF16, D>(O, dO, LSE, delta, rows, dO_copy, bh, Hh, S, x);
     else if (x + 1 < (int)gridDim.x) write_tile_list(lds.tiles, blk_ptr, blk_off, flat_desc, n_tiles, bh, BH, nb, TM, (x - n_delta) * 256);
-    else write_key_runs(lds.runs, blk_off, blk_ptr, kb_start, kb_order, bh, nb, KPW, tail_max);
+    else {
+        if (BF16 && threadIdx.x < 2)
+            delta[((long long)bh * 2 + threadIdx.x) * lse_delta_pitch(S) + S] = threadIdx.x == 0 ? INFINITY : 0.f;
+        write_key_runs(lds.runs, blk_off, blk_ptr, kb_start, kb_order, bh, nb, KPW, tail_max);
+    }
 }
 
 // Load through a wave-uniform base and a 32-bit byte offset per lane (the address needs no 64-bit vector arithmetic).
@@ -118,7 +134,7 @@ __device__ __forceinline__ T load_at(const void* base, uint32_t byte_off) {
 //   dQ^T += K^T . dS^T                A = K^T by transpose reads of the same K tile
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
+    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
     const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, float* __restrict__ dQpart, int Hh, int S, int nb,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
@@ -177,8 +193,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
             dma16(db, __umul24(qr, doss) + pc, gd0 + k * 1024);
         }
     }
-    const float lse2 = LSE[(long long)bh * S + q] * LOG2E;
-    const float dl = delta[(long long)bh * S + q];
+    const float lse2 = lse_delta[(long long)bh * 2 * lse_delta_pitch(S) + q];
+    const float dl = lse_delta[((long long)bh * 2 + 1) * lse_delta_pitch(S) + q];
 
     f32x16_t dqacc[DT];
 #pragma unroll
@@ -346,10 +362,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// bf16 MFMA dK/dV kernel.  A workgroup owns 128 consecutive keys of one block (key = MFMA column
-// = lane % 32) and walks the block's query list in chunks of 64 gathered queries (two half-chunks
-// of 32), which pass through a ring of four LDS buffers; the gathered rows are prefetched into
-// registers one chunk ahead of the ring and their indices one more chunk ahead.
+// bf16 MFMA dK/dV kernel.  A workgroup owns 128 consecutive keys of one block (key = MFMA column = lane % 32) and walks
+// the block's query list in half-chunks of 32 gathered queries.
 //   S   = Q . K^T      A = Q rows (LDS),   B = K^T (registers, loaded once)
 //   dP  = dO . V^T     A = dO rows (LDS),  B = V^T (registers, loaded once)
 //   dV^T += dO^T . P   A = dO^T by transpose reads of the dO tile,  B = P packed from S
@@ -366,39 +380,88 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 // half-chunk later, and the steps are separated by one workgroup barrier per half-chunk.
 // Step hc of the workgroup, local step t = hc - (wavefront % 2), all interleaved:
 //   matrix:  S or dP of half-chunk t + 1,  dV or dK of half-chunk t - 1      vector: P or dS of t
-//   memory (even hc): rows of chunk hc/2 + 2 from registers into the ring, loads of chunk hc/2 + 3.
-// The ring buffer written during steps 2c, 2c + 1 was last read in step 2c - 1 and is first read in 2c + 3.
+//   memory:  rows, LSE and delta of half-chunk hc + 5, list entries of half-chunk hc + 8, straight into LDS.
+//
+// Everything the walk reads goes from global memory to LDS without passing through registers (global_load_lds): rings of
+// eight half-chunks of Q and dO rows, of their LSE and delta (accumulator order) and of the list entries, from which a lane
+// takes the row number it requests.  A half-chunk h is read from the end of step h - 2 to step h + 2 and its slot is
+// requested again in step h + 3; a step ends with a wait for what was requested up to two steps before, then the barrier,
+// so what step s requested is visible from step s + 3 on.  The loop holds no other global loads, so the count of
+// the wait is exact.  (Before: staged through registers -- 8 row loads and 8 LDS writes per wavefront and chunk of
+// 64, 32 registers of rows in flight and the copies from and to the accumulator registers that these forced, 7.1 and 8.6
+// instructions per matrix instruction for the two wavefronts of a pair, now 6.0 and 7.7.  480p, 12 heads, 1D / 2D / 3D partition:
+// 2.80 / 2.66 / 2.13 -> 2.62 / 2.46 / 2.00 ms.  Timing variants of this form: without the row requests -5 %, without the
+// barrier as well -11 %, without the operand reads from LDS -13 %: no single limiter.)
+// Rows past the end of the list repeat its last entry; their LSE is +inf (weight 0) and their delta 0, read from a
+// spare element behind the head's S values.
+// Tile layout: the 64 lanes of one request write 1024 consecutive bytes, i.e. RPI = 4 (8) rows of D = 128 (64) channels; such
+// groups lie GP bytes apart, and 16-byte piece p of a group's row i sits at piece position p ^ fsw(i).  Row and transposed
+// reads are then free of bank conflicts, and for D = 128 only the two low bits of a piece position depend on the row, so
+// that two per-lane addresses and immediate offsets reach every operand.
+//
 // A wavefront issues in order and a matrix instruction occupies the matrix pipe for 32 cycles, so the step is cut
 // into units of one matrix instruction followed by an equal share of the vector, LDS and memory instructions,
 // with scheduling fences between them (two matrix instructions back to back would stall the second one while
-// the vector unit idles).  S / dP of even and odd half-chunks live in two register sets that swap roles, so
-// no accumulator is ever copied.
-// LDS bytes of the pair body: a ring of four 64-row tiles of Q and of dO, their LSE / delta, the packed-P hand-over
+// the vector unit idles).  Operands are fetched two k-steps (eight units) before use.  The first LEAD units of a
+// step carry no vector work: it needs P and LSE / delta, which are only requested from LDS at the start of the step.
+// S / dP of even and odd half-chunks live in two register sets that swap roles, so no accumulator is ever copied.
 template <int D>
-constexpr int dkv_pair_lds_bytes() { return 2 * 4 * 64 * (D + 8) * 2 + 2 * 4 * 64 * 4 + 2 * 2 * 4 * 64 * 16; }
+struct DkvTile {
+    static constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;
+    static constexpr int GP = D == 128 ? 1024 + 64 : 1024 + 144;       // bytes between groups of RPI rows
+    static constexpr int HB = 32 / RPI * GP;                           // bytes of a half-chunk
+    static constexpr int NS = 8;                                       // half-chunks per ring
+    static constexpr int LD0 = 2 * NS * HB;                            // LSE and delta: [NS][64] floats
+    static constexpr int IX0 = LD0 + NS * 64 * 4;                      // list entries: [NS + 1][32]; a request fills two half-chunks
+    static constexpr int X0 = IX0 + (NS + 1) * 32 * 4;                 // packed P: [pair][step parity][key group * 2 + s][lane]
+    static constexpr int BYTES = X0 + 2 * 2 * 4 * 64 * 16;
+    static_assert(X0 % 16 == 0 && BYTES <= 160 * 1024, "LDS of one compute unit");
+    __device__ static __forceinline__ int fsw(int i) { return D == 128 ? i : 2 * ((i >> 1) & 1) + 4 * (i >> 2); }
+};
+
+// 64 lanes x 16 bytes, row `row` of a matrix of `stride` bytes per row (both below 2^24), byte `piece` of it, to LDS lds + IMM.
+template <int IMM>
+__device__ __forceinline__ void dma_row16(const char* base, uint32_t row, uint32_t stride, uint32_t piece, uint32_t lds) {
+    uint32_t off;
+    asm volatile("s_add_u32 m0, %5, %6\n\tv_mad_u32_u24 %0, %1, %2, %3\n\tglobal_load_lds_dwordx4 %0, %4"
+                 : "=&v"(off) : "v"(row), "s"(stride), "v"(piece), "s"(base), "s"(lds), "i"(IMM) : "memory", "m0", "scc");
+}
+
+// f(0), f(1), ... f(N - 1) with the index as a compile-time constant.
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
+
+// Matrix instruction on a sum that stays in accumulator registers.  (This file is compiled so that the results of the matrix
+// instructions it does not name in assembly go to ordinary registers: S and dP are read by vector instructions, which cannot
+// read accumulator registers -- with the compiler's choice for a kernel of this size, everything there, every one of
+// their values takes a copy, one instruction more per matrix instruction.)  The compiler does not see the latency: nothing but
+// further matrix instructions may read the sum until acc_ready.
+__device__ __forceinline__ void mfma_acc(f32x16_t& d, bf16x8_t a, bf16x8_t b) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void acc_ready(f32x16_t& d) { asm volatile("s_nop 15\n\ts_nop 3" : "+a"(d)); }
 
 template <int D>
 __device__ __forceinline__ void dkv_pair_body(
-    char* smem, int bh, int run_id, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO, const float* __restrict__ LSE,
-    const float* __restrict__ delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
+    char* smem, int bh, int run_id, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+    const float* __restrict__ lse_delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int* __restrict__ kb_start, const int* __restrict__ kb_order, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
     const int* __restrict__ kv_rows, int Hh, int S, int nb, long long cap, float scale_log2, float scale) {
-    constexpr int NT = 256;
-    constexpr int QC = 64;
-    constexpr int STR = D + 8;
-    constexpr int KSTEPS = D / 16, DT = D / 32;
-    constexpr int LOADS = QC * D * 2 / 16 / NT;
-    constexpr int NBUF = 4;
-    constexpr int NST = KSTEPS;
-    static_assert(NST == 2 * DT && NST == 2 * LOADS, "one row piece, one k-step and one (s, dt) step per step");
-    constexpr int VP = 8 / NST;               // value pairs per key group and step
-    __bf16(*sQ)[QC * STR] = reinterpret_cast<__bf16(*)[QC * STR]>(smem);
-    __bf16(*sdO)[QC * STR] = reinterpret_cast<__bf16(*)[QC * STR]>(smem + NBUF * QC * STR * 2);
-    float(*sL)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * NBUF * QC * STR * 2);
-    float(*sDl)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * NBUF * QC * STR * 2 + NBUF * QC * 4);
-    // [pair][step parity][kg * 2 + s][lane]: packed P
-    u32x4_t(*sX)[2][4][64] = reinterpret_cast<u32x4_t(*)[2][4][64]>(smem + 2 * NBUF * QC * STR * 2 + 2 * NBUF * QC * 4);
-    static_assert(dkv_pair_lds_bytes<D>() == 2 * NBUF * QC * STR * 2 + 2 * NBUF * QC * 4 + 2 * 2 * 4 * 64 * 16, "LDS carve");
+    using TL = DkvTile<D>;
+    constexpr int KSTEPS = D / 16, DT = D / 32, NST = KSTEPS;
+    constexpr int IPW = 32 / TL::RPI / 4;     // row requests per wavefront, tensor and half-chunk
+    constexpr int NS = TL::NS, HB = TL::HB, GP = TL::GP, RB = TL::RB;
+    constexpr int NRB = D == 128 ? 2 : 4;     // distinct per-lane addresses of the row reads
+    constexpr int NU = 4 * NST, LEAD = 4;     // units per step; units without vector work
+    static_assert(NST == 2 * DT && NST % 4 == 0, "one k-step and one (s, dt) step per step, operand ring of four");
+
+    // value v belongs to unit LEAD + v * (NU - LEAD) / 32: first value of unit n
+    constexpr auto first_value = [](int n) { return n <= LEAD ? 0 : ((n - LEAD) * 32 + NU - LEAD - 1) / (NU - LEAD); };
 
     const int b = bh / Hh, h = bh % Hh;
     const int* ks = kb_start + (long long)bh * (nb + 1);
@@ -406,7 +469,8 @@ __device__ __forceinline__ void dkv_pair_body(
     while (hi - lo > 1) { int mid = (lo + hi) >> 1; if (ks[mid] <= run_id) lo = mid; else hi = mid; }
     const int j = kb_order[(long long)bh * nb + lo], run = run_id - ks[lo];
     const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pair = wave >> 1, role = wave & 1;
     const int l32 = lane & 31, hf = lane >> 5;
     const int kbase = run * 128 + pair * 64;            // first key of the pair inside the block
@@ -446,101 +510,99 @@ __device__ __forceinline__ void dkv_pair_body(
         // row strides in bytes: below 2^24 and rows below 2^24, so a row's offset is one 24-bit multiply (host-checked)
         const uint32_t qss = (uint32_t)(Q.stride_s * 2), doss = (uint32_t)(dO.stride_s * 2);
         const int* list = q_idx + seg + list0;
-        const float* lse_h = LSE + (long long)bh * S;
-        const float* dl_h = delta + (long long)bh * S;
-        const int n_chunks = (cnt + QC - 1) / QC;
-        const int H = 2 * n_chunks;
+        const uint32_t SP = (uint32_t)lse_delta_pitch(S);
+        const char* ld_base = reinterpret_cast<const char*>(lse_delta + (long long)bh * 2 * SP);
+        const int H = (cnt + 63) / 64 * 2;                  // half-chunks, an even number (see the register sets below)
 
-        u32x4_t qreg[LOADS], doreg[LOADS];
-        float lreg = 0.f;
-        uint32_t qn[LOADS], ql = 0;
-        const int ld_row = (wave >> 1) * 32 + (lane & 31);      // the chunk row whose LSE or delta this lane moves
-        bool ql_live = false, rows_live = false;
-        auto prefetch_idx_piece = [&](int c, int i) {       // chunks past the list: indices clamp, rows count as dead
-            const int c0 = c * QC;
-            if (i < LOADS) {
-                const int r = (tid + NT * i) / (D / 8);
-                qn[i] = load_at<uint32_t>(list, (uint32_t)min(c0 + r, cnt - 1) << 2);
-            } else {
-                ql = load_at<uint32_t>(list, (uint32_t)min(c0 + ld_row, cnt - 1) << 2);
-                ql_live = c0 + ld_row < cnt;
-            }
-        };
-        auto prefetch_idx = [&](int c) {
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+        const int* sIdx = reinterpret_cast<const int*>(smem + TL::IX0);
+        const uint32_t pc16 = (uint32_t)((lane % TL::PPR) ^ TL::fsw(lane / TL::PPR)) * 16;
+        const int idx_row = wave * IPW * TL::RPI + lane / TL::PPR;           // + i * RPI: row of request i this lane takes part in
+        // LSE / delta: lanes 0..31 request LSE, lanes 32..63 delta; lane l % 32 = position p holds row ld_row (accumulator
+        // order: the 16 values a lane half needs are contiguous)
+        const int ld_row = ((l32 & 3) << 2) | (((l32 >> 2) & 1) << 1) | (((l32 >> 3) & 1) << 4) | (l32 >> 4);
+        const uint32_t ld_hf = hf ? SP * 4 : 0;
+        // requests of half-chunk x, piece by piece: row numbers from LDS, then LSE / delta, Q rows, dO rows
+        uint32_t qn[IPW];
+        uint32_t lq = 0;
+        auto read_idx = [&](int x) {
+            const int* p = sIdx + (x & (NS - 1)) * 32;
 #pragma unroll
-            for (int i = 0; i <= LOADS; ++i) prefetch_idx_piece(c, i);
+            for (int i = 0; i < IPW; ++i) qn[i] = (uint32_t)p[idx_row + i * TL::RPI];
         };
-        auto load_piece = [&](int i) {
-            if (i < LOADS) {
-                const uint32_t pc = (tid + NT * i) % (D / 8);
-                qreg[i] = load_at<u32x4_t>(qbase, __umul24(qn[i], qss) + pc * 16);
-            } else {
-                const int k = i - LOADS;
-                const uint32_t pc = (tid + NT * k) % (D / 8);
-                doreg[k] = load_at<u32x4_t>(dobase, __umul24(qn[k], doss) + pc * 16);
-            }
+        auto read_ld_idx = [&](int x) { lq = (uint32_t)sIdx[(x & (NS - 1)) * 32 + ld_row]; };
+        auto ld_offset = [&](int x) { return (32 * x + ld_row < cnt ? lq : (uint32_t)S) * 4 + ld_hf; };
+        auto ld_slot = [&](int x) { return lds0 + TL::LD0 + (uint32_t)(x & (NS - 1)) * 256; };
+        // Wavefront 0 of the first pair requests LSE / delta of half-chunk hc + 5, wavefront 0 of the second pair the list
+        // entries of half-chunk hc + 8 (and, with what it will be filled with next, hc + 9) -- without a branch
+        const bool lists = pair == 1;
+        const char* const side_base = lists ? reinterpret_cast<const char*>(list) : ld_base;
+        auto dma_side = [&](int hc) {
+            const uint32_t e = (uint32_t)min(32 * (hc + 8) + lane, cnt - 1) * 4, l = ld_offset(hc + 5);
+            dma4(side_base, lists ? e : l, lists ? lds0 + TL::IX0 + (uint32_t)(hc & (NS - 1)) * 128 : ld_slot(hc + 5));
         };
-        // LSE and delta of the chunk's 64 rows: even wavefronts fetch and store LSE values, odd ones delta values, the
-        // first pair those of rows 0..31 and the second pair those of rows 32..63 (both halves of a wavefront the same
-        // 32) -- free of branches inside the pipelined loop, and a request touches 32 scattered words, not 2 x 64
-        const float* ld_src = (wave & 1) ? dl_h : lse_h;
-        const float ld_mul = (wave & 1) ? 1.f : LOG2E, ld_dead = (wave & 1) ? 0.f : INFINITY;
-        auto load_ld_regs = [&]() {
-            lreg = load_at<float>(ld_src, ql << 2);
-            rows_live = ql_live;
+        auto dma_rows = [&](int x, int i, int tensor) {
+            const uint32_t l = lds0 + (uint32_t)(x & (NS - 1)) * HB + (uint32_t)(wave * IPW + i) * GP;
+            if (tensor == 0) dma_row16<0>(qbase, qn[i], qss, pc16, l);
+            else dma_row16<NS * HB>(dobase, qn[i], doss, pc16, l);
         };
-        auto stage_piece = [&](int buf, int i) {
-            const int k = i < LOADS ? i : i - LOADS;
-            const int piece = tid + NT * k;
-            const int r = piece / (D / 8), pc = piece % (D / 8);
-            if (i < LOADS) *reinterpret_cast<u32x4_t*>(&sQ[buf][r * STR + pc * 8]) = qreg[k];
-            else *reinterpret_cast<u32x4_t*>(&sdO[buf][r * STR + pc * 8]) = doreg[k];
-        };
-        // accumulator order: the 16 values a lane half needs per 32-query group are contiguous
-        const int ld_pos = (ld_row & 32) + ((ld_row & 1) << 4) + (((ld_row & 31) >> 4) << 3) + (((ld_row >> 1) & 1) << 2) + ((ld_row >> 2) & 3);
-        float* const ld_dst = (wave & 1) ? &sDl[0][0] : &sL[0][0];
-        auto stage_ld = [&](int buf) {         // rows past the end of the list: LSE = +inf (weight 0), delta = 0
-            ld_dst[buf * QC + ld_pos] = rows_live ? lreg * ld_mul : ld_dead;
-        };
-        auto load_all = [&]() {
+        auto request_all = [&](int hc) {
+            if (role == 0) { read_ld_idx(hc + 5); dma_side(hc); }
+            read_idx(hc + 5);
 #pragma unroll
-            for (int i = 0; i < 2 * LOADS; ++i) load_piece(i);
-            load_ld_regs();
+            for (int i = 0; i < IPW; ++i) { dma_rows(hc + 5, i, 0); dma_rows(hc + 5, i, 1); }
         };
-        auto stage_all = [&](int buf) {
+        // Ends a step: what this wavefront requested up to two steps before has landed, then everybody's.  A step makes
+        // 2 * IPW requests (role 0: one more, first in the step).
+        auto end_step = [&](auto role_tag) {
+            VMOBA_WAIT_VMCNT(4 * IPW + (decltype(role_tag)::value == 0 ? 1 : 0));
+            __syncthreads();
+        };
+        // prologue: list entries of half-chunks 0..7, then rows of half-chunks 0..4, of which 0..2 have to be here
+        reinterpret_cast<int*>(smem + TL::IX0)[tid] = list[min(tid, cnt - 1)];
+        __syncthreads();
+        if (wave == 0) {
+            for (int x = 0; x < 5; ++x) { read_ld_idx(x); dma4(ld_base, ld_offset(x), ld_slot(x)); }
+        }
 #pragma unroll
-            for (int i = 0; i < 2 * LOADS; ++i) stage_piece(buf, i);
-            stage_ld(buf);
-        };
-        // prologue: chunks 0 and 1 staged, rows of chunk 2 in flight, indices of chunk 3 in flight
-        prefetch_idx(0);
-        load_all();
-        prefetch_idx(1);
-        stage_all(0);
-        load_all();
-        prefetch_idx(2);
-        stage_all(1);
-        load_all();
-        prefetch_idx(3);
+        for (int x = 0; x < 5; ++x) {
+            read_idx(x);
+#pragma unroll
+            for (int i = 0; i < IPW; ++i) { dma_rows(x, i, 0); dma_rows(x, i, 1); }
+        }
+        VMOBA_WAIT_VMCNT(4 * IPW);
+        __syncthreads();
 
         const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         // row operands come from the Q tile for wavefront 0 (S) and from the dO tile for wavefront 1 (dP);
         // transposed operands from the dO tile for wavefront 0 (dV) and from the Q tile for wavefront 1 (dK)
-        const __bf16* rows_tile = role == 0 ? &sQ[0][0] : &sdO[0][0];
-        const __bf16* tr_tile = role == 0 ? &sdO[0][0] : &sQ[0][0];
-        const float* ld_tile = role == 0 ? &sL[0][0] : &sDl[0][0];
-        const int row_lane = rho(l32) * STR + hf * 8;
-        const int tr_lane = tr_lane_offset<STR>(lane);
-        auto half_off = [&](int half) { return ((half >> 1) & (NBUF - 1)) * (QC * STR) + (half & 1) * 32 * STR; };
+        uint32_t rlane[NRB], tlane[2][D == 128 ? 1 : DT];
+        {
+            const int r = rho(l32), grp = r / TL::RPI, i = r % TL::RPI;
+#pragma unroll
+            for (int k = 0; k < NRB; ++k)
+                rlane[k] = (role == 0 ? 0u : (uint32_t)(NS * HB)) + (uint32_t)(grp * GP + i * RB + ((2 * k + hf) ^ TL::fsw(i)) * 16);
+            const int g4 = lane >> 4, e = (lane >> 2) & 3, a = lane & 3;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int tr = 4 * e + hf + 2 * t, tg = tr / TL::RPI, ti = tr % TL::RPI;
+#pragma unroll
+                for (int dt = 0; dt < (D == 128 ? 1 : DT); ++dt)
+                    tlane[t][dt] = (role == 0 ? (uint32_t)(NS * HB) : 0u) +
+                                   (uint32_t)(tg * GP + ti * RB + ((4 * dt + 2 * (g4 & 1) + (a >> 1)) ^ TL::fsw(ti)) * 16 + (a & 1) * 8);
+            }
+        }
+        auto half_off = [&](int half) { return (uint32_t)(half & (NS - 1)) * HB; };
         auto read_rows = [&](int half, int ks) {
-            return *reinterpret_cast<const bf16x8_t*>(rows_tile + half_off(half) + row_lane + ks * 16);
+            return *reinterpret_cast<const bf16x8_t*>(smem + (rlane[ks % NRB] + half_off(half)) + (ks / NRB) * 64);
+        };
+        auto read_tr_half = [&](int half, int step, int part) {     // one of the two 8-byte transpose reads of (s, dt) = (step / DT, step % DT)
+            const int s = step / DT, dt = step % DT;
+            const char* p = smem + (tlane[part][D == 128 ? 0 : dt] + half_off(half)) + s * (16 / TL::RPI) * GP + (D == 128 ? dt * 64 : 0);
+            return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(p));
         };
         auto read_tr = [&](int half, int step) {
-            return tr_operand<STR>(tr_tile + half_off(half) + tr_lane, 0, step / DT, (step % DT) * 32);
-        };
-        auto read_tr_half = [&](int half, int step, int part) {     // the two 8-byte transpose reads of read_tr, one at a time
-            const __bf16* pp = tr_tile + half_off(half) + tr_lane + (16 * (step / DT) + 2 * part) * STR + (step % DT) * 32;
-            return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(pp));
+            return __builtin_shufflevector(read_tr_half(half, step, 0), read_tr_half(half, step, 1), 0, 1, 2, 3, 4, 5, 6, 7);
         };
 
         if (pair_live) {
@@ -552,7 +614,6 @@ __device__ __forceinline__ void dkv_pair_body(
                 const bf16x8_t z8 = __builtin_shufflevector(zb, zb, 0, 1, 2, 3, 4, 5, 6, 7);
                 w_prev[0][0] = w_prev[0][1] = w_prev[1][0] = w_prev[1][1] = z8;
             }
-            __syncthreads();
             // S / dP of half-chunk 0
 #pragma unroll
             for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -561,20 +622,23 @@ __device__ __forceinline__ void dkv_pair_body(
                 for (int kg = 0; kg < 2; ++kg)
                     xa[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, frag[kg][ks], ks == 0 ? zero16 : xa[kg], 0, 0, 0);
             }
-            bf16x8_t rcur = read_rows(1, 0);
-            bf16x8_t tcur = read_tr(0, 0);                  // local step 0 multiplies it by zeros
-            u32x4_t* xbuf = &sX[pair][0][0][lane];          // + parity * 256 + slot * 64
+            bf16x8_t rop[4], top[4];                        // operands of k-steps st .. st + 2, slot = k-step % 4
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                rop[k] = read_rows(1, k);
+                top[k] = read_tr(0, k);                     // local step 0 multiplies them by zeros
+            }
+            u32x4_t* xbuf = reinterpret_cast<u32x4_t*>(smem + TL::X0) + pair * 2 * 4 * 64 + lane;     // + parity * 256 + slot * 64
 
-            // one local step; ROLE and EVEN (parity of the workgroup step hc = t + ROLE) are compile-time
+            // one local step; ROLE is compile-time
             // (x_cur holds S or dP of half-chunk t, x_nxt receives that of t + 1: the two sets swap roles every step)
-            auto local_step = [&](int t, auto role_tag, auto even_tag, f32x16_t(&x_cur)[2], f32x16_t(&x_nxt)[2]) {
+            auto local_step = [&](int t, auto role_tag, f32x16_t(&x_cur)[2], f32x16_t(&x_nxt)[2]) {
                 constexpr int ROLE = decltype(role_tag)::value;
-                constexpr bool EVEN = decltype(even_tag)::value;
                 const int hc = t + ROLE;
-                const int wbuf = ((hc >> 1) + 2) & (NBUF - 1);
+                asm volatile("" : "+v"(x_cur[0]), "+v"(x_cur[1]));      // whole registers across the loop, not 32 values
                 float ld[16];
                 {
-                    const float* lp = ld_tile + ((t >> 1) & (NBUF - 1)) * QC + (t & 1) * 32 + hf * 16;
+                    const float* lp = reinterpret_cast<const float*>(smem + TL::LD0) + (t & (NS - 1)) * 64 + ROLE * 32 + hf * 16;
 #pragma unroll
                     for (int g4 = 0; g4 < 4; ++g4) {
                         const f32x4_t a4 = *reinterpret_cast<const f32x4_t*>(lp + g4 * 4);
@@ -589,108 +653,99 @@ __device__ __forceinline__ void dkv_pair_body(
                 }
                 float w[2][16];
                 const int th = t > 0 ? t - 1 : 0;
+                static_for<NU>([&](auto unit) __attribute__((always_inline)) {
+                    constexpr int n = decltype(unit)::value, st = n >> 2, q = n & 3, kg = q >> 1;
+                    constexpr int s2 = st + 2;                  // the k-step whose operands are fetched now
+                    if (q == 0) rop[s2 & 3] = s2 < NST ? read_rows(t + 1, s2) : read_rows(t + 2, s2 - NST);
+                    if (q == 1) top[s2 & 3] = s2 < NST ? read_tr(th, s2) : read_tr(t, s2 - NST);
+                    if constexpr ((q & 1) == 0)
+                        x_nxt[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rop[st & 3], frag[kg][st], st == 0 ? zero16 : x_nxt[kg], 0, 0, 0);
+                    else
+                        mfma_acc(acc[kg][st % DT], top[st & 3], w_prev[kg][st / DT]);
+                    __builtin_amdgcn_sched_barrier(0);          // the matrix instruction leads its unit
+                    // the unit's share of the 32 values of P or dS, in the order (s, channel of s, key group)
+                    // (an ld passes through an empty assembly statement just before its turn: keeps the arithmetic on it in its unit)
+                    constexpr int V0 = first_value(n), V1 = first_value(n + 1);
+                    if constexpr (n == LEAD - 1) asm volatile("" : "+v"(ld[0]));
+                    static_for<V1 - V0>([&](auto value) __attribute__((always_inline)) {
+                        constexpr int v = V0 + decltype(value)::value, g2 = v & 1, i = v >> 1;
+                        if constexpr (ROLE == 0) {
+                            w[g2][i] = exp2_raw(fmaf(x_cur[g2][i], scale_log2, -ld[i]));
+                        } else {
+                            const u32x4_t pk = pin[g2 * 2 + i / 8];
+                            const uint32_t word = (i % 8) / 2 == 0 ? pk.x : (i % 8) / 2 == 1 ? pk.y : (i % 8) / 2 == 2 ? pk.z : pk.w;
+                            const float pval = (i & 1) ? bf16hi_to_f32(word) : bf16lo_to_f32(word);
+                            w[g2][i] = pval * (x_cur[g2][i] - ld[i]);
+                        }
+                        asm volatile("" : "+v"(w[g2][i]));
+                        if constexpr (g2 == 1 && i < 15) asm volatile("" : "+v"(ld[i + 1]));
+                    });
+                    // packed operands are replaced when their values are complete and their last reader of this step has issued
+                    constexpr int PACK0 = LEAD + 15 * (NU - LEAD) / 32;             // the unit of value 15
+                    static_assert(PACK0 >= NU / 2 - 1, "the readers of the first half have issued");
+                    if (n == PACK0 || n == NU - 1) {
+                        const int sidx = n == NU - 1 ? 1 : 0;
+#pragma unroll
+                        for (int k2 = 0; k2 < 2; ++k2) {
+                            w_prev[k2][sidx] = pack8(&w[k2][8 * sidx]);
+                            if constexpr (ROLE == 0) {
+                                u32x4_t o;
+                                __builtin_memcpy(&o, &w_prev[k2][sidx], 16);
+                                xbuf[(t & 1) * 256 + (k2 * 2 + sidx) * 64] = o;
+                            }
+                        }
+                    }
+                    // the step's requests
+                    if (n == 1) {
+                        read_idx(hc + 5);
+                        if (ROLE == 0) read_ld_idx(hc + 5);
+                    }
+                    if (ROLE == 0 && n == 5) dma_side(hc);
+                    if ((n & 1) == 0 && n >= 6 && n < 6 + 4 * IPW) dma_rows(hc + 5, (n - 6) / 4, ((n - 6) >> 1) & 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            using R0 = std::integral_constant<int, 0>;
+            using R1 = std::integral_constant<int, 1>;
+            // dV or dK of the last half-chunk, whose packed operand the last step left; nothing of S / dP outlives the loop
+            auto drain = [&]() {
 #pragma unroll
                 for (int st = 0; st < NST; ++st) {
-                    // four units per k-step, each one matrix instruction plus a quarter of everything else, fenced so
-                    // that the matrix instructions stay evenly spaced in the (in-order) instruction stream
-                    bf16x8_t rn;
-                    bf16x4_t tlo, thi;
-                    const bool last_st = st + 1 == NST;
+                    if (st + 2 < NST) top[(st + 2) & 3] = read_tr(H - 1, st + 2);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int kg = q >> 1;
-                        if (q == 0) rn = last_st ? read_rows(t + 2, 0) : read_rows(t + 1, st + 1);
-                        if (q == 1) tlo = last_st ? read_tr_half(t, 0, 0) : read_tr_half(th, st + 1, 0);
-                        if (q == 2) thi = last_st ? read_tr_half(t, 0, 1) : read_tr_half(th, st + 1, 1);
-                        if ((q & 1) == 0)
-                            x_nxt[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rcur, frag[kg][st], st == 0 ? zero16 : x_nxt[kg], 0, 0, 0);
-                        else
-                            acc[kg][st % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tcur, w_prev[kg][st / DT], acc[kg][st % DT], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);          // the matrix instruction leads its unit
-                        // the unit's VP values of P or dS: second half of this k-step's values when q is odd, key group kg
-#pragma unroll
-                        for (int u = 0; u < VP; ++u) {
-                            const int i = 2 * VP * st + VP * (q & 1) + u;
-                            if constexpr (ROLE == 0) {
-                                w[kg][i] = exp2_raw(fmaf(x_cur[kg][i], scale_log2, -ld[i]));
-                            } else {
-                                const u32x4_t pk = pin[kg * 2 + i / 8];
-                                const uint32_t word = (i % 8) / 2 == 0 ? pk.x : (i % 8) / 2 == 1 ? pk.y : (i % 8) / 2 == 2 ? pk.z : pk.w;
-                                const float pval = (i & 1) ? bf16hi_to_f32(word) : bf16lo_to_f32(word);
-                                w[kg][i] = pval * (x_cur[kg][i] - ld[i]);
-                            }
-                            asm volatile("" : "+v"(w[kg][i]));
-                        }
-                        // packed operands are replaced as soon as their last reader of this step has issued
-                        if (q == 3 && (st == NST / 2 - 1 || last_st)) {
-                            const int sidx = last_st ? 1 : 0;
-#pragma unroll
-                            for (int k2 = 0; k2 < 2; ++k2) {
-                                w_prev[k2][sidx] = pack8(&w[k2][8 * sidx]);
-                                if constexpr (ROLE == 0) {
-                                    u32x4_t o;
-                                    __builtin_memcpy(&o, &w_prev[k2][sidx], 16);
-                                    xbuf[(t & 1) * 256 + (k2 * 2 + sidx) * 64] = o;
-                                }
-                            }
-                        }
-                        if constexpr (EVEN) {
-                            if (q == 2) stage_piece(wbuf, st);
-                            if (q == 3) load_piece(st);
-                            if (st == 0 && q == 1) { stage_ld(wbuf); load_ld_regs(); }
-                        } else {
-                            if (4 * st + q <= LOADS) prefetch_idx_piece((hc >> 1) + 4, 4 * st + q);     // one index load per unit
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    rcur = rn;
-                    tcur = __builtin_shufflevector(tlo, thi, 0, 1, 2, 3, 4, 5, 6, 7);
+                    for (int kg = 0; kg < 2; ++kg)
+                        mfma_acc(acc[kg][st % DT], top[st & 3], w_prev[kg][st / DT]);
                 }
-            };
-            // a step in which this wavefront has no local step (hc = 0 for wavefront 1, hc = H + 1 for
-            // wavefront 0) still moves its share of the rows
-            auto idle_step = [&](int hc, auto even_tag) {
-                constexpr bool EVEN = decltype(even_tag)::value;
-                if constexpr (EVEN) {
-                    stage_all(((hc >> 1) + 2) & (NBUF - 1));
-                    load_all();
-                } else {
-                    prefetch_idx((hc >> 1) + 4);
-                }
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) { acc_ready(acc[0][dt]); acc_ready(acc[1][dt]); }
             };
             if (role == 0) {
-                for (int c = 0; c < n_chunks; ++c) {
-                    if (c > 0) __syncthreads();
-                    local_step(2 * c, std::integral_constant<int, 0>{}, std::true_type{}, xa, xb);
-                    __syncthreads();
-                    local_step(2 * c + 1, std::integral_constant<int, 0>{}, std::false_type{}, xb, xa);
+                for (int t = 0; t < H; t += 2) {
+                    local_step(t, R0{}, xa, xb);
+                    end_step(R0{});
+                    local_step(t + 1, R0{}, xb, xa);
+                    end_step(R0{});
                 }
-                __syncthreads();
-                local_step(H, std::integral_constant<int, 0>{}, std::true_type{}, xa, xb);       // drain: dV of the last half-chunk
-                __syncthreads();
-                idle_step(H + 1, std::false_type{});
+                drain();
             } else {
-                idle_step(0, std::true_type{});
-                for (int c = 0; c < n_chunks; ++c) {
-                    __syncthreads();
-                    local_step(2 * c, std::integral_constant<int, 1>{}, std::false_type{}, xa, xb);
-                    __syncthreads();
-                    local_step(2 * c + 1, std::integral_constant<int, 1>{}, std::true_type{}, xb, xa);
+                request_all(0);
+                for (int t = 0; t < H; t += 2) {
+                    end_step(R1{});
+                    local_step(t, R1{}, xa, xb);
+                    end_step(R1{});
+                    local_step(t + 1, R1{}, xb, xa);
                 }
-                __syncthreads();
-                local_step(H, std::integral_constant<int, 1>{}, std::false_type{}, xa, xb);      // drain: dK of the last half-chunk
+                drain();
             }
         } else {
             // a pair whose keys lie past the end of the block only helps to move rows
-            __syncthreads();
-            for (int c = 0; c <= n_chunks; ++c) {
-                if (c > 0) __syncthreads();
-                stage_all((c + 2) & (NBUF - 1));
-                load_all();
-                __syncthreads();
-                prefetch_idx(c + 4);
+            for (int hc = 0; hc < H; ++hc) {
+                request_all(hc);
+                if (role == 0) end_step(std::integral_constant<int, 0>{});
+                else end_step(std::integral_constant<int, 1>{});
             }
         }
+        VMOBA_WAIT_VMCNT(0);                   // no request may reach LDS that belongs to another workgroup by then
     }
     {
         const TensorView& dst = role == 0 ? dV : dK;
@@ -724,8 +779,8 @@ __device__ __forceinline__ void dkv_pair_body(
 // without workgroup barriers; the four partial dK^T / dV^T are added through LDS at the end.
 template <int D>
 __device__ __forceinline__ void dkv_tail_body(
-    char* smem, int bh, int rank, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO, const float* __restrict__ LSE,
-    const float* __restrict__ delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
+    char* smem, int bh, int rank, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+    const float* __restrict__ lse_delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int* __restrict__ kb_order, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
     const int* __restrict__ kv_rows, int Hh, int S, int nb, long long cap, float scale_log2, float scale) {
     constexpr int QC = 32;                       // queries per chunk
@@ -736,7 +791,7 @@ __device__ __forceinline__ void dkv_tail_body(
     __bf16(*sT)[4][QC * STR] = reinterpret_cast<__bf16(*)[4][QC * STR]>(smem);
     float(*sL)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * 4 * QC * STR * 2);
     float(*sDl)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * 4 * QC * STR * 2 + 4 * QC * 4);
-    static_assert(2 * 4 * QC * STR * 2 + 2 * 4 * QC * 4 <= dkv_pair_lds_bytes<D>(), "the tail body fits the pair body's LDS");
+    static_assert(2 * 4 * QC * STR * 2 + 2 * 4 * QC * 4 <= DkvTile<D>::BYTES, "the tail body fits the pair body's LDS");
     const int b = bh / Hh, h = bh % Hh;
     const int j = kb_order[(long long)bh * nb + rank];            // longest query list first
     const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
@@ -748,8 +803,8 @@ __device__ __forceinline__ void dkv_tail_body(
     const int list0 = blk_ptr[(long long)bh * (nb + 1) + j];
     const int cnt = blk_ptr[(long long)bh * (nb + 1) + j + 1] - list0;
     const int* list = q_idx + seg + list0;
-    const float* lse_h = LSE + (long long)bh * S;
-    const float* dl_h = delta + (long long)bh * S;
+    const float* lse_h = lse_delta + (long long)bh * 2 * lse_delta_pitch(S);
+    const float* dl_h = lse_h + lse_delta_pitch(S);
 
     // the tail keys: B operands (key = lane % 32); columns past the tail repeat the block's last key and are not written
     const bool key_live = l32 < tail;
@@ -821,7 +876,7 @@ __device__ __forceinline__ void dkv_tail_body(
             *reinterpret_cast<u32x4_t*>(&tdO[row * STR + pc * 8]) = r.d[i];
         }
         if (hf == 0) {                           // rows past the end of the list: LSE = +inf (weight 0), delta = 0
-            tL[ld_pos] = r.live ? r.l * LOG2E : INFINITY;
+            tL[ld_pos] = r.live ? r.l : INFINITY;
             tDl[ld_pos] = r.live ? r.dl : 0.f;
         }
     };
@@ -925,11 +980,11 @@ __device__ __forceinline__ void dkv_tail_body(
 // rather than per head, and the short tail workgroups fill its end, where the long runs finish unevenly.
 template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
+    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
     const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int* __restrict__ kb_start, const int* __restrict__ kb_order, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int nb, long long cap,
     float scale_log2, float scale, const int* __restrict__ kv_rows, int BH, int slots, int group) {
-    __shared__ __align__(16) char smem[dkv_pair_lds_bytes<D>()];
+    __shared__ __align__(16) char smem[DkvTile<D>::BYTES];
     // One-dimensional grid.  Workgroup i runs on XCD i % 8 as that XCD's workgroup number i / 8.  A head's slots are cut
     // into groups of `group` consecutive slots (the runs of one key block, when the blocks are equally long); groups are
     // numbered slot group first, head second -- longest query lists first over the whole launch -- and dealt to the XCDs
@@ -942,9 +997,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(
     const int id = (G / BH) * group + n % group;
     const int runs = kb_start[(long long)bh * (nb + 1) + nb];
     if (id < runs)
-        dkv_pair_body<D>(smem, bh, id, Q, K, V, dO, LSE, delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, dK, dV, rows, kv_rows, Hh, S, nb, cap, scale_log2, scale);
+        dkv_pair_body<D>(smem, bh, id, Q, K, V, dO, lse_delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, dK, dV, rows, kv_rows, Hh, S, nb, cap, scale_log2, scale);
     else if (id - runs < nb)
-        dkv_tail_body<D>(smem, bh, id - runs, Q, K, V, dO, LSE, delta, blk_off, blk_ptr, q_idx, kb_order, dK, dV, rows, kv_rows, Hh, S, nb, cap, scale_log2, scale);
+        dkv_tail_body<D>(smem, bh, id - runs, Q, K, V, dO, lse_delta, blk_off, blk_ptr, q_idx, kb_order, dK, dV, rows, kv_rows, Hh, S, nb, cap, scale_log2, scale);
 }
 
 // dQ[q] = scale * sum over the query's pairs of dQpart[pair]; the partials have the tensors' type.  A head whose
@@ -1007,7 +1062,7 @@ __global__ __launch_bounds__(256) void dq_merge_kernel(const float* __restrict__
 
 struct BwdWs {
     float* dQpart;     // [BH * cap][D], in the tensors' type
-    float* delta;      // [BH][S]
+    float* delta;      // bfloat16: LSE * log2(e) and delta, [BH][2][lse_delta_pitch(S)]; float32: delta, [BH][S]
     int4* tile_desc;   // the flat list of all heads' tiles
     int* n_tiles;      // its length
     int* kb_start;     // [BH][nb + 1]
@@ -1021,7 +1076,7 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {
     char* p = (char*)base;
     size_t off = 0;
     w.dQpart = (float*)(p + off);    off += align_up((size_t)BH * cap * D * es, 256);
-    w.delta = (float*)(p + off);     off += align_up((size_t)BH * S * 4, 256);
+    w.delta = (float*)(p + off);     off += align_up((size_t)BH * (es == 2 ? 2 * (size_t)lse_delta_pitch((int)S) : (size_t)S) * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
@@ -1086,7 +1141,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         const dim3 grid((unsigned)(n_delta + ceil_div64(max_tiles, 256) + 1), (unsigned)BH);
         auto kfn = bf16 ? (D == 128 ? bwd_prepare_kernel<true, 128> : bwd_prepare_kernel<true, 64>)
                         : (D == 128 ? bwd_prepare_kernel<false, 128> : bwd_prepare_kernel<false, 64>);
-        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, ws.kb_start, ws.kb_order,
+        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, ws.kb_start, ws.kb_order,
                                         BH, Hh, (int)S, n_blocks, TM, KPW, bf16 ? 32 : 0, n_delta);
         VMOBA_CHECK_LAUNCH();
     }
@@ -1104,7 +1159,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
             launch_dq_tiles_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
                                 (long long)nnz_capacity, scale_log2, kv_rows);
         } else {
-#define DQ_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
+#define DQ_ARGS Qv, Kv, Vv, dOv, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
             if (D == 128) attn_bwd_dq_mfma_kernel<128><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
             else attn_bwd_dq_mfma_kernel<64><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
 #undef DQ_ARGS
@@ -1132,13 +1187,13 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         const int slots = (int)ceil_div64(grid.x, group) * group;
         VMOBA_PROFILE_BEGIN(2, st);
         const int32_t* krows = key_rows ? key_rows : rows;      // row map of dK and dV
-#define DKV_ARGS Qv, Kv, Vv, dOv, LSE, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
+#define DKV_ARGS blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
         if (!bf16) {
-            launch_dkv_f32(D, grid, st, DKV_ARGS);
+            launch_dkv_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, DKV_ARGS);
         } else {
             const dim3 hgrid((unsigned)(ceil_div64((int64_t)BH * slots, 8) * 8 + 7 * group));   // see the kernel
-            if (D == 128) attn_bwd_dkv_kernel<128><<<hgrid, dim3(256), 0, st>>>(DKV_ARGS, BH, slots, group);
-            else attn_bwd_dkv_kernel<64><<<hgrid, dim3(256), 0, st>>>(DKV_ARGS, BH, slots, group);
+            if (D == 128) attn_bwd_dkv_kernel<128><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
+            else attn_bwd_dkv_kernel<64><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
         }
 #undef DKV_ARGS
         VMOBA_PROFILE_END(2, st);
