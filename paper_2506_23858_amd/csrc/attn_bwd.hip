@@ -22,7 +22,7 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 
 // ---------------------------------------------------------------------------------------------
-// The bfloat16 kernels read LSE * log2(e) and delta from [head][2][pitch] floats: element S of either is what a row past the
+// The bfloat16 kernels read LSE * log2(e) and -delta from [head][2][pitch] floats: element S of either is what a row past the
 // end of a query list reads (LSE +inf, i.e. weight 0, and delta 0).  The float32 kernels read delta from [head][S].
 __host__ __device__ constexpr int lse_delta_pitch(int S) { return (S + 64) / 64 * 64; }
 
@@ -63,7 +63,7 @@ __device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView
         if constexpr (BF16) {
             float* d = delta + (long long)bh * 2 * lse_delta_pitch(S) + q;
             d[0] = LSE[(long long)bh * S + q] * LOG2E;
-            d[lse_delta_pitch(S)] = acc;
+            d[lse_delta_pitch(S)] = -acc;
         } else {
             delta[(long long)bh * S + q] = acc;
         }
@@ -126,29 +126,84 @@ __device__ __forceinline__ T load_at(const void* base, uint32_t byte_off) {
 }
 
 // ---------------------------------------------------------------------------------------------
+// Rows of Q, K, V and dO go from global memory to LDS without passing through registers (global_load_lds, inline assembly, waits
+// written by hand): the 64 lanes of one request write 1024 consecutive bytes, i.e. RPI = 4 (8) rows of D = 128 (64) channels.
+// Such groups of rows lie GP bytes apart, and 16-byte piece p of a group's row i sits at piece position p ^ fsw(i).  Row and
+// transposed reads are then free of bank conflicts, and for D = 128 only the two low bits of a piece position depend on the
+// row, so that two per-lane addresses and immediate offsets reach every operand of a tile.
+template <int D>
+struct RowTile {
+    static constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;
+    static constexpr int GP = D == 128 ? 1024 + 64 : 1024 + 144;       // bytes between groups of RPI rows
+    static constexpr int HB = 32 / RPI * GP;                           // bytes of 32 rows
+    static constexpr int DT = D / 32;
+    static constexpr int NRB = D == 128 ? 2 : 4;                       // distinct per-lane addresses of the row reads
+    static constexpr int NTB = D == 128 ? 1 : DT;                      // and, for each half, of the transposed reads
+    __device__ static __forceinline__ int fsw(int i) { return D == 128 ? i : 2 * ((i >> 1) & 1) + 4 * (i >> 2); }
+    // byte offset inside a row that lane `lane` of a request fetches
+    __device__ static __forceinline__ uint32_t request_piece(int lane) { return (uint32_t)((lane % PPR) ^ fsw(lane / PPR)) * 16; }
+    // Per-lane addresses of the operands of a 32-row tile: contraction over the channels (row rho(l32), k-step ks) ...
+    __device__ static __forceinline__ uint32_t row_lane(int lane, int ks) {
+        const int r = rho(lane & 31), hf = lane >> 5;
+        return (uint32_t)(r / RPI * GP + r % RPI * RB + ((2 * ks + hf) ^ fsw(r % RPI)) * 16);
+    }
+    // ... and over the rows (see tr_lane_offset; half t of the operand, channel tile dt)
+    __device__ static __forceinline__ uint32_t tr_lane(int lane, int t, int dt) {
+        const int g4 = lane >> 4, e = (lane >> 2) & 3, a = lane & 3, hf = lane >> 5;
+        const int r = 4 * e + hf + 2 * t;
+        return (uint32_t)(r / RPI * GP + r % RPI * RB + ((4 * dt + 2 * (g4 & 1) + (a >> 1)) ^ fsw(r % RPI)) * 16 + (a & 1) * 8);
+    }
+    // Operands at byte offset `tile` of `base`; rl = row_lane(., 0 .. NRB - 1), tl = tr_lane(., 0 .. 1, 0 .. NTB - 1)
+    __device__ static __forceinline__ bf16x8_t rows(const char* base, const uint32_t* rl, uint32_t tile, int ks) {
+        return *reinterpret_cast<const bf16x8_t*>(base + (rl[ks % NRB] + tile) + (ks / NRB) * 64);
+    }
+    __device__ static __forceinline__ bf16x8_t transposed(const char* base, const uint32_t (*tl)[NTB], uint32_t tile, int s, int dt) {
+        bf16x4_t h[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (lds_bf16x4_t*)(base + (tl[t][NTB == 1 ? 0 : dt] + tile) + s * (16 / RPI) * GP + (NTB == 1 ? dt * 64 : 0)));
+        return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+};
+
+// 64 lanes x 16 bytes, row `row` of a matrix of `stride` bytes per row (both below 2^24), byte `piece` of it, to LDS lds + IMM.
+template <int IMM>
+__device__ __forceinline__ void dma_row16(const char* base, uint32_t row, uint32_t stride, uint32_t piece, uint32_t lds) {
+    uint32_t off;
+    asm volatile("s_add_u32 m0, %5, %6\n\tv_mad_u32_u24 %0, %1, %2, %3\n\tglobal_load_lds_dwordx4 %0, %4"
+                 : "=&v"(off) : "v"(row), "s"(stride), "v"(piece), "s"(base), "s"(lds), "i"(IMM) : "memory", "m0", "scc");
+}
+
+// ---------------------------------------------------------------------------------------------
 // bf16 MFMA dQ tile kernel.  Same decomposition and operand orientation as the forward tile
 // kernel (query = MFMA column = lane % 32); 4 wavefronts x 32 gathered queries, key chunks of 64:
 //   S^T  = K . Q^T                    A = K rows (LDS),  B = Q^T (registers)
 //   dP^T = V . dO^T                   A = V rows (LDS),  B = dO^T (registers)
 //   dS^T = P^T * (dP^T - delta)       in registers, packed to bf16 as the next B operand
 //   dQ^T += K^T . dS^T                A = K^T by transpose reads of the same K tile
+//
+// The key chunks pass through two LDS buffers, requested one chunk ahead straight from global memory (no registers hold rows in
+// flight; one barrier per chunk).  Before: staged through 32 registers with two barriers per chunk, the end of the block tested in
+// every 32-key group and delta subtracted value by value (now the value the sum for dP starts from): 8.6 instructions per
+// matrix instruction and more, now 6.1.  480p, 12 heads, 1D / 2D / 3D partition: 1.89 / 1.83 / 1.48 -> 1.74 / 1.66 / 1.34 ms.
+// (An operand ring of six instead of four registers changes nothing; fetching operands in pairs makes D = 64 16 % slower.)
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
-    const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, float* __restrict__ dQpart, int Hh, int S, int nb,
+    const int* __restrict__ q_idx, const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, float* __restrict__ dQpart, int Hh, int S,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
-    constexpr int TM = 128, KC = 64;
-    constexpr int STR = D + 8;
+    using TL = RowTile<D>;
+    constexpr int KC = 64;                      // keys per chunk
     constexpr int KSTEPS = D / 16, DT = D / 32;
-    constexpr int LOADS = KC * D * 2 / 16 / 256;
-    __shared__ __align__(1024) char sKV[2 * KC * STR * 2];                     // the K tile, then the V tile
-    __bf16* const sK = reinterpret_cast<__bf16*>(sKV);
-    __bf16* const sV = reinterpret_cast<__bf16*>(sKV + KC * STR * 2);
-    // a wavefront's 32 partial rows on their way out: written as the accumulators hold them, read back as whole rows
+    constexpr int GP = TL::GP, HB = TL::HB, RB = TL::RB, PPR = TL::PPR, RPI = TL::RPI;
+    constexpr int BUF = 4 * HB;                 // a chunk: 64 rows of K, then 64 rows of V
+    constexpr int IPW = KC / RPI / 4;           // requests per wavefront, tensor and chunk
+    __shared__ __align__(1024) char smem[2 * BUF];
+    // The gathered rows of Q and dO pass through the second buffer on their way in; the wavefront's 32 partial rows, through the
+    // first on their way out: written as the accumulators hold them, read back as whole rows.
     constexpr int OPITCH = D * 2 + 16;
-    __shared__ __align__(1024) char sOut[4 * 32 * OPITCH];
-    static_assert(4 * 32 * D * 2 <= 2 * KC * STR * 2, "the gathered Q rows of the four wavefronts fit the K/V tiles");
+    static_assert(4 * 32 * RB <= BUF && 4 * 32 * OPITCH <= BUF, "rows of the four wavefronts fit a buffer");
 
     // One workgroup per tile of the flat list (all heads).  Workgroup ids go round the 8 XCDs, so XCD x = id % 8 takes the
     // x-th eighth of the list: a key block's tiles then share one L2 instead of eight (gridDim.x is a multiple of 8).
@@ -172,77 +227,75 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     const int ent = wave * 32 + l32;
     const int e = min(ent, tc.count - 1);
     const int q = q_idx[seg + tc.list0 + tc.t0 + e];
-    // The wavefront's 32 gathered rows of Q' and of dO go straight to LDS, a whole row per 16 (8) lanes -- one request
-    // covers 4 (8) rows instead of a 32-byte piece of 32 rows -- into the K/V tiles (Q') and the output staging (dO),
-    // both idle at this point; piece p of row r sits at slot p ^ (r % pieces), which keeps the fragment reads below
-    // free of bank conflicts.  Each wavefront reads back only what it wrote.
-    constexpr int RB = D * 2, PPR = RB / 16, RPI = 64 / PPR;     // row bytes, 16-byte pieces per row, rows per request
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const uint32_t gq0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sKV + (uint32_t)wave_u * 32 * RB;
-    const uint32_t gd0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sOut + (uint32_t)wave_u * 32 * OPITCH;
-    {
-        const char* qb = Q.ptr + ((long long)b * Q.stride_b + (long long)h * Q.stride_h) * 2;
-        const char* db = dO.ptr + ((long long)b * dO.stride_b + (long long)h * dO.stride_h) * 2;
-        const uint32_t qss = (uint32_t)(Q.stride_s * 2), doss = (uint32_t)(dO.stride_s * 2);     // host-checked: 24-bit
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+
+    const char* kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * 2;
+    const char* vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * 2;
+    // row strides in bytes: below 2^24 and rows below 2^24, so a row's offset is one 24-bit multiply (host-checked)
+    const uint32_t kss = (uint32_t)(K.stride_s * 2), vss = (uint32_t)(V.stride_s * 2);
+    const uint32_t pc16 = TL::request_piece(lane);
+    const int n_chunks = (tc.L + KC - 1) / KC;
+    // Requests of a chunk: request i of this wavefront fetches rows (wave * IPW + i) * RPI + lane / PPR of it, of K and of V.
+    // krow: where these keys lie -- the key positions themselves or, with keys in place, what kv_rows says, looked up one chunk
+    // before the rows are requested.
+    uint32_t krow[IPW];
+    auto lookup_rows = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < IPW; ++i) {
+            const uint32_t pos = (uint32_t)(tc.k0 + min(c * KC + (wave * IPW + i) * RPI + lane / PPR, tc.L - 1));
+            krow[i] = kv_rows ? (uint32_t)kv_rows[pos] : pos;
+        }
+    };
+    auto request = [&](int c, int i, int tensor) {
+        const uint32_t l = lds0 + (uint32_t)(c & 1) * BUF + (uint32_t)(wave_u * IPW + i) * GP;
+        if (tensor == 0) dma_row16<0>(kbase, krow[i], kss, pc16, l);
+        else dma_row16<2 * HB>(vbase, krow[i], vss, pc16, l);
+    };
+    // The wavefront's 32 gathered rows of Q, then those of dO, go to LDS as whole rows as well (one request covers 4 (8)
+    // rows instead of a 32-byte piece of 32 rows); piece p of row r sits at slot p ^ (r % pieces), which keeps the fragment reads
+    // free of bank conflicts.  A wavefront reads back only what it requested: no barrier.
+    const uint32_t g0 = lds0 + BUF + (uint32_t)wave_u * 32 * RB;
+    auto gather = [&](const char* base, uint32_t stride) {
 #pragma unroll
         for (int k = 0; k < 32 / RPI; ++k) {
             const int r = k * RPI + lane / PPR;
-            const uint32_t qr = (uint32_t)__shfl(q, r, 64);
             const uint32_t pc = (uint32_t)(((lane % PPR) ^ (r & (PPR - 1))) * 16);
-            dma16(qb, __umul24(qr, qss) + pc, gq0 + k * 1024);
-            dma16(db, __umul24(qr, doss) + pc, gd0 + k * 1024);
+            dma16(base, __umul24((uint32_t)__shfl(q, r, 64), stride) + pc, g0 + k * 1024);
         }
-    }
+    };
+    auto fragments = [&](bf16x8_t* f) {
+        const char* g = smem + BUF + wave_u * 32 * RB + l32 * RB;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) f[ks] = *reinterpret_cast<const bf16x8_t*>(g + ((2 * ks + hf) ^ (l32 & (PPR - 1))) * 16);
+    };
+    bf16x8_t qf[KSTEPS], dof[KSTEPS];
+    lookup_rows(0);
+    gather(Q.ptr + ((long long)b * Q.stride_b + (long long)h * Q.stride_h) * 2, (uint32_t)(Q.stride_s * 2));
     const float lse2 = lse_delta[(long long)bh * 2 * lse_delta_pitch(S) + q];
-    const float dl = lse_delta[((long long)bh * 2 + 1) * lse_delta_pitch(S) + q];
+    const float ndl = lse_delta[((long long)bh * 2 + 1) * lse_delta_pitch(S) + q];
+    VMOBA_WAIT_VMCNT(0);
+    asm volatile("" ::: "memory");
+    fragments(qf);
+    __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0): the fragments have been read, their place is free
+    asm volatile("" ::: "memory");
+    gather(dO.ptr + ((long long)b * dO.stride_b + (long long)h * dO.stride_h) * 2, (uint32_t)(dO.stride_s * 2));
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) { request(0, i, 0); request(0, i, 1); }
+    lookup_rows(1);
 
     f32x16_t dqacc[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) dqacc[dt][i] = 0.f;
-
-    const char* kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * 2;
-    const char* vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * 2;
-    // row strides in bytes: below 2^24 and rows below 2^24, so a row's offset is one 24-bit multiply (host-checked)
-    const uint32_t kss = (uint32_t)(K.stride_s * 2), vss = (uint32_t)(V.stride_s * 2);
-    const int n_chunks = (tc.L + KC - 1) / KC;
-
-    u32x4_t kreg[LOADS], vreg[LOADS];
-    // rows of K and V that hold the keys of the chunk to be fetched next: the key positions themselves, or, with keys in
-    // place, what kv_rows says -- looked up one chunk before the rows are fetched, so that two dependent loads never
-    // sit in one chunk's shadow
-    uint32_t krow_n[LOADS];
-    auto lookup_rows = [&](int c) {
-        const int c0 = c * KC;
+    uint32_t rlane[TL::NRB], tlane[2][TL::NTB];
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int r = (tid + 256 * i) / (D / 8);
-            const uint32_t pos = (uint32_t)(tc.k0 + min(c0 + r, tc.L - 1));
-            krow_n[i] = kv_rows ? (uint32_t)kv_rows[pos] : pos;
-        }
-    };
-    auto prefetch = [&](int c) {
+    for (int k = 0; k < TL::NRB; ++k) rlane[k] = TL::row_lane(lane, k);
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int pc = (tid + 256 * i) % (D / 8);
-            kreg[i] = load_at<u32x4_t>(kbase, __umul24(krow_n[i], kss) + pc * 16);
-            vreg[i] = load_at<u32x4_t>(vbase, __umul24(krow_n[i], vss) + pc * 16);
-        }
-        lookup_rows(c + 1);
-    };
-    auto stage = [&]() {
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int piece = tid + 256 * i;
-            const int r = piece / (D / 8), pc = piece % (D / 8);
-            *reinterpret_cast<u32x4_t*>(&sK[r * STR + pc * 8]) = kreg[i];
-            *reinterpret_cast<u32x4_t*>(&sV[r * STR + pc * 8]) = vreg[i];
-        }
-    };
-    const __bf16* sK_lane = sK + rho(l32) * STR + hf * 8;
-    const __bf16* sV_lane = sV + rho(l32) * STR + hf * 8;
-    const __bf16* sKt_lane = sK + tr_lane_offset<STR>(lane);
+        for (int dt = 0; dt < TL::NTB; ++dt) tlane[t][dt] = TL::tr_lane(lane, t, dt);
 
     // A 32-key group is a sequence of 2 * KSTEPS + NU matrix instructions: S^T over the k-steps, dP^T over the k-steps
     // (with P = exp(S - LSE) computed between them), then the third product, first over the keys whose dS is ready
@@ -253,64 +306,58 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     constexpr int NSEQ = 2 * KSTEPS + NU;
     constexpr int AHEAD = 3, RING = AHEAD + 1;
     static_assert(NSEQ % RING == 0, "the second group continues the ring where the first one left it");
-    auto fetch = [&](int mt, int n) -> bf16x8_t {     // operand of instruction n of group mt (n past the end: next group)
+    auto fetch = [&](uint32_t buf, int mt, int n) -> bf16x8_t {     // operand of instruction n of group mt (n past the end: next group)
         if (n >= NSEQ) { mt += 1; n -= NSEQ; }
-        if (n < KSTEPS) return *reinterpret_cast<const bf16x8_t*>(sK_lane + mt * 32 * STR + n * 16);
-        if (n < 2 * KSTEPS) return *reinterpret_cast<const bf16x8_t*>(sV_lane + mt * 32 * STR + (n - KSTEPS) * 16);
+        if (n < KSTEPS) return TL::rows(smem, rlane, buf + mt * HB, n);
+        if (n < 2 * KSTEPS) return TL::rows(smem, rlane, buf + (2 + mt) * HB, n - KSTEPS);
         const int u = n - 2 * KSTEPS;
-        return tr_operand<STR>(sKt_lane, mt * 32, u / DT, (u % DT) * 32);
+        return TL::transposed(smem, tlane, buf + mt * HB, u / DT, u % DT);
     };
-    lookup_rows(0);
-    prefetch(0);
-    bf16x8_t qf[KSTEPS], dof[KSTEPS];
-    VMOBA_WAIT_VMCNT(0);                       // the gathered rows have landed (and the first key chunk with them)
+    VMOBA_WAIT_VMCNT(0);
     asm volatile("" ::: "memory");
-    {
-        const char* gq = sKV + wave_u * 32 * RB + l32 * RB;
-        const char* gd = sOut + wave_u * 32 * OPITCH + l32 * RB;
+    fragments(dof);
+    __syncthreads();                           // the first chunk has landed, the second buffer is free
+    // MASK: the block ends inside the chunk (keys past the end get weight 0).  A separate body, because as a condition inside
+    // one body it costs every 32-key group 45 predicated instructions beside its 24 matrix instructions.
+    auto chunk = [&](int c, auto mask_tag) __attribute__((always_inline)) {
+        constexpr bool MASK = decltype(mask_tag)::value;
+        const uint32_t buf = (uint32_t)(c & 1) * BUF;
+        const bool more = c + 1 < n_chunks;
+        if (more) {
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int slot = (2 * ks + hf) ^ (l32 & (PPR - 1));
-            qf[ks] = *reinterpret_cast<const bf16x8_t*>(gq + slot * 16);
-            dof[ks] = *reinterpret_cast<const bf16x8_t*>(gd + slot * 16);
+            for (int i = 0; i < IPW; ++i) { request(c + 1, i, 0); request(c + 1, i, 1); }
+            lookup_rows(c + 2);
         }
-    }
-    for (int c = 0; c < n_chunks; ++c) {
-        __syncthreads();
-        stage();
-        __syncthreads();
-        if (c + 1 < n_chunks) prefetch(c + 1);
         const int valid = tc.L - c * KC;
-        const int n_mt = valid > 32 ? 2 : 1;
         bf16x8_t op[RING];
 #pragma unroll
-        for (int n = 0; n < RING; ++n) op[n] = fetch(0, n < AHEAD ? n : 0);
+        for (int n = 0; n < RING; ++n) op[n] = fetch(buf, 0, n < AHEAD ? n : 0);
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-            if (mt < n_mt) {
+            if (!MASK || mt * 32 < valid) {
                 f32x16_t sacc, dpacc;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = 0.f; }
+                for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = ndl; }        // the sum for dP - delta starts at -delta
                 float ds[16];
                 bf16x8_t dsf;
                 auto p_value = [&](int i) {           // S^T value -> P^T value, in place
                     sacc[i] = exp2_raw(fmaf(sacc[i], scale_log2, -lse2));
                 };
                 auto ds_value = [&](int i) {
-                    ds[i] = sacc[i] * (dpacc[i] - dl);
+                    ds[i] = sacc[i] * dpacc[i];
                     asm volatile("" : "+v"(ds[i]));
                 };
 #pragma unroll
                 for (int n = 0; n < NSEQ; ++n) {
                     // the operand AHEAD instructions on (the group after the second one waits for the next chunk)
-                    if (n + AHEAD < NSEQ || mt == 0) op[(n + AHEAD) % RING] = fetch(mt, n + AHEAD);
+                    if (n + AHEAD < NSEQ || mt == 0) op[(n + AHEAD) % RING] = fetch(buf, mt, n + AHEAD);
                     if (n < KSTEPS) {
                         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[n % RING], qf[n], sacc, 0, 0, 0);
                     } else if (n < 2 * KSTEPS) {
                         const int ks = n - KSTEPS;
                         dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[n % RING], dof[ks], dpacc, 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
-                        if (ks == 0 && valid < KC) {      // last chunk (uniform branch): keys past the block get weight 0
+                        if (MASK && ks == 0) {
                             const int vh = valid - mt * 32 - hf;
 #pragma unroll
                             for (int i = 0; i < 16; ++i)
@@ -336,10 +383,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
                 }
             }
         }
-    }
+        VMOBA_WAIT_VMCNT(0);                   // the next chunk has landed (this wavefront's share)
+        __syncthreads();
+    };
+    const int n_full = tc.L / KC;
+    for (int c = 0; c < n_full; ++c) chunk(c, std::false_type{});
+    if (n_full < n_chunks) chunk(n_full, std::true_type{});
     {
         // the tile's partials are consecutive rows of dQpart (bfloat16): stores of 1 KB runs instead of 16-byte pieces
-        char* mine = sOut + wave * 32 * OPITCH;                               // this wavefront's rows only: no barrier
+        char* mine = smem + wave * 32 * OPITCH;                               // this wavefront's rows only: no barrier
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -394,10 +446,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 // barrier as well -11 %, without the operand reads from LDS -13 %: no single limiter.)
 // Rows past the end of the list repeat its last entry; their LSE is +inf (weight 0) and their delta 0, read from a
 // spare element behind the head's S values.
-// Tile layout: the 64 lanes of one request write 1024 consecutive bytes, i.e. RPI = 4 (8) rows of D = 128 (64) channels; such
-// groups lie GP bytes apart, and 16-byte piece p of a group's row i sits at piece position p ^ fsw(i).  Row and transposed
-// reads are then free of bank conflicts, and for D = 128 only the two low bits of a piece position depend on the row, so
-// that two per-lane addresses and immediate offsets reach every operand.
 //
 // A wavefront issues in order and a matrix instruction occupies the matrix pipe for 32 cycles, so the step is cut
 // into units of one matrix instruction followed by an equal share of the vector, LDS and memory instructions,
@@ -406,26 +454,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 // step carry no vector work: it needs P and LSE / delta, which are only requested from LDS at the start of the step.
 // S / dP of even and odd half-chunks live in two register sets that swap roles, so no accumulator is ever copied.
 template <int D>
-struct DkvTile {
-    static constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;
-    static constexpr int GP = D == 128 ? 1024 + 64 : 1024 + 144;       // bytes between groups of RPI rows
-    static constexpr int HB = 32 / RPI * GP;                           // bytes of a half-chunk
+struct DkvLds : RowTile<D> {
+    using RowTile<D>::HB;
     static constexpr int NS = 8;                                       // half-chunks per ring
     static constexpr int LD0 = 2 * NS * HB;                            // LSE and delta: [NS][64] floats
     static constexpr int IX0 = LD0 + NS * 64 * 4;                      // list entries: [NS + 1][32]; a request fills two half-chunks
     static constexpr int X0 = IX0 + (NS + 1) * 32 * 4;                 // packed P: [pair][step parity][key group * 2 + s][lane]
     static constexpr int BYTES = X0 + 2 * 2 * 4 * 64 * 16;
     static_assert(X0 % 16 == 0 && BYTES <= 160 * 1024, "LDS of one compute unit");
-    __device__ static __forceinline__ int fsw(int i) { return D == 128 ? i : 2 * ((i >> 1) & 1) + 4 * (i >> 2); }
 };
-
-// 64 lanes x 16 bytes, row `row` of a matrix of `stride` bytes per row (both below 2^24), byte `piece` of it, to LDS lds + IMM.
-template <int IMM>
-__device__ __forceinline__ void dma_row16(const char* base, uint32_t row, uint32_t stride, uint32_t piece, uint32_t lds) {
-    uint32_t off;
-    asm volatile("s_add_u32 m0, %5, %6\n\tv_mad_u32_u24 %0, %1, %2, %3\n\tglobal_load_lds_dwordx4 %0, %4"
-                 : "=&v"(off) : "v"(row), "s"(stride), "v"(piece), "s"(base), "s"(lds), "i"(IMM) : "memory", "m0", "scc");
-}
 
 // f(0), f(1), ... f(N - 1) with the index as a compile-time constant.
 template <int N, int I = 0, class F>
@@ -452,11 +489,10 @@ __device__ __forceinline__ void dkv_pair_body(
     const float* __restrict__ lse_delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int* __restrict__ kb_start, const int* __restrict__ kb_order, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
     const int* __restrict__ kv_rows, int Hh, int S, int nb, long long cap, float scale_log2, float scale) {
-    using TL = DkvTile<D>;
+    using TL = DkvLds<D>;
     constexpr int KSTEPS = D / 16, DT = D / 32, NST = KSTEPS;
     constexpr int IPW = 32 / TL::RPI / 4;     // row requests per wavefront, tensor and half-chunk
-    constexpr int NS = TL::NS, HB = TL::HB, GP = TL::GP, RB = TL::RB;
-    constexpr int NRB = D == 128 ? 2 : 4;     // distinct per-lane addresses of the row reads
+    constexpr int NS = TL::NS, HB = TL::HB, GP = TL::GP;
     constexpr int NU = 4 * NST, LEAD = 4;     // units per step; units without vector work
     static_assert(NST == 2 * DT && NST % 4 == 0, "one k-step and one (s, dt) step per step, operand ring of four");
 
@@ -516,7 +552,7 @@ __device__ __forceinline__ void dkv_pair_body(
 
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
         const int* sIdx = reinterpret_cast<const int*>(smem + TL::IX0);
-        const uint32_t pc16 = (uint32_t)((lane % TL::PPR) ^ TL::fsw(lane / TL::PPR)) * 16;
+        const uint32_t pc16 = TL::request_piece(lane);
         const int idx_row = wave * IPW * TL::RPI + lane / TL::PPR;           // + i * RPI: row of request i this lane takes part in
         // LSE / delta: lanes 0..31 request LSE, lanes 32..63 delta; lane l % 32 = position p holds row ld_row (accumulator
         // order: the 16 values a lane half needs are contiguous)
@@ -576,34 +612,16 @@ __device__ __forceinline__ void dkv_pair_body(
         const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         // row operands come from the Q tile for wavefront 0 (S) and from the dO tile for wavefront 1 (dP);
         // transposed operands from the dO tile for wavefront 0 (dV) and from the Q tile for wavefront 1 (dK)
-        uint32_t rlane[NRB], tlane[2][D == 128 ? 1 : DT];
-        {
-            const int r = rho(l32), grp = r / TL::RPI, i = r % TL::RPI;
+        uint32_t rlane[TL::NRB], tlane[2][TL::NTB];
 #pragma unroll
-            for (int k = 0; k < NRB; ++k)
-                rlane[k] = (role == 0 ? 0u : (uint32_t)(NS * HB)) + (uint32_t)(grp * GP + i * RB + ((2 * k + hf) ^ TL::fsw(i)) * 16);
-            const int g4 = lane >> 4, e = (lane >> 2) & 3, a = lane & 3;
+        for (int k = 0; k < TL::NRB; ++k) rlane[k] = (role == 0 ? 0u : (uint32_t)(NS * HB)) + TL::row_lane(lane, k);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int tr = 4 * e + hf + 2 * t, tg = tr / TL::RPI, ti = tr % TL::RPI;
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int dt = 0; dt < (D == 128 ? 1 : DT); ++dt)
-                    tlane[t][dt] = (role == 0 ? (uint32_t)(NS * HB) : 0u) +
-                                   (uint32_t)(tg * GP + ti * RB + ((4 * dt + 2 * (g4 & 1) + (a >> 1)) ^ TL::fsw(ti)) * 16 + (a & 1) * 8);
-            }
-        }
+            for (int dt = 0; dt < TL::NTB; ++dt) tlane[t][dt] = (role == 0 ? (uint32_t)(NS * HB) : 0u) + TL::tr_lane(lane, t, dt);
         auto half_off = [&](int half) { return (uint32_t)(half & (NS - 1)) * HB; };
-        auto read_rows = [&](int half, int ks) {
-            return *reinterpret_cast<const bf16x8_t*>(smem + (rlane[ks % NRB] + half_off(half)) + (ks / NRB) * 64);
-        };
-        auto read_tr_half = [&](int half, int step, int part) {     // one of the two 8-byte transpose reads of (s, dt) = (step / DT, step % DT)
-            const int s = step / DT, dt = step % DT;
-            const char* p = smem + (tlane[part][D == 128 ? 0 : dt] + half_off(half)) + s * (16 / TL::RPI) * GP + (D == 128 ? dt * 64 : 0);
-            return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(p));
-        };
-        auto read_tr = [&](int half, int step) {
-            return __builtin_shufflevector(read_tr_half(half, step, 0), read_tr_half(half, step, 1), 0, 1, 2, 3, 4, 5, 6, 7);
-        };
+        auto read_rows = [&](int half, int ks) { return TL::rows(smem, rlane, half_off(half), ks); };
+        auto read_tr = [&](int half, int step) { return TL::transposed(smem, tlane, half_off(half), step / DT, step % DT); };
 
         if (pair_live) {
             f32x16_t xa[2] = {zero16, zero16}, xb[2] = {zero16, zero16};    // S or dP of the even / odd local half-chunks
@@ -675,7 +693,7 @@ __device__ __forceinline__ void dkv_pair_body(
                             const u32x4_t pk = pin[g2 * 2 + i / 8];
                             const uint32_t word = (i % 8) / 2 == 0 ? pk.x : (i % 8) / 2 == 1 ? pk.y : (i % 8) / 2 == 2 ? pk.z : pk.w;
                             const float pval = (i & 1) ? bf16hi_to_f32(word) : bf16lo_to_f32(word);
-                            w[g2][i] = pval * (x_cur[g2][i] - ld[i]);
+                            w[g2][i] = pval * (x_cur[g2][i] + ld[i]);
                         }
                         asm volatile("" : "+v"(w[g2][i]));
                         if constexpr (g2 == 1 && i < 15) asm volatile("" : "+v"(ld[i + 1]));
@@ -791,7 +809,7 @@ __device__ __forceinline__ void dkv_tail_body(
     __bf16(*sT)[4][QC * STR] = reinterpret_cast<__bf16(*)[4][QC * STR]>(smem);
     float(*sL)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * 4 * QC * STR * 2);
     float(*sDl)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * 4 * QC * STR * 2 + 4 * QC * 4);
-    static_assert(2 * 4 * QC * STR * 2 + 2 * 4 * QC * 4 <= DkvTile<D>::BYTES, "the tail body fits the pair body's LDS");
+    static_assert(2 * 4 * QC * STR * 2 + 2 * 4 * QC * 4 <= DkvLds<D>::BYTES, "the tail body fits the pair body's LDS");
     const int b = bh / Hh, h = bh % Hh;
     const int j = kb_order[(long long)bh * nb + rank];            // longest query list first
     const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
@@ -914,7 +932,7 @@ __device__ __forceinline__ void dkv_tail_body(
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             pw[i] = exp2_raw(fmaf(sacc[i], scale_log2, -ld[i]));
-            dsw[i] = pw[i] * (dpacc[i] - dl[i]);
+            dsw[i] = pw[i] * (dpacc[i] + dl[i]);
         }
         // dV^T += dO^T . P and dK^T += Q^T . dS
 #pragma unroll
@@ -984,7 +1002,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(
     const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int* __restrict__ kb_start, const int* __restrict__ kb_order, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int nb, long long cap,
     float scale_log2, float scale, const int* __restrict__ kv_rows, int BH, int slots, int group) {
-    __shared__ __align__(16) char smem[DkvTile<D>::BYTES];
+    __shared__ __align__(16) char smem[DkvLds<D>::BYTES];
     // One-dimensional grid.  Workgroup i runs on XCD i % 8 as that XCD's workgroup number i / 8.  A head's slots are cut
     // into groups of `group` consecutive slots (the runs of one key block, when the blocks are equally long); groups are
     // numbered slot group first, head second -- longest query lists first over the whole launch -- and dealt to the XCDs
@@ -1062,7 +1080,7 @@ __global__ __launch_bounds__(256) void dq_merge_kernel(const float* __restrict__
 
 struct BwdWs {
     float* dQpart;     // [BH * cap][D], in the tensors' type
-    float* delta;      // bfloat16: LSE * log2(e) and delta, [BH][2][lse_delta_pitch(S)]; float32: delta, [BH][S]
+    float* delta;      // bfloat16: LSE * log2(e) and -delta, [BH][2][lse_delta_pitch(S)]; float32: delta, [BH][S]
     int4* tile_desc;   // the flat list of all heads' tiles
     int* n_tiles;      // its length
     int* kb_start;     // [BH][nb + 1]
@@ -1159,7 +1177,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
             launch_dq_tiles_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
                                 (long long)nnz_capacity, scale_log2, kv_rows);
         } else {
-#define DQ_ARGS Qv, Kv, Vv, dOv, ws.delta, blk_off, blk_ptr, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, kv_rows
+#define DQ_ARGS Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, (long long)nnz_capacity, scale_log2, kv_rows
             if (D == 128) attn_bwd_dq_mfma_kernel<128><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
             else attn_bwd_dq_mfma_kernel<64><<<grid, dim3(256), 0, st>>>(DQ_ARGS);
 #undef DQ_ARGS

@@ -19,3 +19,15 @@ def test_f32_matrix_kernels_at_tile_edges(chunk, D):
     Q, K, V, dO = (synth.iid_normal(900 + i, (1, S, 2, D)) for i in range(4))
     for tau, kv_in_place in ((0.6, False), (1.0, True)):
         compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, f"f32-edges-{chunk}", kv_in_place=kv_in_place)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [2, 31, 33, 64, 97, 129, 161, 200])
+def test_bf16_backward_kernels_at_tile_edges(chunk, D):
+    """Blocks that end one key before and after a 32-key group, a 64-key chunk, a 128-key run and its tail of at most 32 keys (also a run
+    whose second half has no keys); lists of a few entries and of 400 (longer than the ring of eight half-chunks, ending
+    inside one), keys rearranged and in place."""
+    grid, S = (1, 8, 50), 400
+    Q, K, V, dO = (synth.to_bf16_grid(synth.blurred_noise(940 + i, grid, 2, D, 1.0)) for i in range(4))
+    for tau, kv_in_place in ((0.3, True), (1.0, False)):
+        compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"bf16-edges-{chunk}", kv_in_place=kv_in_place)
