@@ -126,56 +126,6 @@ __device__ __forceinline__ T load_at(const void* base, uint32_t byte_off) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rows of Q, K, V and dO go from global memory to LDS without passing through registers (global_load_lds, inline assembly, waits
-// written by hand): the 64 lanes of one request write 1024 consecutive bytes, i.e. RPI = 4 (8) rows of D = 128 (64) channels.
-// Such groups of rows lie GP bytes apart, and 16-byte piece p of a group's row i sits at piece position p ^ fsw(i).  Row and
-// transposed reads are then free of bank conflicts, and for D = 128 only the two low bits of a piece position depend on the
-// row, so that two per-lane addresses and immediate offsets reach every operand of a tile.
-template <int D>
-struct RowTile {
-    static constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;
-    static constexpr int GP = D == 128 ? 1024 + 64 : 1024 + 144;       // bytes between groups of RPI rows
-    static constexpr int HB = 32 / RPI * GP;                           // bytes of 32 rows
-    static constexpr int DT = D / 32;
-    static constexpr int NRB = D == 128 ? 2 : 4;                       // distinct per-lane addresses of the row reads
-    static constexpr int NTB = D == 128 ? 1 : DT;                      // and, for each half, of the transposed reads
-    __device__ static __forceinline__ int fsw(int i) { return D == 128 ? i : 2 * ((i >> 1) & 1) + 4 * (i >> 2); }
-    // byte offset inside a row that lane `lane` of a request fetches
-    __device__ static __forceinline__ uint32_t request_piece(int lane) { return (uint32_t)((lane % PPR) ^ fsw(lane / PPR)) * 16; }
-    // Per-lane addresses of the operands of a 32-row tile: contraction over the channels (row rho(l32), k-step ks) ...
-    __device__ static __forceinline__ uint32_t row_lane(int lane, int ks) {
-        const int r = rho(lane & 31), hf = lane >> 5;
-        return (uint32_t)(r / RPI * GP + r % RPI * RB + ((2 * ks + hf) ^ fsw(r % RPI)) * 16);
-    }
-    // ... and over the rows (see tr_lane_offset; half t of the operand, channel tile dt)
-    __device__ static __forceinline__ uint32_t tr_lane(int lane, int t, int dt) {
-        const int g4 = lane >> 4, e = (lane >> 2) & 3, a = lane & 3, hf = lane >> 5;
-        const int r = 4 * e + hf + 2 * t;
-        return (uint32_t)(r / RPI * GP + r % RPI * RB + ((4 * dt + 2 * (g4 & 1) + (a >> 1)) ^ fsw(r % RPI)) * 16 + (a & 1) * 8);
-    }
-    // Operands at byte offset `tile` of `base`; rl = row_lane(., 0 .. NRB - 1), tl = tr_lane(., 0 .. 1, 0 .. NTB - 1)
-    __device__ static __forceinline__ bf16x8_t rows(const char* base, const uint32_t* rl, uint32_t tile, int ks) {
-        return *reinterpret_cast<const bf16x8_t*>(base + (rl[ks % NRB] + tile) + (ks / NRB) * 64);
-    }
-    __device__ static __forceinline__ bf16x8_t transposed(const char* base, const uint32_t (*tl)[NTB], uint32_t tile, int s, int dt) {
-        bf16x4_t h[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-            h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                (lds_bf16x4_t*)(base + (tl[t][NTB == 1 ? 0 : dt] + tile) + s * (16 / RPI) * GP + (NTB == 1 ? dt * 64 : 0)));
-        return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
-    }
-};
-
-// 64 lanes x 16 bytes, row `row` of a matrix of `stride` bytes per row (both below 2^24), byte `piece` of it, to LDS lds + IMM.
-template <int IMM>
-__device__ __forceinline__ void dma_row16(const char* base, uint32_t row, uint32_t stride, uint32_t piece, uint32_t lds) {
-    uint32_t off;
-    asm volatile("s_add_u32 m0, %5, %6\n\tv_mad_u32_u24 %0, %1, %2, %3\n\tglobal_load_lds_dwordx4 %0, %4"
-                 : "=&v"(off) : "v"(row), "s"(stride), "v"(piece), "s"(base), "s"(lds), "i"(IMM) : "memory", "m0", "scc");
-}
-
-// ---------------------------------------------------------------------------------------------
 // bf16 MFMA dQ tile kernel.  Same decomposition and operand orientation as the forward tile
 // kernel (query = MFMA column = lane % 32); 4 wavefronts x 32 gathered queries, key chunks of 64:
 //   S^T  = K . Q^T                    A = K rows (LDS),  B = Q^T (registers)
@@ -463,15 +413,6 @@ struct DkvLds : RowTile<D> {
     static constexpr int BYTES = X0 + 2 * 2 * 4 * 64 * 16;
     static_assert(X0 % 16 == 0 && BYTES <= 160 * 1024, "LDS of one compute unit");
 };
-
-// f(0), f(1), ... f(N - 1) with the index as a compile-time constant.
-template <int N, int I = 0, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<N, I + 1>(f);
-    }
-}
 
 // Matrix instruction on a sum that stays in accumulator registers.  (This file is compiled so that the results of the matrix
 // instructions it does not name in assembly go to ordinary registers: S and dP are read by vector instructions, which cannot

@@ -10,9 +10,8 @@
 // MFMA operand plumbing (v_mfma_f32_32x32x16_bf16; lane = 32*hf + l32):
 //   A operand: lane holds row l32, 8 consecutive k at 8*hf;   B operand: column l32, same k.
 //   C/D:       lane holds column l32, rows 8*i + 4*hf + r as value 4*i + r (i, r = 0..3).
-// LDS tiles are row-major [row][D].  The backward kernels pad every row by 8 bf16 (row stride D + 8, 16 bytes); the
-// forward kernel's K/V rings are unpadded and swizzled instead (16-byte piece p of row r sits at piece p ^ f(r), see
-// attn_fwd.hip), because its rows arrive by direct global-to-LDS loads that fill 1024 consecutive bytes.
+// Row tiles in LDS are laid out as RowTile (below) says; the dK/dV kernel's body for short block tails pads its rows instead
+// (row stride D + 8).
 //   * An operand that contracts over the channels of a row is a 16-byte row read.
 //   * An operand that contracts over the ROWS (the transposed tile) is two ds_read_b64_tr_b16:
 //     in each group of 16 lanes, lane 4*e + a supplies the address of 4 consecutive channels of
@@ -25,6 +24,8 @@
 //     and both kinds of LDS access are bank-conflict free with either layout.
 #pragma once
 #include "common.h"
+
+#include <type_traits>
 
 // MFMA row m (0..31) of a 32-row group is fed tile row rho(m):
 //   rho = 16*m[4] + 4*m[1:0] + 2*m[3] + m[2]
@@ -63,6 +64,15 @@ __device__ __forceinline__ bf16x8_t pack8(const float* p) {
     bf16x4_t blo = __builtin_convertvector(lo, bf16x4_t);
     bf16x4_t bhi = __builtin_convertvector(hi, bf16x4_t);
     return __builtin_shufflevector(blo, bhi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// f(0), f(1), ... f(N - 1) with the index as a compile-time constant.
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
 }
 
 struct TileCoord {
@@ -181,3 +191,52 @@ __device__ __forceinline__ void dma4(const char* base, uint32_t byte_off, uint32
 }
 #define VMOBA_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
+// ---------------------------------------------------------------------------------------------
+// Rows of Q, K, V and dO go from global memory to LDS without passing through registers (global_load_lds, inline assembly, waits
+// written by hand): the 64 lanes of one request write 1024 consecutive bytes, i.e. RPI = 4 (8) rows of D = 128 (64) channels.
+// Such groups of rows lie GP bytes apart, and 16-byte piece p of a group's row i sits at piece position p ^ fsw(i).  Row and
+// transposed reads are then free of bank conflicts, and for D = 128 only the two low bits of a piece position depend on the
+// row, so that two per-lane addresses and immediate offsets reach every operand of a tile.
+template <int D>
+struct RowTile {
+    static constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;
+    static constexpr int GP = D == 128 ? 1024 + 64 : 1024 + 144;       // bytes between groups of RPI rows
+    static constexpr int HB = 32 / RPI * GP;                           // bytes of 32 rows
+    static constexpr int DT = D / 32;
+    static constexpr int NRB = D == 128 ? 2 : 4;                       // distinct per-lane addresses of the row reads
+    static constexpr int NTB = D == 128 ? 1 : DT;                      // and, for each half, of the transposed reads
+    __device__ static __forceinline__ int fsw(int i) { return D == 128 ? i : 2 * ((i >> 1) & 1) + 4 * (i >> 2); }
+    // byte offset inside a row that lane `lane` of a request fetches
+    __device__ static __forceinline__ uint32_t request_piece(int lane) { return (uint32_t)((lane % PPR) ^ fsw(lane / PPR)) * 16; }
+    // Per-lane addresses of the operands of a 32-row tile: contraction over the channels (row rho(l32), k-step ks) ...
+    __device__ static __forceinline__ uint32_t row_lane(int lane, int ks) {
+        const int r = rho(lane & 31), hf = lane >> 5;
+        return (uint32_t)(r / RPI * GP + r % RPI * RB + ((2 * ks + hf) ^ fsw(r % RPI)) * 16);
+    }
+    // ... and over the rows (see tr_lane_offset; half t of the operand, channel tile dt)
+    __device__ static __forceinline__ uint32_t tr_lane(int lane, int t, int dt) {
+        const int g4 = lane >> 4, e = (lane >> 2) & 3, a = lane & 3, hf = lane >> 5;
+        const int r = 4 * e + hf + 2 * t;
+        return (uint32_t)(r / RPI * GP + r % RPI * RB + ((4 * dt + 2 * (g4 & 1) + (a >> 1)) ^ fsw(r % RPI)) * 16 + (a & 1) * 8);
+    }
+    // Operands at byte offset `tile` of `base`; rl = row_lane(., 0 .. NRB - 1), tl = tr_lane(., 0 .. 1, 0 .. NTB - 1)
+    __device__ static __forceinline__ bf16x8_t rows(const char* base, const uint32_t* rl, uint32_t tile, int ks) {
+        return *reinterpret_cast<const bf16x8_t*>(base + (rl[ks % NRB] + tile) + (ks / NRB) * 64);
+    }
+    __device__ static __forceinline__ bf16x8_t transposed(const char* base, const uint32_t (*tl)[NTB], uint32_t tile, int s, int dt) {
+        bf16x4_t h[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (lds_bf16x4_t*)(base + (tl[t][NTB == 1 ? 0 : dt] + tile) + s * (16 / RPI) * GP + (NTB == 1 ? dt * 64 : 0)));
+        return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+};
+
+// 64 lanes x 16 bytes, row `row` of a matrix of `stride` bytes per row (both below 2^24), byte `piece` of it, to LDS lds + IMM.
+template <int IMM>
+__device__ __forceinline__ void dma_row16(const char* base, uint32_t row, uint32_t stride, uint32_t piece, uint32_t lds) {
+    uint32_t off;
+    asm volatile("s_add_u32 m0, %5, %6\n\tv_mad_u32_u24 %0, %1, %2, %3\n\tglobal_load_lds_dwordx4 %0, %4"
+                 : "=&v"(off) : "v"(row), "s"(stride), "v"(piece), "s"(base), "s"(lds), "i"(IMM) : "memory", "m0", "scc");
+}
