@@ -215,8 +215,6 @@ int vmoba_select_static(int B, int Hh, int64_t S, int D, int32_t n_blocks, const
  *            goes to row out_rows[q] of O: pass the partition's perm and a tensor in the caller's
  *            token order to skip the inverse partition of O.  LSE stays in block order either way.
  *  kv_rows   optional int32 [S]: keys in place, as in vmoba_select -- key position k is row kv_rows[k] of Kp and Vp.
- *            (bfloat16: the tile kernel keeps the row numbers of a key block in LDS, up to 3072 keys per block;
- *            longer blocks are looked up in global memory, which is correct but slower.)
  *  Limit (bfloat16): one (batch, head) slice of K' and of V' must span less than 4 GiB, i.e.
  *  (S + 256) * stride_s * 2 < 2^32 with a positive stride_s; with kv_rows also S < 2^24 and stride_s * 2 < 2^24;
  *  otherwise VMOBA_ERR_UNSUPPORTED.

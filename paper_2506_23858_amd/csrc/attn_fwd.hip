@@ -79,10 +79,11 @@ __global__ __launch_bounds__(256) void tile_list_kernel(const int* __restrict__ 
 // rows (the address unit needs about as long for one such request as for eight full-row ones).
 //
 // Keys in place (KVR).  K and V may stay where the caller has them: key position p of the block order is then row
-// kv_rows[p] of both.  A tile's slice of that map, kv_rows[k0 .. k0 + L), is copied into LDS (global_load_lds_dword,
-// 64 entries per instruction) one tile ahead -- two tables that alternate, filled for the next tile at the start of
-// the current one -- and a row request reads its row number there instead of advancing an offset.  Blocks longer
-// than a table (TOKMAX keys) look their rows up in global memory, which is correct but waits for the lookup.
+// kv_rows[p] of both.  The row numbers come by way of LDS, too (global_load_lds_dword): those of group g + 8 are requested
+// in step g, those of a tile's first groups while the tile before is worked on, and a row request takes
+// its row number from there one step before it is issued.  (Before: a whole tile's numbers in a table, read where they
+// were needed, so that every row request waited for everything else in the LDS queue, blocks of more than 3584 keys
+// looked up in global memory: 3.00 -> 2.58 ms at 480p, 3D partition, tau = 0.5.)
 template <int D, int NW, bool KVR>
 __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     constexpr int KSTEPS = D / 16, DT = D / 32, UNITS = KSTEPS;
     constexpr int RPI = TL::RPI;            // rows per load instruction
     constexpr int IPW = G / RPI / NW;       // load instructions per wavefront per group
-    constexpr int NDMA = 2 * IPW;           // loads a wavefront issues per step (one K group, one V group)
+    constexpr int NDMA = 2 * IPW + (KVR ? 1 : 0);     // loads a wavefront issues per step (one K group, one V group, row numbers)
     constexpr float LAZY = 8.f;
     static_assert(UNITS % 4 == 0 && UNITS == 2 * DT && IPW >= 1 && IPW * NW * RPI == G && (D == 64 || D == 128), "unit bookkeeping");
     __shared__ __align__(1024) char sK[NR * SLOT];
@@ -105,8 +106,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     // channel group), read back as whole rows, so that the global stores are 1 KB runs instead of 16-byte pieces
     constexpr int OPITCH = D * 2 + 16;
     __shared__ __align__(16) char sOut[NW * 32 * OPITCH];
-    constexpr int TOKMAX = 3072;            // entries per row-number table (two of them fill what is left of the 160 KB)
-    __shared__ __align__(256) int sTok[KVR ? 2 * TOKMAX : 4];
+    // KVR: row numbers of the key groups of the current and of the next tile, rings of 16 groups (a request fills two)
+    constexpr int TOKS = 17 * G;
+    __shared__ __align__(256) int sTok[KVR ? 2 * TOKS : 4];
 
     // Workgroup ids go round the 8 XCDs (each with its own L2), so XCD x = id % 8 takes the x-th eighth of the tile
     // list and its workgroups stride through it: a key block's tiles then share one L2 instead of eight.
@@ -181,34 +183,39 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
             off[i] += adv;
         }
     };
-    // KVR: the row-number table of tile t into table `tb`; the instructions are dealt round the wavefronts, entries
-    // past the block's end repeat its last key
-    auto dma_tokens = [&](const Tile& t, int tb) {
-        if (t.L > TOKMAX) return;
-        const int n_instr = (t.L + 63) >> 6;
-        for (int i = wave; i < n_instr; i += NW) {
-            const int e = min(i * 64 + lane, t.L - 1);
-            dma4(reinterpret_cast<const char*>(kv_rows), (uint32_t)(t.k0 + e) << 2, sTok0 + (uint32_t)(tb * TOKMAX + i * 64) * 4);
-        }
+    // KVR: row numbers of groups x and x + 1 of tile t into ring `tb` (keys past the block's end repeat its last one)
+    auto dma_tokens = [&](const Tile& t, int x, int tb) {
+        dma4(reinterpret_cast<const char*>(kv_rows), (uint32_t)(t.k0 + min(x * G + lane, t.L - 1)) << 2,
+             sTok0 + (uint32_t)(tb * TOKS + (x & 15) * G) * 4);
     };
-    // KVR: request group `grp` of tile t (whose row numbers are in table `tb`) into ring slot `slot`
-    auto request_rows = [&](const Tile& t, const char* base, uint32_t stride, int grp, uint32_t ring0, int slot, int tb) {
-#pragma unroll
-        for (int i = 0; i < IPW; ++i) {
-            const int dr = (wave * IPW + i) * RPI + lane / PPR;
-            const int idx = min(grp * G + dr, t.L - 1);
-            const uint32_t row = t.L <= TOKMAX ? (uint32_t)sTok[tb * TOKMAX + idx] : (uint32_t)kv_rows[t.k0 + idx];
-            dma16(base, __umul24(row, stride) + pc16, ring0 + (uint32_t)(slot & (NR - 1)) * SLOT + (uint32_t)(wave * IPW + i) * TL::GP);
-        }
+    auto dma_first_tokens = [&](const Tile& t, int tb) {          // groups 0..7, two per wavefront
+        if (wave < 4) dma_tokens(t, 2 * wave, tb);
     };
+    // KVR: row of K and V that request i of this wavefront fetches for this lane in group x of the tile of ring `tb`
+    auto row_number = [&](int x, int i, int tb) { return (uint32_t)sTok[tb * TOKS + (x & 15) * G + (wave * IPW + i) * RPI + lane / PPR]; };
+    auto request_row = [&](const char* base, uint32_t stride, uint32_t row, int i, uint32_t ring0, int slot) {
+        dma_row16<0>(base, row, stride, pc16, ring0 + (uint32_t)(slot & (NR - 1)) * SLOT + (uint32_t)(wave * IPW + i) * TL::GP);
+    };
+    uint32_t krow[IPW], vrow[IPW];         // KVR: rows of the next request of K and of V, read from the ring a step before
     int kb = 0, vb = 0;                    // running group counters: group x of the current tile uses slot (kb + x) & 3 / (vb + x) & 3
     int tp = 0;                            // KVR: table that holds the current tile's row numbers
     auto request_first_groups = [&](const Tile& t, int kb_t, int vb_t, int tb) {     // K(0..3), V(0..1) of tile t
         if constexpr (KVR) {
+            uint32_t r[4][IPW];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) request_rows(t, t.kbase, kss, x, sK0, kb_t + x, tb);
+            for (int x = 0; x < 4; ++x)
 #pragma unroll
-            for (int x = 0; x < 2; ++x) request_rows(t, t.vbase, vss, x, sV0, vb_t + x, tb);
+                for (int i = 0; i < IPW; ++i) r[x][i] = row_number(x, i, tb);
+#pragma unroll
+            for (int i = 0; i < IPW; ++i) { krow[i] = row_number(4, i, tb); vrow[i] = r[2][i]; }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int i = 0; i < IPW; ++i) request_row(t.kbase, kss, r[x][i], i, sK0, kb_t + x);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int i = 0; i < IPW; ++i) request_row(t.vbase, vss, r[x][i], i, sV0, vb_t + x);
         } else {
             first_offsets(t);
 #pragma unroll
@@ -233,7 +240,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     Tile cur = decode(flat_desc[f]);
     load_q(cur, query_of(cur));
     if constexpr (KVR) {                   // the first tile's row numbers: nothing to overlap them with
-        dma_tokens(cur, 0);
+        dma_first_tokens(cur, 0);
         VMOBA_WAIT_VMCNT(0);
         __syncthreads();
     }
@@ -343,11 +350,18 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
                 if constexpr (STAGE) {
                     if (u == 1) {
                         if constexpr (KVR) {
-                            // the next tile's row numbers go first: they are then older than this step's row requests and
+                            // the next tile's row numbers go first: they are then older than this step's other requests and
                             // have landed when the next step's wait lets only those stay in flight
-                            if (g == 0) dma_tokens(nxt, tp ^ 1);
-                            request_rows(cur, cur.kbase, kss, g + 4, sK0, kb + g + 4, tp);
-                            request_rows(cur, cur.vbase, vss, g + 2, sV0, vb + g + 2, tp);
+                            if (g == 0) dma_first_tokens(nxt, tp ^ 1);
+#pragma unroll
+                            for (int i = 0; i < IPW; ++i) {
+                                request_row(cur.kbase, kss, krow[i], i, sK0, kb + g + 4);
+                                request_row(cur.vbase, vss, vrow[i], i, sV0, vb + g + 2);
+                                krow[i] = row_number(g + 5, i, tp);       // for the next step
+                                vrow[i] = row_number(g + 3, i, tp);
+                            }
+                            // every wavefront by itself: its row numbers then need no barrier and all waits the same count
+                            dma_tokens(cur, g + 8, tp);
                         } else {
                             request(cur.kbase, k_off, k_last, k_adv, sK0, kb + g + 4);
                             request(cur.vbase, v_off, v_last, v_adv, sV0, vb + g + 2);
