@@ -1189,66 +1189,12 @@ __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, 
     if (lane == 0 && active) wtot[(long long)bh * n_waves + w] = kept;
 }
 
-// Per-query ("local") selection, the block-choice variants of the paper's ablation and of its
-// training-free runs.  LOCAL_TOPK: a query keeps its `topk` most similar blocks; otherwise it keeps the
-// shortest descending prefix of its own row whose sum reaches tau.  Entry j' ranks before j when it is
-// larger, or equal with a lower block index.  One wavefront per 64 queries; a row is spread over the
-// lanes (up to 4 columns each) and every lane counts, or sums, what ranks before its own entries.
-// Same outputs as mask_kernel.
-template <bool LOCAL_TOPK>
-__global__ __launch_bounds__(256) void local_mask_kernel(const float* __restrict__ P, unsigned int* __restrict__ mask,
-                                                         int* __restrict__ wtot, int* __restrict__ wcnt,
-                                                         int S, int nb, int n_waves, int topk, float tau,
-                                                         const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
-    constexpr int MAXC = VMOBA_MAX_BLOCKS / 64;
-    __shared__ float sRow[4][VMOBA_MAX_BLOCKS];
-    __shared__ unsigned int sKeep[4][64][VMOBA_MAX_MASK_WORDS + 1];
-    const int bh = blockIdx.y;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int w = blockIdx.x * 4 + wv;
-    const bool active = w < n_waves;
-    const int q0 = active ? w * 64 : 0;
-    const int words = (nb + 31) / 32;
-    const int rows = active ? min(64, S - q0) : 0;
-    const int ncol = (nb + 63) / 64;
-    for (int r = 0; r < 64; ++r) {
-        const bool live = r < rows;
-        const float* row = P + ((long long)bh * S + q0 + (live ? r : 0)) * nb;
-        float v[MAXC];
-#pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            const int j = c * 64 + lane;
-            v[c] = (c < ncol && j < nb) ? row[j] : -1.f;
-            if (c < ncol && j < nb) sRow[wv][j] = v[c];
-        }
-        __syncthreads();
-        float before[MAXC];
-#pragma unroll
-        for (int c = 0; c < MAXC; ++c) before[c] = 0.f;
-        for (int jp = 0; jp < nb; ++jp) {
-            const float x = sRow[wv][jp];
-#pragma unroll
-            for (int c = 0; c < MAXC; ++c) {
-                if (c < ncol) {               // uniform: columns past the row's end are not ranked
-                    const int j = c * 64 + lane;
-                    const bool first = (x > v[c]) || (x == v[c] && jp < j);
-                    before[c] += first ? (LOCAL_TOPK ? 1.f : x) : 0.f;
-                }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            const int j = c * 64 + lane;
-            const bool keep = live && c < ncol && j < nb && (LOCAL_TOPK ? before[c] < (float)topk : (tau >= 1.f || before[c] < tau));
-            const unsigned long long bal = __ballot(keep);
-            if (lane == 0 && c < ncol) {
-                sKeep[wv][r][2 * c] = (unsigned)bal;
-                if (2 * c + 1 <= VMOBA_MAX_MASK_WORDS) sKeep[wv][r][2 * c + 1] = (unsigned)(bal >> 32);
-            }
-        }
-        __syncthreads();
-    }
-    // lane = row
+// Common end of the per-query selections: lane = row of the wavefront's 64 queries, sKeep[row] its mask words.  Adds the
+// query's own block, writes the mask and counts, per wavefront, how many of its queries keep each block (as mask_kernel does).
+__device__ __forceinline__ void store_local_mask(const unsigned int (*sKeep)[VMOBA_MAX_MASK_WORDS + 1], unsigned int* __restrict__ mask,
+                                                 int* __restrict__ wtot, int* __restrict__ wcnt, int bh, int w, int q0, int rows, bool active,
+                                                 int S, int nb, int n_waves, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
+    const int lane = threadIdx.x & 63, words = (nb + 31) / 32;
     unsigned int mw[VMOBA_MAX_MASK_WORDS];
     const int q = q0 + lane;
     const bool live = lane < rows;
@@ -1257,7 +1203,7 @@ __global__ __launch_bounds__(256) void local_mask_kernel(const float* __restrict
     for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {
         unsigned int g = 0;
         if (live && wd < words) {
-            g = sKeep[wv][lane][wd];
+            g = sKeep[lane][wd];
             if (wd == (own >> 5)) g |= 1u << (own & 31);
             mask[((long long)bh * S + q) * words + wd] = g;
         }
@@ -1278,6 +1224,188 @@ __global__ __launch_bounds__(256) void local_mask_kernel(const float* __restrict
         }
     }
     if (lane == 0 && active) wtot[(long long)bh * n_waves + w] = kept;
+}
+
+// Per-query ("local") selection, the block-choice variants of the paper's ablation and of its training-free runs.
+//
+// Top-k: a query keeps its `topk` most similar blocks, equal values by lowest block index.  One wavefront per 64 queries;
+// a row is held by 1 << lpr_log2 lanes, CPL columns each, in registers, and the k-th largest value is found bit by bit
+// (soft-max values are not negative: their bits order like integers): two instructions per column and bit, and rows whose
+// count hits k before the last bit are done -- usually after about half of the 30 bits.
+// Bound by these instructions and by reading P.  720p, 12 heads, 40 blocks, k = 10: 1079 -> 74 us (before: a row spread over the
+// lanes, every lane counting what ranks before its own columns -- nb LDS broadcasts and two barriers for every row, its loads
+// waited for); the whole selection with 288 blocks, k = 60, 56 160 tokens: 11.0 -> 1.65 ms.
+// A row of NaNs keeps every block (the list capacity then reports the head).
+template <int CPL>
+__global__ __launch_bounds__(256, 4) void local_topk_kernel(const float* __restrict__ P, unsigned int* __restrict__ mask,
+                                                         int* __restrict__ wtot, int* __restrict__ wcnt, int S, int nb, int n_waves, int topk,
+                                                         int lpr_log2, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
+    __shared__ unsigned int sKeep[4][64][VMOBA_MAX_MASK_WORDS + 1];
+    const int bh = blockIdx.y;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int w = blockIdx.x * 4 + wv;
+    const bool active = w < n_waves;
+    const int q0 = active ? w * 64 : 0;
+    const int rows = active ? min(64, S - q0) : 0;
+    const int k = min(topk, nb);
+    const int lpr = 1 << lpr_log2, part = lane & (lpr - 1), c0 = part * CPL;
+    const bool aligned = (nb & 3) == 0 && (reinterpret_cast<uintptr_t>(P) & 15) == 0;          // rows start 16-byte aligned
+    for (int wd = 0; wd < (nb + 31) / 32; ++wd) sKeep[wv][lane][wd] = 0u;
+    auto sum_row = [&](int v) {                  // over the lanes of a row
+        for (int off = 1; off < lpr; off <<= 1) v += __shfl_xor(v, off, 64);
+        return v;
+    };
+    for (int batch = 0; batch < lpr; ++batch) {
+        const int r = (batch << (6 - lpr_log2)) + (lane >> lpr_log2);
+        const bool live = r < rows;
+        const unsigned int* row = reinterpret_cast<const unsigned int*>(P) + ((long long)bh * S + q0 + (live ? r : 0)) * nb + c0;
+        unsigned int v[CPL];                     // columns past the row's end: 0, below every candidate and after every other 0
+        if (aligned) {
+#pragma unroll
+            for (int i = 0; i < CPL; i += 4) {
+                u32x4_t x = {0u, 0u, 0u, 0u};
+                if (live && c0 + i < nb) x = *reinterpret_cast<const u32x4_t*>(row + i);
+                v[i] = x.x; v[i + 1] = x.y; v[i + 2] = x.z; v[i + 3] = x.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) v[i] = (live && c0 + i < nb) ? row[i] : 0u;
+        }
+        unsigned int top = v[0];
+#pragma unroll
+        for (int i = 1; i < CPL; ++i) top = max(top, v[i]);
+        for (int off = 1; off < lpr; off <<= 1) top = max(top, (unsigned int)__shfl_xor((int)top, off, 64));
+        // kth: count(v >= kth) >= k; done: the count is k (or every column is kept)
+        unsigned int kth = 0;
+        bool done = !live || k == nb || top > 0x7f800000u;
+        for (int bit = 29; bit >= 0 && __ballot(!done); --bit) {             // values below 2 have 30 significant bits
+            const unsigned int cand = kth | (1u << bit);
+            int n = 0;
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) n += v[i] >= cand ? 1 : 0;
+            n = sum_row(n);
+            if (!done && n >= k) {
+                kth = cand;
+                done = n == k;
+            }
+        }
+        // more than k columns reach the k-th value only where several equal it: of these, the first ones
+        int take = 64 * 512;                     // columns v > kth are kept, and the first `take` of v == kth
+        if (__ballot(!done)) {
+            int n_gt = 0, n_eq = 0;
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) {
+                n_gt += v[i] > kth ? 1 : 0;
+                n_eq += v[i] == kth ? 1 : 0;
+            }
+            n_gt = sum_row(n_gt);
+            int before = n_eq;                   // equal columns in the row's lanes up to this one
+            for (int off = 1; off < lpr; off <<= 1) {
+                const int o = __shfl_up(before, off, 64);
+                if (part >= off) before += o;
+            }
+            if (!done) take = k - n_gt - (before - n_eq);
+        }
+        unsigned long long keep = 0;
+        if (__ballot(!done)) {
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) {
+                const bool eq = v[i] == kth;
+                keep |= v[i] > kth || (eq && take > 0) ? 1ull << i : 0ull;
+                take -= eq ? 1 : 0;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) keep |= v[i] >= kth ? 1ull << i : 0ull;
+        }
+        if (c0 + CPL > nb) keep &= nb > c0 ? (1ull << (nb - c0)) - 1ull : 0ull;
+        if (live) {
+            const int wd = c0 >> 5, sh = c0 & 31;
+            const unsigned int w0 = (unsigned int)(keep << sh), w1 = (unsigned int)((keep << sh) >> 32);
+            const unsigned int w2 = sh ? (unsigned int)(keep >> (64 - sh)) : 0u;
+            if (w0) atomicOr(&sKeep[wv][r][wd], w0);
+            if (w1) atomicOr(&sKeep[wv][r][wd + 1], w1);
+            if (w2) atomicOr(&sKeep[wv][r][wd + 2], w2);
+        }
+    }
+    __syncthreads();
+    store_local_mask(sKeep[wv], mask, wtot, wcnt, bh, w, q0, rows, active, S, nb, n_waves, own_blk_off, query_pos);
+}
+
+// Threshold: a query keeps the shortest descending prefix of its own row whose sum reaches tau; entry j' ranks before j when
+// it is larger, or equal with a lower block index.  One wavefront per 64 queries; a row is spread over the lanes (NCOL columns
+// each) and every lane sums, in column order, what ranks before its own entries.  Bound by these instructions, nb * NCOL times
+// three per row: soft-max values are not negative, so their bits compare like integers and "larger, or equal with a lower
+// index" is one comparison, with the value minus one bit for columns that come later.  The next row's values are fetched
+// while a row is worked on, and a wavefront's LDS row is its own: no barriers.  The whole selection at 480p, 12 heads, 84 blocks:
+// 1.36 -> 0.62 ms (with barriers, every row's loads waited for and twice the instructions before).
+// A row of NaNs keeps every block.
+template <int NCOL>
+__global__ __launch_bounds__(256) void local_threshold_kernel(const float* __restrict__ P, unsigned int* __restrict__ mask,
+                                                              int* __restrict__ wtot, int* __restrict__ wcnt,
+                                                              int S, int nb, int n_waves, float tau,
+                                                              const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
+    __shared__ __align__(16) int sRow[4][NCOL * 64];
+    __shared__ unsigned int sKeep[4][64][VMOBA_MAX_MASK_WORDS + 1];
+    const int bh = blockIdx.y;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int w = blockIdx.x * 4 + wv;
+    const bool active = w < n_waves;
+    const int q0 = active ? w * 64 : 0;
+    const int rows = active ? min(64, S - q0) : 0;
+    const int* base = reinterpret_cast<const int*>(P) + ((long long)bh * S + q0) * nb;
+    int* const sr = sRow[wv];
+    int nx[NCOL];
+    auto fetch = [&](int r) {
+#pragma unroll
+        for (int c = 0; c < NCOL; ++c) nx[c] = c * 64 + lane < nb ? base[(long long)r * nb + c * 64 + lane] : -1;     // -1: before nothing
+    };
+    if (rows > 0) fetch(0);
+    for (int r = 0; r < rows; ++r) {
+        int v[NCOL];
+        bool nan = false;
+#pragma unroll
+        for (int c = 0; c < NCOL; ++c) {
+            v[c] = nx[c];
+            sr[c * 64 + lane] = v[c];
+            nan |= c * 64 + lane < nb && __int_as_float(v[c]) != __int_as_float(v[c]);
+        }
+        const bool all = tau >= 1.f || __ballot(nan);
+        asm volatile("" ::: "memory");                       // a wavefront's LDS instructions execute in order
+        if (r + 1 < rows) fetch(r + 1);
+        float before[NCOL];
+#pragma unroll
+        for (int c = 0; c < NCOL; ++c) before[c] = 0.f;
+        if (!all) {
+#pragma unroll
+            for (int cp = 0; cp < NCOL; ++cp) {
+                const int n4 = min(64, nb - cp * 64);
+                for (int jp = 0; jp < n4; jp += 4) {
+                    const u32x4_t x4 = *reinterpret_cast<const u32x4_t*>(sr + cp * 64 + jp);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int x = (int)x4[u];
+#pragma unroll
+                        for (int c = 0; c < NCOL; ++c) {
+                            const int later = cp < c ? 1 : cp > c ? 0 : (jp + u < lane ? 1 : 0);     // column jp + u comes before this lane's
+                            before[c] += x > v[c] - later ? __int_as_float(x) : 0.f;
+                        }
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NCOL; ++c) {
+            const unsigned long long bal = __ballot(c * 64 + lane < nb && (all || before[c] < tau));
+            if (lane == 0) {
+                sKeep[wv][r][2 * c] = (unsigned)bal;
+                sKeep[wv][r][2 * c + 1] = (unsigned)(bal >> 32);
+            }
+        }
+        asm volatile("" ::: "memory");
+    }
+    __syncthreads();
+    store_local_mask(sKeep[wv], mask, wtot, wcnt, bh, w, q0, rows, active, S, nb, n_waves, own_blk_off, query_pos);
 }
 
 // Offsets of both list forms, in two small launches.
@@ -1663,10 +1791,21 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
     const unsigned wave_gx = (unsigned)ceil_div64(n_waves, 4);
     const bool local = mode == VMOBA_LOCAL_TOPK || mode == VMOBA_LOCAL_THRESHOLD;
     if (local) {
-        if (mode == VMOBA_LOCAL_TOPK)
-            local_mask_kernel<true><<<dim3(wave_gx, BH), dim3(256), 0, st>>>(P, mask, ws.wtot, ws.wcnt, (int)S, n_blocks, n_waves, topk, tau, own_off, query_pos);
-        else
-            local_mask_kernel<false><<<dim3(wave_gx, BH), dim3(256), 0, st>>>(P, mask, ws.wtot, ws.wcnt, (int)S, n_blocks, n_waves, topk, tau, own_off, query_pos);
+        const dim3 grid(wave_gx, BH);
+        if (mode == VMOBA_LOCAL_TOPK) {
+            // the fewest lanes per row that hold it with at most 64 columns each, in an instantiation per 8 columns
+            int lpr_log2 = 0;
+            while (n_blocks > 64 << lpr_log2) ++lpr_log2;
+            const int cpl = ((n_blocks + (1 << lpr_log2) - 1) >> lpr_log2) + 7;
+            decltype(&local_topk_kernel<8>) kfn[8] = {local_topk_kernel<8>, local_topk_kernel<16>, local_topk_kernel<24>, local_topk_kernel<32>,
+                                                      local_topk_kernel<40>, local_topk_kernel<48>, local_topk_kernel<56>, local_topk_kernel<64>};
+            kfn[cpl / 8 - 1]<<<grid, dim3(256), 0, st>>>(P, mask, ws.wtot, ws.wcnt, (int)S, n_blocks, n_waves, topk, lpr_log2, own_off, query_pos);
+        } else {
+            decltype(&local_threshold_kernel<1>) kfn[8] = {local_threshold_kernel<1>, local_threshold_kernel<2>, local_threshold_kernel<3>,
+                                                           local_threshold_kernel<4>, local_threshold_kernel<5>, local_threshold_kernel<6>,
+                                                           local_threshold_kernel<7>, local_threshold_kernel<8>};
+            kfn[(n_blocks - 1) / 64]<<<grid, dim3(256), 0, st>>>(P, mask, ws.wtot, ws.wcnt, (int)S, n_blocks, n_waves, tau, own_off, query_pos);
+        }
         VMOBA_CHECK_LAUNCH();
     } else {
 #define SCAN_LEVEL(LV, HC, HS)                                                                                        \

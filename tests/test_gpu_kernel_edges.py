@@ -31,3 +31,13 @@ def test_bf16_backward_kernels_at_tile_edges(chunk, D):
     Q, K, V, dO = (synth.to_bf16_grid(synth.blurred_noise(940 + i, grid, 2, D, 1.0)) for i in range(4))
     for tau, kv_in_place in ((0.3, True), (1.0, False)):
         compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"bf16-edges-{chunk}", kv_in_place=kv_in_place)
+
+
+@pytest.mark.parametrize("mode,topk", [(1, 1), (1, 5), (1, 1000), (2, 0), (0x101, 3)])
+@pytest.mark.parametrize("chunk", [48, 43, 42, 6, 5, 3, 2, 1])
+def test_local_selections_at_column_counts(chunk, mode, topk):
+    """Per-query selections with 8, 9, 10, 64, 77, 128, 192 and 384 blocks: columns that fill a lane's share, exceed it by one and by a few, rows
+    held by one to eight lanes, 16-byte aligned or not; keep one, several, all blocks, and the query's own block as well."""
+    grid, S = (1, 16, 24), 384
+    Q, K, V = (synth.to_bf16_grid(synth.iid_normal(970 + i, (1, S, 2, 64))) for i in range(3))
+    compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, 0.4, torch.bfloat16, f"local-{chunk}", mode=mode, topk=topk)
