@@ -758,6 +758,57 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ P
 // bin 1023 - t, so an inclusive prefix sum over t is the descending cumulative sum.
 // BYCOUNT = false: the cut is where the descending cumulative SUM reaches `target` (threshold selection,
 // Eq. 4); BYCOUNT = true: where the descending cumulative COUNT reaches it (a fixed global k).
+// The cut inside one level's bins, by 1024 threads: my_s / my_c = mass and count of bin 1023 - t.  Returns true in the one thread whose
+// bin holds the cut (level 0: or in the last thread when the pool does not reach the target), with the new state in *st.
+struct ScanLds { unsigned long long s[HIST_BINS / 64], c[HIST_BINS / 64]; };
+template <int LEVEL, bool BYCOUNT>
+__device__ __forceinline__ bool scan_level(ScanLds& lds, unsigned long long my_s, unsigned long long my_c, HeadState* st, unsigned long long target,
+                                           int fix_shift) {
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    unsigned long long is = my_s, ic = my_c;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long a = __shfl_up(is, off, 64), c = __shfl_up(ic, off, 64);
+        if (lane >= off) { is += a; ic += c; }
+    }
+    if (lane == 63) { lds.s[wv] = is; lds.c[wv] = ic; }
+    __syncthreads();
+    for (int w = 0; w < wv; ++w) { is += lds.s[w]; ic += lds.c[w]; }
+    __syncthreads();                                     // the caller may scan the next level right away
+    const unsigned long long need = (LEVEL == 0) ? target : st->need;
+    const unsigned long long cexcl = ic - my_c;
+    const unsigned long long incl = BYCOUNT ? ic : is;
+    const unsigned long long excl = BYCOUNT ? cexcl : is - my_s;
+    if (LEVEL == 0 && t == HIST_BINS - 1 && incl < need) {
+        // the whole pool does not reach the target (tau >= 1, or rounding): keep everything
+        st->all = 1u;
+        return true;
+    }
+    if (!(excl < need && need <= incl)) return false;
+    const int bin = HIST_BINS - 1 - t;
+    st->need = need - excl;
+    st->cnt_above = (LEVEL == 0 ? 0ull : st->cnt_above) + cexcl;
+    st->all = 0u;
+    if (LEVEL == 0) st->prefix = ((unsigned)bin) << 20;
+    if (LEVEL == 1) st->prefix |= ((unsigned)bin) << 10;
+    if (LEVEL == 2) {
+        st->prefix |= (unsigned)bin;
+        const float theta = __uint_as_float(st->prefix);
+        unsigned long long take;
+        if (BYCOUNT) {
+            take = st->need;                                                 // entries still missing
+        } else {
+            const unsigned long long each = to_fixed(theta, fix_shift);      // > 0: this bin has mass
+            take = (st->need + each - 1) / each;
+        }
+        if (take > my_c) take = my_c;
+        if (take < 1) take = 1;
+        st->n_tie = (unsigned)my_c;
+        st->take = (unsigned)take;
+    }
+    return true;
+}
+
 template <int LEVEL, bool BYCOUNT>
 __global__ __launch_bounds__(HIST_BINS) void scan_level_kernel(const unsigned int* __restrict__ hist_cnt,
                                                                const unsigned long long* __restrict__ hist_sum,
@@ -765,63 +816,17 @@ __global__ __launch_bounds__(HIST_BINS) void scan_level_kernel(const unsigned in
                                                                unsigned long long target, int fix_shift,
                                                                long long pool_size, long long* __restrict__ k_out,
                                                                float* __restrict__ theta_out) {
-    __shared__ unsigned long long sS[HIST_BINS];
-    __shared__ unsigned long long sC[HIST_BINS];
+    __shared__ ScanLds lds;
     const int bh = blockIdx.x, t = threadIdx.x;
-    const int bin = HIST_BINS - 1 - t;
     HeadState st = state[bh];
     if (LEVEL > 0 && st.all) {
         if (LEVEL == 2 && t == 0) { k_out[bh] = pool_size; theta_out[bh] = 0.f; }
         return;
     }
-    const unsigned long long my_s = hist_sum[(long long)bh * HIST_BINS + bin];
-    const unsigned long long my_c = hist_cnt[(long long)bh * HIST_BINS + bin];
-    sS[t] = my_s;
-    sC[t] = my_c;
-    __syncthreads();
-    for (int off = 1; off < HIST_BINS; off <<= 1) {
-        unsigned long long a = 0, c = 0;
-        if (t >= off) { a = sS[t - off]; c = sC[t - off]; }
-        __syncthreads();
-        sS[t] += a;
-        sC[t] += c;
-        __syncthreads();
-    }
-    const unsigned long long need = (LEVEL == 0) ? target : st.need;
-    const unsigned long long cexcl = sC[t] - my_c;
-    const unsigned long long incl = BYCOUNT ? sC[t] : sS[t];
-    const unsigned long long excl = BYCOUNT ? cexcl : incl - my_s;
-    if (LEVEL == 0 && t == HIST_BINS - 1 && incl < need) {
-        // the whole pool does not reach the target (tau >= 1, or rounding): keep everything
-        HeadState ns = st;
-        ns.all = 1u;
-        state[bh] = ns;
-    }
-    if (excl < need && need <= incl) {
-        HeadState ns = st;
-        ns.need = need - excl;
-        ns.cnt_above = (LEVEL == 0 ? 0ull : st.cnt_above) + cexcl;
-        ns.all = 0u;
-        if (LEVEL == 0) ns.prefix = ((unsigned)bin) << 20;
-        if (LEVEL == 1) ns.prefix = st.prefix | (((unsigned)bin) << 10);
-        if (LEVEL == 2) {
-            ns.prefix = st.prefix | (unsigned)bin;
-            const float theta = __uint_as_float(ns.prefix);
-            unsigned long long take;
-            if (BYCOUNT) {
-                take = ns.need;                                            // entries still missing
-            } else {
-                const unsigned long long each = to_fixed(theta, fix_shift);   // > 0: this bin has mass
-                take = (ns.need + each - 1) / each;
-            }
-            if (take > my_c) take = my_c;
-            if (take < 1) take = 1;
-            ns.n_tie = (unsigned)my_c;
-            ns.take = (unsigned)take;
-            k_out[bh] = (long long)(ns.cnt_above + take);
-            theta_out[bh] = theta;
-        }
-        state[bh] = ns;
+    const long long i = (long long)bh * HIST_BINS + HIST_BINS - 1 - t;
+    if (scan_level<LEVEL, BYCOUNT>(lds, hist_sum[i], hist_cnt[i], &st, target, fix_shift)) {
+        state[bh] = st;
+        if (LEVEL == 2) { k_out[bh] = (long long)(st.cnt_above + st.take); theta_out[bh] = __uint_as_float(st.prefix); }
     }
 }
 
@@ -899,6 +904,23 @@ __global__ __launch_bounds__(256) void pool_rescale_kernel(float* __restrict__ P
 // bin, and those, not the pass over P, set the time when thousands of workgroups flush.
 constexpr int REFINE_NT = 1024;
 template <int LEVEL>
+__device__ __forceinline__ void refine_add(unsigned long long* sPk, unsigned int prefix, unsigned int u) {
+    constexpr int SHIFT_HI = (LEVEL == 1) ? 20 : 10, SHIFT_LO = (LEVEL == 1) ? 10 : 0;
+    if ((u >> SHIFT_HI) == (prefix >> SHIFT_HI))
+        atomicAdd(&sPk[(u >> SHIFT_LO) & (HIST_BINS - 1)], PK_ONE | (unsigned long long)(u & ((1u << SHIFT_LO) - 1u)));
+}
+// count and fixed-point mass of a packed bin
+template <int LEVEL>
+__device__ __forceinline__ void refine_bin(unsigned long long w, unsigned int prefix, int bin, int fix_shift, unsigned long long& cnt, unsigned long long& sum) {
+    constexpr int SHIFT_HI = (LEVEL == 1) ? 20 : 10, SHIFT_LO = (LEVEL == 1) ? 10 : 0;
+    cnt = w >> 40;
+    // every entry of the bin is (lead | its trailing bits) as a float pattern; to_fixed is linear in the
+    // mantissa for a fixed exponent, and the exponent lies in the prefix
+    const unsigned int lead = (prefix >> SHIFT_HI << SHIFT_HI) | ((unsigned int)bin << SHIFT_LO);
+    const int e = (int)(lead >> 23), sh = e - 150 + fix_shift;
+    sum = (cnt && e && sh >= 0) ? (cnt * (unsigned long long)((lead & 0x7fffffu) | 0x800000u) + (w & (PK_ONE - 1))) << sh : 0ull;
+}
+template <int LEVEL>
 __global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __restrict__ P, const HeadState* __restrict__ state,
                                                           unsigned int* __restrict__ hist_cnt,
                                                           unsigned long long* __restrict__ hist_sum,
@@ -909,14 +931,8 @@ __global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __r
     if (st.all) return;
     for (int i = threadIdx.x; i < HIST_BINS; i += REFINE_NT) sPk[i] = 0ull;
     __syncthreads();
-    constexpr int SHIFT_HI = (LEVEL == 1) ? 20 : 10;
-    constexpr int SHIFT_LO = (LEVEL == 1) ? 10 : 0;
-    constexpr unsigned int LOW_MASK = (1u << SHIFT_LO) - 1u;
-    const unsigned int want = st.prefix >> SHIFT_HI;
-    auto take = [&](unsigned int u) {
-        if ((u >> SHIFT_HI) == want)
-            atomicAdd(&sPk[(u >> SHIFT_LO) & (HIST_BINS - 1)], PK_ONE | (unsigned long long)(u & LOW_MASK));
-    };
+    const unsigned int prefix = st.prefix;
+    auto take = [&](unsigned int u) { refine_add<LEVEL>(sPk, prefix, u); };
     const u32x4_t* src = reinterpret_cast<const u32x4_t*>(P + (long long)bh * pool_size);
     // 16-byte loads need every head's pool to start on a 16-byte boundary
     const long long n4 = (pool_size % 4 == 0) ? pool_size / 4 : 0;
@@ -942,17 +958,11 @@ __global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __r
     }
     __syncthreads();
     for (int i = threadIdx.x; i < HIST_BINS; i += REFINE_NT) {
-        const unsigned long long w = sPk[i];
-        if (w) {
-            const unsigned long long cnt = w >> 40, low = w & (PK_ONE - 1);
-            // every entry of the bin is (lead | its trailing bits) as a float pattern; to_fixed is linear in the
-            // mantissa for a fixed exponent, and the exponent lies in the prefix
-            const unsigned int lead = (want << SHIFT_HI) | ((unsigned int)i << SHIFT_LO);
-            const int e = (int)(lead >> 23), sh = e - 150 + fix_shift;
+        unsigned long long cnt, sum;
+        refine_bin<LEVEL>(sPk[i], prefix, i, fix_shift, cnt, sum);
+        if (cnt) {
             atomicAdd(&hist_cnt[(long long)bh * HIST_BINS + i], (unsigned int)cnt);
-            if (e && sh >= 0)
-                atomicAdd(&hist_sum[(long long)bh * HIST_BINS + i],
-                          (cnt * (unsigned long long)((lead & 0x7fffffu) | 0x800000u) + low) << sh);
+            if (sum) atomicAdd(&hist_sum[(long long)bh * HIST_BINS + i], sum);
         }
     }
 }
@@ -1057,35 +1067,34 @@ __device__ __forceinline__ int block_of_position(const int* __restrict__ blk_off
     return lo;
 }
 
-// own_blk_off: null, or blk_off when every query also keeps the block it lies in itself; query_pos: null when query q
+// The mask words of a wavefront's 64 rows: entries above theta, entries equal to it.
+template <int W>
+struct MaskLds { unsigned int gt[64][W + 1], tie[64][W + 1]; };
+// Mask of rows [64 w, 64 w + 64) of head bh by one wavefront, with its LDS of its own (a wavefront's LDS instructions
+// execute in order: no barriers).  W: words per row at most.  tie_base: per row of the head, entries equal to theta in the rows
+// before.  own_blk_off: null, or blk_off when every query also keeps the block it lies in itself; query_pos: null when query q
 // sits at block-order position q, else the position of every query (queries kept in the caller's token order).
-__global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, const HeadState* __restrict__ state,
-                                                   const int* __restrict__ tie_base, unsigned int* __restrict__ mask,
-                                                   int* __restrict__ wtot, int* __restrict__ wcnt,
-                                                   int S, int nb, int n_waves, const int* __restrict__ own_blk_off,
-                                                   const int* __restrict__ query_pos) {
-    __shared__ unsigned int sGt[4][64][VMOBA_MAX_MASK_WORDS + 1];
-    __shared__ unsigned int sTie[4][64][VMOBA_MAX_MASK_WORDS + 1];
-    const int bh = blockIdx.y;
-    const HeadState st = state[bh];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int w = blockIdx.x * 4 + wv;           // global wavefront index = 64-query group
-    const bool active = w < n_waves;             // surplus wavefronts only keep the barriers company
+template <int W>
+__device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restrict__ P, const HeadState& st, const int* __restrict__ tie_base,
+                                          unsigned int* __restrict__ mask, int* __restrict__ wtot, int* __restrict__ wcnt, int bh, int w,
+                                          int S, int nb, int n_waves, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
+    const int lane = threadIdx.x & 63;
+    const bool active = w < n_waves;             // a surplus wavefront has no rows
     const int q0 = active ? w * 64 : 0;
     const int words = (nb + 31) / 32;
     const int rows = active ? min(64, S - q0) : 0;
     // The wavefront's 64 rows of P are one contiguous run of rows * nb values: it is read flat, 16 bytes per lane and
     // eight loads in flight, and every lane ORs the bits of its four values into the rows' mask words in LDS (a group
     // of four can straddle two words or two rows).
-    for (int wd = 0; wd < words; ++wd) { sGt[wv][lane][wd] = 0u; sTie[wv][lane][wd] = 0u; }
-    __syncthreads();
+    for (int wd = 0; wd < words; ++wd) { lds.gt[lane][wd] = 0u; lds.tie[lane][wd] = 0u; }
+    asm volatile("" ::: "memory");
     {
         const int n_el = rows * nb;
         const unsigned int* tile = reinterpret_cast<const unsigned int*>(P + ((long long)bh * S + q0) * nb);
         const bool aligned = (reinterpret_cast<uintptr_t>(tile) & 15) == 0;      // wave-uniform
         const int n4 = (aligned && nb >= 4) ? n_el / 4 : 0;                      // whole groups of four (a group spans at most two rows)
         const float inv_nb = 1.f / (float)nb;
-        auto put = [&](unsigned int (*arr)[VMOBA_MAX_MASK_WORDS + 1], int row, int col, unsigned int bits, int count) {
+        auto put = [&](unsigned int (*arr)[W + 1], int row, int col, unsigned int bits, int count) {
             // `count` (1..4) bits for columns col, col + 1, ... of `row`, continuing in the next row past column nb - 1
             const int here = min(count, nb - col);
             const unsigned int b0 = bits & ((1u << here) - 1u);
@@ -1121,8 +1130,8 @@ __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, 
                     if (st.all || v > st.prefix) gt |= 1u << cidx;
                     else if (v == st.prefix) ti |= 1u << cidx;
                 }
-                put(sGt[wv], row, col, gt, 4);
-                if (ti) put(sTie[wv], row, col, ti, 4);
+                put(lds.gt, row, col, gt, 4);
+                if (ti) put(lds.tie, row, col, ti, 4);
             }
         }
         // what the groups of four did not cover (everything when the run does not start 16-byte aligned)
@@ -1132,26 +1141,26 @@ __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, 
             if ((row + 1) * nb <= e) ++row;
             const int col = e - row * nb;
             const unsigned int v = tile[e];
-            if (st.all || v > st.prefix) put(sGt[wv], row, col, 1u, 1);
-            else if (v == st.prefix) put(sTie[wv], row, col, 1u, 1);
+            if (st.all || v > st.prefix) put(lds.gt, row, col, 1u, 1);
+            else if (v == st.prefix) put(lds.tie, row, col, 1u, 1);
         }
     }
-    __syncthreads();
+    asm volatile("" ::: "memory");
     // lane = row
-    unsigned int mw[VMOBA_MAX_MASK_WORDS];
+    unsigned int mw[W];
     const int q = q0 + lane;
     const bool live = lane < rows;
     if (live) {
         const bool all_ties = (st.take == st.n_tie);
-        int rank = all_ties ? 0 : tie_base[(long long)bh * (S + 1) + q];
+        int rank = all_ties ? 0 : tie_base[q];
         const int own = own_blk_off ? block_of_position(own_blk_off, nb, query_pos ? query_pos[q] : q) : -1;
 #pragma unroll
-        for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {
+        for (int wd = 0; wd < W; ++wd) {
             unsigned int g = 0;
             if (wd < words) {
-                g = sGt[wv][lane][wd];
+                g = lds.gt[lane][wd];
                 if (wd == (own >> 5)) g |= 1u << (own & 31);       // own = -1: no word matches
-                unsigned int t = sTie[wv][lane][wd];
+                unsigned int t = lds.tie[lane][wd];
                 if (all_ties) {
                     g |= t;
                 } else {
@@ -1168,13 +1177,13 @@ __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, 
         }
     } else {
 #pragma unroll
-        for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) mw[wd] = 0;
+        for (int wd = 0; wd < W; ++wd) mw[wd] = 0;
     }
     // per-block count over the 64 rows of this wavefront (word by word, so that a word is one register) and their sum,
     // the number of pairs these 64 queries keep
     int kept = 0;
 #pragma unroll
-    for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {
+    for (int wd = 0; wd < W; ++wd) {
         if (wd * 32 < nb) {
             const unsigned int word = mw[wd];
             const int jn = min(32, nb - wd * 32);
@@ -1187,6 +1196,18 @@ __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, 
         }
     }
     if (lane == 0 && active) wtot[(long long)bh * n_waves + w] = kept;
+}
+
+__global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, const HeadState* __restrict__ state,
+                                                   const int* __restrict__ tie_base, unsigned int* __restrict__ mask,
+                                                   int* __restrict__ wtot, int* __restrict__ wcnt,
+                                                   int S, int nb, int n_waves, const int* __restrict__ own_blk_off,
+                                                   const int* __restrict__ query_pos) {
+    __shared__ MaskLds<VMOBA_MAX_MASK_WORDS> lds[4];
+    const int bh = blockIdx.y, wv = threadIdx.x >> 6;
+    const HeadState st = state[bh];
+    mask_rows<VMOBA_MAX_MASK_WORDS>(lds[wv], P, st, tie_base + (long long)bh * (S + 1), mask, wtot, wcnt, bh, blockIdx.x * 4 + wv, S, nb, n_waves,
+                                    own_blk_off, query_pos);
 }
 
 // Common end of the per-query selections: lane = row of the wavefront's 64 queries, sKeep[row] its mask words.  Adds the
@@ -1449,14 +1470,12 @@ __global__ __launch_bounds__(256) void wave_scan_kernel(int* __restrict__ wcnt, 
 // so no list entry of it is ever read (the merge kernels recognise the same head by row_ptr[S] > cap) -- and the status
 // word is set.  Also row_ptr[S], the head's number of pairs; write_k != 0 (per-query modes, or every query keeps its
 // own block: the number of kept pairs is not the k of the cut) copies it to k_out, write_k == 2 also clears theta_out.
-__global__ __launch_bounds__(64) void blk_ptr_kernel(const int* __restrict__ row_tot, int* __restrict__ blk_ptr,
-                                                     int* __restrict__ row_ptr, long long* __restrict__ k_out,
-                                                     float* __restrict__ theta_out, int nb, int S, long long cap,
-                                                     int* __restrict__ dev_status, int write_k) {
-    const int bh = blockIdx.x, lane = threadIdx.x;
+__device__ __forceinline__ void block_offsets(const int* cnt, int* __restrict__ blk_ptr, int* __restrict__ row_ptr, long long* __restrict__ k_out,
+                                              float* __restrict__ theta_out, int bh, int nb, int S, long long cap, int* __restrict__ dev_status,
+                                              int write_k) {
+    const int lane = threadIdx.x & 63;
     const int per = (nb + 63) / 64;                  // consecutive blocks per lane
     const int j0 = min(nb, lane * per), j1 = min(nb, j0 + per);
-    const int* cnt = row_tot + (long long)bh * (nb + 1);
     int* out = blk_ptr + (long long)bh * (nb + 1);
     int mine = 0;
     for (int j = j0; j < j1; ++j) mine += cnt[j];
@@ -1480,6 +1499,157 @@ __global__ __launch_bounds__(64) void blk_ptr_kernel(const int* __restrict__ row
         if (write_k) k_out[bh] = cnt[nb];
         if (write_k == 2) theta_out[bh] = 0.f;
     }
+}
+
+__global__ __launch_bounds__(64) void blk_ptr_kernel(const int* __restrict__ row_tot, int* __restrict__ blk_ptr,
+                                                     int* __restrict__ row_ptr, long long* __restrict__ k_out,
+                                                     float* __restrict__ theta_out, int nb, int S, long long cap,
+                                                     int* __restrict__ dev_status, int write_k) {
+    block_offsets(row_tot + (long long)blockIdx.x * (nb + 1), blk_ptr, row_ptr, k_out, theta_out, blockIdx.x, nb, S, cap, dev_status, write_k);
+}
+
+// Offsets of both list forms for one head by the NW wavefronts of a workgroup (what wave_scan_kernel and blk_ptr_kernel do).
+template <int NW>
+__device__ __forceinline__ void head_offsets(int* sTot, int* __restrict__ wcnt, int* __restrict__ wtot, int* __restrict__ blk_ptr, int* __restrict__ row_ptr,
+                                             long long* __restrict__ k_out, float* __restrict__ theta_out, int bh, int nb, int S, int n_waves, long long cap,
+                                             int* __restrict__ dev_status, int write_k) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int j = wv; j <= nb; j += NW) {
+        int* col = j < nb ? wcnt + ((long long)bh * nb + j) * n_waves : wtot + (long long)bh * n_waves;
+        int carry = 0;
+        for (int base = 0; base < n_waves; base += 64) {
+            const int v = base + lane < n_waves ? col[base + lane] : 0;
+            int incl = v;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(incl, off, 64);
+                if (lane >= off) incl += o;
+            }
+            if (base + lane < n_waves) col[base + lane] = carry + incl - v;
+            carry += __shfl(incl, 63, 64);
+        }
+        if (lane == 0) sTot[j] = carry;
+    }
+    __syncthreads();
+    if (wv == 0) block_offsets(sTot, blk_ptr, row_ptr, k_out, theta_out, bh, nb, S, cap, dev_status, write_k);
+}
+
+// Everything between the scores and the lists -- the three radix levels, tie ranks, mask, list offsets -- for a small pool, one
+// workgroup per head in one launch instead of ten that take 2 to 7 us each whatever their size.  Bound by the latency of its
+// dozen dependent trips to the L2.  Same integers, same results as the kernels above.  Whole selection, 12 heads x 1560 tokens x 20
+// blocks: 57 -> 45 us; 2 heads x 512 x 16 (float32, with the score kernel's smaller share per workgroup): 72 -> 36 us.  The line
+// lies at 2^15 values: from about 6 x 10^4 on (four rounds of rows per wavefront) the separate launches are as fast or faster (at 10^5
+// values 70 against 84 us; with the cut alone in one workgroup 70 as well).
+constexpr long long SMALL_POOL = 1 << 15;
+constexpr int SMALL_ROWS = 4096, SMALL_WORDS = 4;
+template <bool BYCOUNT>
+__global__ __launch_bounds__(HIST_BINS) void small_cut_kernel(const float* __restrict__ P, const unsigned int* __restrict__ hist_cnt,
+                                                              const unsigned long long* __restrict__ hist_sum, unsigned long long target, int fix_shift,
+                                                              unsigned int* __restrict__ mask, int* __restrict__ wtot, int* __restrict__ wcnt,
+                                                              int* __restrict__ blk_ptr, int* __restrict__ row_ptr, long long* __restrict__ k_out,
+                                                              float* __restrict__ theta_out, int* __restrict__ dev_status, int S, int nb, int n_waves,
+                                                              long long cap, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos,
+                                                              int write_k) {
+    constexpr int NW = HIST_BINS / 64;
+    __shared__ ScanLds scan;
+    __shared__ HeadState sState;
+    __shared__ unsigned long long sPk[HIST_BINS];
+    __shared__ int sTies[SMALL_ROWS];
+    __shared__ MaskLds<SMALL_WORDS> sMask[NW];
+    __shared__ int sTot[SMALL_WORDS * 32 + 1];
+    __shared__ int sW[NW];
+    const int bh = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int pool = S * nb;
+    const unsigned int* p = reinterpret_cast<const unsigned int*>(P) + (long long)bh * pool;
+    const bool aligned = (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+    // ---- the cut
+    HeadState st = {0, 0, 0, 0, 0, 0};
+    {
+        const long long i = (long long)bh * HIST_BINS + HIST_BINS - 1 - t;
+        if (t == 0) sState = st;
+        __syncthreads();
+        if (scan_level<0, BYCOUNT>(scan, hist_sum[i], hist_cnt[i], &st, target, fix_shift)) sState = st;
+        __syncthreads();
+        st = sState;
+    }
+    auto refine = [&](auto level) {
+        constexpr int LEVEL = decltype(level)::value;
+        sPk[t] = 0ull;
+        __syncthreads();
+        const int n4 = aligned ? pool / 4 : 0;
+        for (int i0 = t; i0 < n4; i0 += 4 * HIST_BINS) {
+            u32x4_t v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const u32x4_t none = {~0u, ~0u, ~0u, ~0u};      // matches no prefix
+                v[k] = i0 + k * HIST_BINS < n4 ? reinterpret_cast<const u32x4_t*>(p)[i0 + k * HIST_BINS] : none;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) refine_add<LEVEL>(sPk, st.prefix, v[k][u]);
+        }
+        for (int i = 4 * n4 + t; i < pool; i += HIST_BINS) refine_add<LEVEL>(sPk, st.prefix, p[i]);
+        __syncthreads();
+        const int bin = HIST_BINS - 1 - t;
+        unsigned long long cnt, sum;
+        refine_bin<LEVEL>(sPk[bin], st.prefix, bin, fix_shift, cnt, sum);
+        if (scan_level<LEVEL, BYCOUNT>(scan, sum, cnt, &st, target, fix_shift)) sState = st;
+        __syncthreads();
+        st = sState;
+    };
+    if (!st.all) {                                       // same decision in every thread
+        refine(std::integral_constant<int, 1>{});
+        refine(std::integral_constant<int, 2>{});
+    }
+    if (t == 0) {
+        k_out[bh] = st.all ? (long long)pool : (long long)(st.cnt_above + st.take);
+        theta_out[bh] = st.all ? 0.f : __uint_as_float(st.prefix);
+    }
+    // ---- ranks of the entries equal to theta, needed when some but not all of them are kept
+    if (!st.all && st.take != st.n_tie) {
+        for (int q = wv; q < S; q += NW) {
+            int c = 0;
+            for (int j0 = 0; j0 < nb; j0 += 64) c += __popcll(__ballot(j0 + lane < nb && p[(long long)q * nb + j0 + lane] == st.prefix));
+            if (lane == 0) sTies[q] = c;
+        }
+        __syncthreads();
+        constexpr int PER = SMALL_ROWS / HIST_BINS;
+        int v[PER], sum = 0;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            v[e] = t * PER + e < S ? sTies[t * PER + e] : 0;
+            sum += v[e];
+        }
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) sW[wv] = incl;
+        __syncthreads();
+        int run = incl - sum;
+        for (int w = 0; w < wv; ++w) run += sW[w];
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            if (t * PER + e < S) sTies[t * PER + e] = run;
+            run += v[e];
+        }
+        __syncthreads();
+    }
+    // ---- mask and per-wavefront counts, list offsets
+    for (int w = wv; w < n_waves; w += NW)
+        mask_rows<SMALL_WORDS>(sMask[wv], P, st, sTies, mask, wtot, wcnt, bh, w, S, nb, n_waves, own_blk_off, query_pos);
+    __syncthreads();
+    head_offsets<NW>(sTot, wcnt, wtot, blk_ptr, row_ptr, k_out, theta_out, bh, nb, S, n_waves, cap, dev_status, write_k);
+}
+
+__global__ __launch_bounds__(1024) void head_offsets_kernel(int* __restrict__ wcnt, int* __restrict__ wtot, int* __restrict__ blk_ptr,
+                                                            int* __restrict__ row_ptr, long long* __restrict__ k_out, float* __restrict__ theta_out,
+                                                            int nb, int S, int n_waves, long long cap, int* __restrict__ dev_status, int write_k) {
+    __shared__ int sTot[VMOBA_MAX_BLOCKS + 1];
+    head_offsets<16>(sTot, wcnt, wtot, blk_ptr, row_ptr, k_out, theta_out, blockIdx.x, nb, S, n_waves, cap, dev_status, write_k);
 }
 
 // Workgroup i of n runs on XCD i % 8; this index makes the workgroups of one XCD neighbours in the work list, so runs
@@ -1713,7 +1883,8 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
     // pool soft-max: the radix levels run over the pool-normalised values, which only exist after the row statistics
     unsigned int* score_hist = pool_softmax ? nullptr : ws.hist_cnt;
     const int n_tiles = (int)ceil_div64(S, QT);
-    const int tiles_per_wg = 4;
+    // (float32 kernel) up to four tiles per workgroup, which loads the means once for them -- but not while compute units idle
+    const int tiles_per_wg = (int)std::min<int64_t>(4, std::max<int64_t>(1, (int64_t)n_tiles * BH / (2 * vmoba_num_cus())));
     dim3 sgrid((unsigned)ceil_div64(n_tiles, tiles_per_wg), (unsigned)BH);
 #define LAUNCH_SCORE(DD)                                                                                  \
     do {                                                                                                  \
@@ -1790,7 +1961,15 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
 
     const unsigned wave_gx = (unsigned)ceil_div64(n_waves, 4);
     const bool local = mode == VMOBA_LOCAL_TOPK || mode == VMOBA_LOCAL_THRESHOLD;
-    if (local) {
+    const int write_k = local ? 2 : (own_off ? 1 : 0);
+    const bool small = !local && pool <= SMALL_POOL && S <= SMALL_ROWS && n_blocks <= SMALL_WORDS * 32;
+    if (small) {
+        auto kfn = mode == VMOBA_GLOBAL_TOPK ? small_cut_kernel<true> : small_cut_kernel<false>;
+        kfn<<<dim3(BH), dim3(HIST_BINS), 0, st>>>(P, ws.hist_cnt, ws.hist_sum, target, fix_shift, mask, ws.wtot, ws.wcnt, blk_ptr, row_ptr,
+                                                  (long long*)k_out, theta_out, dev_status, (int)S, n_blocks, n_waves, (long long)nnz_capacity,
+                                                  own_off, query_pos, write_k);
+        VMOBA_CHECK_LAUNCH();
+    } else if (local) {
         const dim3 grid(wave_gx, BH);
         if (mode == VMOBA_LOCAL_TOPK) {
             // the fewest lanes per row that hold it with at most 64 columns each, in an instantiation per 8 columns
@@ -1835,11 +2014,19 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
                                                             (int)S, n_blocks, n_waves, own_off, query_pos);
         VMOBA_CHECK_LAUNCH();
     }
-    wave_scan_kernel<<<dim3(n_blocks + 1, BH), dim3(256), 0, st>>>(ws.wcnt, ws.wtot, ws.row_tot, n_blocks, n_waves);
-    VMOBA_CHECK_LAUNCH();
-    blk_ptr_kernel<<<dim3(BH), dim3(64), 0, st>>>(ws.row_tot, blk_ptr, row_ptr, (long long*)k_out, theta_out, n_blocks, (int)S,
-                                                 (long long)nnz_capacity, dev_status, local ? 2 : (own_off ? 1 : 0));
-    VMOBA_CHECK_LAUNCH();
+    if (!small && n_waves <= 64) {
+        // rows of counts of at most 64 entries: one workgroup per head scans all of them, a launch less (69 -> 66 us with 49
+        // wavefronts of queries and 40 blocks; with 200 and 80 it is 8 us slower)
+        head_offsets_kernel<<<dim3(BH), dim3(1024), 0, st>>>(ws.wcnt, ws.wtot, blk_ptr, row_ptr, (long long*)k_out, theta_out, n_blocks, (int)S,
+                                                             n_waves, (long long)nnz_capacity, dev_status, write_k);
+        VMOBA_CHECK_LAUNCH();
+    } else if (!small) {
+        wave_scan_kernel<<<dim3(n_blocks + 1, BH), dim3(256), 0, st>>>(ws.wcnt, ws.wtot, ws.row_tot, n_blocks, n_waves);
+        VMOBA_CHECK_LAUNCH();
+        blk_ptr_kernel<<<dim3(BH), dim3(64), 0, st>>>(ws.row_tot, blk_ptr, row_ptr, (long long*)k_out, theta_out, n_blocks, (int)S,
+                                                     (long long)nnz_capacity, dev_status, write_k);
+        VMOBA_CHECK_LAUNCH();
+    }
     fill_lists_kernel<<<dim3(wave_gx, BH), dim3(256), 0, st>>>(mask, row_ptr, ws.wtot, blk_ptr, ws.wcnt, q_idx, col_idx,
                                                               pair_pos, (int)S, n_blocks, n_waves,
                                                               (long long)nnz_capacity);
