@@ -18,7 +18,9 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
 # attn_bwd: its large kernel names the matrix instructions whose sums belong in accumulator registers and interleaves matrix and
 # vector instructions one by one; results of the others go to ordinary registers, and the vectorizer, which would gather the
 # vector instructions in one place, stays off.
-FILE_FLAGS = {"attn_bwd.hip": ["-fno-slp-vectorize", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# attn_split: the same choice of registers (its largest kernel spills otherwise).
+FILE_FLAGS = {"attn_bwd.hip": ["-fno-slp-vectorize", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "attn_split.hip": ["-fno-slp-vectorize", "-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def sources():

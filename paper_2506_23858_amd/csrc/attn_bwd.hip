@@ -22,10 +22,6 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 
 // ---------------------------------------------------------------------------------------------
-// The bfloat16 kernels read LSE * log2(e) and -delta from [head][2][pitch] floats: element S of either is what a row past the
-// end of a query list reads (LSE +inf, i.e. weight 0, and delta 0).  The float32 kernels read delta from [head][S].
-__host__ __device__ constexpr int lse_delta_pitch(int S) { return (S + 64) / 64 * 64; }
-
 // What a backward call needs before its first large kernel, in one launch: workgroups with blockIdx.x below n_delta compute
 // delta, the next ones write the flat tile list of the dQ kernel (256 tile ids each), the last one of every head the key
 // runs of the dK/dV kernel.  (Four launches before; each of the small ones took about 5 us whatever its size.)
@@ -60,13 +56,9 @@ __device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView
 #pragma unroll
     for (int off = LPQ / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (q < S && part == 0) {
-        if constexpr (BF16) {
-            float* d = delta + (long long)bh * 2 * lse_delta_pitch(S) + q;
-            d[0] = LSE[(long long)bh * S + q] * LOG2E;
-            d[lse_delta_pitch(S)] = -acc;
-        } else {
-            delta[(long long)bh * S + q] = acc;
-        }
+        float* d = delta + (long long)bh * 2 * lse_delta_pitch(S) + q;
+        d[0] = LSE[(long long)bh * S + q] * LOG2E;
+        d[lse_delta_pitch(S)] = -acc;
     }
 }
 
@@ -106,15 +98,16 @@ template <bool BF16, int D>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorView dO, const float* __restrict__ LSE, float* __restrict__ delta, const int* __restrict__ rows,
                                                           char* __restrict__ dO_copy, const int* __restrict__ blk_ptr,
                                                           const int* __restrict__ blk_off, int4* __restrict__ flat_desc, int* __restrict__ n_tiles,
-                                                          int* __restrict__ kb_start, int* __restrict__ kb_order, int BH, int Hh, int S, int nb,
+                                                          int* __restrict__ clear, int* __restrict__ kb_start, int* __restrict__ kb_order, int BH, int Hh, int S, int nb,
                                                           int TM, int KPW, int tail_max, int n_delta) {
     __shared__ union { TileListLds tiles; KeyRunLds runs; } lds;
     const int bh = blockIdx.y, x = blockIdx.x;
     if (x < n_delta) delta_rows<BF16, D>(O, dO, LSE, delta, rows, dO_copy, bh, Hh, S, x);
     else if (x + 1 < (int)gridDim.x) write_tile_list(lds.tiles, blk_ptr, blk_off, flat_desc, n_tiles, bh, BH, nb, TM, (x - n_delta) * 256);
     else {
-        if (BF16 && threadIdx.x < 2)
+        if (threadIdx.x < 2)
             delta[((long long)bh * 2 + threadIdx.x) * lse_delta_pitch(S) + S] = threadIdx.x == 0 ? INFINITY : 0.f;
+        if (clear && bh == 0 && threadIdx.x == 2) *clear = 0;
         write_key_runs(lds.runs, blk_off, blk_ptr, kb_start, kb_order, bh, nb, KPW, tail_max);
     }
 }
@@ -1021,12 +1014,14 @@ __global__ __launch_bounds__(256) void dq_merge_kernel(const float* __restrict__
 
 struct BwdWs {
     float* dQpart;     // [BH * cap][D], in the tensors' type
-    float* delta;      // bfloat16: LSE * log2(e) and -delta, [BH][2][lse_delta_pitch(S)]; float32: delta, [BH][S]
+    float* delta;      // LSE * log2(e) and -delta, [BH][2][lse_delta_pitch(S)]
     int4* tile_desc;   // the flat list of all heads' tiles
-    int* n_tiles;      // its length
+    int* n_tiles;      // its length, then the split kernels' flag
     int* kb_start;     // [BH][nb + 1]
     int* kb_order;     // [BH][nb]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
+    char* QD6;         // float32: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
+    char* KV6;
     size_t total;
 };
 
@@ -1035,12 +1030,14 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {
     char* p = (char*)base;
     size_t off = 0;
     w.dQpart = (float*)(p + off);    off += align_up((size_t)BH * cap * D * es, 256);
-    w.delta = (float*)(p + off);     off += align_up((size_t)BH * (es == 2 ? 2 * (size_t)lse_delta_pitch((int)S) : (size_t)S) * 4, 256);
+    w.delta = (float*)(p + off);     off += align_up((size_t)BH * 2 * (size_t)lse_delta_pitch((int)S) * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
+    w.QD6 = p + off;                 off += es == 4 ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.KV6 = p + off;                 off += es == 4 ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
 }
@@ -1093,14 +1090,16 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
 
     // ---- delta, tile list, key runs
     const int TM = 128;                     // queries per dQ tile
-    const int KPW = bf16 ? 128 : 64;        // keys per dK/dV workgroup
+    const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
+    int* const not_finite = ws.n_tiles + 1;
+    const int KPW = bf16 || split ? 128 : 64;        // keys per dK/dV workgroup
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
     {
         const int n_delta = (int)ceil_div64(S, 256 / (D / (bf16 ? 8 : 4)));
         const dim3 grid((unsigned)(n_delta + ceil_div64(max_tiles, 256) + 1), (unsigned)BH);
         auto kfn = bf16 ? (D == 128 ? bwd_prepare_kernel<true, 128> : bwd_prepare_kernel<true, 64>)
                         : (D == 128 ? bwd_prepare_kernel<false, 128> : bwd_prepare_kernel<false, 64>);
-        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, ws.kb_start, ws.kb_order,
+        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, not_finite, ws.kb_start, ws.kb_order,
                                         BH, Hh, (int)S, n_blocks, TM, KPW, bf16 ? 32 : 0, n_delta);
         VMOBA_CHECK_LAUNCH();
     }
@@ -1110,12 +1109,23 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         dOv.stride_h = S * D;
         dOv.stride_s = D;
     }
+    if (split) {
+        launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.QD6, 6, 0, not_finite);
+        launch_split_rows(D, BH, Hh, (int)S, st, dOv, nullptr, ws.QD6, 6, 3, not_finite);
+        launch_split_rows(D, BH, Hh, (int)S, st, Kv, kv_rows, ws.KV6, 6, 0, not_finite);
+        launch_split_rows(D, BH, Hh, (int)S, st, Vv, kv_rows, ws.KV6, 6, 3, not_finite);
+        VMOBA_CHECK_LAUNCH();
+    }
+    const int pitch = lse_delta_pitch((int)S);
     // ---- dQ
     {
         VMOBA_PROFILE_BEGIN(1, st);
         const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);     // one workgroup per tile
         if (!bf16) {
-            launch_dq_tiles_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
+            if (split)
+                launch_dq_tiles_split(D, grid, st, ws.QD6, ws.KV6, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, not_finite, ws.dQpart, (int)S, pitch,
+                                      (long long)nnz_capacity, scale_log2);
+            launch_dq_tiles_f32(D, grid, st, split ? not_finite : nullptr, Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
                                 (long long)nnz_capacity, scale_log2, kv_rows);
         } else {
 #define DQ_ARGS Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, (long long)nnz_capacity, scale_log2, kv_rows
@@ -1139,18 +1149,22 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     {
         // a multiple of 8 so that (workgroup id % 8) is the same for every head; + 8 for the per-XCD rounding
         dim3 grid((unsigned)((S / KPW + n_blocks + 7) / 8 * 8 + 8 + (bf16 ? n_blocks : 0)), (unsigned)BH);
-        // slots of the matrix-core kernel in groups of one block's runs (the usual block: S / n_blocks keys, a last run of at
-        // most 32 keys goes to the tail workgroups)
+        // slots of the matrix-core kernels in groups of one block's runs (the usual block: S / n_blocks keys; bfloat16: a last run
+        // of at most 32 keys goes to the tail workgroups)
         const int64_t usual = S / n_blocks;
-        const int group = (int)std::max<int64_t>(1, (usual % KPW > 0 && usual % KPW <= 32) ? usual / KPW : ceil_div64(usual, KPW));
+        const int group = (int)std::max<int64_t>(1, (bf16 && usual % KPW > 0 && usual % KPW <= 32) ? usual / KPW : ceil_div64(usual, KPW));
         const int slots = (int)ceil_div64(grid.x, group) * group;
+        const dim3 hgrid((unsigned)(ceil_div64((int64_t)BH * slots, 8) * 8 + 7 * group));   // see the kernel
         VMOBA_PROFILE_BEGIN(2, st);
         const int32_t* krows = key_rows ? key_rows : rows;      // row map of dK and dV
 #define DKV_ARGS blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
         if (!bf16) {
-            launch_dkv_f32(D, grid, st, Qv, Kv, Vv, dOv, LSE, ws.delta, DKV_ARGS);
+            if (split)
+                launch_dkv_split(D, hgrid, st, ws.QD6, ws.KV6, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, not_finite, dKv, dVv, krows,
+                                 Hh, (int)S, pitch, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, BH, slots, group);
+            const int parts = split ? 2 : 1;
+            launch_dkv_f32(D, dim3(grid.x * parts, grid.y), st, split ? not_finite : nullptr, parts, Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS);
         } else {
-            const dim3 hgrid((unsigned)(ceil_div64((int64_t)BH * slots, 8) * 8 + 7 * group));   // see the kernel
             if (D == 128) attn_bwd_dkv_kernel<128><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
             else attn_bwd_dkv_kernel<64><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
         }

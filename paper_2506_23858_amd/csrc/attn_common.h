@@ -153,17 +153,42 @@ static inline dim3 flat_tile_grid(int BH, int64_t max_tiles, int64_t cap, int TM
     const int64_t a = (int64_t)BH * max_tiles, b = ((cap / TM + nb) * (int64_t)BH + 15) / 8 * 8;
     return dim3((unsigned)(a < b ? a : b));
 }
-// float32 tile kernels (attn_f32.hip)
-void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
+// Pitch of the LSE * log2(e) and -delta arrays the backward kernels read, [head][2][pitch]: element S of either is what a row past
+// the end of a query list reads (LSE +inf, i.e. weight 0, and delta 0).
+__host__ __device__ constexpr int lse_delta_pitch(int S) { return (S + 64) / 64 * 64; }
+
+// float32 tile kernels (attn_f32.hip).  run_if: null, or a flag on the device without which they leave at once.
+void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const int* run_if, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
                           const int4* flat_desc, const int* n_tiles, float* Opart, float* lse_part, int Hh, long long cap,
                           float scale_log2, const int* kv_rows);
-void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* n_tiles,
+void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const int* run_if, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+                         const float* lse_delta, const int* q_idx, const int4* flat_desc, const int* n_tiles,
                          float* dQpart, int Hh, int S, long long cap, float scale_log2, const int* kv_rows);
-void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-                    const float* LSE, const float* delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,
+// parts: 64-key parts per entry of the run table (1, or 2 where the table counts runs of 128 keys)
+void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const int* run_if, int parts, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+                    const float* lse_delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,
                     const int* kb_order, const TensorView& dK, const TensorView& dV, const int* rows, int Hh, int S, int nb, long long cap,
                     float scale_log2, float scale, const int* kv_rows);
+// The same on the bfloat16 matrix instruction, from rows split into three terms each (attn_split.hip).
+void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const TensorView& X, const int* map, char* dst, int planes, int plane0, int* not_finite);
+void launch_fwd_tiles_split(int D, dim3 grid, hipStream_t st, const char* Q3, const char* KV6, const int* q_idx, const int4* flat_desc,
+                            const int* n_tiles, const int* not_finite, float* Opart, float* lse_part, int S, long long cap, float scale_log2);
+void launch_dq_tiles_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* q_idx,
+                           const int4* flat_desc, const int* n_tiles, const int* not_finite, float* dQpart, int S, int pitch, long long cap,
+                           float scale_log2);
+void launch_dkv_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* blk_off, const int* blk_ptr,
+                      const int* q_idx, const int* kb_start, const int* kb_order, const int* not_finite, const TensorView& dK, const TensorView& dV,
+                      const int* rows, int Hh, int S, int pitch, int nb, long long cap, float scale_log2, float scale, int BH, int slots, int group);
+// float32 calls with enough work -- multiply-adds of one product over all pairs the lists can hold -- take the split kernels, if
+// 32-bit offsets reach every split row of a head.  What they cost beside their products is seven passes over the inputs
+// and ten launches in a training step; what they save grows with the pairs and with the length of the blocks (below some 64 keys
+// the partial rows set the time).  Training step (forward) with / without them, us: blocks of 300 keys, work 6.7e7:
+// 207 / 251 (95 / 107), 2.4e9: 421 / 613 (153 / 176); 128 keys, 3.0e8: 210 / 212; 64 keys, 3.0e8: 225 / 228 (98 / 97), 2.4e9: 538 / 570
+// (205 / 217); 32 keys, 3.0e8: 263 / 255, 2.4e9: 880 / 936 (298 / 287).
+static inline bool use_split(int BH, int64_t S, int D, int n_blocks, int64_t cap) {
+    const double len = (double)S / n_blocks, work = (double)BH * (double)cap * (double)D * len;
+    return work * (len / 128) * (len / 128) >= 2e8 && S < (1 << 24) && (uint64_t)S * 12 * (uint64_t)D < ((uint64_t)1 << 32);
+}
 // Compute units of the current device (queried once).
 int vmoba_num_cus();
 

@@ -1,6 +1,9 @@
 // Block-sparse attention kernels for float32 tensors, forward and backward, on the float32 matrix instruction
 // v_mfma_f32_32x32x2_f32 (every product and sum in float32; 64 cycles for 4096 FLOP, 157 TFLOP/s on the whole chip).
 //
+// For the calls that the kernels on split operands (attn_split.hip) do not take: small ones (use_split), and those whose tensors hold
+// infinities or NaNs.
+//
 // Work decomposition as in the bfloat16 kernels: a tile is up to 128 gathered queries of one key block (forward, dQ), a
 // run is up to 64 keys of one block that meet the block's whole query list (dK/dV).
 //
@@ -188,12 +191,13 @@ __device__ __forceinline__ const char* head_ptr(const TensorView& t, int b, int 
 // Forward: S^T = K . Q^T, online soft-max (query on the lane), O^T += V^T . P^T.
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_fwd_tile_f32_kernel(
-    TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
+    const int* __restrict__ run_if, TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
     const int* __restrict__ n_tiles, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int KC = 32, TILE = KeyRows<D>::TILE, DT = D / 32;
     __shared__ __align__(1024) char sKV[2][2][TILE];              // [buffer][K, V]
     F32Tile t;
+    if (run_if && !*run_if) return;
     if (!take_tile(flat_desc, n_tiles, t)) return;
     const int b = t.bh / Hh, h = t.bh % Hh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -277,12 +281,13 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_tile_f32_kernel(
 // The fragments of Q and dO and the accumulators take 192 registers: one wavefront per SIMD.
 template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
+    const int* __restrict__ run_if, TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
     const int* __restrict__ q_idx, const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles,
     float* __restrict__ dQpart, int Hh, int S, long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int KC = 32, TILE = KeyRows<D>::TILE, DT = D / 32;
     __shared__ __align__(1024) char sKV[2][2][TILE];
     F32Tile t;
+    if (run_if && !*run_if) return;
     if (!take_tile(flat_desc, n_tiles, t)) return;
     const int b = t.bh / Hh, h = t.bh % Hh;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -297,8 +302,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
     float qf[D / 2], dof[D / 2];
     load_row_half<D>(head_ptr(Q, b, h) + (long long)q * Q.stride_s * 4, hf, qf);
     load_row_half<D>(head_ptr(dO, b, h) + (long long)q * dO.stride_s * 4, hf, dof);
-    const float lse2 = LSE[(long long)t.bh * S + q] * LOG2E;
-    const float dl = delta[(long long)t.bh * S + q];
+    const float lse2 = lse_delta[(long long)t.bh * 2 * lse_delta_pitch(S) + q];
+    const float ndl = lse_delta[((long long)t.bh * 2 + 1) * lse_delta_pitch(S) + q];
     const TileReads<D> rd(lane);
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     f32x16_t acc[DT];
@@ -322,7 +327,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const float p = exp2_raw(fmaf(s[v], scale_log2, -lse2));
-            dp[v] = p * (dp[v] - dl);
+            dp[v] = p * (dp[v] + ndl);
         }
         if (left < KC) {                                          // keys past the block's end
 #pragma unroll
@@ -351,23 +356,27 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
 // rarely full, and the two query halves keep the LDS traffic of a shared chunk.
 template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ LSE, const float* __restrict__ delta,
+    const int* __restrict__ run_if, int parts, TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
     const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
     const int* __restrict__ kb_start, const int* __restrict__ kb_order, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int nb, long long cap,
     float scale_log2, float scale, const int* __restrict__ kv_rows) {
     constexpr int KPW = 64, QC = 64, RB = 4 * D, HALF = 32 * RB, DT = D / 32, IPW = QC * RB / 1024 / 4, RPI = 1024 / RB, PPR = RB / 16;
     __shared__ __align__(1024) char sT[2][2][2 * HALF];           // [buffer][Q, dO]
-    __shared__ float sLD[2][2][QC];                               // [buffer][LSE, delta]
+    __shared__ float sLD[2][2][QC];                               // [buffer][LSE, -delta]
+    if (run_if && !*run_if) return;
+    const int run_id = (int)blockIdx.x / parts, part = (int)blockIdx.x % parts;
     const int bh = blockIdx.y, b = bh / Hh, h = bh % Hh;
     const int* ks = kb_start + (long long)bh * (nb + 1);
-    if ((int)blockIdx.x >= ks[nb]) return;
+    if (run_id >= ks[nb]) return;
     int lo = 0, hi = nb;
-    while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (ks[mid] <= (int)blockIdx.x) lo = mid; else hi = mid; }
+    while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (ks[mid] <= run_id) lo = mid; else hi = mid; }
     const int j = kb_order[(long long)bh * nb + lo];
     const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5, kw = wave & 1, qh = wave >> 1;
-    const int kk = ((int)blockIdx.x - ks[lo]) * KPW + kw * 32 + l32;
+    const int key0 = ((run_id - ks[lo]) * parts + part) * KPW;
+    if (key0 >= L) return;
+    const int kk = key0 + kw * 32 + l32;
     const bool live = kk < L;
     const bool wave_live = kk - l32 < L;                          // any key of this wavefront exists
     const int krow = k0 + min(kk, L - 1);
@@ -403,7 +412,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
                 dma16_at(dobase + q * dO.stride_s * 4 + piece, td + (uint32_t)n * 1024);
             }
             if (wave < 2) {
-                const float* src = (wave == 0 ? LSE : delta) + (long long)bh * S + idx;
+                const float* src = lse_delta + ((long long)bh * 2 + wave) * lse_delta_pitch(S) + idx;
                 dma4_at(reinterpret_cast<const char*>(src), lds_address(reinterpret_cast<const char*>(&sLD[c & 1][wave][0])));
             }
         };
@@ -438,8 +447,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int v = 4 * i + r;
-                    s[v] = exp2_raw(fmaf(s[v], scale_log2, -l4[r] * LOG2E));
-                    dp[v] = s[v] * (dp[v] - d4[r]);
+                    s[v] = exp2_raw(fmaf(s[v], scale_log2, -l4[r]));
+                    dp[v] = s[v] * (dp[v] + d4[r]);
                 }
             }
             if (left < 32) {                                      // rows past the end of the list
@@ -490,25 +499,25 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
 
 }  // namespace
 
-void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
+void launch_fwd_tiles_f32(int D, dim3 grid, hipStream_t st, const int* run_if, const TensorView& Q, const TensorView& K, const TensorView& V, const int* q_idx,
                           const int4* flat_desc, const int* n_tiles, float* Opart, float* lse_part, int Hh, long long cap,
                           float scale_log2, const int* kv_rows) {
     auto kfn = D == 128 ? attn_fwd_tile_f32_kernel<128> : attn_fwd_tile_f32_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, q_idx, flat_desc, n_tiles, Opart, lse_part, Hh, cap, scale_log2, kv_rows);
+    kfn<<<grid, dim3(256), 0, st>>>(run_if, Q, K, V, q_idx, flat_desc, n_tiles, Opart, lse_part, Hh, cap, scale_log2, kv_rows);
 }
 
-void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-                         const float* LSE, const float* delta, const int* q_idx, const int4* flat_desc, const int* n_tiles,
+void launch_dq_tiles_f32(int D, dim3 grid, hipStream_t st, const int* run_if, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+                         const float* lse_delta, const int* q_idx, const int4* flat_desc, const int* n_tiles,
                          float* dQpart, int Hh, int S, long long cap, float scale_log2, const int* kv_rows) {
     auto kfn = D == 128 ? attn_bwd_dq_f32_kernel<128> : attn_bwd_dq_f32_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, dO, LSE, delta, q_idx, flat_desc, n_tiles, dQpart, Hh, S, cap, scale_log2, kv_rows);
+    kfn<<<grid, dim3(256), 0, st>>>(run_if, Q, K, V, dO, lse_delta, q_idx, flat_desc, n_tiles, dQpart, Hh, S, cap, scale_log2, kv_rows);
 }
 
-void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-                    const float* LSE, const float* delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,
+void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const int* run_if, int parts, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+                    const float* lse_delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,
                     const int* kb_order, const TensorView& dK, const TensorView& dV, const int* rows, int Hh, int S, int nb, long long cap,
                     float scale_log2, float scale, const int* kv_rows) {
     auto kfn = D == 128 ? attn_bwd_dkv_f32_kernel<128> : attn_bwd_dkv_f32_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(Q, K, V, dO, LSE, delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, dK, dV, rows, Hh, S, nb, cap,
+    kfn<<<grid, dim3(256), 0, st>>>(run_if, parts, Q, K, V, dO, lse_delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, dK, dV, rows, Hh, S, nb, cap,
                                     scale_log2, scale, kv_rows);
 }

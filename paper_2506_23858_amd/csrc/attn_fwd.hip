@@ -20,8 +20,9 @@ constexpr float LN2 = 0.6931471805599453f;
 
 // The flat tile list of a forward call (see write_tile_list); grid: 256 tile ids x head.
 __global__ __launch_bounds__(256) void tile_list_kernel(const int* __restrict__ blk_ptr, const int* __restrict__ blk_off,
-                                                        int4* __restrict__ flat_desc, int* __restrict__ n_tiles, int BH, int nb, int TM) {
+                                                        int4* __restrict__ flat_desc, int* __restrict__ n_tiles, int* __restrict__ clear, int BH, int nb, int TM) {
     __shared__ TileListLds lds;
+    if (clear && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *clear = 0;
     write_tile_list(lds, blk_ptr, blk_off, flat_desc, n_tiles, blockIdx.y, BH, nb, TM, blockIdx.x * 256);
 }
 
@@ -534,7 +535,9 @@ struct FwdWs {
     float* Opart;      // [BH * cap][D], in the tensors' type
     float* lse_part;   // [BH * cap]
     int4* tile_desc;   // the flat list of all heads' tiles
-    int* n_tiles;      // its length
+    int* n_tiles;      // its length, then the split kernels' flag
+    char* Q3;          // float32: [BH][S][3][D], the terms of Q, and [BH][S][6][D], those of K and V in block order (see attn_split.hip)
+    char* KV6;
     size_t total;
 };
 
@@ -543,7 +546,7 @@ struct FwdWs {
 int64_t vmoba_max_tiles(int64_t cap, int TM) { return (cap / TM + VMOBA_MAX_BLOCKS + 7) / 8 * 8; }
 namespace {
 
-FwdWs carve_fwd(void* base, int BH, int D, int64_t cap, int es) {       // es: bytes per element of the partial rows
+FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {       // es: bytes per element of the partial rows
     FwdWs w;
     char* p = (char*)base;
     size_t off = 0;
@@ -551,6 +554,8 @@ FwdWs carve_fwd(void* base, int BH, int D, int64_t cap, int es) {       // es: b
     w.lse_part = (float*)(p + off);  off += align_up((size_t)BH * cap * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
+    w.Q3 = p + off;                  off += es == 4 ? align_up((size_t)BH * S * 6 * D, 256) : 0;
+    w.KV6 = p + off;                 off += es == 4 ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
 }
@@ -558,8 +563,7 @@ FwdWs carve_fwd(void* base, int BH, int D, int64_t cap, int es) {       // es: b
 }  // namespace
 
 size_t vmoba_attn_fwd_workspace_bytes(int B, int Hh, int64_t S, int D, int64_t cap, int dtype) {
-    (void)S;
-    return carve_fwd(nullptr, B * Hh, D, cap, dtype == VMOBA_BF16 ? 2 : 4).total;
+    return carve_fwd(nullptr, B * Hh, S, D, cap, dtype == VMOBA_BF16 ? 2 : 4).total;
 }
 
 // Compute units of the current device (queried once).
@@ -592,7 +596,7 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     if (Kp->dtype != dt || Vp->dtype != dt || O->dtype != dt) return VMOBA_ERR_UNSUPPORTED;
     const int BH = B * Hh;
     if (nnz_capacity > INT32_MAX || (int64_t)BH * nnz_capacity * D > ((int64_t)1 << 40)) return VMOBA_ERR_UNSUPPORTED;
-    FwdWs ws = carve_fwd(workspace, BH, D, nnz_capacity, dt == VMOBA_BF16 ? 2 : 4);
+    FwdWs ws = carve_fwd(workspace, BH, S, D, nnz_capacity, dt == VMOBA_BF16 ? 2 : 4);
     if (workspace_bytes < ws.total) return VMOBA_ERR_WORKSPACE;
     if (((uintptr_t)workspace) & 255) return VMOBA_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
@@ -611,14 +615,25 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     // rows are fetched once per 256 queries); D = 64: 128-query tiles, two workgroups of 4 wavefronts per compute unit;
     // float32: one workgroup per tile of 128 queries
     const bool wide = bf16 && D == 128;
+    const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
     const int TM = wide ? 256 : 128;
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
     tile_list_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-        blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, BH, n_blocks, TM);
+        blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, split ? ws.n_tiles + 1 : nullptr, BH, n_blocks, TM);
     VMOBA_CHECK_LAUNCH();
+    if (split) {
+        launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.Q3, 3, 0, ws.n_tiles + 1);
+        launch_split_rows(D, BH, Hh, (int)S, st, Kv, kv_rows, ws.KV6, 6, 0, ws.n_tiles + 1);
+        launch_split_rows(D, BH, Hh, (int)S, st, Vv, kv_rows, ws.KV6, 6, 3, ws.n_tiles + 1);
+        VMOBA_CHECK_LAUNCH();
+    }
     VMOBA_PROFILE_BEGIN(0, st);
     if (!bf16) {
-        launch_fwd_tiles_f32(D, flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks), st, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles,
+        const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);
+        if (split)
+            launch_fwd_tiles_split(D, grid, st, ws.Q3, ws.KV6, q_idx, ws.tile_desc, ws.n_tiles, ws.n_tiles + 1, ws.Opart, ws.lse_part, (int)S,
+                                   (long long)nnz_capacity, scale_log2);
+        launch_fwd_tiles_f32(D, grid, st, split ? ws.n_tiles + 1 : nullptr, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles,
                              ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows);
     } else {
         const dim3 pgrid((unsigned)std::min<int64_t>((wide ? 1 : 2) * (int64_t)vmoba_num_cus(), (int64_t)BH * max_tiles));

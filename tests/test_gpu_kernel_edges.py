@@ -1,10 +1,14 @@
 """Sizes at which the tile kernels and the selection kernels can go wrong: edges of tiles, remainders, the smallest of a
 range.  Every case runs a whole layer against the CPU oracle (bounds: tests/gpu_util.py)."""
+import math
+
 import numpy as np
 import pytest
 import torch
 
+from oracle import vmoba_oracle as vo
 from paper_2506_23858_amd import synth
+from tests import gpu_util as gu
 from tests.test_gpu_parity import compare_layer
 
 pytestmark = pytest.mark.gpu
@@ -41,3 +45,43 @@ def test_local_selections_at_column_counts(chunk, mode, topk):
     grid, S = (1, 16, 24), 384
     Q, K, V = (synth.to_bf16_grid(synth.iid_normal(970 + i, (1, S, 2, 64))) for i in range(3))
     compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, 0.4, torch.bfloat16, f"local-{chunk}", mode=mode, topk=topk)
+
+
+def check_heads(case, g, Q, K, V, dO, heads):
+    """Attention outputs of some heads against the oracle under the GPU's own mask."""
+    perm, D = g["perm"], Q.shape[3]
+    for h in heads:
+        q, k, v, d = (x[0, perm, h].astype(np.float64) for x in (Q, K, V, dO))
+        m = g["mask"][0, h]
+        O, LSE = vo.masked_attention_fwd(q, k, v, m, g["blk_off"], 1.0 / math.sqrt(D))
+        dQ, dK, dV = vo.masked_attention_bwd(q, k, v, m, g["blk_off"], 1.0 / math.sqrt(D), d)
+        live = np.isfinite(LSE)
+        gu.check_output(case, "LSE", g["LSE"][0, h][live], LSE[live], torch.float32)
+        for name, ref in (("Op", O), ("dQp", dQ), ("dKp", dK), ("dVp", dV)):
+            gu.check_output(case, name.rstrip("p"), g[name][0, h], ref, torch.float32)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [31, 33, 97, 129, 300])
+def test_f32_split_kernels_at_tile_edges(chunk, D):
+    """float32 calls large enough for the kernels on split operands: blocks that end around a 32-key group and around a run of 128 keys
+    (one key, and one wavefront's keys and one more, in the last run), lists that end inside a 32-query chunk."""
+    grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
+    Q, K, V, dO = (synth.iid_normal(1000 + i, (1, S, heads, D)) for i in range(4))
+    g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, 0.95 if chunk < 200 else 0.4, torch.float32, kv_in_place=chunk == 97)
+    check_heads(f"f32-split-{chunk}-{D}", g, Q, K, V, dO, (0, heads - 1))
+
+
+def test_f32_split_kernels_hand_infinities_to_the_float32_ones():
+    """An infinity has no terms to split into: an infinite channel of one value row makes that channel of every query that keeps the key
+    infinite (NaN where the merge meets it again with weight 0), and nothing else, as it does in a call of any size."""
+    grid, S, heads, D = (1, 48, 50), 2400, 8, 128
+    Q, K, V, dO = (synth.iid_normal(1010 + i, (1, S, heads, D)) for i in range(4))
+    ref = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), 300, 0.4, torch.float32)
+    V[0, 777, 3, 5] = np.inf
+    g = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), 300, 0.4, torch.float32)
+    keeps = g["mask"][0, 3][:, 777 // 300]
+    assert keeps.any() and not keeps.all()
+    assert (g["Op"][0, 3][keeps, 5] == np.inf).any() and not np.isfinite(g["Op"][0, 3][keeps, 5]).any()
+    g["Op"][0, 3][keeps, 5] = ref["Op"][0, 3][keeps, 5]
+    gu.check_output("f32-split-inf", "O", g["Op"], ref["Op"], torch.float32)
