@@ -698,16 +698,20 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
 // ---------------------------------------------------------------------------------------------
 // More than 256 blocks: P holds the scaled scores (score_mfma_kernel with RAW); this kernel turns every row into its
 // soft-max in place and takes the first radix level.  One wavefront per row, a lane owns columns lane, lane + 64, ...
+// Bound by the read and write of P; one packed LDS atomic per entry, in two interleaved copies of the words (a count and a sum,
+// two atomics, before).
+constexpr int SOFTMAX_COPIES = 1;                       // log2 of the histogram's replicas
+constexpr int SOFTMAX_MAX_ROWS = 2048;                  // rows of a workgroup: 2048 x 512 entries, what a packed word can count
 __global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ P, unsigned int* __restrict__ hist_cnt,
                                                            unsigned long long* __restrict__ hist_sum, int S, int nb,
                                                            int fix_shift, float2* __restrict__ row_stat) {
     constexpr int MAXC = VMOBA_MAX_BLOCKS / 64;
-    __shared__ unsigned int sCnt[HIST_BINS];
-    __shared__ unsigned long long sSum[HIST_BINS];
+    __shared__ unsigned long long sPk[HIST_BINS << SOFTMAX_COPIES];
     const int bh = blockIdx.y;
-    for (int i = threadIdx.x; i < HIST_BINS; i += 256) { sCnt[i] = 0u; sSum[i] = 0ull; }
+    for (int i = threadIdx.x; i < (HIST_BINS << SOFTMAX_COPIES); i += 256) sPk[i] = 0ull;
     __syncthreads();
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int copy = lane & ((1 << SOFTMAX_COPIES) - 1);
     for (int q = blockIdx.x * 4 + wv; q < S; q += gridDim.x * 4) {
         float* row = P + ((long long)bh * S + q) * nb;
         float v[MAXC];
@@ -723,6 +727,7 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ P
         float den = 0.f;
 #pragma unroll
         for (int c = 0; c < MAXC; ++c) {
+            if (c * 64 >= nb) continue;       // the same columns in every lane
             v[c] = expf(v[c] - m);            // exp(-inf) = 0 past the row's end
             den += v[c];
         }
@@ -735,22 +740,12 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ P
             if (j < nb) {
                 const float p = v[c] / den;
                 row[j] = p;
-                if (hist_cnt) {
-                    const unsigned int bin = min(__float_as_uint(p) >> 20, (unsigned)(HIST_BINS - 1));
-                    atomicAdd(&sCnt[bin], 1u);
-                    atomicAdd(&sSum[bin], to_fixed(p, fix_shift));
-                }
+                if (hist_cnt) packed_hist_add(sPk, SOFTMAX_COPIES, copy, p);
             }
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < HIST_BINS; i += 256) {
-        const unsigned int c = sCnt[i];
-        if (c) {
-            atomicAdd(&hist_cnt[(long long)bh * HIST_BINS + i], c);
-            atomicAdd(&hist_sum[(long long)bh * HIST_BINS + i], sSum[i]);
-        }
-    }
+    if (hist_cnt) packed_hist_flush(sPk, SOFTMAX_COPIES, hist_cnt, hist_sum, bh, fix_shift, threadIdx.x, 256);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1661,6 +1656,9 @@ __device__ __forceinline__ int xcd_contiguous(int i, int n) {
 
 // Fill q_idx (block-major), col_idx and pair_pos (query-major).  One wavefront per 64 queries,
 // lane = query; a ballot per block gives every query its rank inside the wavefront.
+// Bound by the walk over the blocks (a ballot, a rank and two predicated stores each), so it is taken as seldom as the LDS allows:
+// 16-bit entries in a window of 4096, 40 KB per workgroup, against block and place (6 bytes) in one of 2048, 48 KB.  Whole selection,
+// 12 heads x 28 520 tokens x 165 blocks: 498 -> 435 us; x 32 760 x 84 (which one window held before): 247 -> 239 us.
 __global__ __launch_bounds__(256) void fill_lists_kernel(const unsigned int* __restrict__ mask, int* __restrict__ row_ptr,
                                                          const int* __restrict__ wbase,
                                                          const int* __restrict__ blk_ptr, const int* __restrict__ wcnt,
@@ -1670,15 +1668,17 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(const unsigned int* __r
     // The query-major entries of a wavefront's 64 rows form one contiguous run of col_idx / pair_pos.  They are collected
     // in LDS, a window of FILL_STAGE entries at a time, and written out as whole runs; a lane writing its own row's
     // entries straight to global memory touches a different cache line in every lane of every store.  A run longer
-    // than the window walks the blocks once per window (the walk is a few hundred instructions; the window size sets
-    // how many wavefronts a compute unit holds).
-    constexpr int FILL_STAGE = 2048;
-    __shared__ unsigned short sCol[4][FILL_STAGE];
-    __shared__ int sPos[4][FILL_STAGE];
+    // than the window walks the blocks once per window.  An entry is kept as block * 64 + rank among the wavefront's
+    // queries in the block, 16 bits; its place in the block-major list is that rank plus the wavefront's start in the
+    // block, looked up when the entry is written out.
+    constexpr int FILL_STAGE = 4096;
+    static_assert(VMOBA_MAX_BLOCKS * 64 <= 65536, "block and rank share 16 bits");
+    __shared__ unsigned short sEnt[4][FILL_STAGE];
+    __shared__ int sBase[4][VMOBA_MAX_BLOCKS];
     const int bh = blockIdx.y;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int w = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wv;
-    const bool active = w < n_waves;
+    if (w >= n_waves) return;                                            // no barrier below
     const int words = (nb + 31) / 32;
     // where this wavefront's entries of block j start in the block-major list: lane l keeps it for blocks l, l + 64, ...
     // (the walk below reads it with a lane broadcast: no LDS round trip inside the loop)
@@ -1686,10 +1686,11 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(const unsigned int* __r
 #pragma unroll
     for (int i = 0; i < VMOBA_MAX_BLOCKS / 64; ++i) {
         const int j = lane + 64 * i;
-        vbase[i] = (active && j < nb) ? blk_ptr[(long long)bh * (nb + 1) + j] + wcnt[((long long)bh * nb + j) * n_waves + w] : 0;
+        vbase[i] = 0;
+        if (j < nb) sBase[wv][j] = vbase[i] = blk_ptr[(long long)bh * (nb + 1) + j] + wcnt[((long long)bh * nb + j) * n_waves + w];
     }
     const int q = w * 64 + lane;
-    const bool live = active && q < S;
+    const bool live = q < S;
     unsigned int mw[VMOBA_MAX_MASK_WORDS];
 #pragma unroll
     for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd)
@@ -1705,53 +1706,40 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(const unsigned int* __r
         const int o = __shfl_up(incl, off, 64);
         if (lane >= off) incl += o;
     }
-    const long long run0 = active ? wbase[(long long)bh * n_waves + w] : 0;
-    const long long run1 = run0 + __shfl(incl, 63, 64);             // the wavefront's run: [run0, run1)
-    const long long r0 = run0 + incl - cnt;
-    if (live) row_ptr[(long long)bh * (S + 1) + q] = (int)r0;
-    const long long seg = (long long)bh * cap;
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    const bool staged = run1 <= cap;                                     // wave-uniform; false only for a head that overflowed
-    const int n_run = (int)(run1 - run0);
-    // window 0 always runs (it also writes q_idx); an overflowed head writes its entries below cap one by one
-    for (int win0 = 0; win0 == 0 || (staged && win0 < n_run); win0 += FILL_STAGE) {
-        long long r = r0;
-        int lr = (int)(r0 - run0) - win0;                                // position inside the window
+    const int run0 = wbase[(long long)bh * n_waves + w], n_run = __shfl(incl, 63, 64);   // the wavefront's run: [run0, run0 + n_run)
+    if (live) row_ptr[(long long)bh * (S + 1) + q] = run0 + incl - cnt;
+    // a head that kept more than `cap` pairs has an all-zero blk_ptr: no entry of its lists is ever read, and none is written
+    if (row_ptr[(long long)bh * (S + 1) + S] > cap) return;
+    int* const qi = q_idx + (long long)bh * cap;
+    int* const ci = col_idx + (long long)bh * cap + run0;
+    int* const pp = pair_pos + (long long)bh * cap + run0;
+    for (int win0 = 0; win0 < n_run; win0 += FILL_STAGE) {
+        int lr = incl - cnt - win0;                                      // position inside the window
 #pragma unroll
-        for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {          // word by word, so that a word is one register
+        for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {              // word by word, so that a word is one register
             if (wd * 32 >= nb) continue;
             const unsigned int word = mw[wd];
             const int jn = min(32, nb - wd * 32);
             for (int b = 0; b < jn; ++b) {
-                const int j = wd * 32 + b;
                 const bool bit = (word >> b) & 1u;
                 const unsigned long long bal = __ballot(bit);
                 const int base_j = __builtin_amdgcn_readlane(vbase[wd >> 1], (wd & 1) * 32 + b);
+                const unsigned rank = __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
                 if (bit) {
-                    const long long pos = (long long)base_j + __popcll(bal & lt_mask);
-                    if (win0 == 0 && pos < cap) q_idx[seg + pos] = q;
-                    if (staged) {
-                        if ((unsigned)lr < (unsigned)FILL_STAGE) {
-                            sCol[wv][lr] = (unsigned short)j;
-                            sPos[wv][lr] = (int)pos;
-                        }
-                        ++lr;
-                    } else {
-                        if (r < cap) { col_idx[seg + r] = j; pair_pos[seg + r] = (int)pos; }
-                        ++r;
-                    }
+                    if (win0 == 0) qi[base_j + (int)rank] = q;
+                    if ((unsigned)lr < (unsigned)FILL_STAGE) sEnt[wv][lr] = (unsigned short)((wd * 32 + b) * 64 + rank);
+                    ++lr;
                 }
             }
         }
-        if (staged) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            const int n = min(FILL_STAGE, n_run - win0);
-            for (int i = lane; i < n; i += 64) {
-                col_idx[seg + run0 + win0 + i] = sCol[wv][i];
-                pair_pos[seg + run0 + win0 + i] = sPos[wv][i];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        const int n = min(FILL_STAGE, n_run - win0);
+        for (int i = lane; i < n; i += 64) {
+            const int e = sEnt[wv][i];
+            ci[win0 + i] = e >> 6;
+            pp[win0 + i] = sBase[wv][e >> 6] + (e & 63);
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -1930,7 +1918,7 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
                 else LAUNCH_SCORE_MFMA(64, true, true, 0, nbc, jb0);
                 VMOBA_CHECK_LAUNCH();
             }
-            softmax_rows_kernel<<<dim3((unsigned)std::min<int64_t>(ceil_div64(S, 4 * 8), 2048), (unsigned)BH), dim3(256), 0, st>>>(
+            softmax_rows_kernel<<<dim3((unsigned)std::max<int64_t>(std::min<int64_t>(ceil_div64(S, 4 * 8), 2048), ceil_div64(S, SOFTMAX_MAX_ROWS)), (unsigned)BH), dim3(256), 0, st>>>(
                 P, score_hist, ws.hist_sum, (int)S, n_blocks, fix_shift, row_stat);
         } else if (D == 128 && fly) LAUNCH_SCORE_MFMA(128, true, false, 0, n_blocks, 0);
         else if (D == 128) LAUNCH_SCORE_TILES(128);

@@ -47,6 +47,18 @@ def test_local_selections_at_column_counts(chunk, mode, topk):
     compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, 0.4, torch.bfloat16, f"local-{chunk}", mode=mode, topk=topk)
 
 
+@pytest.mark.parametrize("blocks", [63, 64, 65, 128, 257, 512])
+def test_pair_lists_longer_than_a_window(blocks):
+    """Every pair kept: 64 queries hold one entry window less a row, exactly one, one and a row, two, four and a row, eight; the mass cut of more than
+    256 blocks counts its histogram by another kernel and has to agree that the whole pool is kept."""
+    S = 512
+    chunk = -(-S // blocks)
+    grid = (1, 1, blocks * chunk)
+    Q, K, V = (synth.to_bf16_grid(synth.iid_normal(1020 + i, (1, blocks * chunk, 1, 64))) for i in range(3))
+    for tau, mode, topk in ((1.0, 0, 0), (0.4, 1, blocks)):
+        compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"lists-{blocks}", mode=mode, topk=topk)
+
+
 def check_heads(case, g, Q, K, V, dO, heads):
     """Attention outputs of some heads against the oracle under the GPU's own mask."""
     perm, D = g["perm"], Q.shape[3]
