@@ -112,12 +112,6 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorVi
     }
 }
 
-// Load through a wave-uniform base and a 32-bit byte offset per lane (the address needs no 64-bit vector arithmetic).
-template <typename T>
-__device__ __forceinline__ T load_at(const void* base, uint32_t byte_off) {
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte_off);
-}
-
 // ---------------------------------------------------------------------------------------------
 // bf16 MFMA dQ tile kernel.  Same decomposition and operand orientation as the forward tile
 // kernel (query = MFMA column = lane % 32); 4 wavefronts x 32 gathered queries, key chunks of 64:
@@ -158,7 +152,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     TileCoord tc;
     const int4 fd = flat_desc[f];               // {first list entry, count | head << 10, first key, block length}
     tc.list0 = fd.x;
-    tc.t0 = 0;
     tc.count = fd.y & 1023;
     tc.k0 = fd.z;
     tc.L = fd.w;
@@ -169,7 +162,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 
     const int ent = wave * 32 + l32;
     const int e = min(ent, tc.count - 1);
-    const int q = q_idx[seg + tc.list0 + tc.t0 + e];
+    const int q = q_idx[seg + tc.list0 + e];
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
 
@@ -344,7 +337,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
                 v.y = pack_bf16x2(dqacc[dt][4 * g + 2], dqacc[dt][4 * g + 3]);
                 *reinterpret_cast<u32x2_t*>(mine + l32 * OPITCH + (dt * 32 + g * 8 + hf * 4) * 2) = v;
             }
-        char* dst = reinterpret_cast<char*>(dQpart) + (seg + tc.list0 + tc.t0) * (long long)(D * 2);
+        char* dst = reinterpret_cast<char*>(dQpart) + (seg + tc.list0) * (long long)(D * 2);
         constexpr int LPR = D * 2 / 16;                                       // lanes per row
 #pragma unroll
         for (int k = 0; k < 32 * LPR / 64; ++k) {

@@ -78,7 +78,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 struct TileCoord {
     int count;    // valid entries in the tile (1..TM)
     int list0;    // first list entry of the tile, relative to the head's segment
-    int t0;       // always 0 (the tile's offset is folded into list0)
     int k0, L;    // first key position and number of keys of the tile's key block
 };
 

@@ -51,7 +51,6 @@ static inline bool tensor_ok(const vmoba_tensor* t) {
         if (hipGetLastError() != hipSuccess) return VMOBA_ERR_HIP; \
     } while (0)
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 __device__ __forceinline__ float bf16lo_to_f32(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16hi_to_f32(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
