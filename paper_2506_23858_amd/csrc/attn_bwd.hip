@@ -403,12 +403,19 @@ struct DkvLds : RowTile<D> {
 // Matrix instruction on a sum that stays in accumulator registers.  (This file is compiled so that the results of the matrix
 // instructions it does not name in assembly go to ordinary registers: S and dP are read by vector instructions, which cannot
 // read accumulator registers -- with the compiler's choice for a kernel of this size, everything there, every one of
-// their values takes a copy, one instruction more per matrix instruction.)  The compiler does not see the latency: nothing but
-// further matrix instructions may read the sum until acc_ready.
+// their values takes a copy, one instruction more per matrix instruction.)  The compiler sees neither that such an instruction needs
+// two wait states after a vector instruction that wrote one of its operands, nor how long its result takes: a pack that
+// feeds one lies whole units before it, and acc_ready stands between the last of them and everything else that touches the sums.
+// (tests/test_matrix_wait_states.py follows the compiled code for both.)
 __device__ __forceinline__ void mfma_acc(f32x16_t& d, bf16x8_t a, bf16x8_t b) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void acc_ready(f32x16_t& d) { asm volatile("s_nop 15\n\ts_nop 3" : "+a"(d)); }
+__device__ __forceinline__ void acc_ready(f32x16_t (&d)[2][2]) {
+    asm volatile("s_nop 15" : "+a"(d[0][0]), "+a"(d[0][1]), "+a"(d[1][0]), "+a"(d[1][1]));
+}
+__device__ __forceinline__ void acc_ready(f32x16_t (&d)[2][4]) {
+    asm volatile("s_nop 15" : "+a"(d[0][0]), "+a"(d[0][1]), "+a"(d[0][2]), "+a"(d[0][3]), "+a"(d[1][0]), "+a"(d[1][1]), "+a"(d[1][2]), "+a"(d[1][3]));
+}
 
 template <int D>
 __device__ __forceinline__ void dkv_pair_body(
@@ -652,17 +659,17 @@ __device__ __forceinline__ void dkv_pair_body(
             };
             using R0 = std::integral_constant<int, 0>;
             using R1 = std::integral_constant<int, 1>;
-            // dV or dK of the last half-chunk, whose packed operand the last step left; nothing of S / dP outlives the loop
+            // dV or dK of the last half-chunk, whose packed operand the last step left; nothing of S / dP outlives the loop.  These matrix
+            // instructions are the compiler's: what it moves here it may move, and waits for.
             auto drain = [&]() {
+                acc_ready(acc);
 #pragma unroll
                 for (int st = 0; st < NST; ++st) {
                     if (st + 2 < NST) top[(st + 2) & 3] = read_tr(H - 1, st + 2);
 #pragma unroll
                     for (int kg = 0; kg < 2; ++kg)
-                        mfma_acc(acc[kg][st % DT], top[st & 3], w_prev[kg][st / DT]);
+                        acc[kg][st % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(top[st & 3], w_prev[kg][st / DT], acc[kg][st % DT], 0, 0, 0);
                 }
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) { acc_ready(acc[0][dt]); acc_ready(acc[1][dt]); }
             };
             if (role == 0) {
                 for (int t = 0; t < H; t += 2) {
