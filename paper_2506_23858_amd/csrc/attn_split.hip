@@ -339,13 +339,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(const char* _
         if (c + 1 < n_chunks) request(c + 1);
         const char* sK = smem[c & 1];
         const char* sV = smem[c & 1] + ST::TILE;
-        f32x16_t s = st.over_channels(sK, qf, [](int) {});
-        const int left = t.L - c * 32 - hf;
-        if (left < 32) {                                          // keys past the block's end: weight 0
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (acc_row(v, 0) >= left) s[v] = -INFINITY;
-        }
+        const f32x16_t s = st.over_channels(sK, qf, [](int) {});
         float p[16];
         const f32x16_t dp = st.over_channels(sV, dof, [&](int j) __attribute__((always_inline)) {
 #pragma unroll
@@ -354,6 +348,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(const char* _
                 asm volatile("" : "+v"(p[v]));
             }
         });
+        const int left = t.L - c * 32 - hf;                       // value v is key acc_row(v, 0) of this lane half
+        if (left < 32) {                                          // keys past the block's end: weight 0 (whatever the sign of the scale)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (acc_row(v, 0) >= left) p[v] = 0.f;
+        }
         Terms w;
         auto ds_pair = [&](int j) __attribute__((always_inline)) { w.pair(j, p[2 * j] * (dp[2 * j] + ndl), p[2 * j + 1] * (dp[2 * j + 1] + ndl)); };
 #pragma unroll

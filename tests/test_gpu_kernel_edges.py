@@ -59,14 +59,15 @@ def test_pair_lists_longer_than_a_window(blocks):
         compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"lists-{blocks}", mode=mode, topk=topk)
 
 
-def check_heads(case, g, Q, K, V, dO, heads):
+def check_heads(case, g, Q, K, V, dO, heads, scale=None):
     """Attention outputs of some heads against the oracle under the GPU's own mask."""
-    perm, D = g["perm"], Q.shape[3]
+    perm = g["perm"]
+    scale = 1.0 / math.sqrt(Q.shape[3]) if scale is None else scale
     for h in heads:
         q, k, v, d = (x[0, perm, h].astype(np.float64) for x in (Q, K, V, dO))
         m = g["mask"][0, h]
-        O, LSE = vo.masked_attention_fwd(q, k, v, m, g["blk_off"], 1.0 / math.sqrt(D))
-        dQ, dK, dV = vo.masked_attention_bwd(q, k, v, m, g["blk_off"], 1.0 / math.sqrt(D), d)
+        O, LSE = vo.masked_attention_fwd(q, k, v, m, g["blk_off"], scale)
+        dQ, dK, dV = vo.masked_attention_bwd(q, k, v, m, g["blk_off"], scale, d)
         live = np.isfinite(LSE)
         gu.check_output(case, "LSE", g["LSE"][0, h][live], LSE[live], torch.float32)
         for name, ref in (("Op", O), ("dQp", dQ), ("dKp", dK), ("dVp", dV)):
@@ -82,6 +83,17 @@ def test_f32_split_kernels_at_tile_edges(chunk, D):
     Q, K, V, dO = (synth.iid_normal(1000 + i, (1, S, heads, D)) for i in range(4))
     g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, 0.95 if chunk < 200 else 0.4, torch.float32, kv_in_place=chunk == 97)
     check_heads(f"f32-split-{chunk}-{D}", g, Q, K, V, dO, (0, heads - 1))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("scale", [-0.07, 0.0])
+def test_f32_split_kernels_take_a_scale_of_any_sign(scale, D):
+    """Scores that count downwards and scores that do not count, with keys past the block's end in the last 32-key group (blocks of 97 and 300)."""
+    grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
+    Q, K, V, dO = (synth.iid_normal(1030 + i, (1, S, heads, D)) for i in range(4))
+    for chunk, tau in ((97, 0.95), (300, 0.4)):
+        g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, softmax_scale=scale)
+        check_heads(f"f32-split-scale-{scale}-{chunk}-{D}", g, Q, K, V, dO, (0, heads - 1), scale)
 
 
 def test_f32_split_kernels_hand_infinities_to_the_float32_ones():
