@@ -276,8 +276,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
                 for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = ndl; }        // the sum for dP - delta starts at -delta
                 float ds[16];
                 bf16x8_t dsf;
+                const int vh = valid - mt * 32 - hf;  // MASK: value i belongs to a key of the block when acc_row(i, 0) < vh
                 auto p_value = [&](int i) {           // S^T value -> P^T value, in place
                     sacc[i] = exp2_raw(fmaf(sacc[i], scale_log2, -lse2));
+                    if (MASK && acc_row(i, 0) >= vh) sacc[i] = 0.f;
                 };
                 auto ds_value = [&](int i) {
                     ds[i] = sacc[i] * dpacc[i];
@@ -293,12 +295,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
                         const int ks = n - KSTEPS;
                         dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[n % RING], dof[ks], dpacc, 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
-                        if (MASK && ks == 0) {
-                            const int vh = valid - mt * 32 - hf;
-#pragma unroll
-                            for (int i = 0; i < 16; ++i)
-                                if (acc_row(i, 0) >= vh) sacc[i] = -INFINITY;
-                        }
 #pragma unroll
                         for (int v = 0; v < 16 / KSTEPS; ++v) p_value(ks * (16 / KSTEPS) + v);
                     } else {

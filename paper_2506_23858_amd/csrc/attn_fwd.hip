@@ -10,6 +10,7 @@
 #include "attn_common.h"
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -89,7 +90,7 @@ template <int D, int NW, bool KVR>
 __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
     const int* __restrict__ n_tiles, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
-    long long cap, float scale_log2, const int* __restrict__ kv_rows) {
+    long long cap, float scale_log2, uint32_t q_sign, const int* __restrict__ kv_rows) {
     constexpr int G = 32;                   // keys per group
     using TL = RowTile<D>;
     constexpr int PPR = TL::PPR;            // 16-byte pieces per row
@@ -270,6 +271,10 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
 
         VMOBA_WAIT_VMCNT(0);                       // this wavefront's K(0..3), V(0..1) (and Q rows) have landed
         __syncthreads();                           // ... and everybody else's
+        if (q_sign) {                              // a negative scale: the scores of -Q with the scale's magnitude
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(u32x4_t, qf[ks]) ^ q_sign);
+        }
         // S^T(0), and the operands of the first two units of step 0
         if (odd) {
 #pragma unroll
@@ -636,8 +641,12 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         launch_fwd_tiles_f32(D, grid, st, split ? ws.n_tiles + 1 : nullptr, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles,
                              ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows);
     } else {
+        // the kernel's running maximum and its mask of the keys past a block's end need a positive scale: the sign goes to Q, and the
+        // smallest normal number does for 0 (it leaves every weight at 1)
+        const float magnitude = std::max(std::fabs(scale_log2), FLT_MIN);
+        const uint32_t q_sign = scale_log2 < 0.f ? 0x80008000u : 0u;
         const dim3 pgrid((unsigned)std::min<int64_t>((wide ? 1 : 2) * (int64_t)vmoba_num_cus(), (int64_t)BH * max_tiles));
-#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows
+#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, magnitude, q_sign, kv_rows
         if (wide && kv_rows) attn_fwd_tile_mfma_kernel<128, 8, true><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);
         else if (wide) attn_fwd_tile_mfma_kernel<128, 8, false><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);
         else if (kv_rows) attn_fwd_tile_mfma_kernel<64, 4, true><<<pgrid, dim3(256), 0, st>>>(MFMA_ARGS);

@@ -59,7 +59,7 @@ def test_pair_lists_longer_than_a_window(blocks):
         compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"lists-{blocks}", mode=mode, topk=topk)
 
 
-def check_heads(case, g, Q, K, V, dO, heads, scale=None):
+def check_heads(case, g, Q, K, V, dO, heads, scale=None, dtype=torch.float32):
     """Attention outputs of some heads against the oracle under the GPU's own mask."""
     perm = g["perm"]
     scale = 1.0 / math.sqrt(Q.shape[3]) if scale is None else scale
@@ -69,9 +69,9 @@ def check_heads(case, g, Q, K, V, dO, heads, scale=None):
         O, LSE = vo.masked_attention_fwd(q, k, v, m, g["blk_off"], scale)
         dQ, dK, dV = vo.masked_attention_bwd(q, k, v, m, g["blk_off"], scale, d)
         live = np.isfinite(LSE)
-        gu.check_output(case, "LSE", g["LSE"][0, h][live], LSE[live], torch.float32)
+        gu.check_output(case, "LSE", g["LSE"][0, h][live], LSE[live], dtype)
         for name, ref in (("Op", O), ("dQp", dQ), ("dKp", dK), ("dVp", dV)):
-            gu.check_output(case, name.rstrip("p"), g[name][0, h], ref, torch.float32)
+            gu.check_output(case, name.rstrip("p"), g[name][0, h], ref, dtype)
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -94,6 +94,17 @@ def test_f32_split_kernels_take_a_scale_of_any_sign(scale, D):
     for chunk, tau in ((97, 0.95), (300, 0.4)):
         g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, softmax_scale=scale)
         check_heads(f"f32-split-scale-{scale}-{chunk}-{D}", g, Q, K, V, dO, (0, heads - 1), scale)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("scale", [-0.09, 0.0])
+def test_bf16_kernels_take_a_scale_of_any_sign(scale, D):
+    """The same for the bfloat16 kernels: blocks of one 32-key group and less, of one and a part, of whole groups, of a 64-key chunk and a part."""
+    grid, S, heads = (1, 8, 50), 400, 2
+    Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(1040 + i, (1, S, heads, D))) for i in range(4))
+    for chunk, kv_in_place in ((20, False), (33, True), (64, False), (97, True)):
+        g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, 0.6, torch.bfloat16, softmax_scale=scale, kv_in_place=kv_in_place)
+        check_heads(f"bf16-scale-{scale}-{chunk}-{D}", g, Q, K, V, dO, range(heads), scale, torch.bfloat16)
 
 
 def test_f32_split_kernels_hand_infinities_to_the_float32_ones():
