@@ -1087,7 +1087,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     // ---- delta, tile list, key runs
     const int TM = 128;                     // queries per dQ tile
     const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
-    int* const not_finite = ws.n_tiles + 1;
+    int* const out_of_range = ws.n_tiles + 1;
     const int KPW = bf16 || split ? 128 : 64;        // keys per dK/dV workgroup
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
     {
@@ -1095,7 +1095,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         const dim3 grid((unsigned)(n_delta + ceil_div64(max_tiles, 256) + 1), (unsigned)BH);
         auto kfn = bf16 ? (D == 128 ? bwd_prepare_kernel<true, 128> : bwd_prepare_kernel<true, 64>)
                         : (D == 128 ? bwd_prepare_kernel<false, 128> : bwd_prepare_kernel<false, 64>);
-        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, not_finite, ws.kb_start, ws.kb_order,
+        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, out_of_range, ws.kb_start, ws.kb_order,
                                         BH, Hh, (int)S, n_blocks, TM, KPW, bf16 ? 32 : 0, n_delta);
         VMOBA_CHECK_LAUNCH();
     }
@@ -1106,10 +1106,10 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         dOv.stride_s = D;
     }
     if (split) {
-        launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.QD6, 6, 0, not_finite);
-        launch_split_rows(D, BH, Hh, (int)S, st, dOv, nullptr, ws.QD6, 6, 3, not_finite);
-        launch_split_rows(D, BH, Hh, (int)S, st, Kv, kv_rows, ws.KV6, 6, 0, not_finite);
-        launch_split_rows(D, BH, Hh, (int)S, st, Vv, kv_rows, ws.KV6, 6, 3, not_finite);
+        launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.QD6, 6, 0, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, dOv, nullptr, ws.QD6, 6, 3, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, Kv, kv_rows, ws.KV6, 6, 0, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, Vv, kv_rows, ws.KV6, 6, 3, out_of_range);
         VMOBA_CHECK_LAUNCH();
     }
     const int pitch = lse_delta_pitch((int)S);
@@ -1119,9 +1119,9 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);     // one workgroup per tile
         if (!bf16) {
             if (split)
-                launch_dq_tiles_split(D, grid, st, ws.QD6, ws.KV6, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, not_finite, ws.dQpart, (int)S, pitch,
+                launch_dq_tiles_split(D, grid, st, ws.QD6, ws.KV6, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, out_of_range, ws.dQpart, (int)S, pitch,
                                       (long long)nnz_capacity, scale_log2);
-            launch_dq_tiles_f32(D, grid, st, split ? not_finite : nullptr, Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
+            launch_dq_tiles_f32(D, grid, st, split ? out_of_range : nullptr, Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
                                 (long long)nnz_capacity, scale_log2, kv_rows);
         } else {
 #define DQ_ARGS Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S, (long long)nnz_capacity, scale_log2, kv_rows
@@ -1156,10 +1156,10 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
 #define DKV_ARGS blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
         if (!bf16) {
             if (split)
-                launch_dkv_split(D, hgrid, st, ws.QD6, ws.KV6, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, not_finite, dKv, dVv, krows,
+                launch_dkv_split(D, hgrid, st, ws.QD6, ws.KV6, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, out_of_range, dKv, dVv, krows,
                                  Hh, (int)S, pitch, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, BH, slots, group);
             const int parts = split ? 2 : 1;
-            launch_dkv_f32(D, dim3(grid.x * parts, grid.y), st, split ? not_finite : nullptr, parts, Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS);
+            launch_dkv_f32(D, dim3(grid.x * parts, grid.y), st, split ? out_of_range : nullptr, parts, Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS);
         } else {
             if (D == 128) attn_bwd_dkv_kernel<128><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
             else attn_bwd_dkv_kernel<64><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);

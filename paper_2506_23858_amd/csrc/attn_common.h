@@ -169,14 +169,14 @@ void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const int* run_if, int par
                     const int* kb_order, const TensorView& dK, const TensorView& dV, const int* rows, int Hh, int S, int nb, long long cap,
                     float scale_log2, float scale, const int* kv_rows);
 // The same on the bfloat16 matrix instruction, from rows split into three terms each (attn_split.hip).
-void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const TensorView& X, const int* map, char* dst, int planes, int plane0, int* not_finite);
+void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const TensorView& X, const int* map, char* dst, int planes, int plane0, int* out_of_range);
 void launch_fwd_tiles_split(int D, dim3 grid, hipStream_t st, const char* Q3, const char* KV6, const int* q_idx, const int4* flat_desc,
-                            const int* n_tiles, const int* not_finite, float* Opart, float* lse_part, int S, long long cap, float scale_log2);
+                            const int* n_tiles, const int* out_of_range, float* Opart, float* lse_part, int S, long long cap, float scale_log2);
 void launch_dq_tiles_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* q_idx,
-                           const int4* flat_desc, const int* n_tiles, const int* not_finite, float* dQpart, int S, int pitch, long long cap,
+                           const int4* flat_desc, const int* n_tiles, const int* out_of_range, float* dQpart, int S, int pitch, long long cap,
                            float scale_log2);
 void launch_dkv_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* blk_off, const int* blk_ptr,
-                      const int* q_idx, const int* kb_start, const int* kb_order, const int* not_finite, const TensorView& dK, const TensorView& dV,
+                      const int* q_idx, const int* kb_start, const int* kb_order, const int* out_of_range, const TensorView& dK, const TensorView& dV,
                       const int* rows, int Hh, int S, int pitch, int nb, long long cap, float scale_log2, float scale, int BH, int slots, int group);
 // float32 calls with enough work -- multiply-adds of one product over all pairs the lists can hold -- take the split kernels, if
 // 32-bit offsets reach every split row of a head.  What they cost beside their products is seven passes over the inputs

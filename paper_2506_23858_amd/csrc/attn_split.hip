@@ -2,16 +2,21 @@
 // the matrix pipe (the kernels of attn_f32.hip, on the float32 instruction, keep the small ones).
 //
 // Every float32 operand x is split into three bfloat16 terms, x = h + m + l (each the rounding of what the ones before leave:
-// 8 + 8 + 8 mantissa bits, exact to 2^-27 |x|), and a product of two operands is the sum of the six products of terms whose
+// 8 + 8 + 8 mantissa bits, exact to 2^-27 |x| while the last bit stands above bfloat16's smallest number, 2^-133), and a product of two operands is the sum of the six products of terms whose
 // orders add up to at most two: h h + (h m + m h) + (h l + l h + m m); what is left out is below 2^-25 |a b|.  Products of terms are
 // exact in float32 and summed there, small ones first.  The result is closer to the exact one than the
 // float32 instruction's, whose chain of sums is eight times as long per k-step (relative error of a product over 128 / 1024 normal
 // values: 1.7e-7 / 5.1e-7 against 2.0e-7 / 5.9e-7), at six 32-cycle instructions for eight of 64 cycles.
 //
 // Inputs are split once per call, into rows of planes (split_rows_kernel), so that tiles travel from global memory straight to LDS
-// and are laid out like the bfloat16 kernels' (RowTile); the soft-max weights and dS are split in registers.  Terms of
-// an infinity or NaN would not recombine to it: the split kernel raises a flag when it meets one, and then these kernels
-// leave at once and those of attn_f32.hip, launched behind them, do the work instead.
+// and are laid out like the bfloat16 kernels' (RowTile); the soft-max weights and dS are split in registers.
+//
+// Range.  Terms of an infinity or NaN would not recombine to it, and those of a small number lose its last bits: the split kernel raises
+// a flag when it meets a value that is neither 0 nor of a magnitude from 2^-100 up to 2^26, and then these kernels
+// leave at once and those of attn_f32.hip, launched behind them, do the work instead.  Weights and dS can be as small as float32
+// goes -- a key that no query attends to has only such -- so they are split after a multiplication by 2^16, which makes
+// three terms of every normal number exact, and the sums they enter are multiplied by 2^-16 when they are
+// written.  With inputs below 2^26 the largest sum, dK' of 2^22 queries, stays below 2^124.
 //
 // Work decomposition, orientation and operand plumbing as in the bfloat16 kernels (attn_common.h).
 //
@@ -28,6 +33,8 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
+constexpr float LIFT = 0x1p16f, UNLIFT = 0x1p-16f;                                // of weights and dS, see above
+constexpr uint32_t SMALLEST = 27u << 23, TOO_LARGE = 153u << 23;                  // 2^-100 and 2^26 as float bits
 
 // two floats -> their bfloat16 pairs h, m, l (low half = a)
 __device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
@@ -41,7 +48,7 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& 
 // [BH][S][planes][D].  One thread per eight channels.  Bound by HBM: 4 bytes in, 6 out per value.
 template <int D>
 __global__ __launch_bounds__(256) void split_rows_kernel(TensorView X, const int* __restrict__ map, char* __restrict__ dst, int planes, int plane0, int Hh,
-                                                         int S, int* __restrict__ not_finite) {
+                                                         int S, int* __restrict__ out_of_range) {
     constexpr int PPR = D / 8;
     const int bh = blockIdx.y, b = bh / Hh, h = bh % Hh;
     const int r = blockIdx.x * (256 / PPR) + threadIdx.x / PPR, piece = threadIdx.x % PPR;
@@ -57,13 +64,13 @@ __global__ __launch_bounds__(256) void split_rows_kernel(TensorView X, const int
         uint32_t th, tm, tl;
         split2(a, c, th, tm, tl);
         t[0][i] = th; t[1][i] = tm; t[2][i] = tl;
-        // the leading term carries every infinity and NaN, and the values that round up to one
-        bad |= (th & 0x7f80u) == 0x7f80u || (th & 0x7f800000u) == 0x7f800000u;
+        const uint32_t ua = __float_as_uint(a) & 0x7fffffffu, uc = __float_as_uint(c) & 0x7fffffffu;
+        bad |= (ua && ua - SMALLEST >= TOO_LARGE - SMALLEST) || (uc && uc - SMALLEST >= TOO_LARGE - SMALLEST);
     }
     char* d = dst + (((long long)bh * S + r) * planes + plane0) * (D * 2) + piece * 16;
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x4_t*>(d + p * D * 2) = t[p];
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(not_finite, 1);
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(out_of_range, 1);
 }
 
 // The terms of 16 values per lane in accumulator order, as the B operand of a product over the tile's rows: filled pair by pair.
@@ -198,13 +205,13 @@ __device__ __forceinline__ bool take_split_tile(const int4* __restrict__ flat_de
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_fwd_tile_split_kernel(const char* __restrict__ Q3, const char* __restrict__ KV6, const int* __restrict__ q_idx,
                                                                      const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles,
-                                                                     const int* __restrict__ not_finite, float* __restrict__ Opart,
+                                                                     const int* __restrict__ out_of_range, float* __restrict__ Opart,
                                                                      float* __restrict__ lse_part, int S, long long cap, float scale_log2) {
     using ST = SplitTile<D>;
     constexpr int DT = ST::DT, IPW = ST::IPW, RB6 = 12 * D;
     __shared__ __align__(1024) char smem[2 * ST::TILE];
     SplitDesc t;
-    if (*not_finite || !take_split_tile(flat_desc, n_tiles, t)) return;
+    if (*out_of_range || !take_split_tile(flat_desc, n_tiles, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const long long seg = (long long)t.bh * cap;
@@ -263,7 +270,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_tile_split_kernel(const char*
         auto weights = [&](int j) __attribute__((always_inline)) {
             const float p0 = exp2_raw(s[2 * j] - m_run), p1 = exp2_raw(s[2 * j + 1] - m_run);
             l_run += p0 + p1;
-            w.pair(j, p0, p1);
+            w.pair(j, p0 * LIFT, p1 * LIFT);
         };
 #pragma unroll
         for (int j = 0; j < 4; ++j) weights(j);
@@ -276,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_tile_split_kernel(const char*
     const float l_tot = swap_halves_sum(l_run);
     if (ent < t.count) {
         const long long pair = seg + t.list0 + ent;
-        const float inv = 1.f / l_tot;
+        const float inv = 1.f / l_tot * UNLIFT;
         float* dst = Opart + pair * D;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -297,13 +304,13 @@ template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(const char* __restrict__ QD6, const char* __restrict__ KV6,
                                                                    const float* __restrict__ lse_delta, const int* __restrict__ q_idx,
                                                                    const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles,
-                                                                   const int* __restrict__ not_finite, float* __restrict__ dQpart, int S, int pitch,
+                                                                   const int* __restrict__ out_of_range, float* __restrict__ dQpart, int S, int pitch,
                                                                    long long cap, float scale_log2) {
     using ST = SplitTile<D>;
     constexpr int DT = ST::DT, IPW = ST::IPW, RB6 = 12 * D;
     __shared__ __align__(1024) char smem[2][2 * ST::TILE];
     SplitDesc t;
-    if (*not_finite || !take_split_tile(flat_desc, n_tiles, t)) return;
+    if (*out_of_range || !take_split_tile(flat_desc, n_tiles, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const long long seg = (long long)t.bh * cap;
@@ -344,7 +351,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(const char* _
         const f32x16_t dp = st.over_channels(sV, dof, [&](int j) __attribute__((always_inline)) {
 #pragma unroll
             for (int v = 2 * j; v < 2 * j + 2; ++v) {
-                p[v] = exp2_raw(fmaf(s[v], scale_log2, -lse2));
+                p[v] = exp2_raw(fmaf(s[v], scale_log2, -lse2)) * LIFT;
                 asm volatile("" : "+v"(p[v]));
             }
         });
@@ -366,7 +373,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(const char* _
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const f32x4_t o = {acc[dt][4 * i], acc[dt][4 * i + 1], acc[dt][4 * i + 2], acc[dt][4 * i + 3]};
+                const f32x4_t o = {acc[dt][4 * i] * UNLIFT, acc[dt][4 * i + 1] * UNLIFT, acc[dt][4 * i + 2] * UNLIFT, acc[dt][4 * i + 3] * UNLIFT};
                 *reinterpret_cast<f32x4_t*>(dst + dt * 32 + i * 8 + hf * 4) = o;
             }
     }
@@ -380,13 +387,13 @@ template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_split_kernel(
     const char* __restrict__ QD6, const char* __restrict__ KV6, const float* __restrict__ lse_delta, const int* __restrict__ blk_off,
     const int* __restrict__ blk_ptr, const int* __restrict__ q_idx, const int* __restrict__ kb_start, const int* __restrict__ kb_order,
-    const int* __restrict__ not_finite, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int pitch, int nb, long long cap,
+    const int* __restrict__ out_of_range, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int pitch, int nb, long long cap,
     float scale_log2, float scale, int BH, int slots, int group) {
     using ST = SplitTile<D>;
     constexpr int DT = ST::DT, IPW = ST::IPW, RB6 = 12 * D;
     __shared__ __align__(1024) char smem[2][2 * ST::TILE];        // [buffer][Q, dO]
     __shared__ float sLD[2][64];                                  // [buffer]: LSE, -delta in accumulator order
-    if (*not_finite) return;
+    if (*out_of_range) return;
     // groups of one block's runs to the XCDs in turn, heads inside a group number (see attn_bwd_dkv_kernel): 2.51 -> 2.22 ms
     const int n = (int)blockIdx.x >> 3, G = (n / group) * 8 + ((int)blockIdx.x & 7);
     if (G >= BH * (slots / group)) return;
@@ -459,7 +466,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_split_kernel(
             Terms pw, dw;
             const f32x16_t dp = st.template over_channels<true>(tdO, vf, [&](int j) __attribute__((always_inline)) {
 #pragma unroll
-                for (int v = 2 * j; v < 2 * j + 2; ++v) p[v] = exp2_raw(fmaf(s[v], scale_log2, -ld[v]));
+                for (int v = 2 * j; v < 2 * j + 2; ++v) p[v] = exp2_raw(fmaf(s[v], scale_log2, -ld[v])) * LIFT;
                 pw.pair(j, p[2 * j], p[2 * j + 1]);
             });
             st.template over_rows<false>(tdO, pw, acc[0], [&](int j) __attribute__((always_inline)) {
@@ -476,8 +483,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_split_kernel(
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const f32x4_t ov = {acc[0][dt][4 * i], acc[0][dt][4 * i + 1], acc[0][dt][4 * i + 2], acc[0][dt][4 * i + 3]};
-                const f32x4_t ok = {acc[1][dt][4 * i] * scale, acc[1][dt][4 * i + 1] * scale, acc[1][dt][4 * i + 2] * scale, acc[1][dt][4 * i + 3] * scale};
+                f32x4_t ov, ok;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    ov[r] = acc[0][dt][4 * i + r] * UNLIFT;
+                    ok[r] = acc[1][dt][4 * i + r] * UNLIFT * scale;
+                }
                 *reinterpret_cast<f32x4_t*>(pv + dt * 32 + i * 8 + hf * 4) = ov;
                 *reinterpret_cast<f32x4_t*>(pk + dt * 32 + i * 8 + hf * 4) = ok;
             }
@@ -486,29 +497,29 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_split_kernel(
 
 }  // namespace
 
-void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const TensorView& X, const int* map, char* dst, int planes, int plane0, int* not_finite) {
+void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const TensorView& X, const int* map, char* dst, int planes, int plane0, int* out_of_range) {
     const dim3 grid((unsigned)ceil_div64(S, 256 / (D / 8)), (unsigned)BH);
     auto kfn = D == 128 ? split_rows_kernel<128> : split_rows_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(X, map, dst, planes, plane0, Hh, S, not_finite);
+    kfn<<<grid, dim3(256), 0, st>>>(X, map, dst, planes, plane0, Hh, S, out_of_range);
 }
 
 void launch_fwd_tiles_split(int D, dim3 grid, hipStream_t st, const char* Q3, const char* KV6, const int* q_idx, const int4* flat_desc,
-                            const int* n_tiles, const int* not_finite, float* Opart, float* lse_part, int S, long long cap, float scale_log2) {
+                            const int* n_tiles, const int* out_of_range, float* Opart, float* lse_part, int S, long long cap, float scale_log2) {
     auto kfn = D == 128 ? attn_fwd_tile_split_kernel<128> : attn_fwd_tile_split_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(Q3, KV6, q_idx, flat_desc, n_tiles, not_finite, Opart, lse_part, S, cap, scale_log2);
+    kfn<<<grid, dim3(256), 0, st>>>(Q3, KV6, q_idx, flat_desc, n_tiles, out_of_range, Opart, lse_part, S, cap, scale_log2);
 }
 
 void launch_dq_tiles_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* q_idx,
-                           const int4* flat_desc, const int* n_tiles, const int* not_finite, float* dQpart, int S, int pitch, long long cap,
+                           const int4* flat_desc, const int* n_tiles, const int* out_of_range, float* dQpart, int S, int pitch, long long cap,
                            float scale_log2) {
     auto kfn = D == 128 ? attn_bwd_dq_split_kernel<128> : attn_bwd_dq_split_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(QD6, KV6, lse_delta, q_idx, flat_desc, n_tiles, not_finite, dQpart, S, pitch, cap, scale_log2);
+    kfn<<<grid, dim3(256), 0, st>>>(QD6, KV6, lse_delta, q_idx, flat_desc, n_tiles, out_of_range, dQpart, S, pitch, cap, scale_log2);
 }
 
 void launch_dkv_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* blk_off, const int* blk_ptr,
-                      const int* q_idx, const int* kb_start, const int* kb_order, const int* not_finite, const TensorView& dK, const TensorView& dV,
+                      const int* q_idx, const int* kb_start, const int* kb_order, const int* out_of_range, const TensorView& dK, const TensorView& dV,
                       const int* rows, int Hh, int S, int pitch, int nb, long long cap, float scale_log2, float scale, int BH, int slots, int group) {
     auto kfn = D == 128 ? attn_bwd_dkv_split_kernel<128> : attn_bwd_dkv_split_kernel<64>;
-    kfn<<<grid, dim3(256), 0, st>>>(QD6, KV6, lse_delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, not_finite, dK, dV, rows, Hh, S, pitch, nb,
+    kfn<<<grid, dim3(256), 0, st>>>(QD6, KV6, lse_delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, out_of_range, dK, dV, rows, Hh, S, pitch, nb,
                                     cap, scale_log2, scale, BH, slots, group);
 }

@@ -120,3 +120,44 @@ def test_f32_split_kernels_hand_infinities_to_the_float32_ones():
     assert (g["Op"][0, 3][keeps, 5] == np.inf).any() and not np.isfinite(g["Op"][0, 3][keeps, 5]).any()
     g["Op"][0, 3][keeps, 5] = ref["Op"][0, 3][keeps, 5]
     gu.check_output("f32-split-inf", "O", g["Op"], ref["Op"], torch.float32)
+
+
+def relative_error(got, ref):
+    return float(np.linalg.norm(got.astype(np.float64) - ref) / np.linalg.norm(ref))
+
+
+@pytest.mark.parametrize("powers", [(60, 55), (110, 0), (0, 110), (118, 0)])
+def test_f32_split_kernels_on_small_magnitudes(powers):
+    """dO and V scaled by powers of two: everything they enter scales along, exactly but for what falls below the smallest normal number (last
+    bit 2^-149: 1e-7 of values of 2^-126 and up).  Operands below 2^-100 have no three terms of eight bits: such a call takes the
+    float32 kernels, whose sums differ from the others' by up to 1e-6."""
+    grid, S, heads, D = (1, 48, 50), 2400, 8, 128
+    Q, K, V, dO = (synth.iid_normal(1050 + i, (1, S, heads, D)) for i in range(4))
+    do_pow, v_pow = powers
+    a, b = (gu.run_gpu(Q, K, v, d, grid, (0, 0, 0), 300, 0.4, torch.float32)
+            for v, d in ((V, dO), (V * np.float32(2.0 ** -v_pow), dO * np.float32(2.0 ** -do_pow))))
+    for name, power in (("Op", v_pow), ("dVp", do_pow), ("dQp", do_pow + v_pow), ("dKp", do_pow + v_pow)):
+        err = relative_error(b[name].astype(np.float64) * 2.0 ** power, a[name].astype(np.float64))
+        print(f"   {name}: {err:.2e}", flush=True)
+        assert err <= (1e-7 if max(powers) < 100 else 1e-6), (name, err)
+
+
+def test_f32_split_kernels_on_small_weights():
+    """A key with weights of about 2^-124 in every row that keeps it: its dV and dK are sums of such numbers alone and keep float32's relative
+    precision (1e-4: the exponent itself is exact to 2^-17 there, 5e-6 of the weight; eight bits of a weight are 4e-3)."""
+    grid, S, heads, D = (1, 48, 50), 2400, 8, 128
+    Q, K, V, dO = (synth.iid_normal(1060 + i, (1, S, heads, D)) for i in range(4))
+    Q[..., 0], K[..., 0] = 16.0, 0.0
+    K[:, 777] = 0.0
+    K[:, 777, :, 0] = -55.0
+    g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), 300, 1.0, torch.float32)
+    pos, scale = int(g["inv_perm"][777]), 1.0 / math.sqrt(D)
+    for h in (0, heads - 1):
+        q, k, v, d = (x[0, g["perm"], h].astype(np.float64) for x in (Q, K, V, dO))
+        O, LSE = vo.masked_attention_fwd(q, k, v, g["mask"][0, h], g["blk_off"], scale)
+        w = np.exp(scale * q @ k[pos] - LSE)
+        assert 2.0 ** -126 < w.min() and w.max() < 2.0 ** -120
+        dS = w * (d @ v[pos] - (d * O).sum(1))
+        errs = relative_error(g["dVp"][0, h, pos], w @ d), relative_error(g["dKp"][0, h, pos], scale * dS @ q)
+        print("   dV %.2e dK %.2e" % errs, flush=True)
+        assert max(errs) <= 1e-4
