@@ -1016,12 +1016,12 @@ struct BwdWs {
     int* kb_start;     // [BH][nb + 1]
     int* kb_order;     // [BH][nb]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
-    char* QD6;         // float32: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
+    char* QD6;         // split kernels: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
     char* KV6;
     size_t total;
 };
 
-BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {
+BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool split) {
     BwdWs w;
     char* p = (char*)base;
     size_t off = 0;
@@ -1032,16 +1032,17 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
-    w.QD6 = p + off;                 off += es == 4 ? align_up((size_t)BH * S * 12 * D, 256) : 0;
-    w.KV6 = p + off;                 off += es == 4 ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.QD6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
 }
 
 }  // namespace
 
-size_t vmoba_attn_bwd_workspace_bytes(int B, int Hh, int64_t S, int D, int64_t cap, int dtype) {
-    return carve_bwd(nullptr, B * Hh, S, D, cap, dtype == VMOBA_BF16 ? 2 : 4).total;
+size_t vmoba_attn_bwd_workspace_bytes(int B, int Hh, int64_t S, int D, int nb, int64_t cap, int dtype) {
+    const bool bf16 = dtype == VMOBA_BF16;
+    return carve_bwd(nullptr, B * Hh, S, D, cap, bf16 ? 2 : 4, !bf16 && use_split(B * Hh, S, D, nb, cap)).total;
 }
 
 extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t* blk_off,
@@ -1066,11 +1067,12 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         return VMOBA_ERR_UNSUPPORTED;
     const int BH = B * Hh;
     if (nnz_capacity > INT32_MAX) return VMOBA_ERR_UNSUPPORTED;
-    BwdWs ws = carve_bwd(workspace, BH, S, D, nnz_capacity, dt == VMOBA_BF16 ? 2 : 4);
+    const bool bf16 = dt == VMOBA_BF16;
+    const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
+    BwdWs ws = carve_bwd(workspace, BH, S, D, nnz_capacity, bf16 ? 2 : 4, split);
     if (workspace_bytes < ws.total) return VMOBA_ERR_WORKSPACE;
     if (((uintptr_t)workspace) & 255) return VMOBA_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    const bool bf16 = dt == VMOBA_BF16;
     const TensorView Qv = make_view(Qp), Kv = make_view(Kp), Vv = make_view(Vp), Ov = make_view(O);
     const TensorView dQv = make_view(dQ), dKv = make_view(dK), dVv = make_view(dV);
     TensorView dOv = make_view(dO);
@@ -1086,7 +1088,6 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
 
     // ---- delta, tile list, key runs
     const int TM = 128;                     // queries per dQ tile
-    const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
     int* const out_of_range = ws.n_tiles + 1;
     const int KPW = bf16 || split ? 128 : 64;        // keys per dK/dV workgroup
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);

@@ -541,7 +541,7 @@ struct FwdWs {
     float* lse_part;   // [BH * cap]
     int4* tile_desc;   // the flat list of all heads' tiles
     int* n_tiles;      // its length, then the split kernels' flag
-    char* Q3;          // float32: [BH][S][3][D], the terms of Q, and [BH][S][6][D], those of K and V in block order (see attn_split.hip)
+    char* Q3;          // split kernels: [BH][S][3][D], the terms of Q, and [BH][S][6][D], those of K and V in block order (see attn_split.hip)
     char* KV6;
     size_t total;
 };
@@ -551,7 +551,7 @@ struct FwdWs {
 int64_t vmoba_max_tiles(int64_t cap, int TM) { return (cap / TM + VMOBA_MAX_BLOCKS + 7) / 8 * 8; }
 namespace {
 
-FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {       // es: bytes per element of the partial rows
+FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool split) {       // es: bytes per element of the partial rows
     FwdWs w;
     char* p = (char*)base;
     size_t off = 0;
@@ -559,16 +559,17 @@ FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es) {    
     w.lse_part = (float*)(p + off);  off += align_up((size_t)BH * cap * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
-    w.Q3 = p + off;                  off += es == 4 ? align_up((size_t)BH * S * 6 * D, 256) : 0;
-    w.KV6 = p + off;                 off += es == 4 ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.Q3 = p + off;                  off += split ? align_up((size_t)BH * S * 6 * D, 256) : 0;
+    w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
 }
 
 }  // namespace
 
-size_t vmoba_attn_fwd_workspace_bytes(int B, int Hh, int64_t S, int D, int64_t cap, int dtype) {
-    return carve_fwd(nullptr, B * Hh, S, D, cap, dtype == VMOBA_BF16 ? 2 : 4).total;
+size_t vmoba_attn_fwd_workspace_bytes(int B, int Hh, int64_t S, int D, int nb, int64_t cap, int dtype) {
+    const bool bf16 = dtype == VMOBA_BF16;
+    return carve_fwd(nullptr, B * Hh, S, D, cap, bf16 ? 2 : 4, !bf16 && use_split(B * Hh, S, D, nb, cap)).total;
 }
 
 // Compute units of the current device (queried once).
@@ -601,11 +602,12 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     if (Kp->dtype != dt || Vp->dtype != dt || O->dtype != dt) return VMOBA_ERR_UNSUPPORTED;
     const int BH = B * Hh;
     if (nnz_capacity > INT32_MAX || (int64_t)BH * nnz_capacity * D > ((int64_t)1 << 40)) return VMOBA_ERR_UNSUPPORTED;
-    FwdWs ws = carve_fwd(workspace, BH, S, D, nnz_capacity, dt == VMOBA_BF16 ? 2 : 4);
+    const bool bf16 = dt == VMOBA_BF16;
+    const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
+    FwdWs ws = carve_fwd(workspace, BH, S, D, nnz_capacity, bf16 ? 2 : 4, split);
     if (workspace_bytes < ws.total) return VMOBA_ERR_WORKSPACE;
     if (((uintptr_t)workspace) & 255) return VMOBA_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
-    const bool bf16 = dt == VMOBA_BF16;
     const TensorView Qv = make_view(Qp), Kv = make_view(Kp), Vv = make_view(Vp), Ov = make_view(O);
     const float scale_log2 = softmax_scale * LOG2E;
     // the bfloat16 kernel addresses the rows of one (batch, head) slice of K and V with 32-bit byte offsets
@@ -620,7 +622,6 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     // rows are fetched once per 256 queries); D = 64: 128-query tiles, two workgroups of 4 wavefronts per compute unit;
     // float32: one workgroup per tile of 128 queries
     const bool wide = bf16 && D == 128;
-    const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
     const int TM = wide ? 256 : 128;
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
     tile_list_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(

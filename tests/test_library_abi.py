@@ -94,3 +94,16 @@ def test_workspace_sizes_grow_with_capacity(L):
     assert vb.vmoba_workspace_bytes(99, 1, 2, 512, 64, 16, 1000, vb.VMOBA_F32) == 0
     assert 2048 < vb.nnz_capacity_for(512, 16, 0.25) <= 2048 + 32
     assert vb.nnz_capacity_for(512, 16, 1.0) == 512 * 16
+
+
+@pytest.mark.parametrize("op,rows,planes", [(vb.OP_ATTN_FWD, 0, 18), (vb.OP_ATTN_BWD, 2, 24)])
+def test_float32_workspace_holds_split_planes_only_where_they_are_used(op, rows, planes):
+    """Beyond a bfloat16 call's workspace: two bytes per value of the partial rows (and of dO's copy); planes of split operands
+    for calls that multiply those, and none for small ones or those whose split rows 32-bit offsets would not reach."""
+    def extra(heads, S, D, nb, cap):
+        f32, bf16 = (vb.vmoba_workspace_bytes(op, 1, heads, S, D, nb, cap, t) for t in (vb.VMOBA_F32, vb.VMOBA_BF16))
+        return f32 - bf16 - 2 * D * heads * (cap + (rows // 2) * S)
+    small, large, huge = (2, 512, 64, 16, 2048), (12, 14080, 128, 36, 126720), (1, 3 << 20, 128, 36, 1 << 24)
+    assert 0 <= extra(*small) < 1024
+    assert 0 <= extra(*large) - planes * 128 * 12 * 14080 < 1024
+    assert 0 <= extra(*huge) < 1024
