@@ -109,14 +109,15 @@ def unpack_mask(words: np.ndarray, nb: int) -> np.ndarray:
 
 
 def run_gpu(Q, K, V, dO, grid, block=(0, 0, 0), chunk=0, tau=0.25, dtype=torch.float32,
-            score_scale=None, softmax_scale=None, mode=0, topk=0, fused_io=False, q_in_place=False, kv_in_place=False):
+            score_scale=None, softmax_scale=None, mode=0, topk=0, fused_io=False, q_in_place=False, kv_in_place=False, packed=False):
     """Whole layer on the GPU.  Q, K, V, dO: numpy [B, S, Hh, D] float32 (dO may be None).
     With fused_io the attention calls write O and the gradients in the caller's token order
     themselves; their block-order views (Op, dQp, ...) are then gathered here on the host.
     With q_in_place the library never moves Q and numbers the queries by token: P, mask, LSE are
     brought to block order here (row p = token perm[p]) so that they compare with the oracle's;
     the lists stay as written (query ids = token ids) next to `mask_q`, the mask in that order.
-    With kv_in_place (implies q_in_place) the library moves nothing at all."""
+    With kv_in_place (implies q_in_place) the library moves nothing at all.
+    packed: Q, K and V are views of one [B, S, 3, Hh, D] tensor."""
     B, S, Hh, D = Q.shape
     plan = vb.LayerPlan(B, Hh, D, grid, block, chunk, tau, dtype, score_scale=score_scale,
                         softmax_scale=softmax_scale, need_bwd=dO is not None, mode=mode, topk=topk, fused_io=fused_io,
@@ -125,6 +126,8 @@ def run_gpu(Q, K, V, dO, grid, block=(0, 0, 0), chunk=0, tau=0.25, dtype=torch.f
     assert plan.S == S
     fused_io = plan.fused_io
     q, k, v = (to_dev(x, dtype) for x in (Q, K, V))
+    if packed:
+        q, k, v = torch.stack([q, k, v], dim=2).unbind(2)
     plan.forward(q, k, v)
     out = {}
     if dO is not None:
@@ -163,6 +166,16 @@ def run_gpu(Q, K, V, dO, grid, block=(0, 0, 0), chunk=0, tau=0.25, dtype=torch.f
         for n in ("dQ", "dK", "dV"):
             out[n + "p"] = block_order(out[n]) if fused_io else np32(getattr(plan, n + "p").permute(0, 2, 1, 3))
     return out
+
+
+def multiplies_split_operands(plan) -> bool:
+    """Whether a float32 plan's attention calls take the kernels on split operands, as the library's own rule says: only then does
+    a call's workspace hold their planes (18 bytes per channel of a row and head), beyond the partial rows and small tables."""
+    f32, bf16 = (vb.vmoba_workspace_bytes(vb.OP_ATTN_FWD, plan.B, plan.Hh, plan.S, plan.D, plan.nb, plan.cap, t)
+                 for t in (vb.VMOBA_F32, vb.VMOBA_BF16))
+    planes = f32 - bf16 - 2 * plan.D * plan.B * plan.Hh * plan.cap
+    assert planes < 1024 or planes >= 18 * plan.D * plan.B * plan.Hh * plan.S
+    return planes >= 1024
 
 
 def check_lists(g, b, h):

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from oracle import vmoba_oracle as vo
-from paper_2506_23858_amd import synth
+from paper_2506_23858_amd import binding as vb, synth
 from tests import gpu_util as gu
 from tests.test_gpu_parity import compare_layer
 
@@ -59,19 +59,19 @@ def test_pair_lists_longer_than_a_window(blocks):
         compare_layer(Q, K, V, None, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"lists-{blocks}", mode=mode, topk=topk)
 
 
-def check_heads(case, g, Q, K, V, dO, heads, scale=None, dtype=torch.float32):
-    """Attention outputs of some heads against the oracle under the GPU's own mask."""
+def check_heads(case, g, Q, K, V, dO, heads, scale=None, dtype=torch.float32, b=0):
+    """Attention outputs of some heads of a batch element against the oracle under the GPU's own mask."""
     perm = g["perm"]
     scale = 1.0 / math.sqrt(Q.shape[3]) if scale is None else scale
     for h in heads:
-        q, k, v, d = (x[0, perm, h].astype(np.float64) for x in (Q, K, V, dO))
-        m = g["mask"][0, h]
+        q, k, v, d = (x[b, perm, h].astype(np.float64) for x in (Q, K, V, dO))
+        m = g["mask"][b, h]
         O, LSE = vo.masked_attention_fwd(q, k, v, m, g["blk_off"], scale)
         dQ, dK, dV = vo.masked_attention_bwd(q, k, v, m, g["blk_off"], scale, d)
         live = np.isfinite(LSE)
-        gu.check_output(case, "LSE", g["LSE"][0, h][live], LSE[live], dtype)
+        gu.check_output(case, "LSE", g["LSE"][b, h][live], LSE[live], dtype)
         for name, ref in (("Op", O), ("dQp", dQ), ("dKp", dK), ("dVp", dV)):
-            gu.check_output(case, name.rstrip("p"), g[name][0, h], ref, dtype)
+            gu.check_output(case, name.rstrip("p"), g[name][b, h], ref, dtype)
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -82,6 +82,7 @@ def test_f32_split_kernels_at_tile_edges(chunk, D):
     grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
     Q, K, V, dO = (synth.iid_normal(1000 + i, (1, S, heads, D)) for i in range(4))
     g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, 0.95 if chunk < 200 else 0.4, torch.float32, kv_in_place=chunk == 97)
+    assert gu.multiplies_split_operands(g["plan"])
     check_heads(f"f32-split-{chunk}-{D}", g, Q, K, V, dO, (0, heads - 1))
 
 
@@ -93,6 +94,7 @@ def test_f32_split_kernels_take_a_scale_of_any_sign(scale, D):
     Q, K, V, dO = (synth.iid_normal(1030 + i, (1, S, heads, D)) for i in range(4))
     for chunk, tau in ((97, 0.95), (300, 0.4)):
         g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, softmax_scale=scale)
+        assert gu.multiplies_split_operands(g["plan"])
         check_heads(f"f32-split-scale-{scale}-{chunk}-{D}", g, Q, K, V, dO, (0, heads - 1), scale)
 
 
@@ -113,6 +115,7 @@ def test_f32_split_kernels_hand_infinities_to_the_float32_ones():
     grid, S, heads, D = (1, 48, 50), 2400, 8, 128
     Q, K, V, dO = (synth.iid_normal(1010 + i, (1, S, heads, D)) for i in range(4))
     ref = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), 300, 0.4, torch.float32)
+    assert gu.multiplies_split_operands(ref["plan"])
     V[0, 777, 3, 5] = np.inf
     g = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), 300, 0.4, torch.float32)
     keeps = g["mask"][0, 3][:, 777 // 300]
@@ -136,6 +139,7 @@ def test_f32_split_kernels_on_small_magnitudes(powers):
     do_pow, v_pow = powers
     a, b = (gu.run_gpu(Q, K, v, d, grid, (0, 0, 0), 300, 0.4, torch.float32)
             for v, d in ((V, dO), (V * np.float32(2.0 ** -v_pow), dO * np.float32(2.0 ** -do_pow))))
+    assert gu.multiplies_split_operands(a["plan"])
     for name, power in (("Op", v_pow), ("dVp", do_pow), ("dQp", do_pow + v_pow), ("dKp", do_pow + v_pow)):
         err = relative_error(b[name].astype(np.float64) * 2.0 ** power, a[name].astype(np.float64))
         print(f"   {name}: {err:.2e}", flush=True)
@@ -151,6 +155,7 @@ def test_f32_split_kernels_on_small_weights():
     K[:, 777] = 0.0
     K[:, 777, :, 0] = -55.0
     g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), 300, 1.0, torch.float32)
+    assert gu.multiplies_split_operands(g["plan"])
     pos, scale = int(g["inv_perm"][777]), 1.0 / math.sqrt(D)
     for h in (0, heads - 1):
         q, k, v, d = (x[0, g["perm"], h].astype(np.float64) for x in (Q, K, V, dO))
@@ -161,3 +166,99 @@ def test_f32_split_kernels_on_small_weights():
         errs = relative_error(g["dVp"][0, h, pos], w @ d), relative_error(g["dKp"][0, h, pos], scale * dS @ q)
         print("   dV %.2e dK %.2e" % errs, flush=True)
         assert max(errs) <= 1e-4
+
+
+@pytest.mark.parametrize("layout", [{}, {"fused_io": True}, {"q_in_place": True}, {"kv_in_place": True}])
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_kernels_in_every_layout(D, layout):
+    """Two videos, Q, K and V views of one packed projection: operands split from block order and from the caller's rows, dO with and
+    without its block-order copy, dK and dV written through a row map."""
+    grid, block, heads = (4, 15, 20), (2, 7, 9), 12 if D == 64 else 6
+    S = grid[0] * grid[1] * grid[2]
+    Q, K, V, dO = (synth.blurred_noise(1070 + i, (2 * grid[0],) + grid[1:], heads, D, 1.0).reshape(2, S, heads, D) for i in range(4))
+    g = gu.run_gpu(Q, K, V, dO, grid, block, 0, 0.9, torch.float32, packed=True, **layout)
+    assert gu.multiplies_split_operands(g["plan"])
+    for b, h in ((0, 0), (1, heads - 1)):
+        check_heads(f"f32-split-layout-{'-'.join(layout)}-{D}", g, Q, K, V, dO, (h,), b=b)
+
+
+@pytest.mark.parametrize("chunk,layout", [(97, {}), (129, {"kv_in_place": True}), (300, {"fused_io": True})])
+def test_f32_calls_of_values_that_do_not_split_and_the_next_one(chunk, layout):
+    """One infinite value of dO in one head, one NaN of V in another: the whole call is handed to the float32 kernels, backward included, which
+    then walk a run table of 128 keys in halves of 64.  What the two values do not enter matches the oracle;
+    the call after it, of finite values in the same buffers, has the bits of the call before."""
+    grid, S, heads, D = (1, 48, 50), 2400, 8, 128
+    Q, K, V, dO = (synth.iid_normal(1080 + i, (1, S, heads, D)) for i in range(4))
+    plan = vb.LayerPlan(1, heads, D, grid, (0, 0, 0), chunk, 0.95 if chunk < 200 else 0.4, torch.float32, **layout)
+    assert gu.multiplies_split_operands(plan)
+
+    def run(V, dO):
+        plan.forward(*(gu.to_dev(x, torch.float32) for x in (Q, K, V)))
+        plan.backward(gu.to_dev(dO, torch.float32))
+        torch.cuda.synchronize()
+        assert int(plan.dev_status.item()) == 0
+        return {n: gu.np32(getattr(plan, n))[0] for n in ("O", "dQ", "dK", "dV")}
+
+    before = run(V, dO)
+    assert all(np.isfinite(x).all() for x in before.values())
+    q_bad, k_bad, dO_bad, V_bad = 1234, 777, dO.copy(), V.copy()
+    dO_bad[0, q_bad, 2, 9] = np.inf
+    V_bad[0, k_bad, 5, 7] = np.nan
+    got = run(V_bad, dO_bad)
+    mask = gu.unpack_mask(plan.mask.cpu().numpy(), plan.nb)[0]             # perm is the identity here: query and key ids are tokens
+    touched = {n: np.zeros((S, heads, D), bool) for n in before}
+    block = np.arange(S) // chunk
+    keys = mask[2, q_bad][block]                                           # keys that the query of the infinite dO meets
+    queries = mask[5][:, k_bad // chunk]                                   # queries that meet the key of the NaN
+    touched["dQ"][q_bad, 2] = touched["dK"][keys, 2] = True
+    touched["dV"][keys, 2, 9] = True
+    touched["O"][queries, 5, 7] = touched["dQ"][queries, 5] = True
+    touched["dK"][mask[5][queries].any(0)[block], 5] = True
+    for n, x in before.items():
+        t = touched[n]
+        if n in ("dQ", "dK"):                                              # (a zero weight may spare single channels of O and dV)
+            assert t.any() and not np.isfinite(got[n][t]).any(), n
+        gu.check_output(f"f32-split-not-finite-{chunk}", n, got[n][~t], x[~t], torch.float32)
+    after = run(V, dO)
+    for n in before:
+        assert np.array_equal(before[n], after[n]), n
+
+
+@pytest.mark.parametrize("S,chunk,mode,topk", [
+    (256, 2, 0, 0), (256, 2, 0x103, 9), (257, 2, 0, 0),       # 128 blocks: the most the one-launch cut takes, and one more
+    (4096, 512, 0, 0), (4096, 512, 4, 0), (4097, 512, 0, 0),  # 4096 rows of 8 values, and one row more
+    (331, 5, 0x100, 0), (331, 5, 3, 20), (331, 5, 4, 0),      # pools of 331 x 67 values: only the first head's is 16-byte aligned
+    (3, 3, 0, 0), (67, 1, 3, 3),                              # one block; as many blocks as queries
+])
+def test_cut_among_equal_values(S, chunk, mode, topk):
+    """Query rows and key blocks that repeat, so that runs of equal values cross the cut: it keeps the k best of the GPU's own P, equal ones by
+    query, then block, and k is the shortest prefix that reaches tau of the mass (or topk * S)."""
+    heads, D, tau = 3, 64, 0.37
+    nb = -(-S // chunk)
+    Q, K, V = (synth.iid_normal(1090 + i, (1, S, heads, D)) for i in range(3))
+    Q = np.ascontiguousarray(Q[:, np.arange(S) // 7 * 7 % S])
+    K = np.ascontiguousarray(K[:, np.arange(S) % (max(1, nb // 3) * chunk)])
+    g = gu.run_gpu(Q, K, V, None, (1, 1, S), (0, 0, 0), chunk, tau, torch.float32, mode=mode, topk=topk)
+    total = 1.0 if mode == 4 else float(S)
+    cut_ties = 0
+    for h in range(heads):
+        p = g["P"][0, h].reshape(-1)
+        order = np.lexsort((np.arange(p.size), -p))
+        mass = np.cumsum(p[order], dtype=np.float64)
+        if mode & 0xff == 3:
+            k = topk * S
+        else:
+            k = int(np.searchsorted(mass, np.float32(tau) * total)) + 1
+            # (both sides' sums are exact to far less than 1e-6: no prefix may end that close)
+            assert np.abs(mass[max(0, k - 2):k] - np.float32(tau) * total).min() > 1e-6 * total
+        keep = np.zeros(p.size, bool)
+        keep[order[:k]] = True
+        cut_ties += bool(k < p.size and p[order[k]] == p[order[k - 1]])
+        keep = keep.reshape(S, nb)
+        if mode & 0x100:
+            keep[np.arange(S), np.arange(S) // chunk] = True
+        else:
+            assert int(g["k"][0, h]) == k
+        assert np.array_equal(g["mask"][0, h], keep), (h, k, int((g["mask"][0, h] != keep).sum()))
+        gu.check_lists(g, 0, h)
+    assert cut_ties or nb == 1 or S <= 67

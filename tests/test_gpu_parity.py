@@ -247,8 +247,8 @@ def test_keys_in_place(dtype, D):
 
 
 def test_keys_in_place_block_longer_than_the_row_table():
-    """A key block of 4000 keys: more than the forward tile kernel's in-LDS table of row numbers holds, so its rows are
-    looked up in global memory; next to it a block of 608 keys that uses the table."""
+    """A key block of 4000 keys, 125 groups whose row numbers go round the forward tile kernel's LDS ring of 16 groups many times, next to
+    one of 608 keys."""
     grid = (2, 48, 48)
     S = grid[0] * grid[1] * grid[2]
     Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(190 + i, (1, S, 1, 128))) for i in range(4))
