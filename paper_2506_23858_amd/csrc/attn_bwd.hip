@@ -97,13 +97,13 @@ __device__ __forceinline__ void write_key_runs(KeyRunLds& lds, const int* __rest
 template <bool BF16, int D>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorView dO, const float* __restrict__ LSE, float* __restrict__ delta, const int* __restrict__ rows,
                                                           char* __restrict__ dO_copy, const int* __restrict__ blk_ptr,
-                                                          const int* __restrict__ blk_off, int4* __restrict__ flat_desc, int* __restrict__ n_tiles,
+                                                          const int* __restrict__ blk_off, const int* __restrict__ head_tiles, int4* __restrict__ flat_desc, int* __restrict__ n_tiles,
                                                           int* __restrict__ clear, int* __restrict__ kb_start, int* __restrict__ kb_order, int BH, int Hh, int S, int nb,
                                                           int TM, int KPW, int tail_max, int n_delta) {
     __shared__ union { TileListLds tiles; KeyRunLds runs; } lds;
     const int bh = blockIdx.y, x = blockIdx.x;
     if (x < n_delta) delta_rows<BF16, D>(O, dO, LSE, delta, rows, dO_copy, bh, Hh, S, x);
-    else if (x + 1 < (int)gridDim.x) write_tile_list(lds.tiles, blk_ptr, blk_off, flat_desc, n_tiles, bh, BH, nb, TM, (x - n_delta) * 256);
+    else if (x + 1 < (int)gridDim.x) write_tile_list(lds.tiles, blk_ptr, blk_off, head_tiles, flat_desc, n_tiles, bh, BH, nb, TM, (x - n_delta) * 256);
     else {
         if (threadIdx.x < 2)
             delta[((long long)bh * 2 + threadIdx.x) * lse_delta_pitch(S) + S] = threadIdx.x == 0 ? INFINITY : 0.f;
@@ -1013,6 +1013,7 @@ struct BwdWs {
     float* delta;      // LSE * log2(e) and -delta, [BH][2][lse_delta_pitch(S)]
     int4* tile_desc;   // the flat list of all heads' tiles
     int* n_tiles;      // its length, then the split kernels' flag
+    int* head_tiles;   // [BH]
     int* kb_start;     // [BH][nb + 1]
     int* kb_order;     // [BH][nb]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
@@ -1029,6 +1030,7 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool 
     w.delta = (float*)(p + off);     off += align_up((size_t)BH * 2 * (size_t)lse_delta_pitch((int)S) * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
+    w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
@@ -1092,11 +1094,13 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     const int KPW = bf16 || split ? 128 : 64;        // keys per dK/dV workgroup
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
     {
+        const int* head_tiles = heads_counted_first(BH, n_blocks) ? ws.head_tiles : nullptr;
+        if (head_tiles) launch_head_tiles(st, blk_ptr, ws.head_tiles, BH, n_blocks, TM);
         const int n_delta = (int)ceil_div64(S, 256 / (D / (bf16 ? 8 : 4)));
         const dim3 grid((unsigned)(n_delta + ceil_div64(max_tiles, 256) + 1), (unsigned)BH);
         auto kfn = bf16 ? (D == 128 ? bwd_prepare_kernel<true, 128> : bwd_prepare_kernel<true, 64>)
                         : (D == 128 ? bwd_prepare_kernel<false, 128> : bwd_prepare_kernel<false, 64>);
-        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, out_of_range, ws.kb_start, ws.kb_order,
+        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, head_tiles, ws.tile_desc, ws.n_tiles, out_of_range, ws.kb_start, ws.kb_order,
                                         BH, Hh, (int)S, n_blocks, TM, KPW, bf16 ? 32 : 0, n_delta);
         VMOBA_CHECK_LAUNCH();
     }

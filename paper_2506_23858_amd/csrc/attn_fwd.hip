@@ -21,10 +21,23 @@ constexpr float LN2 = 0.6931471805599453f;
 
 // The flat tile list of a forward call (see write_tile_list); grid: 256 tile ids x head.
 __global__ __launch_bounds__(256) void tile_list_kernel(const int* __restrict__ blk_ptr, const int* __restrict__ blk_off,
-                                                        int4* __restrict__ flat_desc, int* __restrict__ n_tiles, int* __restrict__ clear, int BH, int nb, int TM) {
+                                                        const int* __restrict__ head_tiles, int4* __restrict__ flat_desc, int* __restrict__ n_tiles, int* __restrict__ clear,
+                                                        int BH, int nb, int TM) {
     __shared__ TileListLds lds;
     if (clear && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *clear = 0;
-    write_tile_list(lds, blk_ptr, blk_off, flat_desc, n_tiles, blockIdx.y, BH, nb, TM, blockIdx.x * 256);
+    write_tile_list(lds, blk_ptr, blk_off, head_tiles, flat_desc, n_tiles, blockIdx.y, BH, nb, TM, blockIdx.x * 256);
+}
+
+// head_tiles[h] = number of tiles of head h; one wavefront per head.
+__global__ __launch_bounds__(256) void head_tiles_kernel(const int* __restrict__ blk_ptr, int* __restrict__ head_tiles, int BH, int nb, int TM) {
+    const int h = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (h >= BH) return;
+    const int* bp = blk_ptr + (long long)h * (nb + 1);
+    int n = 0;
+    for (int j = lane; j < nb; j += 64) n += (bp[j + 1] - bp[j] + TM - 1) / TM;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off, 64);
+    if (lane == 0) head_tiles[h] = n;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -541,12 +554,17 @@ struct FwdWs {
     float* lse_part;   // [BH * cap]
     int4* tile_desc;   // the flat list of all heads' tiles
     int* n_tiles;      // its length, then the split kernels' flag
+    int* head_tiles;   // [BH]
     char* Q3;          // split kernels: [BH][S][3][D], the terms of Q, and [BH][S][6][D], those of K and V in block order (see attn_split.hip)
     char* KV6;
     size_t total;
 };
 
 }  // namespace
+
+void launch_head_tiles(hipStream_t st, const int* blk_ptr, int* head_tiles, int BH, int nb, int TM) {
+    head_tiles_kernel<<<dim3((unsigned)ceil_div64(BH, 4)), dim3(256), 0, st>>>(blk_ptr, head_tiles, BH, nb, TM);
+}
 // Grid width (tiles per head) for tiles of TM list entries: a host-side bound on sum_j ceil(cnt_j / TM).
 int64_t vmoba_max_tiles(int64_t cap, int TM) { return (cap / TM + VMOBA_MAX_BLOCKS + 7) / 8 * 8; }
 namespace {
@@ -559,6 +577,7 @@ FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool 
     w.lse_part = (float*)(p + off);  off += align_up((size_t)BH * cap * 4, 256);
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
+    w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
     w.Q3 = p + off;                  off += split ? align_up((size_t)BH * S * 6 * D, 256) : 0;
     w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
@@ -624,8 +643,10 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     const bool wide = bf16 && D == 128;
     const int TM = wide ? 256 : 128;
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
+    const int* head_tiles = heads_counted_first(BH, n_blocks) ? ws.head_tiles : nullptr;
+    if (head_tiles) launch_head_tiles(st, blk_ptr, ws.head_tiles, BH, n_blocks, TM);
     tile_list_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
-        blk_ptr, blk_off, ws.tile_desc, ws.n_tiles, split ? ws.n_tiles + 1 : nullptr, BH, n_blocks, TM);
+        blk_ptr, blk_off, head_tiles, ws.tile_desc, ws.n_tiles, split ? ws.n_tiles + 1 : nullptr, BH, n_blocks, TM);
     VMOBA_CHECK_LAUNCH();
     if (split) {
         launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.Q3, 3, 0, ws.n_tiles + 1);

@@ -262,3 +262,13 @@ def test_cut_among_equal_values(S, chunk, mode, topk):
         assert np.array_equal(g["mask"][0, h], keep), (h, k, int((g["mask"][0, h] != keep).sum()))
         gu.check_lists(g, 0, h)
     assert cut_ties or nb == 1 or S <= 67
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tile_list_of_many_heads(dtype):
+    """600 heads x 16 blocks, past the number from which on the heads' tiles are counted in a launch of their own: the first, a middle and the
+    last head."""
+    S, heads, D = 64, 600, 64
+    Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(1100 + i, (1, S, heads, D))) for i in range(4))
+    g = gu.run_gpu(Q, K, V, dO, (1, 1, S), (0, 0, 0), 4, 0.5, dtype)
+    check_heads(f"many-heads-{gu.dtype_name(dtype)}", g, Q, K, V, dO, (0, 299, heads - 1), dtype=dtype)
