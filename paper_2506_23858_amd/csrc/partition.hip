@@ -1,5 +1,5 @@
 // vmoba_partition: token -> key-block rearrangement of Sec. 3.2, Eq. 1 (and its inverse).
-// One kernel: a workgroup takes a run of block-order positions, finds their tokens -- from the grid
+// One kernel: a workgroup takes a run of 16-byte pieces of the (token, head) rows in block order, finds the tokens of its positions -- from the grid
 // description in closed form (and then also writes its part of perm / inv_perm / blk_off), or from
 // perm -- and moves 16-byte pieces of the (token, head) rows between the caller's order and block
 // order.  (With the index arrays in a launch of their own a small call spent a third of its time there.)
@@ -46,23 +46,38 @@ struct CopyDesc {
     int n_tensors;
 };
 
-// Work items of a workgroup's positions are ordered (position, head, piece) with the 16-byte piece of the INPUT row
-// fastest, so a wavefront reads whole rows and, in the caller's layout, the heads of one token that lie next to each other.
-// BUILD: perm, inv_perm and blk_off are written (by the workgroups of the first batch element and tensor) instead of perm
-// being read.
-constexpr int MAX_POS = 256;       // positions per workgroup
+// The 16-byte pieces of one batch element's INPUT rows are numbered (position, head, piece), the piece fastest, so a wavefront reads
+// whole rows and, in the caller's layout, the heads of one token that lie next to each other; a workgroup moves
+// CHUNK consecutive ones.
+// BUILD: perm, inv_perm and blk_off are written (by the workgroups of the first batch element and tensor, every position by the one that
+// holds its first piece) instead of perm being read.
+// Bound by HBM (5.2 to 6.7 TB/s).  What matters is how much a workgroup moves: with gathered reads 256 pieces, one per thread, with scattered
+// writes 512.  Q, K, V of 40 heads x 32 760 tokens with 2048 / 1024 / 512 / 256 pieces: 391 / 377 / 374 / 336 us, K and V of 12 heads
+// x 112 320 tokens 261 / 253 / 260 / 235; the inverse of one tensor, 40 heads, 131 / 123 / 123 / 133.
+constexpr int chunk_pieces(bool inverse) { return inverse ? 512 : 256; }
+constexpr int INDEX_CHUNK = 256;                       // positions per workgroup when only the index arrays are wanted
 template <bool INVERSE, bool BUILD>
 __global__ __launch_bounds__(256) void permute_rows_kernel(GridDesc g, CopyDesc d, int* __restrict__ perm, int* __restrict__ inv_perm,
-                                                           int* __restrict__ blk_off, int n_pos, int Hh, int D) {
-    __shared__ int sTok[MAX_POS];
+                                                           int* __restrict__ blk_off, int Hh, int D, unsigned chunk0) {
+    constexpr int CHUNK = chunk_pieces(INVERSE), U = CHUNK / 256;
+    __shared__ int sTok[INDEX_CHUNK];
+    static_assert(CHUNK / 8 + 1 <= INDEX_CHUNK && INDEX_CHUNK <= 256, "a thread per position of the workgroup");
     const int t = blockIdx.z, b = blockIdx.y, tid = threadIdx.x;
-    const int p0 = blockIdx.x * n_pos, np = min(n_pos, g.S - p0);
+    const bool copy = t < d.n_tensors;
+    const int in_es = d.in_bf16[t] ? 2 : 4;
+    const int sh = __builtin_ctz(D * in_es / 16);      // 8, 16 or 32 pieces per input row
+    const unsigned per_pos = copy ? (unsigned)Hh << sh : 1u, chunk = copy ? CHUNK : INDEX_CHUNK;
+    const unsigned long long total = (unsigned long long)g.S * per_pos, first = ((unsigned long long)chunk0 + blockIdx.x) * chunk;
+    if (first >= total) return;
+    const int p0 = (int)(total >> 32 ? first / per_pos : (unsigned)first / per_pos);
+    const int skip = (int)(first - (unsigned long long)p0 * per_pos);       // pieces of position p0 that belong to the workgroup before
+    const int np = min((int)((skip + chunk - 1) / per_pos) + 1, g.S - p0);
     if (tid < np) {
         const int p = p0 + tid;
         if constexpr (BUILD) {
             const Place pl = place_of(g, p);
             sTok[tid] = pl.token;
-            if (b == 0 && t == 0) {
+            if (b == 0 && t == 0 && (tid > 0 || skip == 0)) {
                 perm[p] = pl.token;
                 inv_perm[pl.token] = p;
                 if (pl.rank == 0) blk_off[pl.block] = p;
@@ -72,44 +87,38 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(GridDesc g, CopyDesc 
             sTok[tid] = perm[p];
         }
     }
-    if (t >= d.n_tensors) return;                      // only the index arrays are wanted
+    if (!copy) return;                                 // only the index arrays are wanted
     __syncthreads();
-    const int in_es = d.in_bf16[t] ? 2 : 4;
-    const int pieces = D * in_es / 16;                 // 16-byte pieces per input row: 8, 16 or 32
-    const int sh = __builtin_ctz(pieces);
-    const int n_items = np * Hh << sh;
     const TensorView in = d.in[t], out = d.out[t];
     const bool cvt = (!d.in_bf16[t]) && d.out_bf16[t];
     const char* in_b = in.ptr + (long long)b * in.stride_b * in_es;
     char* out_b = out.ptr + (long long)b * out.stride_b * (cvt ? 2 : in_es);
     const float inv_hh = 1.f / (float)Hh;
-    constexpr int U = 4;                               // loads in flight per thread
-    for (int i0 = tid; i0 < n_items; i0 += 256 * U) {
-        u32x4_t v[U];
-        char* dst[U];
+    const int n_items = (int)min((unsigned long long)CHUNK, total - first);
+    u32x4_t v[U];
+    char* dst[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = min(i0 + 256 * u, n_items - 1);
-            const int piece = i & (pieces - 1), r = i >> sh;
-            int pl = (int)((float)r * inv_hh);         // r / Hh (at most 255), one off at most
-            if (pl * Hh > r) --pl;
-            if ((pl + 1) * Hh <= r) ++pl;
-            const int h = r - pl * Hh;
-            const int tok = sTok[pl], s_in = INVERSE ? p0 + pl : tok, s_out = INVERSE ? tok : p0 + pl;
-            v[u] = *reinterpret_cast<const u32x4_t*>(in_b + ((long long)s_in * in.stride_s + (long long)h * in.stride_h) * in_es + piece * 16);
-            dst[u] = out_b + ((long long)s_out * out.stride_s + (long long)h * out.stride_h) * (cvt ? 2 : in_es) + piece * (cvt ? 8 : 16);
-        }
+    for (int u = 0; u < U; ++u) {
+        const int i = skip + min(tid + 256 * u, n_items - 1);
+        const int piece = i & ((1 << sh) - 1), r = i >> sh;
+        int pl = (int)((float)r * inv_hh);             // r / Hh, one off at most
+        if (pl * Hh > r) --pl;
+        if ((pl + 1) * Hh <= r) ++pl;
+        const int h = r - pl * Hh;
+        const int tok = sTok[pl], s_in = INVERSE ? p0 + pl : tok, s_out = INVERSE ? tok : p0 + pl;
+        v[u] = *reinterpret_cast<const u32x4_t*>(in_b + ((long long)s_in * in.stride_s + (long long)h * in.stride_h) * in_es + piece * 16);
+        dst[u] = out_b + ((long long)s_out * out.stride_s + (long long)h * out.stride_h) * (cvt ? 2 : in_es) + piece * (cvt ? 8 : 16);
+    }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i0 + 256 * u >= n_items) break;
-            if (!cvt) {
-                *reinterpret_cast<u32x4_t*>(dst[u]) = v[u];
-            } else {
-                u32x2_t w;
-                w.x = pack_bf16x2(__uint_as_float(v[u].x), __uint_as_float(v[u].y));
-                w.y = pack_bf16x2(__uint_as_float(v[u].z), __uint_as_float(v[u].w));
-                *reinterpret_cast<u32x2_t*>(dst[u]) = w;
-            }
+    for (int u = 0; u < U; ++u) {
+        if (tid + 256 * u >= n_items) break;
+        if (!cvt) {
+            *reinterpret_cast<u32x4_t*>(dst[u]) = v[u];
+        } else {
+            u32x2_t w;
+            w.x = pack_bf16x2(__uint_as_float(v[u].x), __uint_as_float(v[u].y));
+            w.y = pack_bf16x2(__uint_as_float(v[u].z), __uint_as_float(v[u].w));
+            *reinterpret_cast<u32x2_t*>(dst[u]) = w;
         }
     }
 }
@@ -155,7 +164,7 @@ extern "C" int vmoba_partition(const vmoba_grid* g, int inverse, int B, int Hh, 
     const bool build_index = !inverse && (inv_perm || blk_off);   // both null: perm is reused as given
     if (build_index && (!inv_perm || !blk_off)) return VMOBA_ERR_INVALID_ARG;
     if (n_tensors > 0 && (!in || !out)) return VMOBA_ERR_INVALID_ARG;
-    CopyDesc cd;
+    CopyDesc cd = {};
     cd.n_tensors = n_tensors;
     for (int i = 0; i < n_tensors; ++i) {
         if (!tensor_ok(&in[i]) || !tensor_ok(&out[i])) return VMOBA_ERR_INVALID_ARG;
@@ -183,15 +192,15 @@ extern "C" int vmoba_partition(const vmoba_grid* g, int inverse, int B, int Hh, 
     }
     gd.S = (int)S;
     gd.n_blocks = nb;
-    // 512 to 2048 16-byte pieces of 16 bit numbers per workgroup: few enough to spread a small call over the chip (1024
-    // workgroups), enough to pay for finding the tokens; the index arrays alone: 256 positions
-    const int64_t per_pos = (int64_t)Hh * (D / 8);
-    const int64_t spread = std::max<int64_t>(S * B * n_tensors / 1024, ceil_div64(512, per_pos));
-    const int n_pos = n_tensors == 0 ? MAX_POS : (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)MAX_POS, 2048 / per_pos, spread}));
-    const dim3 grid((unsigned)ceil_div64(S, n_pos), (unsigned)(n_tensors ? B : 1), (unsigned)std::max(n_tensors, 1));
-    VMOBA_PROFILE_BEGIN(3, st);
+    int64_t chunks = n_tensors ? 0 : ceil_div64(S, INDEX_CHUNK);
+    for (int i = 0; i < n_tensors; ++i) chunks = std::max(chunks, ceil_div64(S * Hh * (D * (cd.in_bf16[i] ? 2 : 4) / 16), chunk_pieces(inverse)));
     auto kfn = inverse ? permute_rows_kernel<true, false> : build_index ? permute_rows_kernel<false, true> : permute_rows_kernel<false, false>;
-    kfn<<<grid, dim3(256), 0, st>>>(gd, cd, perm, inv_perm, blk_off, n_pos, Hh, D);
+    VMOBA_PROFILE_BEGIN(3, st);
+    constexpr int64_t PER_LAUNCH = 1 << 23;             // (a launch holds less than 2^32 threads)
+    for (int64_t c0 = 0; c0 < chunks; c0 += PER_LAUNCH) {
+        const dim3 grid((unsigned)std::min(PER_LAUNCH, chunks - c0), (unsigned)(n_tensors ? B : 1), (unsigned)std::max(n_tensors, 1));
+        kfn<<<grid, dim3(256), 0, st>>>(gd, cd, perm, inv_perm, blk_off, Hh, D, (unsigned)c0);
+    }
     VMOBA_PROFILE_END(3, st);
     VMOBA_CHECK_LAUNCH();
     return VMOBA_OK;

@@ -272,3 +272,33 @@ def test_tile_list_of_many_heads(dtype):
     Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(1100 + i, (1, S, heads, D))) for i in range(4))
     g = gu.run_gpu(Q, K, V, dO, (1, 1, S), (0, 0, 0), 4, 0.5, dtype)
     check_heads(f"many-heads-{gu.dtype_name(dtype)}", g, Q, K, V, dO, (0, 299, heads - 1), dtype=dtype)
+
+
+@pytest.mark.parametrize("Hh,D,S,tin,tout", [
+    (1, 64, 1, torch.bfloat16, torch.bfloat16), (1, 64, 331, torch.bfloat16, torch.bfloat16),     # 33 positions of 8 pieces in a workgroup's 256
+    (3, 64, 97, torch.float32, torch.float32), (5, 128, 67, torch.float32, torch.bfloat16),       # positions that straddle workgroups
+    (16, 128, 8, torch.bfloat16, torch.bfloat16), (17, 128, 31, torch.bfloat16, torch.bfloat16),  # one position per workgroup, and a piece row more
+    (40, 128, 13, torch.float32, torch.float32),                                                  # a position in five workgroups
+])
+def test_partition_across_workgroup_borders(Hh, D, S, tin, tout):
+    """Moves and index arrays where workgroups' runs of pieces and the rows of a position do not line up; two batch elements, two tensors of
+    their own type, a forward move that reads perm, its inverse, and a call for the index arrays alone."""
+    g = vb.make_grid(1, 1, S, 0, 0, 0, max(1, S // 3)) if S < 300 else vb.make_grid(1, 3, S, 1, 2, 7)
+    S, nb = vb.vmoba_partition_dims(g)
+    perm, inv_perm, blk_off = vo.partition_index(g.T, g.H, g.W, g.bt, g.bh, g.bw, g.chunk)
+    x, y = torch.randn(2, S, Hh, D, device="cuda").to(tin), torch.randn(2, S, Hh, D, device="cuda").to(torch.bfloat16)
+    order = torch.from_numpy(perm.astype(np.int64)).cuda()
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for ins, outs in (([], []), ([x, y], [torch.empty_like(x, dtype=tout), torch.empty_like(y)])):
+        idx = [torch.full((n,), -1, **i32) for n in (S, S, nb + 1)]
+        vb.vmoba_partition(g, 0, 2, Hh, D, ins, outs, *idx)
+        for got, ref in zip(idx, (perm, inv_perm, blk_off)):
+            assert np.array_equal(got.cpu().numpy(), ref)
+        for a, b in zip(ins, outs):
+            assert torch.equal(b, a[:, order].to(b.dtype))
+    again = torch.empty_like(outs[0])
+    vb.vmoba_partition(g, 0, 2, Hh, D, [x], [again], idx[0], None, None)
+    assert torch.equal(again, outs[0])
+    back = [torch.empty_like(t) for t in outs]
+    vb.vmoba_partition(g, 1, 2, Hh, D, outs, back, idx[0], None, None)
+    assert torch.equal(back[0], x.to(tout)) and torch.equal(back[1], y)
