@@ -142,20 +142,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     constexpr int OPITCH = D * 2 + 16;
     static_assert(4 * 32 * RB <= BUF && 4 * 32 * OPITCH <= BUF, "rows of the four wavefronts fit a buffer");
 
-    // One workgroup per tile of the flat list (all heads).  Workgroup ids go round the 8 XCDs, so XCD x = id % 8 takes the
-    // x-th eighth of the list: a key block's tiles then share one L2 instead of eight (gridDim.x is a multiple of 8).
-    const int total = *n_tiles;
-    const int per_xcd = (total + 7) >> 3;
-    const int slot = (int)(blockIdx.x >> 3);
-    const int f = (int)(blockIdx.x & 7) * per_xcd + slot;
-    if (slot >= per_xcd || f >= total) return;
-    TileCoord tc;
-    const int4 fd = flat_desc[f];               // {first list entry, count | head << 10, first key, block length}
-    tc.list0 = fd.x;
-    tc.count = fd.y & 1023;
-    tc.k0 = fd.z;
-    tc.L = fd.w;
-    const int bh = fd.y >> 10, b = bh / Hh, h = bh % Hh;
+    Tile tc;
+    if (!take_tile(flat_desc, n_tiles, tc)) return;
+    const int bh = tc.bh, b = bh / Hh, h = bh % Hh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, hf = lane >> 5;
     const long long seg = (long long)bh * cap;

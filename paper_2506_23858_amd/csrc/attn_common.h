@@ -75,11 +75,23 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-struct TileCoord {
-    int count;    // valid entries in the tile (1..TM)
+struct Tile {
     int list0;    // first list entry of the tile, relative to the head's segment
+    int count;    // valid entries in the tile (1..TM)
+    int bh;       // batch element and head
     int k0, L;    // first key position and number of keys of the tile's key block
 };
+__device__ __forceinline__ Tile tile_of(const int4 d) { return {d.x, d.y & 1023, d.y >> 10, d.z, d.w}; }      // see write_tile_list
+// The tile of a workgroup of a kernel with one workgroup per entry of the flat list (all heads); false: none.  Workgroup ids go round
+// the 8 XCDs, so XCD x = id % 8 takes the x-th eighth of the list: a key block's tiles then share one L2 instead of eight
+// (gridDim.x is a multiple of 8).
+__device__ __forceinline__ bool take_tile(const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, Tile& t) {
+    const int total = *n_tiles, per_xcd = (total + 7) >> 3, slot = (int)(blockIdx.x >> 3);
+    const int f = (int)(blockIdx.x & 7) * per_xcd + slot;
+    if (slot >= per_xcd || f >= total) return false;
+    t = tile_of(flat_desc[f]);
+    return true;
+}
 
 inline __device__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 

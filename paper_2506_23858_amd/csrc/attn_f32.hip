@@ -28,11 +28,8 @@
 // and the 4-byte reads of 32 consecutive channels of a row stay inside one 128-byte run.
 #include "attn_common.h"
 
-#include <algorithm>
-
 namespace {
 
-constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
 // 64 lanes x 16 (4) bytes from a 64-bit address per lane to LDS: lane i writes lds_addr + 16 (4) * i.
@@ -166,23 +163,6 @@ __device__ __forceinline__ void product_over_rows(const TileReads<D>& rd, const 
     }
 }
 
-struct F32Tile { int list0, count, bh, k0, L; };
-// Entry of the flat tile list (see write_tile_list) this workgroup takes, XCD x = id % 8 the x-th eighth of it.
-__device__ __forceinline__ bool take_tile(const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, F32Tile& t) {
-    const int total = *n_tiles;
-    const int per_xcd = (total + 7) >> 3;
-    const int slot = (int)(blockIdx.x >> 3);
-    const int f = (int)(blockIdx.x & 7) * per_xcd + slot;
-    if (slot >= per_xcd || f >= total) return false;
-    const int4 d = flat_desc[f];
-    t.list0 = d.x;
-    t.count = d.y & 1023;
-    t.bh = d.y >> 10;
-    t.k0 = d.z;
-    t.L = d.w;
-    return true;
-}
-
 __device__ __forceinline__ const char* head_ptr(const TensorView& t, int b, int h) {
     return t.ptr + ((long long)b * t.stride_b + (long long)h * t.stride_h) * 4;
 }
@@ -196,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_tile_f32_kernel(
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int KC = 32, TILE = KeyRows<D>::TILE, DT = D / 32;
     __shared__ __align__(1024) char sKV[2][2][TILE];              // [buffer][K, V]
-    F32Tile t;
+    Tile t;
     if (run_if && !*run_if) return;
     if (!take_tile(flat_desc, n_tiles, t)) return;
     const int b = t.bh / Hh, h = t.bh % Hh;
@@ -286,7 +266,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
     float* __restrict__ dQpart, int Hh, int S, long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int KC = 32, TILE = KeyRows<D>::TILE, DT = D / 32;
     __shared__ __align__(1024) char sKV[2][2][TILE];
-    F32Tile t;
+    Tile t;
     if (run_if && !*run_if) return;
     if (!take_tile(flat_desc, n_tiles, t)) return;
     const int b = t.bh / Hh, h = t.bh % Hh;

@@ -143,31 +143,26 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     const uint32_t sV0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sV;
     const uint32_t sTok0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)sTok;
 
-    // ---- per-tile state.  Descriptor: {first list entry, count | head << 10, first key, block length}
-    struct Tile {
-        int list0, count, bh, k0, L;
+    // ---- per-tile state
+    struct FwdTile : Tile {
         const char* kbase;
         const char* vbase;
         long long seg;
     };
     auto decode = [&](const int4 d) {
-        Tile t;
-        t.list0 = d.x;
-        t.count = d.y & 1023;
-        t.bh = d.y >> 10;
-        t.k0 = d.z;
-        t.L = d.w;
+        FwdTile t;
+        static_cast<Tile&>(t) = tile_of(d);
         const int b = t.bh / Hh, h = t.bh % Hh;
         t.kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * 2;
         t.vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * 2;
         t.seg = (long long)t.bh * cap;
         return t;
     };
-    auto query_of = [&](const Tile& t) {                          // surplus rows repeat the tile's last query
+    auto query_of = [&](const FwdTile& t) {                          // surplus rows repeat the tile's last query
         return q_idx[t.seg + t.list0 + min(ent, t.count - 1)];
     };
     bf16x8_t qf[KSTEPS];
-    auto load_q = [&](const Tile& t, int q) {
+    auto load_q = [&](const FwdTile& t, int q) {
         const int b = t.bh / Hh, h = t.bh % Hh;
         const char* src = Q.ptr + ((long long)b * Q.stride_b + (long long)q * Q.stride_s + (long long)h * Q.stride_h) * 2;
 #pragma unroll
@@ -214,7 +209,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     uint32_t krow[IPW], vrow[IPW];         // KVR: rows of the next request of K and of V, read from the ring a step before
     int kb = 0, vb = 0;                    // running group counters: group x of the current tile uses slot (kb + x) & 3 / (vb + x) & 3
     int tp = 0;                            // KVR: table that holds the current tile's row numbers
-    auto request_first_groups = [&](const Tile& t, int kb_t, int vb_t, int tb) {     // K(0..3), V(0..1) of tile t
+    auto request_first_groups = [&](const FwdTile& t, int kb_t, int vb_t, int tb) {     // K(0..3), V(0..1) of tile t
         if constexpr (KVR) {
             uint32_t r[4][IPW];
 #pragma unroll
@@ -252,7 +247,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     auto readV = [&](int x, int u) { return TL::transposed(sV, tlane, (uint32_t)((vb + x) & (NR - 1)) * SLOT, u / DT, u % DT); };
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-    Tile cur = decode(flat_desc[f]);
+    FwdTile cur = decode(flat_desc[f]);
     load_q(cur, query_of(cur));
     if constexpr (KVR) {                   // the first tile's row numbers: nothing to overlap them with
         dma_first_tokens(cur, 0);
@@ -300,7 +295,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
         opK[1] = readK(1, 1);
         opV[0] = opK[0];
         opV[1] = opK[1];
-        const Tile nxt = decode(nd);
+        const FwdTile nxt = decode(nd);
         const int nq = query_of(nxt);              // needed a tile later: the load has the whole tile to land
 
         // one pipeline step; the flags are compile-time: QK / PV = the step has a first / second product, SM = it has a

@@ -27,11 +27,8 @@
 // turn for the six products of a k-step instead of one: no faster, spills in the forward kernel, and larger errors in dK and dV.
 #include "attn_common.h"
 
-#include <algorithm>
-
 namespace {
 
-constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr float LIFT = 0x1p16f, UNLIFT = 0x1p-16f;                                // of weights and dS, see above
 constexpr uint32_t SMALLEST = 27u << 23, TOO_LARGE = 153u << 23;                  // 2^-100 and 2^26 as float bits
@@ -188,16 +185,6 @@ __device__ __forceinline__ void load_terms(const char* row, int hf, bf16x8_t (&f
         for (int ks = 0; ks < D / 16; ++ks) f[p][ks] = *reinterpret_cast<const bf16x8_t*>(row + (p * D + ks * 16 + hf * 8) * 2);
 }
 
-struct SplitDesc { int list0, count, bh, k0, L; };
-__device__ __forceinline__ bool take_split_tile(const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, SplitDesc& t) {
-    const int total = *n_tiles, per_xcd = (total + 7) >> 3, slot = (int)(blockIdx.x >> 3);
-    const int f = (int)(blockIdx.x & 7) * per_xcd + slot;
-    if (slot >= per_xcd || f >= total) return false;
-    const int4 d = flat_desc[f];
-    t = {d.x, d.y & 1023, d.y >> 10, d.z, d.w};
-    return true;
-}
-
 // ---------------------------------------------------------------------------------------------
 // Forward tile kernel: 4 wavefronts x 32 gathered queries, one key block, 32 keys at a time.  One buffer for K and one for V: the next
 // keys are requested as soon as S^T of these is complete, the next values after O^T; two workgroups per compute unit fill
@@ -210,8 +197,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_tile_split_kernel(const char*
     using ST = SplitTile<D>;
     constexpr int DT = ST::DT, IPW = ST::IPW, RB6 = 12 * D;
     __shared__ __align__(1024) char smem[2 * ST::TILE];
-    SplitDesc t;
-    if (*out_of_range || !take_split_tile(flat_desc, n_tiles, t)) return;
+    Tile t;
+    if (*out_of_range || !take_tile(flat_desc, n_tiles, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const long long seg = (long long)t.bh * cap;
@@ -309,8 +296,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_split_kernel(const char* _
     using ST = SplitTile<D>;
     constexpr int DT = ST::DT, IPW = ST::IPW, RB6 = 12 * D;
     __shared__ __align__(1024) char smem[2][2 * ST::TILE];
-    SplitDesc t;
-    if (*out_of_range || !take_split_tile(flat_desc, n_tiles, t)) return;
+    Tile t;
+    if (*out_of_range || !take_tile(flat_desc, n_tiles, t)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const long long seg = (long long)t.bh * cap;
