@@ -99,11 +99,14 @@ __global__ __launch_bounds__(256) void head_tiles_kernel(const int* __restrict__
 // its row number from there one step before it is issued.  (Before: a whole tile's numbers in a table, read where they
 // were needed, so that every row request waited for everything else in the LDS queue, blocks of more than 3584 keys
 // looked up in global memory: 3.00 -> 2.58 ms at 480p, 3D partition, tau = 0.5.)
-template <int D, int NW, bool KVR>
+//
+// NEG: the scores of -Q, for a negative scale (the scale given is its magnitude).  An instantiation of its own: as a test before every tile it
+// made the others 0.1 to 0.3 % slower (forward call, 111 600 tokens, 40 heads, 5 of 165 blocks: 7.26 -> 7.28 ms).
+template <int D, int NW, bool KVR, bool NEG>
 __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
     const int* __restrict__ n_tiles, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
-    long long cap, float scale_log2, uint32_t q_sign, const int* __restrict__ kv_rows) {
+    long long cap, float scale_log2, const int* __restrict__ kv_rows) {
     constexpr int G = 32;                   // keys per group
     using TL = RowTile<D>;
     constexpr int PPR = TL::PPR;            // 16-byte pieces per row
@@ -143,15 +146,21 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     const uint32_t sV0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sV;
     const uint32_t sTok0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)sTok;
 
-    // ---- per-tile state
-    struct FwdTile : Tile {
+    // ---- per-tile state (fields of its own: derived from Tile it compiles to code that is 0.3 % slower)
+    struct FwdTile {
+        int list0, count, bh, k0, L;
         const char* kbase;
         const char* vbase;
         long long seg;
     };
     auto decode = [&](const int4 d) {
+        const Tile c = tile_of(d);
         FwdTile t;
-        static_cast<Tile&>(t) = tile_of(d);
+        t.list0 = c.list0;
+        t.count = c.count;
+        t.bh = c.bh;
+        t.k0 = c.k0;
+        t.L = c.L;
         const int b = t.bh / Hh, h = t.bh % Hh;
         t.kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * 2;
         t.vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * 2;
@@ -175,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     // are 32-bit (checked on the host); an offset past the block's last row is clamped to it.
     const uint32_t pc16 = TL::request_piece(lane);
     uint32_t k_off[IPW], v_off[IPW], k_last[IPW], v_last[IPW];
-    auto first_offsets = [&](const Tile& t) {
+    auto first_offsets = [&](const FwdTile& t) {
 #pragma unroll
         for (int i = 0; i < IPW; ++i) {
             const int dr = (wave * IPW + i) * RPI + lane / PPR;
@@ -194,11 +203,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
         }
     };
     // KVR: row numbers of groups x and x + 1 of tile t into ring `tb` (keys past the block's end repeat its last one)
-    auto dma_tokens = [&](const Tile& t, int x, int tb) {
+    auto dma_tokens = [&](const FwdTile& t, int x, int tb) {
         dma4(reinterpret_cast<const char*>(kv_rows), (uint32_t)(t.k0 + min(x * G + lane, t.L - 1)) << 2,
              sTok0 + (uint32_t)(tb * TOKS + (x & 15) * G) * 4);
     };
-    auto dma_first_tokens = [&](const Tile& t, int tb) {          // groups 0..7, two per wavefront
+    auto dma_first_tokens = [&](const FwdTile& t, int tb) {          // groups 0..7, two per wavefront
         if (wave < 4) dma_tokens(t, 2 * wave, tb);
     };
     // KVR: row of K and V that request i of this wavefront fetches for this lane in group x of the tile of ring `tb`
@@ -279,9 +288,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
 
         VMOBA_WAIT_VMCNT(0);                       // this wavefront's K(0..3), V(0..1) (and Q rows) have landed
         __syncthreads();                           // ... and everybody else's
-        if (q_sign) {                              // a negative scale: the scores of -Q with the scale's magnitude
+        if constexpr (NEG) {
 #pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(u32x4_t, qf[ks]) ^ q_sign);
+            for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(u32x4_t, qf[ks]) ^ 0x80008000u);
         }
         // S^T(0), and the operands of the first two units of step 0
         if (odd) {
@@ -661,13 +670,18 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         // the kernel's running maximum and its mask of the keys past a block's end need a positive scale: the sign goes to Q, and the
         // smallest normal number does for 0 (it leaves every weight at 1)
         const float magnitude = std::max(std::fabs(scale_log2), FLT_MIN);
-        const uint32_t q_sign = scale_log2 < 0.f ? 0x80008000u : 0u;
         const dim3 pgrid((unsigned)std::min<int64_t>((wide ? 1 : 2) * (int64_t)vmoba_num_cus(), (int64_t)BH * max_tiles));
-#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, magnitude, q_sign, kv_rows
-        if (wide && kv_rows) attn_fwd_tile_mfma_kernel<128, 8, true><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);
-        else if (wide) attn_fwd_tile_mfma_kernel<128, 8, false><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);
-        else if (kv_rows) attn_fwd_tile_mfma_kernel<64, 4, true><<<pgrid, dim3(256), 0, st>>>(MFMA_ARGS);
-        else attn_fwd_tile_mfma_kernel<64, 4, false><<<pgrid, dim3(256), 0, st>>>(MFMA_ARGS);
+#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, magnitude, kv_rows
+#define LAUNCH_FWD(NEG)                                                                                                       \
+    do {                                                                                                                      \
+        if (wide && kv_rows) attn_fwd_tile_mfma_kernel<128, 8, true, NEG><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);            \
+        else if (wide) attn_fwd_tile_mfma_kernel<128, 8, false, NEG><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);                 \
+        else if (kv_rows) attn_fwd_tile_mfma_kernel<64, 4, true, NEG><<<pgrid, dim3(256), 0, st>>>(MFMA_ARGS);                \
+        else attn_fwd_tile_mfma_kernel<64, 4, false, NEG><<<pgrid, dim3(256), 0, st>>>(MFMA_ARGS);                            \
+    } while (0)
+        if (scale_log2 < 0.f) LAUNCH_FWD(true);
+        else LAUNCH_FWD(false);
+#undef LAUNCH_FWD
 #undef MFMA_ARGS
     }
     VMOBA_PROFILE_END(0, st);
