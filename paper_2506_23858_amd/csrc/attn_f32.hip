@@ -20,7 +20,8 @@
 //
 // Measured on 14 040 tokens x 12 heads x 128 (36 blocks of 390 keys, 785 K kept pairs): forward 1.45 ms (109 TFLOP/s), dQ
 // 2.32 ms (102), dK/dV 3.34 ms (94, the last run of a block holds 6 keys of 64); the plain FMA kernels before took 15.3,
-// 15.4 and 72 ms (a query or key per lane: one LDS broadcast read per four FMAs, and 512 registers with spills in dK/dV).
+// 15.4 and 72 ms (a query or key per lane: one LDS broadcast read per four FMAs, and 512 registers with spills in dK/dV).  That call
+// comes here only when its operands are out of the other kernels' range; the smallest layers are bound by their launches.
 // A dense product on the same instruction reaches 153 TFLOP/s.
 //
 // Rows travel from global memory straight to LDS (16 bytes per lane), one chunk ahead in a second buffer, one barrier per
