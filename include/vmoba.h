@@ -101,7 +101,8 @@ int vmoba_layer_kind(int layer);
 /* Token count S = T*H*W and block count N_b of a partition (Eq. 1-2).  Host pointers. */
 int vmoba_partition_dims(const vmoba_grid* g, int64_t* S, int32_t* n_blocks);
 
-/* Bytes of workspace `op` needs for this geometry.  nnz_capacity is per (batch, head). */
+/* Bytes of workspace `op` needs for this geometry.  nnz_capacity is per (batch, head).  Pass the attention calls' own n_blocks
+ * and nnz_capacity: for float32 they also decide whether the operands are split into bfloat16 terms, which takes room. */
 size_t vmoba_workspace_bytes(int op, int B, int Hh, int64_t S, int D, int32_t n_blocks,
                              int64_t nnz_capacity, int dtype);
 
@@ -206,7 +207,7 @@ int vmoba_select_static(int B, int Hh, int64_t S, int D, int32_t n_blocks, const
  * vmoba_attn_fwd -- Step 3 of Sec. 3.1: every query attends to the keys/values of its selected
  * blocks only.  O(q) = sum_n softmax_n(softmax_scale * <Q'(q), K'(n)>) V'(n) over the keys n of
  * the selected blocks; LSE [B, Hh, S] float32 is the natural-log-sum-exp of the scaled scores.
- * A query that selected nothing gets O = 0 and LSE = -inf.
+ * A query that selected nothing gets O = 0 and LSE = -inf.  softmax_scale is any finite number.
  * Inputs: Q as vmoba_select saw it (block-order Q', or the caller's Q with token ids as query ids), block-order
  * K', V', blk_off, and the lists written by vmoba_select with the same nnz_capacity.  O and LSE are indexed
  * by query id.  Accumulation and soft-max are float32; bfloat16 inputs are multiplied on the

@@ -1,5 +1,5 @@
 """Sizes at which the tile kernels and the selection kernels can go wrong: edges of tiles, remainders, the smallest of a
-range.  Every case runs a whole layer against the CPU oracle (bounds: tests/gpu_util.py)."""
+range.  Most cases run a whole layer against the CPU oracle (bounds: tests/gpu_util.py)."""
 import math
 
 import numpy as np
@@ -22,7 +22,8 @@ def test_f32_matrix_kernels_at_tile_edges(chunk, D):
     grid, S = (1, 8, 25), 200
     Q, K, V, dO = (synth.iid_normal(900 + i, (1, S, 2, D)) for i in range(4))
     for tau, kv_in_place in ((0.6, False), (1.0, True)):
-        compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, f"f32-edges-{chunk}", kv_in_place=kv_in_place)
+        g, _ = compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32, f"f32-edges-{chunk}", kv_in_place=kv_in_place)
+        assert not gu.multiplies_split_operands(g["plan"])
 
 
 @pytest.mark.parametrize("D", [64, 128])
