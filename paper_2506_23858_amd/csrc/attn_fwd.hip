@@ -49,64 +49,81 @@ __global__ __launch_bounds__(256) void head_tiles_kernel(const int* __restrict__
 //   S^T[key, q] = K[key, :] . Q[q, :]          A = K rows from LDS, B = Q^T held in registers
 //   O^T[d, q]  += V^T[d, key] . P^T[key, q]    A = V^T by transpose reads, B = P^T packed from S^T
 // With the query on the lane, the row maximum and row sum of the online soft-max are reductions
-// over a lane's own registers plus one exchange between the lane halves (v_permlane32_swap).  The
-// running maximum is only raised when a group exceeds it by more than 2^8 (the probabilities then
-// stay below 2^8, well inside float32 / bf16 range), so the accumulator rescale is rare; the final
-// division by the row sum makes the result independent of which maximum was used.  The row sum is
-// kept per lane half and the halves are added once at the end (they always agree on the maximum).
+// over a lane's own registers plus one exchange between the lane halves (v_permlane32_swap).
 //
-// Pipeline.  A wavefront's instruction stream is a three-stage software pipeline: step g issues
-//     S^T(g+1) = K(g+1) . Q^T               (matrix)
-//     P(g)     = soft-max piece of S^T(g)   (vector)
-//     O^T     += V(g-1)^T . P(g-1)^T        (matrix)
-// interleaved unit by unit (unit u = k-step u of the first product and (s, dt) = (u / DT, u % DT)
-// of the second), with the LDS operands of unit u + 2 fetched during unit u, so neither LDS
-// latency nor the soft-max sits between dependent matrix instructions.  S^T and P live in two
-// register sets that swap roles every step.
+// One stream of key groups.  A workgroup is persistent: it strides through its XCD's share of the flat tile list (all heads,
+// see write_tile_list), and the key groups of its tiles form one sequence that is worked on without a break.  Step n of a wavefront,
+// a three-stage software pipeline, issues
+//     S^T(n+1) = K(n+1) . Q^T               (matrix)
+//     P(n)     = soft-max piece of S^T(n)   (vector)
+//     O^T     += V(n-1)^T . P(n-1)^T        (matrix)
+// unit by unit (unit u = k-step u of the first product and (s, dt) = (u / DT, u % DT) of the second), with the LDS operands
+// of unit u + 2 fetched during unit u, so neither LDS latency nor the soft-max sits between dependent matrix instructions.
+// S^T and P live in two register sets that swap roles every step.  A tile's last step computes S^T of the next tile's first group, and the
+// next tile's first step ends the tile's second product: no steps with half of the work missing at a tile's ends.  A tile
+// counts as at least four groups (surplus ones are masked like the keys past a block's end), which is what the look-ahead of the
+// row requests needs.
+//
+// What bounds it: two wavefronts of a SIMD together issue one instruction, scalar ones and waits included, every 4.5 cycles or so, and the clock
+// falls as the rate rises (1.8 GHz here, 2.4 without load).  A step is 150 instructions for 16 matrix instructions (165 before): row
+// offsets advance in the request itself, ring slots change names, and everything that only happens at a tile's ends stays out of the
+// steps between.  With the steps at a tile's ends gone as well, the kernel takes, before -> after, at 480p, 12 heads, 1D / 2D / 3D with keys
+// in place (and tau = 0.5): 1.34 / 1.42 / 2.65 -> 1.26 / 1.26 / 2.49 ms; at 720p, 10 of 40 blocks per query, 8.5 -> 8.0 ms.  Timing variants:
+// no LDS operand reads -12 %, no exponentials -15 %, no row requests -10 %, the barrier in every second step only -3 %.
 //
 // Rows.  K and V groups are loaded straight from global memory into rings of four LDS slots each
 // (global_load_lds_dwordx4: 64 lanes x 16 bytes land in 1024 consecutive LDS bytes), so no
-// registers hold rows in flight and a group is requested two steps before it is first read.  A
-// slot is a 32-row RowTile: groups of rows 64 bytes apart instead of a swizzle over all 16 pieces of a
-// row, so that two per-lane addresses and immediate offsets reach every operand (about 12 address
-// instructions less in a step of 170; 480p, 12 heads, 1D / 2D / 3D partition: 1.33 / 1.48 / 1.11 -> 1.29 / 1.42 / 1.07 ms).
-// Rows past the end of the block repeat its last key; the
-// surplus keys of the last group are masked to -inf in the soft-max.
+// registers hold rows in flight.  A slot is a 32-row RowTile: two per-lane addresses and immediate offsets reach every operand.
+// Rows past the end of the block repeat its last key; the surplus keys of the last group are masked to -inf in the soft-max.
+// The next tile's query rows go the same way, into the place of the partial rows, from where the Q^T registers are filled in the
+// last step but one; their list entries, one tile earlier, into a small ring, and the descriptor another tile earlier.
 //
-// Ordering.  The loads are issued by inline assembly, so their waits are written by hand: every
-// step that requests rows starts with s_waitcnt vmcnt(loads of one step) -- the wavefront's own
-// loads of two steps ago have landed -- followed by the workgroup barrier, which makes every
-// wavefront's loads of two steps ago visible.  Step g requests K(g+4) into the slot of K(g) (last
-// read in step g-1) and V(g+2) into the slot of V(g-2) (last read in step g-1); K(g+2) and V(g)
-// are first read at the end of step g.
+// Soft-max.  The running maximum is only raised when a group exceeds it by more than 2^8 (the probabilities then
+// stay below 2^8, well inside float32 / bf16 range), so that a step only compares its largest score with a limit and the rescaling is
+// rare; the final division by the row sum makes the result independent of which maximum was used.  The row sum is
+// kept per lane half and the halves are added once at the end (they always agree on the maximum).
 //
-// Persistence.  A workgroup strides through its XCD's share of the flat tile list (all heads, see
-// write_tile_list) and overlaps the start of its next tile with the end of the current one:
-// the next descriptor and the next tile's query index are fetched at the start of the tile, and its
-// query rows (into the Q^T registers, the first product is done by then) and K(0..3), V(0..1)
-// during the last soft-max step, into slots nobody reads any more (the rings are indexed by
-// running group counters, so the next tile's first V slots differ from the slots of the two groups
-// the last two steps read).
+// Ordering.  The loads are issued by inline assembly, so their waits are written by hand: a step starts with a wait for what this
+// wavefront requested up to two steps before -- loads and stores count down in order, and all wavefronts issue the same
+// sequence of them -- followed by the workgroup barrier, which makes everybody's rows visible.  Step n requests K(n+4) into the
+// slot of K(n) (last read in step n-1) and V(n+2) into the slot of V(n-2) (last read in step n-1); K(n+2) and V(n) are first
+// read at the end of step n.  The barrier is the bare instruction: operands on their way from LDS across it lie in slots that
+// are not requested again before the step after, which cannot begin before they have been used.
 //
-// Output.  A wavefront writes its 32 partial rows to LDS as the accumulators hold them (8 bytes
+// Output.  In the step after a tile's last a wavefront writes its 32 partial rows to LDS as the accumulators hold them (8 bytes
 // per lane and channel group) and reads them back as whole rows: the tile's partials are
 // consecutive rows of Opart, so each store request is a 1 KB run instead of 16-byte pieces of 32
-// rows (the address unit needs about as long for one such request as for eight full-row ones).
+// rows (the address unit needs about as long for one such request as for eight full-row ones).  Surplus rows of a tile repeat its
+// last entry bit for bit and are stored to its place, so that every wavefront issues the same number of stores.
 //
 // Keys in place (KVR).  K and V may stay where the caller has them: key position p of the block order is then row
 // kv_rows[p] of both.  The row numbers come by way of LDS, too (global_load_lds_dword): those of group g + 8 are requested
-// in step g, those of a tile's first groups while the tile before is worked on, and a row request takes
-// its row number from there one step before it is issued.  (Before: a whole tile's numbers in a table, read where they
-// were needed, so that every row request waited for everything else in the LDS queue, blocks of more than 3584 keys
-// looked up in global memory: 3.00 -> 2.58 ms at 480p, 3D partition, tau = 0.5.)
+// in step g, those of a tile's first groups two tiles ahead, and a row request takes its row number from there one step before it is issued.
 //
-// NEG: the scores of -Q, for a negative scale (the scale given is its magnitude).  An instantiation of its own: as a test before every tile it
-// made the others 0.1 to 0.3 % slower (forward call, 111 600 tokens, 40 heads, 5 of 165 blocks: 7.26 -> 7.28 ms).
+// NEG: the scores of -Q, for a negative scale (the scale given is its magnitude).
+struct FwdArgs {
+    TensorView Q, K, V;
+    const int* q_idx;
+    const int4* flat_desc;
+    const int* n_tiles;
+    float *Opart, *lse_part;
+    long long cap;
+    const int* kv_rows;
+    int Hh;
+    float scale_log2;
+    int q_offsets_32;      // a row of Q is reached from its head by a 32-bit offset, a product of two numbers below 2^24
+};
 template <int D, int NW, bool KVR, bool NEG>
-__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
-    TensorView Q, TensorView K, TensorView V, const int* __restrict__ q_idx, const int4* __restrict__ flat_desc,
-    const int* __restrict__ n_tiles, float* __restrict__ Opart, float* __restrict__ lse_part, int Hh,
-    long long cap, float scale_log2, const int* __restrict__ kv_rows) {
+__global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(FwdArgs by_value) {
+    // What is only needed at a tile's ends is read from the arguments again each time: there are not enough scalar registers to keep it.
+    auto args = [&]() {
+        auto p = (const __attribute__((address_space(4))) FwdArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return p;
+    };
+    const int* const n_tiles = by_value.n_tiles;
+    const float scale_log2 = by_value.scale_log2;
+    const int* const kv_rows = by_value.kv_rows;
     constexpr int G = 32;                   // keys per group
     using TL = RowTile<D>;
     constexpr int PPR = TL::PPR;            // 16-byte pieces per row
@@ -114,19 +131,21 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     constexpr int NR = 4;                   // ring slots per tensor
     constexpr int KSTEPS = D / 16, DT = D / 32, UNITS = KSTEPS;
     constexpr int RPI = TL::RPI;            // rows per load instruction
-    constexpr int IPW = G / RPI / NW;       // load instructions per wavefront per group
-    constexpr int NDMA = 2 * IPW + (KVR ? 1 : 0);     // loads a wavefront issues per step (one K group, one V group, row numbers)
-    constexpr float LAZY = 8.f;
-    static_assert(UNITS % 4 == 0 && UNITS == 2 * DT && IPW >= 1 && IPW * NW * RPI == G && (D == 64 || D == 128), "unit bookkeeping");
-    __shared__ __align__(1024) char sK[NR * SLOT];
-    __shared__ __align__(1024) char sV[NR * SLOT];
-    // a wavefront's 32 partial rows on their way out: written as the accumulators hold them (8 bytes per lane and
-    // channel group), read back as whole rows, so that the global stores are 1 KB runs instead of 16-byte pieces
+    static_assert(G == RPI * NW, "one load instruction per wavefront, tensor and group");
+    static_assert(UNITS % 4 == 0 && UNITS == 2 * DT && (D == 64 || D == 128), "unit bookkeeping");
+    constexpr int MIN_GROUPS = 4;           // groups a tile counts as, at least
+    const float lazy = 8.f / scale_log2;    // a row's maximum is raised by more than 2^8 only
+    // the partial rows of a wavefront: 32 rows, written 8 bytes per lane and channel group, read back as whole rows
     constexpr int OPITCH = D * 2 + 16;
-    __shared__ __align__(16) char sOut[NW * 32 * OPITCH];
-    // KVR: row numbers of the key groups of the current and of the next tile, rings of 16 groups (a request fills two)
+    constexpr int V0 = NR * SLOT, OUT0 = 2 * NR * SLOT, OUTW = 32 * OPITCH, IDX0 = OUT0 + NW * OUTW, DESC0 = IDX0 + 2 * NW * 64 * 4,
+                  TOK0 = DESC0 + NW * 64 * 4;
+    // KVR: row numbers of the key groups of three tiles, rings of 16 groups (a request fills two)
     constexpr int TOKS = 17 * G;
-    __shared__ __align__(256) int sTok[KVR ? 2 * TOKS : 4];
+    __shared__ __align__(1024) char smem[TOK0 + (KVR ? 3 * TOKS * 4 : 0)];
+    // requests and stores of a wavefront, always in this order: every step the rows of K and V (KVR: and row numbers); then, in a tile's
+    // first step, (KVR: row numbers,) the partial rows and LSE of the tile before, a descriptor, list entries, query rows
+    constexpr int N_STEP = KVR ? 3 : 2, N_FIRST = (KVR ? 1 : 0) + D * 2 * 32 / 1024 + 1 + 2 + 32 / RPI;
+    static_assert(N_STEP + N_FIRST < 64, "what the wait counter holds");
 
     // Workgroup ids go round the 8 XCDs (each with its own L2), so XCD x = id % 8 takes the x-th eighth of the tile
     // list and its workgroups stride through it: a key block's tiles then share one L2 instead of eight.
@@ -136,113 +155,105 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
     const int f_step = by_xcd ? (int)(gridDim.x >> 3) : (int)gridDim.x;
     const int per_xcd = by_xcd ? (total + 7) >> 3 : total;
     const int f_end = min(total, (xcd + 1) * per_xcd);
-    int f = xcd * per_xcd + (by_xcd ? (int)(blockIdx.x >> 3) : (int)blockIdx.x);
-    if (f >= f_end) return;
+    const int f0 = xcd * per_xcd + (by_xcd ? (int)(blockIdx.x >> 3) : (int)blockIdx.x);
+    if (f0 >= f_end) return;
+    int tiles_left = (f_end - f0 + f_step - 1) / f_step;             // tiles whose partial rows are still to be written
+    const int f_last = f0 + (tiles_left - 1) * f_step;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
-    const int ent = wave * 32 + l32;
-    const uint32_t sK0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sK;
-    const uint32_t sV0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sV;
-    const uint32_t sTok0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)sTok;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t lds_rows = lds0 + (uint32_t)wave * TL::GP;         // this wavefront's share of ring slot 0 of K
+    char* const mine = smem + OUT0 + wave * OUTW;                     // this wavefront's partial rows, or next query rows
+    const uint32_t lds_mine = lds0 + OUT0 + (uint32_t)wave * OUTW;
 
-    // ---- per-tile state (fields of its own: derived from Tile it compiles to code that is 0.3 % slower)
     struct FwdTile {
-        int list0, count, bh, k0, L;
-        const char* kbase;
-        const char* vbase;
-        long long seg;
+        int L, count, k0, bh;
+        long long pair;                    // its first list entry, which is the first row of its partials, too
+        const char *q, *k, *v;             // the head's rows
     };
-    auto decode = [&](const int4 d) {
+    auto make_tile = [&](int4 d, const FwdTile& before) {            // (consecutive tiles mostly are the same head's)
         const Tile c = tile_of(d);
-        FwdTile t;
-        t.list0 = c.list0;
-        t.count = c.count;
-        t.bh = c.bh;
-        t.k0 = c.k0;
+        FwdTile t = before;
         t.L = c.L;
-        const int b = t.bh / Hh, h = t.bh % Hh;
-        t.kbase = K.ptr + ((long long)b * K.stride_b + (long long)h * K.stride_h) * 2;
-        t.vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * 2;
-        t.seg = (long long)t.bh * cap;
+        t.count = c.count;
+        t.k0 = c.k0;
+        t.bh = c.bh;
+        const auto a = args();
+        t.pair = (long long)c.bh * a->cap + c.list0;
+        if (__builtin_expect(c.bh != before.bh, 0)) {
+            const int b = c.bh / a->Hh, h = c.bh - b * a->Hh;
+            t.q = a->Q.ptr + (b * a->Q.stride_b + h * a->Q.stride_h) * 2;
+            t.k = a->K.ptr + (b * a->K.stride_b + h * a->K.stride_h) * 2;
+            t.v = a->V.ptr + (b * a->V.stride_b + h * a->V.stride_h) * 2;
+        }
         return t;
     };
-    auto query_of = [&](const FwdTile& t) {                          // surplus rows repeat the tile's last query
-        return q_idx[t.seg + t.list0 + min(ent, t.count - 1)];
+    auto tile_at = [&](int f, const FwdTile& before) {
+        const u32x4_t d = ((const __attribute__((address_space(4))) u32x4_t*)(uintptr_t)args()->flat_desc)[f];
+        return make_tile(make_int4((int)d.x, (int)d.y, (int)d.z, (int)d.w), before);
+    };
+    auto groups_of = [&](const FwdTile& t) { return max((t.L + G - 1) / G, MIN_GROUPS); };
+    // past the end of the workgroup's tiles: the last one again (its loads only)
+    auto request_descriptor = [&](int f) {
+        dma4(reinterpret_cast<const char*>(args()->flat_desc + min(f, f_last)), (uint32_t)min(lane, 3) * 4, lds0 + DESC0 + (uint32_t)wave * 256);
+    };
+
+    // list entries of the wavefront's queries (surplus rows repeat the tile's last query): tile's ring half `par`
+    auto request_entries = [&](const FwdTile& t, int par) {
+        dma4(reinterpret_cast<const char*>(args()->q_idx + t.pair), (uint32_t)min(wave * 32 + l32, t.count - 1) * 4, lds0 + IDX0 + (uint32_t)(par * NW + wave) * 256);
+    };
+    // The wavefront's 32 query rows, whole rows; piece p of row r sits at slot p ^ (r % pieces), which keeps the fragment reads free of
+    // bank conflicts.  A wavefront reads back only what it requested: no barrier.
+    auto request_queries = [&](const FwdTile& t, int par) {
+        const auto a = args();
+        const int* e = reinterpret_cast<const int*>(smem + IDX0) + (par * NW + wave) * 64 + lane / PPR;
+        auto piece = [&](int k) { return (uint32_t)(((lane % PPR) ^ ((k * RPI + lane / PPR) & (PPR - 1))) * 16); };
+        if (__builtin_expect(a->q_offsets_32, 1)) {
+            static_for<32 / RPI>([&](auto k) {
+                constexpr int k_ = decltype(k)::value;
+                dma_row16<k_ * 1024>(t.q, (uint32_t)e[k_ * RPI], (uint32_t)(a->Q.stride_s * 2), piece(k_), lds_mine);
+            });
+        } else {
+#pragma unroll
+            for (int k = 0; k < 32 / RPI; ++k) dma16_at(t.q + e[k * RPI] * (a->Q.stride_s * 2) + piece(k), (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_mine + k * 1024));
+        }
     };
     bf16x8_t qf[KSTEPS];
-    auto load_q = [&](const FwdTile& t, int q) {
-        const int b = t.bh / Hh, h = t.bh % Hh;
-        const char* src = Q.ptr + ((long long)b * Q.stride_b + (long long)q * Q.stride_s + (long long)h * Q.stride_h) * 2;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_t*>(src + (ks * 16 + hf * 8) * 2);
+    auto read_query = [&](int ks) {
+        u32x4_t x = *reinterpret_cast<const u32x4_t*>(mine + l32 * TL::RB + ((2 * ks + hf) ^ (l32 & (PPR - 1))) * 16);
+        if constexpr (NEG) x ^= 0x80008000u;
+        qf[ks] = __builtin_bit_cast(bf16x8_t, x);
     };
-    const uint32_t kss = (uint32_t)(K.stride_s * 2), vss = (uint32_t)(V.stride_s * 2);
-    const uint32_t k_adv = G * kss, v_adv = G * vss;
 
-    // Load instruction i of this wavefront fills row group wave * IPW + i of a slot.  Byte offsets from the head's base
-    // are 32-bit (checked on the host); an offset past the block's last row is clamped to it.
+    // Row requests: row `dr` of a group is this lane's.  Byte offsets from the head's base are 32-bit (checked on the host); an offset past
+    // the block's last row is clamped to it.
     const uint32_t pc16 = TL::request_piece(lane);
-    uint32_t k_off[IPW], v_off[IPW], k_last[IPW], v_last[IPW];
-    auto first_offsets = [&](const FwdTile& t) {
-#pragma unroll
-        for (int i = 0; i < IPW; ++i) {
-            const int dr = (wave * IPW + i) * RPI + lane / PPR;
-            k_off[i] = (uint32_t)(t.k0 + dr) * kss + pc16;
-            v_off[i] = (uint32_t)(t.k0 + dr) * vss + pc16;
-            k_last[i] = (uint32_t)(t.k0 + t.L - 1) * kss + pc16;
-            v_last[i] = (uint32_t)(t.k0 + t.L - 1) * vss + pc16;
-        }
+    const int dr = wave * RPI + lane / PPR;
+    const uint32_t kss = (uint32_t)(by_value.K.stride_s * 2), vss = (uint32_t)(by_value.V.stride_s * 2);
+    const uint32_t k_adv = G * kss, v_adv = G * vss;
+    const char *k_base, *v_base;
+    uint32_t k_off = 0, v_off = 0, k_last = 0, v_last = 0;
+    auto begin_k = [&](const FwdTile& t) {
+        k_base = t.k;
+        k_off = (uint32_t)(t.k0 + dr) * kss + pc16;
+        k_last = (uint32_t)(t.k0 + t.L - 1) * kss + pc16;
     };
-    // request the next group of a tensor into ring slot `slot`; every call advances the offsets by one group
-    auto request = [&](const char* base, uint32_t* off, const uint32_t* last, uint32_t adv, uint32_t ring0, int slot) {
-#pragma unroll
-        for (int i = 0; i < IPW; ++i) {
-            dma16(base, min(off[i], last[i]), ring0 + (uint32_t)(slot & (NR - 1)) * SLOT + (uint32_t)(wave * IPW + i) * TL::GP);
-            off[i] += adv;
-        }
+    auto begin_v = [&](const FwdTile& t) {
+        v_base = t.v;
+        v_off = (uint32_t)(t.k0 + dr) * vss + pc16;
+        v_last = (uint32_t)(t.k0 + t.L - 1) * vss + pc16;
     };
     // KVR: row numbers of groups x and x + 1 of tile t into ring `tb` (keys past the block's end repeat its last one)
-    auto dma_tokens = [&](const FwdTile& t, int x, int tb) {
+    auto request_row_numbers = [&](const FwdTile& t, int x, int tb) {
         dma4(reinterpret_cast<const char*>(kv_rows), (uint32_t)(t.k0 + min(x * G + lane, t.L - 1)) << 2,
-             sTok0 + (uint32_t)(tb * TOKS + (x & 15) * G) * 4);
+             lds0 + TOK0 + (uint32_t)(tb * TOKS + (x & 15) * G) * 4);
     };
-    auto dma_first_tokens = [&](const FwdTile& t, int tb) {          // groups 0..7, two per wavefront
-        if (wave < 4) dma_tokens(t, 2 * wave, tb);
-    };
-    // KVR: row of K and V that request i of this wavefront fetches for this lane in group x of the tile of ring `tb`
-    auto row_number = [&](int x, int i, int tb) { return (uint32_t)sTok[tb * TOKS + (x & 15) * G + (wave * IPW + i) * RPI + lane / PPR]; };
-    auto request_row = [&](const char* base, uint32_t stride, uint32_t row, int i, uint32_t ring0, int slot) {
-        dma_row16<0>(base, row, stride, pc16, ring0 + (uint32_t)(slot & (NR - 1)) * SLOT + (uint32_t)(wave * IPW + i) * TL::GP);
-    };
-    uint32_t krow[IPW], vrow[IPW];         // KVR: rows of the next request of K and of V, read from the ring a step before
-    int kb = 0, vb = 0;                    // running group counters: group x of the current tile uses slot (kb + x) & 3 / (vb + x) & 3
-    int tp = 0;                            // KVR: table that holds the current tile's row numbers
-    auto request_first_groups = [&](const FwdTile& t, int kb_t, int vb_t, int tb) {     // K(0..3), V(0..1) of tile t
-        if constexpr (KVR) {
-            uint32_t r[4][IPW];
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int i = 0; i < IPW; ++i) r[x][i] = row_number(x, i, tb);
-#pragma unroll
-            for (int i = 0; i < IPW; ++i) { krow[i] = row_number(4, i, tb); vrow[i] = r[2][i]; }
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int i = 0; i < IPW; ++i) request_row(t.kbase, kss, r[x][i], i, sK0, kb_t + x);
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int i = 0; i < IPW; ++i) request_row(t.vbase, vss, r[x][i], i, sV0, vb_t + x);
-        } else {
-            first_offsets(t);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) request(t.kbase, k_off, k_last, k_adv, sK0, kb_t + x);
-#pragma unroll
-            for (int x = 0; x < 2; ++x) request(t.vbase, v_off, v_last, v_adv, sV0, vb_t + x);
-        }
-    };
+    // groups 0..7, two per wavefront (with eight wavefronts, by two each: all issue the same number of requests)
+    auto request_first_row_numbers = [&](const FwdTile& t, int tb) { request_row_numbers(t, 2 * (wave & 3), tb); };
+    // KVR: row of K and V that this lane requests of group x of the tile of ring `tb`
+    auto row_number = [&](int x, int tb) { return (uint32_t) reinterpret_cast<const int*>(smem + TOK0)[tb * TOKS + (x & 15) * G + dr]; };
+    uint32_t krow = 0, vrow = 0;           // KVR: rows of the next request of K and of V, read from the ring a step before
 
     uint32_t rlane[TL::NRB], tlane[2][TL::NTB];
 #pragma unroll
@@ -250,220 +261,258 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int dt = 0; dt < TL::NTB; ++dt) tlane[t][dt] = TL::tr_lane(lane, t, dt);
-    auto readK = [&](int x, int ks) { return TL::rows(sK, rlane, (uint32_t)((kb + x) & (NR - 1)) * SLOT, ks); };
+        for (int dt = 0; dt < TL::NTB; ++dt) tlane[t][dt] = V0 + TL::tr_lane(lane, t, dt);
+    // Ring offsets of the slots n, n + 1, n + 2, n + 3 of the step n to come: they change places every step.
+    uint32_t r0 = 0, r1 = SLOT, r2 = 2 * SLOT, r3 = 3 * SLOT;
+    auto readK = [&](uint32_t off, int ks) { return TL::rows(smem, rlane, off, ks); };
     // transposed operand: channel tile dt = u % DT, 16-row step s = u / DT
-    auto readV = [&](int x, int u) { return TL::transposed(sV, tlane, (uint32_t)((vb + x) & (NR - 1)) * SLOT, u / DT, u % DT); };
+    auto readV = [&](uint32_t off, int u) { return TL::transposed(smem, tlane, off, u / DT, u % DT); };
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-    FwdTile cur = decode(flat_desc[f]);
-    load_q(cur, query_of(cur));
-    if constexpr (KVR) {                   // the first tile's row numbers: nothing to overlap them with
-        dma_first_tokens(cur, 0);
+    // ---- the first tile's rows: nothing to overlap them with
+    int f_next = f0 + 3 * f_step;
+    FwdTile none{};
+    none.bh = -1;
+    FwdTile cur = tile_at(f0, none), nxt = tile_at(min(f0 + f_step, f_last), cur), nn = tile_at(min(f0 + 2 * f_step, f_last), nxt);
+    long long out_pair = 0;                // first pair and last entry of the tile before `cur`
+    int out_last = -1;                     // -1: there is none
+    int par = 0, tp = 0;                   // list-entry ring half and row-number ring of `cur`
+    request_entries(cur, 0);
+    request_entries(nxt, 1);
+    if constexpr (KVR) {
+        request_first_row_numbers(cur, 0);
+        request_first_row_numbers(nxt, 1);
         VMOBA_WAIT_VMCNT(0);
         __syncthreads();
     }
-    request_first_groups(cur, kb, vb, 0);
-
-    for (;;) {
-        const int fn = f + f_step;
-        const bool has_next = fn < f_end;
-        const int4 nd = flat_desc[has_next ? fn : f];   // without a next tile the look-ahead repeats this one (loads only)
-        const int L = cur.L;
-        const int Gt = (L + G - 1) / G;
-        // A tile has Ge >= 2 steps with a soft-max (a block of one group gets a second, fully masked one) and
-        // Ge - 2 of them are "middle" steps.  The two register sets swap roles every step; the set that starts is
-        // chosen so that the last soft-max step always finds S^T in sB and P(g-1) in pA.
-        const int Ge = max(Gt, 2);
-        const int n_mid = Ge - 2;
-        const bool odd = n_mid & 1;
-
-        f32x16_t oacc[DT];
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) oacc[dt] = zero16;
-        float m_run = -INFINITY, l_run = 0.f;      // l_run: this lane half's share of the row sum
-        bf16x8_t opK[4], opV[4];                    // operands of units u .. u + 2, slot = unit % 4
-        f32x16_t sA = zero16, sB = zero16;
-        bf16x8_t pA[2], pB[2];
-
-        VMOBA_WAIT_VMCNT(0);                       // this wavefront's K(0..3), V(0..1) (and Q rows) have landed
-        __syncthreads();                           // ... and everybody else's
-        if constexpr (NEG) {
-#pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(u32x4_t, qf[ks]) ^ 0x80008000u);
-        }
-        // S^T(0), and the operands of the first two units of step 0
-        if (odd) {
-#pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(readK(0, ks), qf[ks], sB, 0, 0, 0);
+    begin_k(cur);
+    begin_v(cur);
+    static_for<4>([&](auto x) {
+        constexpr int X = decltype(x)::value;
+        if constexpr (KVR) {
+            dma_row16<X * SLOT>(k_base, row_number(X, 0), kss, pc16, lds_rows);
+            if constexpr (X < 2) dma_row16<V0 + X * SLOT>(v_base, row_number(X, 0), vss, pc16, lds_rows);
         } else {
-#pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(readK(0, ks), qf[ks], sA, 0, 0, 0);
+            dma16_advance(k_base, min(k_off, k_last), k_off, k_adv, lds_rows, X * SLOT);
+            if constexpr (X < 2) dma16_advance(v_base, min(v_off, v_last), v_off, v_adv, lds_rows, V0 + X * SLOT);
         }
-        opK[0] = readK(1, 0);
-        opK[1] = readK(1, 1);
-        opV[0] = opK[0];
-        opV[1] = opK[1];
-        const FwdTile nxt = decode(nd);
-        const int nq = query_of(nxt);              // needed a tile later: the load has the whole tile to land
-
-        // one pipeline step; the flags are compile-time: QK / PV = the step has a first / second product, SM = it has a
-        // soft-max (MASK: with the keys past the block's end masked), NEXTPV = the next step has a second product,
-        // STAGE = it requests rows
-        auto step = [&](int g, auto qk_t, auto pv_t, auto sm_t, auto mask_t, auto nextpv_t, auto stage_t, f32x16_t& s_cur,
-                        f32x16_t& s_nxt, bf16x8_t(&p_new)[2], bf16x8_t(&p_prev)[2]) {
-            constexpr bool QK = decltype(qk_t)::value, PV = decltype(pv_t)::value, SM = decltype(sm_t)::value;
-            constexpr bool MASK = decltype(mask_t)::value, NEXTPV = decltype(nextpv_t)::value, STAGE = decltype(stage_t)::value;
-            constexpr bool LAST_SM = SM && !QK;       // the first product is complete: Q^T may be replaced
-            if constexpr (STAGE) { VMOBA_WAIT_VMCNT(NDMA); __syncthreads(); }
-            if constexpr (LAST_SM) { VMOBA_WAIT_VMCNT(0); __syncthreads(); }
-            uint32_t w[8];                            // P of this step as packed bf16 pairs (accumulator values 2j, 2j + 1)
-            float m_new = m_run, alpha = 1.f;
-            bool raise = false;
+    });
+    VMOBA_WAIT_VMCNT(6);                   // the list entries are here
+    request_queries(cur, 0);
+    VMOBA_WAIT_VMCNT(0);
+    __syncthreads();
 #pragma unroll
-            for (int u = 0; u < UNITS; ++u) {
-                const int u2 = u + 2;
-                bf16x8_t nk = opK[u2 & 3], nv = opV[u2 & 3];
-                if (u2 < UNITS) {
-                    if constexpr (QK) nk = readK(g + 1, u2);
-                    if constexpr (PV) nv = readV(g - 1, u2);
-                } else {
-                    if constexpr (QK) nk = readK(g + 2, u2 - UNITS);
-                    if constexpr (NEXTPV) nv = readV(g, u2 - UNITS);
-                }
-                if constexpr (QK) s_nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(opK[u & 3], qf[u], u == 0 ? zero16 : s_nxt, 0, 0, 0);
-                if constexpr (PV) oacc[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(opV[u & 3], p_prev[u / DT], oacc[u % DT], 0, 0, 0);
-                if constexpr (SM) {
-                    if (u == 0) {
-                        if constexpr (MASK) {
-                            const int vh = L - g * G - hf;          // accumulator value i is key row acc_row(i, 0) + hf
+    for (int ks = 0; ks < KSTEPS; ++ks) read_query(ks);
+    f32x16_t oacc[DT];
 #pragma unroll
-                            for (int i = 0; i < 16; ++i)
-                                if (acc_row(i, 0) >= vh) s_cur[i] = -INFINITY;
-                        }
-                        float mx = fmaxf(s_cur[0], s_cur[1]);
+    for (int dt = 0; dt < DT; ++dt) oacc[dt] = zero16;
+    float m_run = 0.f, l_run = 0.f, limit = 0.f, m_out = 0.f, l_out = 0.f;      // l: this lane half's share of the row sum; _out: of the tile before
+    bf16x8_t opK[4], opV[4];                    // operands of units u .. u + 2, slot = unit % 4
+    f32x16_t sA = zero16, sB = zero16;
+    const bf16x8_t p_none = __builtin_bit_cast(bf16x8_t, u32x4_t{0u, 0u, 0u, 0u});
+    bf16x8_t pA[2] = {p_none, p_none}, pB[2] = {p_none, p_none};
 #pragma unroll
-                        for (int i = 2; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s_cur[i]), s_cur[i + 1]);
-                        mx = swap_halves_max(mx * scale_log2);            // scale_log2 > 0
-                        raise = mx > m_run + LAZY;
-                        m_new = raise ? mx : m_run;
-                        alpha = raise ? exp2_raw(m_run - m_new) : 1.f;
-                        m_run = m_new;
-                        l_run *= alpha;
-                    } else {
-                        // the 8 value pairs are spread over units 1 .. UNITS - 1; a pair is packed as soon as it exists
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            if (1 + (j * (UNITS - 1)) / 8 == u) {
-                                const float p0 = exp2_raw(fmaf(s_cur[2 * j], scale_log2, -m_new));
-                                const float p1 = exp2_raw(fmaf(s_cur[2 * j + 1], scale_log2, -m_new));
-                                l_run += p0 + p1;
-                                w[j] = pack_bf16x2(p0, p1);
-                                asm volatile("" : "+v"(w[j]));     // keeps the pair in this unit (it is only read a step later)
-                            }
-                        }
-                        asm volatile("" : "+v"(l_run));
-                        if (u == UNITS - 1) {
-                            const u32x4_t lo = {w[0], w[1], w[2], w[3]}, hi = {w[4], w[5], w[6], w[7]};
-                            __builtin_memcpy(&p_new[0], &lo, 16);
-                            __builtin_memcpy(&p_new[1], &hi, 16);
-                        }
-                    }
-                }
-                if constexpr (STAGE) {
-                    if (u == 1) {
-                        if constexpr (KVR) {
-                            // the next tile's row numbers go first: they are then older than this step's other requests and
-                            // have landed when the next step's wait lets only those stay in flight
-                            if (g == 0) dma_first_tokens(nxt, tp ^ 1);
-#pragma unroll
-                            for (int i = 0; i < IPW; ++i) {
-                                request_row(cur.kbase, kss, krow[i], i, sK0, kb + g + 4);
-                                request_row(cur.vbase, vss, vrow[i], i, sV0, vb + g + 2);
-                                krow[i] = row_number(g + 5, i, tp);       // for the next step
-                                vrow[i] = row_number(g + 3, i, tp);
-                            }
-                            // every wavefront by itself: its row numbers then need no barrier and all waits the same count
-                            dma_tokens(cur, g + 8, tp);
-                        } else {
-                            request(cur.kbase, k_off, k_last, k_adv, sK0, kb + g + 4);
-                            request(cur.vbase, v_off, v_last, v_adv, sV0, vb + g + 2);
-                        }
-                    }
-                }
-                if constexpr (LAST_SM) {
-                    // the next tile's query rows (Q^T is free: the first product is complete) and its first key groups (all K
-                    // slots are free, the two V slots after the current tile's last two as well): two steps ahead of their use
-                    if (u == 1) {
-                        load_q(nxt, nq);
-                        request_first_groups(nxt, kb + g + 1, vb + g + 1, tp ^ 1);
-                    }
-                }
-                opK[u2 & 3] = nk;
-                opV[u2 & 3] = nv;
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (PV && SM) {                 // the accumulator holds groups <= g - 1, all relative to the old maximum
-                if (__builtin_amdgcn_ballot_w64(raise)) {
-#pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
-                }
-            }
-        };
-        using T = std::true_type;
-        using F = std::false_type;
-        //   (g,  QK,  PV,  SM,  MASK, NEXTPV, STAGE, S^T(g), S^T(g+1), P(g), P(g-1))
-        int g = 1;
-        if (odd) {
-            step(0, T{}, F{}, T{}, T{}, T{}, T{}, sB, sA, pB, pA);
-            step(1, T{}, T{}, T{}, F{}, T{}, T{}, sA, sB, pA, pB);
-            g = 2;
-        } else {
-            step(0, T{}, F{}, T{}, T{}, T{}, T{}, sA, sB, pA, pB);
-        }
-        for (int it = 0; it < (n_mid >> 1); ++it) {
-            step(g, T{}, T{}, T{}, F{}, T{}, T{}, sB, sA, pB, pA);
-            step(g + 1, T{}, T{}, T{}, F{}, T{}, T{}, sA, sB, pA, pB);
-            g += 2;
-        }
-        step(g, F{}, T{}, T{}, T{}, T{}, F{}, sB, sA, pB, pA);          // g = Ge - 1: last soft-max
-        step(g + 1, F{}, T{}, F{}, F{}, F{}, F{}, sA, sB, pA, pB);      // final step (g + 1 = Ge): second product of group Ge - 1
-
-        // ---- partial output: O^T value i of tile dt <-> channel 32*dt + 8*(i>>2) + 4*hf + (i&3)
-        const float l_tot = swap_halves_sum(l_run);
-        {
-            const float inv = 1.f / l_tot;
-            char* mine = sOut + wave * 32 * OPITCH;                               // this wavefront's rows only: no barrier
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    u32x2_t v;
-                    v.x = pack_bf16x2(oacc[dt][4 * gq + 0] * inv, oacc[dt][4 * gq + 1] * inv);
-                    v.y = pack_bf16x2(oacc[dt][4 * gq + 2] * inv, oacc[dt][4 * gq + 3] * inv);
-                    *reinterpret_cast<u32x2_t*>(mine + l32 * OPITCH + (dt * 32 + gq * 8 + hf * 4) * 2) = v;
-                }
-            // the tile's partials are consecutive rows of Opart (bfloat16): row = first pair of the tile + entry
-            char* dst = reinterpret_cast<char*>(Opart) + (cur.seg + cur.list0) * (long long)(D * 2);
-            constexpr int LPR = D * 2 / 16;                                       // lanes per row
-#pragma unroll
-            for (int k = 0; k < 32 * LPR / 64; ++k) {
-                const int row = k * (64 / LPR) + lane / LPR, piece = lane % LPR;
-                const u32x4_t x = *reinterpret_cast<const u32x4_t*>(mine + row * OPITCH + piece * 16);
-                const int e = wave * 32 + row;
-                if (e < cur.count) *reinterpret_cast<u32x4_t*>(dst + (long long)e * (D * 2) + piece * 16) = x;
-            }
-            if (ent < cur.count && hf == 0) lse_part[cur.seg + cur.list0 + ent] = (m_run + log2f(l_tot)) * LN2;
-        }
-        if (!has_next) break;
-        f = fn;
-        cur = nxt;
-        kb += Ge;
-        vb += Ge;
-        tp ^= 1;
+    for (int ks = 0; ks < KSTEPS; ++ks) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(readK(0, ks), qf[ks], sA, 0, 0, 0);
+    opK[0] = readK(SLOT, 0);
+    opK[1] = readK(SLOT, 1);
+    opV[0] = opK[0];                            // (the first step's second product is thrown away)
+    opV[1] = opK[1];
+    int g = 0, Ge = groups_of(cur);             // group of `cur` and the number of them
+    if constexpr (KVR) {
+        krow = Ge > 4 ? row_number(4, 0) : row_number(0, 1);
+        vrow = row_number(2, 0);
     }
+
+    enum { FIRST, SECOND, THIRD, MIDDLE, BEFORE_LAST, LAST };
+    // One step; which of the tile's it is, is compile-time.
+    auto step = [&](auto which, f32x16_t& s_cur, f32x16_t& s_nxt, bf16x8_t(&p_new)[2], bf16x8_t(&p_prev)[2]) __attribute__((always_inline)) {
+        constexpr int WHICH = decltype(which)::value;
+        if constexpr (WHICH == SECOND || WHICH == THIRD) VMOBA_WAIT_VMCNT(N_STEP + N_FIRST);       // the first step's rows are older than its other requests
+        else VMOBA_WAIT_VMCNT(N_STEP);
+        asm volatile("s_barrier" ::: "memory");
+        if constexpr (WHICH != THIRD && WHICH != MIDDLE) {
+            if (__builtin_expect((g + 1) * G > cur.L, WHICH == LAST)) {     // keys past the block's end; accumulator value i is key row acc_row(i, 0) + hf
+                const int vh = cur.L - g * G - hf;
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (acc_row(i, 0) >= vh) s_cur[i] = -INFINITY;
+            }
+        }
+        float alpha = 1.f;
+        int raised = 0;                         // (opaque: otherwise the comparison is kept instead)
+        asm volatile("" : "+s"(raised));
+        uint32_t w[8];                          // P of this step as packed bf16 pairs (accumulator values 2j, 2j + 1)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            const int u2 = u + 2;
+            const bf16x8_t nk = u2 < UNITS ? readK(r1, u2) : readK(r2, u2 - UNITS);
+            const bf16x8_t nv = u2 < UNITS ? readV(r3, u2) : readV(r0, u2 - UNITS);
+            s_nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(opK[u & 3], qf[u], u == 0 ? zero16 : s_nxt, 0, 0, 0);
+            // (the tile's second step begins its second product)
+            oacc[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(opV[u & 3], p_prev[u / DT], WHICH == SECOND && u < DT ? zero16 : oacc[u % DT], 0, 0, 0);
+            if constexpr (WHICH == BEFORE_LAST) read_query(u);      // the next step's first product is the next tile's first
+            if (u == 0) {
+                float mx = fmaxf(s_cur[0], s_cur[1]);
+#pragma unroll
+                for (int i = 2; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s_cur[i]), s_cur[i + 1]);
+                if constexpr (WHICH == FIRST) {
+                    m_out = m_run;
+                    l_out = l_run;
+                    mx = swap_halves_max(mx);
+                    m_run = mx * scale_log2;                         // scale_log2 > 0
+                    limit = mx + lazy;
+                    l_run = 0.f;
+                } else if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > limit) != 0, 0)) {      // some row's new maximum passes its limit
+                    asm volatile("" : "+v"(mx));
+                    mx = swap_halves_max(mx);
+                    const float m_new = mx > limit ? mx * scale_log2 : m_run;
+                    alpha = exp2_raw(m_run - m_new);
+                    limit = mx > limit ? mx + lazy : limit;
+                    m_run = m_new;
+                    l_run *= alpha;
+                    raised = 1;
+                }
+            }
+            // 8 value pairs over the other units; a pair is packed as soon as it exists
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (1 + j * (UNITS - 1) / 8 == u) {
+                    const float p0 = exp2_raw(fmaf(s_cur[2 * j], scale_log2, -m_run));
+                    const float p1 = exp2_raw(fmaf(s_cur[2 * j + 1], scale_log2, -m_run));
+                    l_run += p0 + p1;
+                    w[j] = pack_bf16x2(p0, p1);
+                    asm volatile("" : "+v"(w[j]));  // keeps the pair in this unit (it is only read a step later)
+                }
+            }
+            asm volatile("" : "+v"(l_run));
+            if (u == 1) {
+                // K(n+4) into the slot of K(n), V(n+2) into that of V(n-2)
+                if constexpr (WHICH < BEFORE_LAST) {
+                    if (__builtin_expect(g == Ge - 4, 0)) begin_k(nxt);
+                } else if constexpr (WHICH == BEFORE_LAST) {
+                    begin_v(nxt);
+                }
+                if constexpr (KVR) {
+                    const int tn = tp == 2 ? 0 : tp + 1;
+                    dma_row16<0>(k_base, krow, kss, pc16, lds_rows + r0);
+                    dma_row16<V0>(v_base, vrow, vss, pc16, lds_rows + r2);
+                    // for the next step (after the last one: group 4 of the next tile or, if that has no more than four, the first of the one behind it)
+                    if (WHICH == LAST && groups_of(nxt) == 4) krow = row_number(0, tp == 0 ? 2 : tp - 1);
+                    else krow = g + 5 < Ge ? row_number(g + 5, tp) : row_number(g + 5 - Ge, tn);
+                    vrow = g + 3 < Ge ? row_number(g + 3, tp) : row_number(g + 3 - Ge, tn);
+                    // every wavefront by itself: its row numbers then need no barrier and all waits the same count
+                    request_row_numbers(cur, g + 8, tp);
+                } else {
+                    dma16_advance(k_base, min(k_off, k_last), k_off, k_adv, lds_rows, r0);
+                    dma16_advance(v_base, min(v_off, v_last), v_off, v_adv, lds_rows + V0, r2);
+                }
+            }
+            opK[u2 & 3] = nk;
+            opV[u2 & 3] = nv;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (WHICH != FIRST) {
+            if (__builtin_expect(raised, 0)) {  // the accumulator holds groups <= g - 1, all relative to the old maximum
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[dt][i] *= alpha;
+            }
+        }
+        const u32x4_t lo = {w[0], w[1], w[2], w[3]}, hi = {w[4], w[5], w[6], w[7]};
+        p_new[0] = __builtin_bit_cast(bf16x8_t, lo);
+        p_new[1] = __builtin_bit_cast(bf16x8_t, hi);
+        const uint32_t r = r0;
+        r0 = r1;
+        r1 = r2;
+        r2 = r3;
+        r3 = r;
+        ++g;
+    };
+    // Partial rows of the tile before: O^T value i of tile dt <-> channel 32*dt + 8*(i>>2) + 4*hf + (i&3)
+    auto write_partials = [&]() {
+        const float l_tot = swap_halves_sum(l_out);
+        const float inv = 1.f / l_tot;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+                u32x2_t v;
+                v.x = pack_bf16x2(oacc[dt][4 * gq + 0] * inv, oacc[dt][4 * gq + 1] * inv);
+                v.y = pack_bf16x2(oacc[dt][4 * gq + 2] * inv, oacc[dt][4 * gq + 3] * inv);
+                *reinterpret_cast<u32x2_t*>(mine + l32 * OPITCH + (dt * 32 + gq * 8 + hf * 4) * 2) = v;
+            }
+        // the tile's partials are consecutive rows of Opart (bfloat16): row = first pair of the tile + entry
+        const auto a = args();
+        constexpr int LPR = D * 2 / 16;                                       // lanes per row
+        char* dst = reinterpret_cast<char*>(a->Opart) + out_pair * (D * 2) + lane % LPR * 16;
+        const int row0 = wave * 32 + lane / LPR;
+        u32x4_t x[32 * LPR / 64];
+#pragma unroll
+        for (int k = 0; k < 32 * LPR / 64; ++k) x[k] = *reinterpret_cast<const u32x4_t*>(mine + (k * (64 / LPR) + lane / LPR) * OPITCH + lane % LPR * 16);
+        if (__builtin_expect(wave * 32 + 31 <= out_last, 1)) {
+#pragma unroll
+            for (int k = 0; k < 32 * LPR / 64; ++k) *reinterpret_cast<u32x4_t*>(dst + (row0 + k * (64 / LPR)) * (D * 2)) = x[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < 32 * LPR / 64; ++k) *reinterpret_cast<u32x4_t*>(dst + min(row0 + k * (64 / LPR), out_last) * (D * 2)) = x[k];
+        }
+        a->lse_part[out_pair + min(wave * 32 + l32, out_last)] = (m_out + log2f(l_tot)) * LN2;
+    };
+    using First = std::integral_constant<int, FIRST>;
+    using Second = std::integral_constant<int, SECOND>;
+    using Third = std::integral_constant<int, THIRD>;
+    using Middle = std::integral_constant<int, MIDDLE>;
+    using BeforeLast = std::integral_constant<int, BEFORE_LAST>;
+    using Last = std::integral_constant<int, LAST>;
+    for (;;) {
+        step(First{}, sA, sB, pB, pA);
+        if constexpr (KVR) request_first_row_numbers(nn, tp == 0 ? 2 : tp - 1);
+        if (__builtin_expect(out_last >= 0, 1)) write_partials();
+        request_descriptor(f_next);
+        request_entries(nn, par);
+        request_queries(nxt, par ^ 1);
+        if (__builtin_expect(out_last < 0, 0)) VMOBA_WAIT_VMCNT(0);          // (no partial rows: the waits would count too few)
+        step(Second{}, sB, sA, pA, pB);
+        if (Ge > 4) {
+            step(Third{}, sA, sB, pB, pA);
+            while (g < Ge - 3) {                // the steps come in pairs that swap the two register sets
+                step(Middle{}, sB, sA, pA, pB);
+                step(Middle{}, sA, sB, pB, pA);
+            }
+            if (g < Ge - 2) {
+                step(Middle{}, sB, sA, pA, pB);
+            } else {
+                sA = sB;
+                pA[0] = pB[0];
+                pA[1] = pB[1];
+            }
+        }
+        step(BeforeLast{}, sA, sB, pB, pA);
+        step(Last{}, sB, sA, pA, pB);
+        out_pair = cur.pair;
+        out_last = cur.count - 1;
+        if (--tiles_left == 0) break;
+        const u32x4_t d = *reinterpret_cast<const u32x4_t*>(smem + DESC0 + wave * 256);
+        cur = nxt;
+        nxt = nn;
+        nn = make_tile(make_int4(__builtin_amdgcn_readfirstlane((int)d.x), __builtin_amdgcn_readfirstlane((int)d.y),
+                                 __builtin_amdgcn_readfirstlane((int)d.z), __builtin_amdgcn_readfirstlane((int)d.w)), nxt);
+        f_next += f_step;
+        g = 0;
+        Ge = groups_of(cur);
+        par ^= 1;
+        tp = tp == 2 ? 0 : tp + 1;
+    }
+    // second product of the last tile's last group
+    VMOBA_WAIT_VMCNT(0);                   // (no request may reach LDS that belongs to another workgroup by the kernel's end, either)
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) oacc[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(readV(r3, u), pA[u / DT], oacc[u % DT], 0, 0, 0);
+    m_out = m_run;
+    l_out = l_run;
+    write_partials();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -670,8 +719,9 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         // the kernel's running maximum and its mask of the keys past a block's end need a positive scale: the sign goes to Q, and the
         // smallest normal number does for 0 (it leaves every weight at 1)
         const float magnitude = std::max(std::fabs(scale_log2), FLT_MIN);
+        const int q_offsets_32 = S < (1 << 24) && Qp->stride_s > 0 && Qp->stride_s * 2 < (1 << 24) && (uint64_t)S * (uint64_t)Qp->stride_s * 2 < ((uint64_t)1 << 32);
         const dim3 pgrid((unsigned)std::min<int64_t>((wide ? 1 : 2) * (int64_t)vmoba_num_cus(), (int64_t)BH * max_tiles));
-#define MFMA_ARGS Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, magnitude, kv_rows
+#define MFMA_ARGS FwdArgs{Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles, ws.Opart, ws.lse_part, (long long)nnz_capacity, kv_rows, Hh, magnitude, q_offsets_32}
 #define LAUNCH_FWD(NEG)                                                                                                       \
     do {                                                                                                                      \
         if (wide && kv_rows) attn_fwd_tile_mfma_kernel<128, 8, true, NEG><<<pgrid, dim3(512), 0, st>>>(MFMA_ARGS);            \

@@ -110,6 +110,36 @@ def test_bf16_kernels_take_a_scale_of_any_sign(scale, D):
         check_heads(f"bf16-scale-{scale}-{chunk}-{D}", g, Q, K, V, dO, range(heads), scale, torch.bfloat16)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [20, 96, 97, 160, 161, 224, 300])
+def test_bf16_forward_over_many_tiles(chunk, D):
+    """Every workgroup of the forward tile kernel walks several tiles of several heads (64 heads x 400 queries): blocks of one to ten key groups --
+    as many as a tile counts at least, fewer, an odd and an even number, the last one whole or not -- beside a shorter one at the end, lists that end inside
+    a tile, scores so far apart that the running maximum rises often; keys rearranged and in place."""
+    grid, S, heads = (1, 8, 50), 400, 64
+    Q, K, V = (synth.to_bf16_grid(synth.iid_normal(1060 + i, (1, S, heads, D))) for i in range(3))
+    for scale, tau, kv_in_place in ((None, 0.7, True), (0.5, 1.0, False)):
+        g = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), chunk, tau, torch.bfloat16, softmax_scale=scale, kv_in_place=kv_in_place)
+        for h in (0, 31, 63):
+            q, k, v = (x[0, g["perm"], h].astype(np.float64) for x in (Q, K, V))
+            O, LSE = vo.masked_attention_fwd(q, k, v, g["mask"][0, h], g["blk_off"], 1.0 / math.sqrt(D) if scale is None else scale)
+            live = np.isfinite(LSE)
+            gu.check_output(f"bf16-tiles-{chunk}-{D}", "LSE", g["LSE"][0, h][live], LSE[live], torch.bfloat16)
+            gu.check_output(f"bf16-tiles-{chunk}-{D}", "O", g["Op"][0, h], O, torch.bfloat16)
+
+
+def test_bf16_forward_takes_query_rows_far_apart():
+    """Rows of Q 16 MB and more apart (their offsets do not fit 32 bits) give the same bits as rows that are neighbours."""
+    grid, S, D, pitch = (1, 8, 40), 320, 128, (1 << 23) + 8
+    Q, K, V = (gu.to_dev(synth.to_bf16_grid(synth.iid_normal(1070 + i, (1, S, 1, D))), torch.bfloat16) for i in range(3))
+    wide = torch.empty((S - 1) * pitch + D, dtype=torch.bfloat16, device="cuda").as_strided((1, S, 1, D), (S * pitch, pitch, D, 1))
+    wide.copy_(Q)
+    plan = vb.LayerPlan(1, 1, D, grid, chunk=64, tau=0.7, dtype=torch.bfloat16, need_bwd=False, q_in_place=True)
+    O = [plan.forward(q, K, V).clone() for q in (Q, wide)]
+    torch.cuda.synchronize()
+    assert torch.equal(*O) and float(O[0].float().abs().max()) > 0
+
+
 def test_f32_split_kernels_hand_infinities_to_the_float32_ones():
     """An infinity has no terms to split into: an infinite channel of one value row makes that channel of every query that keeps the key
     infinite (NaN where the merge meets it again with weight 0), and nothing else, as it does in a call of any size."""
