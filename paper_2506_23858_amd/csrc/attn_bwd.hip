@@ -68,9 +68,15 @@ __device__ __forceinline__ void delta_rows(const TensorView& O, const TensorView
 // order: the short ones fill the tail of the launch): kb_order[r] = block at rank r,
 // kb_start[r] = number of runs of the blocks at ranks 0..r-1.
 // A last run of at most tail_max keys is not counted: the tail body takes those keys.
-struct KeyRunLds { int cnt[VMOBA_MAX_BLOCKS]; int runs[VMOBA_MAX_BLOCKS]; int wave[4]; };
+// slot_desc (bfloat16, instead of the other two): what the workgroup of a head's slot has to do, so that it learns it with one load and not
+// with a search (it begins alone on its compute unit; search and look-ups took 7000 of the 30 000 cycles it spent outside its loop,
+// beside 75 000 to 450 000 in it): {first key position, keys from there to the block's end, first list entry, list length}; slots past the
+// runs are the blocks' tails, with TAIL_SLOT added to the number of keys; 0 keys: nothing.
+constexpr int TAIL_SLOT = 1 << 30;
+struct KeyRunLds { int cnt[VMOBA_MAX_BLOCKS]; int runs[VMOBA_MAX_BLOCKS]; int order[VMOBA_MAX_BLOCKS]; int start[VMOBA_MAX_BLOCKS]; int wave[4]; };
 __device__ __forceinline__ void write_key_runs(KeyRunLds& lds, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr,
-                                               int* __restrict__ kb_start, int* __restrict__ kb_order, int bh, int nb, int KPW, int tail_max) {
+                                               int* __restrict__ kb_start, int* __restrict__ kb_order, int4* __restrict__ slot_desc, int slots, int bh, int nb,
+                                               int KPW, int tail_max) {
     const int t = threadIdx.x;
     const int* bp = blk_ptr + (long long)bh * (nb + 1);
     for (int j = t; j < nb; j += 256) lds.cnt[j] = bp[j + 1] - bp[j];
@@ -79,7 +85,8 @@ __device__ __forceinline__ void write_key_runs(KeyRunLds& lds, const int* __rest
         const int cnt = lds.cnt[j];
         int rank = 0;
         for (int i = 0; i < nb; ++i) rank += (lds.cnt[i] > cnt || (lds.cnt[i] == cnt && i < j)) ? 1 : 0;
-        kb_order[(long long)bh * nb + rank] = j;
+        if (slot_desc) lds.order[rank] = j;
+        else kb_order[(long long)bh * nb + rank] = j;
         const int L = blk_off[j + 1] - blk_off[j];
         const int tail = L % KPW;
         lds.runs[rank] = (tail > 0 && tail <= tail_max) ? L / KPW : (L + KPW - 1) / KPW;
@@ -88,6 +95,30 @@ __device__ __forceinline__ void write_key_runs(KeyRunLds& lds, const int* __rest
     const int r0 = 2 * t < nb ? lds.runs[2 * t] : 0, r1 = 2 * t + 1 < nb ? lds.runs[2 * t + 1] : 0;
     int total;
     const int excl = block_exclusive_sum256(r0 + r1, lds.wave, &total);
+    if (slot_desc) {
+        if (2 * t < nb) lds.start[2 * t] = excl;
+        if (2 * t + 1 < nb) lds.start[2 * t + 1] = excl + r0;
+        __syncthreads();
+        for (int i = t; i < slots; i += 256) {
+            int4 d = make_int4(0, 0, 0, 0);
+            int lo = i - total;                // rank of the slot's block
+            if (i < total) {
+                int hi = nb;                   // largest rank with start[rank] <= i
+                lo = 0;
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (lds.start[mid] <= i) lo = mid; else hi = mid;
+                }
+            }
+            if (lo < nb) {
+                const int j = lds.order[lo], L = blk_off[j + 1] - blk_off[j], tail = L % KPW;
+                if (i < total) d = make_int4(blk_off[j] + (i - lds.start[lo]) * KPW, L - (i - lds.start[lo]) * KPW, bp[j], lds.cnt[j]);
+                else if (tail <= tail_max) d = make_int4(blk_off[j] + L - tail, tail ? tail + TAIL_SLOT : 0, bp[j], lds.cnt[j]);
+            }
+            slot_desc[(long long)bh * slots + i] = d;
+        }
+        return;
+    }
     int* out = kb_start + (long long)bh * (nb + 1);
     if (2 * t < nb) out[2 * t] = excl;
     if (2 * t + 1 < nb) out[2 * t + 1] = excl + r0;
@@ -98,8 +129,8 @@ template <bool BF16, int D>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorView dO, const float* __restrict__ LSE, float* __restrict__ delta, const int* __restrict__ rows,
                                                           char* __restrict__ dO_copy, const int* __restrict__ blk_ptr,
                                                           const int* __restrict__ blk_off, const int* __restrict__ head_tiles, int4* __restrict__ flat_desc, int* __restrict__ n_tiles,
-                                                          int* __restrict__ clear, int* __restrict__ kb_start, int* __restrict__ kb_order, int BH, int Hh, int S, int nb,
-                                                          int TM, int KPW, int tail_max, int n_delta) {
+                                                          int* __restrict__ clear, int* __restrict__ kb_start, int* __restrict__ kb_order, int4* __restrict__ slot_desc, int slots,
+                                                          int BH, int Hh, int S, int nb, int TM, int KPW, int tail_max, int n_delta) {
     __shared__ union { TileListLds tiles; KeyRunLds runs; } lds;
     const int bh = blockIdx.y, x = blockIdx.x;
     if (x < n_delta) delta_rows<BF16, D>(O, dO, LSE, delta, rows, dO_copy, bh, Hh, S, x);
@@ -108,7 +139,7 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorVi
         if (threadIdx.x < 2)
             delta[((long long)bh * 2 + threadIdx.x) * lse_delta_pitch(S) + S] = threadIdx.x == 0 ? INFINITY : 0.f;
         if (clear && bh == 0 && threadIdx.x == 2) *clear = 0;
-        write_key_runs(lds.runs, blk_off, blk_ptr, kb_start, kb_order, bh, nb, KPW, tail_max);
+        write_key_runs(lds.runs, blk_off, blk_ptr, kb_start, kb_order, BF16 ? slot_desc : nullptr, slots, bh, nb, KPW, tail_max);
     }
 }
 
@@ -345,7 +376,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 // for a transposed operand), not the matrix pipe.  So the 128 keys are held by two PAIRS of
 // wavefronts with 64 keys (two 32-key groups) each, and the two wavefronts of a pair split the products:
 //   wavefront 0 of the pair:  S  = Q  . K^T  ->  P = exp(S - LSE)  ->  dV^T += dO^T . P
-//   wavefront 1 of the pair:  dP = dO . V^T  ->  dS = P * (dP - delta)  ->  dK^T += Q^T . dS
+//   wavefront 1 of the pair:  dP - delta = dO . V^T - delta  ->  dS = P * (dP - delta)  ->  dK^T += Q^T . dS
 // so every operand fetched from LDS feeds two matrix instructions (one per key group), and each
 // wavefront keeps only one set of fragments (K or V) and one accumulator tile (dV^T or dK^T).
 // P travels from wavefront 0 to wavefront 1 as packed bf16 through a small LDS buffer (same lane,
@@ -354,6 +385,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 // Step hc of the workgroup, local step t = hc - (wavefront % 2), all interleaved:
 //   matrix:  S or dP of half-chunk t + 1,  dV or dK of half-chunk t - 1      vector: P or dS of t
 //   memory:  rows, LSE and delta of half-chunk hc + 5, list entries of half-chunk hc + 8, straight into LDS.
+// The rows are requested by wavefronts 1 alone: wavefronts 0 have the exponentials and were 200 of 1740 cycles behind at every barrier
+// (now 1650 cycles a step, 1024 of them matrix instructions; the clock is at 1.57 GHz then, 2.4 without load).  -delta is the value the sums for dP
+// start from: 32 additions a step less.  Backward calls of 14 040 tokens x 12 heads x 128 / 2 x 6601 x 16 x 64, with the slot descriptors
+// and the row-wise output: 737 / 540 -> 720 / 521 us; 480p, 1D / 2D / 3D: -1 / -1 / -2 %.
 //
 // Everything the walk reads goes from global memory to LDS without passing through registers (global_load_lds): rings of
 // eight half-chunks of Q and dO rows, of their LSE and delta (accumulator order) and of the list entries, from which a lane
@@ -404,13 +439,12 @@ __device__ __forceinline__ void acc_ready(f32x16_t (&d)[2][4]) {
 
 template <int D>
 __device__ __forceinline__ void dkv_pair_body(
-    char* smem, int bh, int run_id, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-    const float* __restrict__ lse_delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int* __restrict__ kb_start, const int* __restrict__ kb_order, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
-    const int* __restrict__ kv_rows, int Hh, int S, int nb, long long cap, float scale_log2, float scale) {
+    char* smem, int bh, const int4 desc, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+    const float* __restrict__ lse_delta, const int* __restrict__ q_idx, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
+    const int* __restrict__ kv_rows, int Hh, int S, long long cap, float scale_log2, float scale) {
     using TL = DkvLds<D>;
     constexpr int KSTEPS = D / 16, DT = D / 32, NST = KSTEPS;
-    constexpr int IPW = 32 / TL::RPI / 4;     // row requests per wavefront, tensor and half-chunk
+    constexpr int IPW = 32 / TL::RPI / 2;     // row requests per wavefront 1 of a pair, tensor and half-chunk
     constexpr int NS = TL::NS, HB = TL::HB, GP = TL::GP;
     constexpr int NU = 4 * NST, LEAD = 4;     // units per step; units without vector work
     static_assert(NST == 2 * DT && NST % 4 == 0, "one k-step and one (s, dt) step per step, operand ring of four");
@@ -419,33 +453,25 @@ __device__ __forceinline__ void dkv_pair_body(
     constexpr auto first_value = [](int n) { return n <= LEAD ? 0 : ((n - LEAD) * 32 + NU - LEAD - 1) / (NU - LEAD); };
 
     const int b = bh / Hh, h = bh % Hh;
-    const int* ks = kb_start + (long long)bh * (nb + 1);
-    int lo = 0, hi = nb;
-    while (hi - lo > 1) { int mid = (lo + hi) >> 1; if (ks[mid] <= run_id) lo = mid; else hi = mid; }
-    const int j = kb_order[(long long)bh * nb + lo], run = run_id - ks[lo];
-    const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
+    const int k0 = desc.x, L = desc.y;                  // first key position of the run, keys from there to the block's end
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pair = wave >> 1, role = wave & 1;
     const int l32 = lane & 31, hf = lane >> 5;
-    const int kbase = run * 128 + pair * 64;            // first key of the pair inside the block
+    const int kbase = pair * 64;                        // first key of the pair inside the run
     const bool pair_live = kbase < L;
-    const long long seg = (long long)bh * cap;
-    const int list0 = blk_ptr[(long long)bh * (nb + 1) + j];
-    const int cnt = blk_ptr[(long long)bh * (nb + 1) + j + 1] - list0;
+    const int cnt = desc.w;
+    const int* const list = q_idx + (long long)bh * cap + desc.z;
+    const int first_entry = cnt > 0 ? list[min(tid, cnt - 1)] : 0;       // requested before the fragments: the rows wait for it
 
     // fragments of the pair's keys: K rows for wavefront 0, V rows for wavefront 1 (B operands, key = lane % 32)
     bf16x8_t frag[2][KSTEPS];
-    int krow[2];
-    bool key_live[2];
     {
         const TensorView& src = role == 0 ? K : V;
 #pragma unroll
         for (int kg = 0; kg < 2; ++kg) {
-            const int kk = kbase + kg * 32 + l32;
-            key_live[kg] = kk < L;
-            krow[kg] = k0 + min(kk, L - 1);
-            const long long kin = kv_rows ? kv_rows[krow[kg]] : krow[kg];     // row of K / V that holds this key
+            const int krow = k0 + min(kbase + kg * 32 + l32, L - 1);
+            const long long kin = kv_rows ? kv_rows[krow] : krow;     // row of K / V that holds this key
             const char* sp = src.ptr + ((long long)b * src.stride_b + kin * src.stride_s + (long long)h * src.stride_h) * 2;
 #pragma unroll
             for (int ks = 0; ks < KSTEPS; ++ks) frag[kg][ks] = *reinterpret_cast<const bf16x8_t*>(sp + (ks * 16 + hf * 8) * 2);
@@ -464,7 +490,6 @@ __device__ __forceinline__ void dkv_pair_body(
         const char* dobase = dO.ptr + ((long long)b * dO.stride_b + (long long)h * dO.stride_h) * 2;
         // row strides in bytes: below 2^24 and rows below 2^24, so a row's offset is one 24-bit multiply (host-checked)
         const uint32_t qss = (uint32_t)(Q.stride_s * 2), doss = (uint32_t)(dO.stride_s * 2);
-        const int* list = q_idx + seg + list0;
         const uint32_t SP = (uint32_t)lse_delta_pitch(S);
         const char* ld_base = reinterpret_cast<const char*>(lse_delta + (long long)bh * 2 * SP);
         const int H = (cnt + 63) / 64 * 2;                  // half-chunks, an even number (see the register sets below)
@@ -472,7 +497,7 @@ __device__ __forceinline__ void dkv_pair_body(
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
         const int* sIdx = reinterpret_cast<const int*>(smem + TL::IX0);
         const uint32_t pc16 = TL::request_piece(lane);
-        const int idx_row = wave * IPW * TL::RPI + lane / TL::PPR;           // + i * RPI: row of request i this lane takes part in
+        const int idx_row = pair * IPW * TL::RPI + lane / TL::PPR;           // + i * RPI: row of request i this lane takes part in
         // LSE / delta: lanes 0..31 request LSE, lanes 32..63 delta; lane l % 32 = position p holds row ld_row (accumulator
         // order: the 16 values a lane half needs are contiguous)
         const int ld_row = ((l32 & 3) << 2) | (((l32 >> 2) & 1) << 1) | (((l32 >> 3) & 1) << 4) | (l32 >> 4);
@@ -496,36 +521,45 @@ __device__ __forceinline__ void dkv_pair_body(
             const uint32_t e = (uint32_t)min(32 * (hc + 8) + lane, cnt - 1) * 4, l = ld_offset(hc + 5);
             dma4(side_base, lists ? e : l, lists ? lds0 + TL::IX0 + (uint32_t)(hc & (NS - 1)) * 128 : ld_slot(hc + 5));
         };
-        auto dma_rows = [&](int x, int i, int tensor) {
-            const uint32_t l = lds0 + (uint32_t)(x & (NS - 1)) * HB + (uint32_t)(wave * IPW + i) * GP;
+        const uint32_t lds_rows = lds0 + (uint32_t)pair * IPW * GP;
+        auto dma_rows = [&](uint32_t off, int i, int tensor) {
+            const uint32_t l = lds_rows + off + (uint32_t)i * GP;
             if (tensor == 0) dma_row16<0>(qbase, qn[i], qss, pc16, l);
             else dma_row16<NS * HB>(dobase, qn[i], doss, pc16, l);
         };
         auto request_all = [&](int hc) {
-            if (role == 0) { read_ld_idx(hc + 5); dma_side(hc); }
-            read_idx(hc + 5);
+            if (role == 0) {
+                read_ld_idx(hc + 5);
+                dma_side(hc);
+            } else {
+                read_idx(hc + 5);
 #pragma unroll
-            for (int i = 0; i < IPW; ++i) { dma_rows(hc + 5, i, 0); dma_rows(hc + 5, i, 1); }
+                for (int i = 0; i < IPW; ++i) { dma_rows((uint32_t)((hc + 5) & (NS - 1)) * HB, i, 0); dma_rows((uint32_t)((hc + 5) & (NS - 1)) * HB, i, 1); }
+            }
         };
         // Ends a step: what this wavefront requested up to two steps before has landed, then everybody's.  A step makes
         // 2 * IPW requests (role 0: one more, first in the step).
         auto end_step = [&](auto role_tag) {
-            VMOBA_WAIT_VMCNT(4 * IPW + (decltype(role_tag)::value == 0 ? 1 : 0));
+            VMOBA_WAIT_VMCNT(decltype(role_tag)::value == 0 ? 2 : 4 * IPW);
             __syncthreads();
         };
         // prologue: list entries of half-chunks 0..7, then rows of half-chunks 0..4, of which 0..2 have to be here
-        reinterpret_cast<int*>(smem + TL::IX0)[tid] = list[min(tid, cnt - 1)];
+        reinterpret_cast<int*>(smem + TL::IX0)[tid] = first_entry;
         __syncthreads();
-        if (wave == 0) {
-            for (int x = 0; x < 5; ++x) { read_ld_idx(x); dma4(ld_base, ld_offset(x), ld_slot(x)); }
-        }
+        read_ld_idx(wave);
+        dma4(ld_base, ld_offset(wave), ld_slot(wave));
+        if (wave == 0) { read_ld_idx(4); dma4(ld_base, ld_offset(4), ld_slot(4)); }
+        if (role == 1) {
 #pragma unroll
-        for (int x = 0; x < 5; ++x) {
-            read_idx(x);
+            for (int x = 0; x < 5; ++x) {
+                read_idx(x);
 #pragma unroll
-            for (int i = 0; i < IPW; ++i) { dma_rows(x, i, 0); dma_rows(x, i, 1); }
+                for (int i = 0; i < IPW; ++i) { dma_rows((uint32_t)x * HB, i, 0); dma_rows((uint32_t)x * HB, i, 1); }
+            }
+            VMOBA_WAIT_VMCNT(4 * IPW);
+        } else {
+            VMOBA_WAIT_VMCNT(0);
         }
-        VMOBA_WAIT_VMCNT(4 * IPW);
         __syncthreads();
 
         const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -539,8 +573,9 @@ __device__ __forceinline__ void dkv_pair_body(
 #pragma unroll
             for (int dt = 0; dt < TL::NTB; ++dt) tlane[t][dt] = (role == 0 ? (uint32_t)(NS * HB) : 0u) + TL::tr_lane(lane, t, dt);
         auto half_off = [&](int half) { return (uint32_t)(half & (NS - 1)) * HB; };
-        auto read_rows = [&](int half, int ks) { return TL::rows(smem, rlane, half_off(half), ks); };
-        auto read_tr = [&](int half, int step) { return TL::transposed(smem, tlane, half_off(half), step / DT, step % DT); };
+        auto next_off = [&](uint32_t off) { return off == (NS - 1) * HB ? 0u : off + HB; };
+        auto read_rows = [&](uint32_t off, int ks) { return TL::rows(smem, rlane, off, ks); };
+        auto read_tr = [&](uint32_t off, int step) { return TL::transposed(smem, tlane, off, step / DT, step % DT); };
 
         if (pair_live) {
             f32x16_t xa[2] = {zero16, zero16}, xb[2] = {zero16, zero16};    // S or dP of the even / odd local half-chunks
@@ -551,20 +586,36 @@ __device__ __forceinline__ void dkv_pair_body(
                 const bf16x8_t z8 = __builtin_shufflevector(zb, zb, 0, 1, 2, 3, 4, 5, 6, 7);
                 w_prev[0][0] = w_prev[0][1] = w_prev[1][0] = w_prev[1][1] = z8;
             }
-            // S / dP of half-chunk 0
+            // LSE (wavefront 0) or -delta (wavefront 1) of a half-chunk's 32 rows, as the accumulators want them: the 16 of this lane half
+            auto read_ld = [&](int half) {
+                const f32x4_t* lp = reinterpret_cast<const f32x4_t*>(smem + TL::LD0 + (half & (NS - 1)) * 256 + role * 128 + hf * 64);
+                f32x16_t r;
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const f32x4_t a4 = lp[g4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) r[g4 * 4 + u] = a4[u];
+                }
+                return r;
+            };
+            // S / dP of half-chunk 0; the sums for dP - delta start at -delta
+            f32x16_t start = role == 0 ? zero16 : read_ld(0);
 #pragma unroll
             for (int ks = 0; ks < KSTEPS; ++ks) {
-                const bf16x8_t a = read_rows(0, ks);
+                const bf16x8_t a = read_rows(0u, ks);
 #pragma unroll
                 for (int kg = 0; kg < 2; ++kg)
-                    xa[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, frag[kg][ks], ks == 0 ? zero16 : xa[kg], 0, 0, 0);
+                    xa[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, frag[kg][ks], ks == 0 ? start : xa[kg], 0, 0, 0);
             }
+            if (role == 1) start = read_ld(1);
             bf16x8_t rop[4], top[4];                        // operands of k-steps st .. st + 2, slot = k-step % 4
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
-                rop[k] = read_rows(1, k);
-                top[k] = read_tr(0, k);                     // local step 0 multiplies them by zeros
+                rop[k] = read_rows(HB, k);
+                top[k] = read_tr(0u, k);                    // local step 0 multiplies them by zeros
             }
+            // ring offsets of half-chunks t - 1 (step 0: 0, times zeros), t, t + 1, t + 2 and of the one whose rows are requested
+            uint32_t o_prev = 0, o_cur = 0, o_1 = HB, o_2 = 2 * HB, o_req = half_off(5 + role);
             u32x4_t* xbuf = reinterpret_cast<u32x4_t*>(smem + TL::X0) + pair * 2 * 4 * 64 + lane;     // + parity * 256 + slot * 64
 
             // one local step; ROLE is compile-time
@@ -573,49 +624,43 @@ __device__ __forceinline__ void dkv_pair_body(
                 constexpr int ROLE = decltype(role_tag)::value;
                 const int hc = t + ROLE;
                 asm volatile("" : "+v"(x_cur[0]), "+v"(x_cur[1]));      // whole registers across the loop, not 32 values
-                float ld[16];
-                {
-                    const float* lp = reinterpret_cast<const float*>(smem + TL::LD0) + (t & (NS - 1)) * 64 + ROLE * 32 + hf * 16;
-#pragma unroll
-                    for (int g4 = 0; g4 < 4; ++g4) {
-                        const f32x4_t a4 = *reinterpret_cast<const f32x4_t*>(lp + g4 * 4);
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) ld[g4 * 4 + u] = a4[u];
-                    }
-                }
+                // wavefront 0: LSE of half-chunk t; wavefront 1: what the sums for dP of half-chunk t + 1 start from, read a step before
+                const f32x16_t ld = ROLE == 0 ? read_ld(t) : start;
                 u32x4_t pin[4];
                 if constexpr (ROLE == 1) {
 #pragma unroll
                     for (int sl = 0; sl < 4; ++sl) pin[sl] = xbuf[(t & 1) * 256 + sl * 64];
                 }
                 float w[2][16];
-                const int th = t > 0 ? t - 1 : 0;
+                float l[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) l[i] = ld[i];
                 static_for<NU>([&](auto unit) __attribute__((always_inline)) {
                     constexpr int n = decltype(unit)::value, st = n >> 2, q = n & 3, kg = q >> 1;
                     constexpr int s2 = st + 2;                  // the k-step whose operands are fetched now
-                    if (q == 0) rop[s2 & 3] = s2 < NST ? read_rows(t + 1, s2) : read_rows(t + 2, s2 - NST);
-                    if (q == 1) top[s2 & 3] = s2 < NST ? read_tr(th, s2) : read_tr(t, s2 - NST);
+                    if (q == 0) rop[s2 & 3] = s2 < NST ? read_rows(o_1, s2) : read_rows(o_2, s2 - NST);
+                    if (q == 1) top[s2 & 3] = s2 < NST ? read_tr(o_prev, s2) : read_tr(o_cur, s2 - NST);
                     if constexpr ((q & 1) == 0)
-                        x_nxt[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rop[st & 3], frag[kg][st], st == 0 ? zero16 : x_nxt[kg], 0, 0, 0);
+                        x_nxt[kg] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rop[st & 3], frag[kg][st], st > 0 ? x_nxt[kg] : ROLE == 0 ? zero16 : ld, 0, 0, 0);
                     else
                         mfma_acc(acc[kg][st % DT], top[st & 3], w_prev[kg][st / DT]);
                     __builtin_amdgcn_sched_barrier(0);          // the matrix instruction leads its unit
                     // the unit's share of the 32 values of P or dS, in the order (s, channel of s, key group)
                     // (an ld passes through an empty assembly statement just before its turn: keeps the arithmetic on it in its unit)
                     constexpr int V0 = first_value(n), V1 = first_value(n + 1);
-                    if constexpr (n == LEAD - 1) asm volatile("" : "+v"(ld[0]));
+                    if constexpr (ROLE == 0 && n == LEAD - 1) asm volatile("" : "+v"(l[0]));
                     static_for<V1 - V0>([&](auto value) __attribute__((always_inline)) {
                         constexpr int v = V0 + decltype(value)::value, g2 = v & 1, i = v >> 1;
                         if constexpr (ROLE == 0) {
-                            w[g2][i] = exp2_raw(fmaf(x_cur[g2][i], scale_log2, -ld[i]));
+                            w[g2][i] = exp2_raw(fmaf(x_cur[g2][i], scale_log2, -l[i]));
                         } else {
                             const u32x4_t pk = pin[g2 * 2 + i / 8];
                             const uint32_t word = (i % 8) / 2 == 0 ? pk.x : (i % 8) / 2 == 1 ? pk.y : (i % 8) / 2 == 2 ? pk.z : pk.w;
                             const float pval = (i & 1) ? bf16hi_to_f32(word) : bf16lo_to_f32(word);
-                            w[g2][i] = pval * (x_cur[g2][i] + ld[i]);
+                            w[g2][i] = pval * x_cur[g2][i];
                         }
                         asm volatile("" : "+v"(w[g2][i]));
-                        if constexpr (g2 == 1 && i < 15) asm volatile("" : "+v"(ld[i + 1]));
+                        if constexpr (ROLE == 0 && g2 == 1 && i < 15) asm volatile("" : "+v"(l[i + 1]));
                     });
                     // packed operands are replaced when their values are complete and their last reader of this step has issued
                     constexpr int PACK0 = LEAD + 15 * (NU - LEAD) / 32;             // the unit of value 15
@@ -632,15 +677,21 @@ __device__ __forceinline__ void dkv_pair_body(
                             }
                         }
                     }
+                    if (ROLE == 1 && n == NU - 6) start = read_ld(t + 2);
                     // the step's requests
                     if (n == 1) {
-                        read_idx(hc + 5);
                         if (ROLE == 0) read_ld_idx(hc + 5);
+                        else read_idx(hc + 5);
                     }
                     if (ROLE == 0 && n == 5) dma_side(hc);
-                    if ((n & 1) == 0 && n >= 6 && n < 6 + 4 * IPW) dma_rows(hc + 5, (n - 6) / 4, ((n - 6) >> 1) & 1);
+                    if (ROLE == 1 && (n & 1) == 0 && n >= 6 && n < 6 + 4 * IPW) dma_rows(o_req, (n - 6) / 4, ((n - 6) >> 1) & 1);
                     __builtin_amdgcn_sched_barrier(0);
                 });
+                o_prev = o_cur;
+                o_cur = o_1;
+                o_1 = o_2;
+                o_2 = next_off(o_2);
+                if (ROLE == 1) o_req = next_off(o_req);
             };
             using R0 = std::integral_constant<int, 0>;
             using R1 = std::integral_constant<int, 1>;
@@ -650,7 +701,7 @@ __device__ __forceinline__ void dkv_pair_body(
                 acc_ready(acc);
 #pragma unroll
                 for (int st = 0; st < NST; ++st) {
-                    if (st + 2 < NST) top[(st + 2) & 3] = read_tr(H - 1, st + 2);
+                    if (st + 2 < NST) top[(st + 2) & 3] = read_tr(o_prev, st + 2);
 #pragma unroll
                     for (int kg = 0; kg < 2; ++kg)
                         acc[kg][st % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(top[st & 3], w_prev[kg][st / DT], acc[kg][st % DT], 0, 0, 0);
@@ -684,24 +735,34 @@ __device__ __forceinline__ void dkv_pair_body(
         }
         VMOBA_WAIT_VMCNT(0);                   // no request may reach LDS that belongs to another workgroup by then
     }
-    {
+    // The sums leave through LDS (the rings are free): written as the accumulators hold them, 8 bytes per lane, read back as whole rows, so that
+    // a store request is four (eight) whole rows instead of 16-byte pieces of 32.
+    __syncthreads();
+    if (pair_live) {
+        constexpr int OPITCH = D * 2 + 16, LPR = D * 2 / 16;          // LPR: lanes per row
+        static_assert(4 * 64 * OPITCH <= TL::BYTES, "rows of the four wavefronts fit the rings");
+        char* const mine = smem + wave * 64 * OPITCH;                 // this wavefront's rows only: no barrier
         const TensorView& dst = role == 0 ? dV : dK;
         const float f = role == 0 ? 1.f : scale;
 #pragma unroll
-        for (int kg = 0; kg < 2; ++kg) {
-            if (pair_live && key_live[kg]) {
-                const int kout = rows ? rows[krow[kg]] : krow[kg];
-                char* pd = dst.ptr + ((long long)b * dst.stride_b + (long long)kout * dst.stride_s + (long long)h * dst.stride_h) * 2;
+        for (int kg = 0; kg < 2; ++kg)
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
+            for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int d = dt * 32 + g * 8 + hf * 4;
-                        u32x2_t wv;
-                        wv.x = pack_bf16x2(acc[kg][dt][4 * g + 0] * f, acc[kg][dt][4 * g + 1] * f);
-                        wv.y = pack_bf16x2(acc[kg][dt][4 * g + 2] * f, acc[kg][dt][4 * g + 3] * f);
-                        *reinterpret_cast<u32x2_t*>(pd + d * 2) = wv;
-                    }
+                for (int g = 0; g < 4; ++g) {
+                    u32x2_t wv;
+                    wv.x = pack_bf16x2(acc[kg][dt][4 * g + 0] * f, acc[kg][dt][4 * g + 1] * f);
+                    wv.y = pack_bf16x2(acc[kg][dt][4 * g + 2] * f, acc[kg][dt][4 * g + 3] * f);
+                    *reinterpret_cast<u32x2_t*>(mine + (kg * 32 + l32) * OPITCH + (dt * 32 + g * 8 + hf * 4) * 2) = wv;
+                }
+        char* const base = dst.ptr + ((long long)b * dst.stride_b + (long long)h * dst.stride_h) * 2 + lane % LPR * 16;
+#pragma unroll
+        for (int k = 0; k < LPR; ++k) {
+            const int r = k * (64 / LPR) + lane / LPR;
+            const u32x4_t x = *reinterpret_cast<const u32x4_t*>(mine + r * OPITCH + lane % LPR * 16);
+            if (kbase + r < L) {
+                const int pos = k0 + kbase + r;
+                *reinterpret_cast<u32x4_t*>(base + (long long)(rows ? rows[pos] : pos) * dst.stride_s * 2) = x;
             }
         }
     }
@@ -716,10 +777,9 @@ __device__ __forceinline__ void dkv_pair_body(
 // without workgroup barriers; the four partial dK^T / dV^T are added through LDS at the end.
 template <int D>
 __device__ __forceinline__ void dkv_tail_body(
-    char* smem, int bh, int rank, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
-    const float* __restrict__ lse_delta, const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int* __restrict__ kb_order, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
-    const int* __restrict__ kv_rows, int Hh, int S, int nb, long long cap, float scale_log2, float scale) {
+    char* smem, int bh, const int4 desc, const TensorView& Q, const TensorView& K, const TensorView& V, const TensorView& dO,
+    const float* __restrict__ lse_delta, const int* __restrict__ q_idx, const TensorView& dK, const TensorView& dV, const int* __restrict__ rows,
+    const int* __restrict__ kv_rows, int Hh, int S, long long cap, float scale_log2, float scale) {
     constexpr int QC = 32;                       // queries per chunk
     constexpr int STR = D + 8;
     constexpr int KSTEPS = D / 16, DT = D / 32;
@@ -730,22 +790,17 @@ __device__ __forceinline__ void dkv_tail_body(
     float(*sDl)[QC] = reinterpret_cast<float(*)[QC]>(smem + 2 * 4 * QC * STR * 2 + 4 * QC * 4);
     static_assert(2 * 4 * QC * STR * 2 + 2 * 4 * QC * 4 <= DkvLds<D>::BYTES, "the tail body fits the pair body's LDS");
     const int b = bh / Hh, h = bh % Hh;
-    const int j = kb_order[(long long)bh * nb + rank];            // longest query list first
-    const int k0 = blk_off[j], L = blk_off[j + 1] - k0;
-    const int tail = L % 128;
-    if (tail == 0 || tail > 32) return;
+    const int tail = desc.y - TAIL_SLOT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, hf = lane >> 5;
-    const long long seg = (long long)bh * cap;
-    const int list0 = blk_ptr[(long long)bh * (nb + 1) + j];
-    const int cnt = blk_ptr[(long long)bh * (nb + 1) + j + 1] - list0;
-    const int* list = q_idx + seg + list0;
+    const int cnt = desc.w;
+    const int* list = q_idx + (long long)bh * cap + desc.z;
     const float* lse_h = lse_delta + (long long)bh * 2 * lse_delta_pitch(S);
     const float* dl_h = lse_h + lse_delta_pitch(S);
 
     // the tail keys: B operands (key = lane % 32); columns past the tail repeat the block's last key and are not written
     const bool key_live = l32 < tail;
-    const int krow = k0 + min(L - tail + l32, L - 1);
+    const int krow = desc.x + min(l32, tail - 1);
     bf16x8_t kf[KSTEPS], vf[KSTEPS];
     {
         const long long kin = kv_rows ? kv_rows[krow] : krow;         // row of K and V that holds this key
@@ -917,9 +972,8 @@ __device__ __forceinline__ void dkv_tail_body(
 // rather than per head, and the short tail workgroups fill its end, where the long runs finish unevenly.
 template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(
-    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
-    const int* __restrict__ blk_off, const int* __restrict__ blk_ptr, const int* __restrict__ q_idx,
-    const int* __restrict__ kb_start, const int* __restrict__ kb_order, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, int nb, long long cap,
+    TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta, const int* __restrict__ q_idx,
+    const int4* __restrict__ slot_desc, TensorView dK, TensorView dV, const int* __restrict__ rows, int Hh, int S, long long cap,
     float scale_log2, float scale, const int* __restrict__ kv_rows, int BH, int slots, int group) {
     __shared__ __align__(16) char smem[DkvLds<D>::BYTES];
     // One-dimensional grid.  Workgroup i runs on XCD i % 8 as that XCD's workgroup number i / 8.  A head's slots are cut
@@ -932,11 +986,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(
     if (G >= BH * (slots / group)) return;
     const int bh = G % BH;
     const int id = (G / BH) * group + n % group;
-    const int runs = kb_start[(long long)bh * (nb + 1) + nb];
-    if (id < runs)
-        dkv_pair_body<D>(smem, bh, id, Q, K, V, dO, lse_delta, blk_off, blk_ptr, q_idx, kb_start, kb_order, dK, dV, rows, kv_rows, Hh, S, nb, cap, scale_log2, scale);
-    else if (id - runs < nb)
-        dkv_tail_body<D>(smem, bh, id - runs, Q, K, V, dO, lse_delta, blk_off, blk_ptr, q_idx, kb_order, dK, dV, rows, kv_rows, Hh, S, nb, cap, scale_log2, scale);
+    const int4 desc = slot_desc[(long long)bh * slots + id];
+    if (desc.y == 0) return;
+    if (desc.y < TAIL_SLOT)
+        dkv_pair_body<D>(smem, bh, desc, Q, K, V, dO, lse_delta, q_idx, dK, dV, rows, kv_rows, Hh, S, cap, scale_log2, scale);
+    else
+        dkv_tail_body<D>(smem, bh, desc, Q, K, V, dO, lse_delta, q_idx, dK, dV, rows, kv_rows, Hh, S, cap, scale_log2, scale);
 }
 
 // dQ[q] = scale * sum over the query's pairs of dQpart[pair]; the partials have the tensors' type.  A head whose
@@ -1005,13 +1060,27 @@ struct BwdWs {
     int* head_tiles;   // [BH]
     int* kb_start;     // [BH][nb + 1]
     int* kb_order;     // [BH][nb]
+    int4* slot_desc;   // bfloat16: [BH][dkv_slots]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
     char* QD6;         // split kernels: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
     char* KV6;
     size_t total;
 };
 
-BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool split) {
+// Slots of the matrix-core dK/dV kernels per head: `group` consecutive ones are one block's runs (the usual block: S / nb keys; bfloat16:
+// a last run of at most 32 keys goes to the tail workgroups); in all a multiple of group and of 8 (workgroup id % 8 is then the same for every
+// head), + 8 for the per-XCD rounding.
+struct DkvSlots { int grid_x, group, slots; };
+DkvSlots dkv_slots(int64_t S, int nb, int KPW, bool bf16) {
+    const int64_t usual = S / nb;
+    DkvSlots d;
+    d.grid_x = (int)((S / KPW + nb + 7) / 8 * 8 + 8 + (bf16 ? nb : 0));
+    d.group = (int)std::max<int64_t>(1, (bf16 && usual % KPW > 0 && usual % KPW <= 32) ? usual / KPW : ceil_div64(usual, KPW));
+    d.slots = (int)ceil_div64(d.grid_x, d.group) * d.group;
+    return d;
+}
+
+BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int nb, int64_t cap, int es, bool split) {
     BwdWs w;
     char* p = (char*)base;
     size_t off = 0;
@@ -1022,6 +1091,7 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool 
     w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
+    w.slot_desc = (int4*)(p + off);  off += es == 2 ? align_up((size_t)BH * dkv_slots(S, nb, 128, true).slots * 16, 256) : 0;
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
     w.QD6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
@@ -1033,7 +1103,7 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool 
 
 size_t vmoba_attn_bwd_workspace_bytes(int B, int Hh, int64_t S, int D, int nb, int64_t cap, int dtype) {
     const bool bf16 = dtype == VMOBA_BF16;
-    return carve_bwd(nullptr, B * Hh, S, D, cap, bf16 ? 2 : 4, !bf16 && use_split(B * Hh, S, D, nb, cap)).total;
+    return carve_bwd(nullptr, B * Hh, S, D, nb, cap, bf16 ? 2 : 4, !bf16 && use_split(B * Hh, S, D, nb, cap)).total;
 }
 
 extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t* blk_off,
@@ -1060,7 +1130,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     if (nnz_capacity > INT32_MAX) return VMOBA_ERR_UNSUPPORTED;
     const bool bf16 = dt == VMOBA_BF16;
     const bool split = !bf16 && use_split(BH, S, D, n_blocks, nnz_capacity);
-    BwdWs ws = carve_bwd(workspace, BH, S, D, nnz_capacity, bf16 ? 2 : 4, split);
+    BwdWs ws = carve_bwd(workspace, BH, S, D, n_blocks, nnz_capacity, bf16 ? 2 : 4, split);
     if (workspace_bytes < ws.total) return VMOBA_ERR_WORKSPACE;
     if (((uintptr_t)workspace) & 255) return VMOBA_ERR_INVALID_ARG;
     hipStream_t st = (hipStream_t)stream;
@@ -1081,6 +1151,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     const int TM = 128;                     // queries per dQ tile
     int* const out_of_range = ws.n_tiles + 1;
     const int KPW = bf16 || split ? 128 : 64;        // keys per dK/dV workgroup
+    const DkvSlots dkv = dkv_slots(S, n_blocks, KPW, bf16);
     const int64_t max_tiles = std::min<int64_t>(vmoba_max_tiles(nnz_capacity, TM), (nnz_capacity / TM + n_blocks + 7) / 8 * 8);
     {
         const int* head_tiles = heads_counted_first(BH, n_blocks) ? ws.head_tiles : nullptr;
@@ -1089,7 +1160,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         const dim3 grid((unsigned)(n_delta + ceil_div64(max_tiles, 256) + 1), (unsigned)BH);
         auto kfn = bf16 ? (D == 128 ? bwd_prepare_kernel<true, 128> : bwd_prepare_kernel<true, 64>)
                         : (D == 128 ? bwd_prepare_kernel<false, 128> : bwd_prepare_kernel<false, 64>);
-        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, head_tiles, ws.tile_desc, ws.n_tiles, out_of_range, ws.kb_start, ws.kb_order,
+        kfn<<<grid, dim3(256), 0, st>>>(Ov, dOv, LSE, ws.delta, rows, ws.dO_copy, blk_ptr, blk_off, head_tiles, ws.tile_desc, ws.n_tiles, out_of_range, ws.kb_start, ws.kb_order, ws.slot_desc, dkv.slots,
                                         BH, Hh, (int)S, n_blocks, TM, KPW, bf16 ? 32 : 0, n_delta);
         VMOBA_CHECK_LAUNCH();
     }
@@ -1137,26 +1208,20 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     }
     // ---- dK, dV
     {
-        // a multiple of 8 so that (workgroup id % 8) is the same for every head; + 8 for the per-XCD rounding
-        dim3 grid((unsigned)((S / KPW + n_blocks + 7) / 8 * 8 + 8 + (bf16 ? n_blocks : 0)), (unsigned)BH);
-        // slots of the matrix-core kernels in groups of one block's runs (the usual block: S / n_blocks keys; bfloat16: a last run
-        // of at most 32 keys goes to the tail workgroups)
-        const int64_t usual = S / n_blocks;
-        const int group = (int)std::max<int64_t>(1, (bf16 && usual % KPW > 0 && usual % KPW <= 32) ? usual / KPW : ceil_div64(usual, KPW));
-        const int slots = (int)ceil_div64(grid.x, group) * group;
-        const dim3 hgrid((unsigned)(ceil_div64((int64_t)BH * slots, 8) * 8 + 7 * group));   // see the kernel
+        const dim3 hgrid((unsigned)(ceil_div64((int64_t)BH * dkv.slots, 8) * 8 + 7 * dkv.group));   // see the kernel
         VMOBA_PROFILE_BEGIN(2, st);
         const int32_t* krows = key_rows ? key_rows : rows;      // row map of dK and dV
 #define DKV_ARGS blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
         if (!bf16) {
             if (split)
                 launch_dkv_split(D, hgrid, st, ws.QD6, ws.KV6, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, out_of_range, dKv, dVv, krows,
-                                 Hh, (int)S, pitch, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, BH, slots, group);
+                                 Hh, (int)S, pitch, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, BH, dkv.slots, dkv.group);
             const int parts = split ? 2 : 1;
-            launch_dkv_f32(D, dim3(grid.x * parts, grid.y), st, split ? out_of_range : nullptr, parts, Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS);
+            launch_dkv_f32(D, dim3((unsigned)(dkv.grid_x * parts), (unsigned)BH), st, split ? out_of_range : nullptr, parts, Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS);
         } else {
-            if (D == 128) attn_bwd_dkv_kernel<128><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
-            else attn_bwd_dkv_kernel<64><<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS, BH, slots, group);
+            auto kfn = D == 128 ? attn_bwd_dkv_kernel<128> : attn_bwd_dkv_kernel<64>;
+            kfn<<<hgrid, dim3(256), 0, st>>>(Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.slot_desc, dKv, dVv, krows, Hh, (int)S, (long long)nnz_capacity,
+                                             scale_log2, softmax_scale, kv_rows, BH, dkv.slots, dkv.group);
         }
 #undef DKV_ARGS
         VMOBA_PROFILE_END(2, st);
