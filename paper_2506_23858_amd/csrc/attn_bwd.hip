@@ -145,39 +145,41 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(TensorView O, TensorVi
 
 // ---------------------------------------------------------------------------------------------
 // bf16 MFMA dQ tile kernel.  Same decomposition and operand orientation as the forward tile
-// kernel (query = MFMA column = lane % 32); 4 wavefronts x 32 gathered queries, key chunks of 64:
+// kernel (query = MFMA column); 4 wavefronts x 32 gathered queries, key chunks of 64:
 //   S^T  = K . Q^T                    A = K rows (LDS),  B = Q^T (registers)
 //   dP^T = V . dO^T                   A = V rows (LDS),  B = dO^T (registers)
 //   dS^T = P^T * (dP^T - delta)       in registers, packed to bf16 as the next B operand
 //   dQ^T += K^T . dS^T                A = K^T by transpose reads of the same K tile
 //
 // The key chunks pass through two LDS buffers, requested one chunk ahead straight from global memory (no registers hold rows in
-// flight; one barrier per chunk).  Before: staged through 32 registers with two barriers per chunk, the end of the block tested in
-// every 32-key group and delta subtracted value by value (now the value the sum for dP starts from): 8.6 instructions per
-// matrix instruction and more, now 6.1.  480p, 12 heads, 1D / 2D / 3D partition: 1.89 / 1.83 / 1.48 -> 1.74 / 1.66 / 1.34 ms.
-// (An operand ring of six instead of four registers changes nothing; fetching operands in pairs makes D = 64 16 % slower.)
+// flight; one barrier per chunk); -delta is the value the sum for dP starts from, only a block's last chunk is masked.
+// What bounds it: inside its loop, two workgroups per compute unit keep the matrix pipes busy for 90 % of the cycles, and the card's power limit
+// holds the clock at 1.6-1.8 GHz meanwhile, so the products are on the 16-row instruction, which does the same work with less power
+// (RowTile16; every operand feeds two of them, one per 16 queries).  A quarter of a workgroup's time lies before and behind the loop.
+// Backward call, 480p, 12 heads, 1D / 2D / 3D partition: 4.13 / 4.18 / 3.23 -> 4.05 / 4.00 / 3.18 ms (dQ kernel -5 %); 2 x 6601 x 16 x 64: 520 -> 511 us
+// (there as much by rows that lie free of bank conflicts).
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
     const int* __restrict__ q_idx, const int4* __restrict__ flat_desc, const int* __restrict__ n_tiles, float* __restrict__ dQpart, int Hh, int S,
     long long cap, float scale_log2, const int* __restrict__ kv_rows) {
-    using TL = RowTile<D>;
+    using TL = RowTile16<D>;
     constexpr int KC = 64;                      // keys per chunk
-    constexpr int KSTEPS = D / 16, DT = D / 32;
-    constexpr int GP = TL::GP, HB = TL::HB, RB = TL::RB, PPR = TL::PPR, RPI = TL::RPI;
+    constexpr int KSTEPS = D / 32, CT = D / 16;  // k-steps of the first two products, channel tiles of the third
+    constexpr int HB = TL::HB, RB = TL::RB, PPR = TL::PPR, RPI = TL::RPI;
     constexpr int BUF = 4 * HB;                 // a chunk: 64 rows of K, then 64 rows of V
     constexpr int IPW = KC / RPI / 4;           // requests per wavefront, tensor and chunk
     __shared__ __align__(1024) char smem[2 * BUF];
     // The gathered rows of Q and dO pass through the second buffer on their way in; the wavefront's 32 partial rows, through the
     // first on their way out: written as the accumulators hold them, read back as whole rows.
     constexpr int OPITCH = D * 2 + 16;
-    static_assert(4 * 32 * RB <= BUF && 4 * 32 * OPITCH <= BUF, "rows of the four wavefronts fit a buffer");
+    static_assert(4 * 32 * RB == BUF && 4 * 32 * OPITCH <= 2 * BUF, "rows of the four wavefronts fit a buffer, and both");
 
     Tile tc;
     if (!take_tile(flat_desc, n_tiles, tc)) return;
     const int bh = tc.bh, b = bh / Hh, h = bh % Hh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, hf = lane >> 5;
+    const int l32 = lane & 31, l16 = lane & 15, g = lane >> 4;
     const long long seg = (long long)bh * cap;
 
     const int ent = wave * 32 + l32;
@@ -190,7 +192,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     const char* vbase = V.ptr + ((long long)b * V.stride_b + (long long)h * V.stride_h) * 2;
     // row strides in bytes: below 2^24 and rows below 2^24, so a row's offset is one 24-bit multiply (host-checked)
     const uint32_t kss = (uint32_t)(K.stride_s * 2), vss = (uint32_t)(V.stride_s * 2);
-    const uint32_t pc16 = TL::request_piece(lane);
+    static_assert(IPW % TL::NPC == 0, "the same for every wavefront");
+    uint32_t pc16[TL::NPC];
+#pragma unroll
+    for (int i = 0; i < TL::NPC; ++i) pc16[i] = TL::request_piece(lane, i);
     const int n_chunks = (tc.L + KC - 1) / KC;
     // Requests of a chunk: request i of this wavefront fetches rows (wave * IPW + i) * RPI + lane / PPR of it, of K and of V.
     // krow: where these keys lie -- the key positions themselves or, with keys in place, what kv_rows says, looked up one chunk
@@ -204,32 +209,41 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
         }
     };
     auto request = [&](int c, int i, int tensor) {
-        const uint32_t l = lds0 + (uint32_t)(c & 1) * BUF + (uint32_t)(wave_u * IPW + i) * GP;
-        if (tensor == 0) dma_row16<0>(kbase, krow[i], kss, pc16, l);
-        else dma_row16<2 * HB>(vbase, krow[i], vss, pc16, l);
+        const uint32_t l = lds0 + (uint32_t)(c & 1) * BUF + (uint32_t)(wave_u * IPW + i) * 1024;
+        if (tensor == 0) dma_row16<0>(kbase, krow[i], kss, pc16[i % TL::NPC], l);
+        else dma_row16<2 * HB>(vbase, krow[i], vss, pc16[i % TL::NPC], l);
     };
     // The wavefront's 32 gathered rows of Q, then those of dO, go to LDS as whole rows as well (one request covers 4 (8)
-    // rows instead of a 32-byte piece of 32 rows); piece p of row r sits at slot p ^ (r % pieces), which keeps the fragment reads
-    // free of bank conflicts.  A wavefront reads back only what it requested: no barrier.
+    // rows instead of a 32-byte piece of 32 rows); laid out like the key rows.  A wavefront reads back only what it requested: no barrier.
     const uint32_t g0 = lds0 + BUF + (uint32_t)wave_u * 32 * RB;
     auto gather = [&](const char* base, uint32_t stride) {
 #pragma unroll
         for (int k = 0; k < 32 / RPI; ++k) {
             const int r = k * RPI + lane / PPR;
-            const uint32_t pc = (uint32_t)(((lane % PPR) ^ (r & (PPR - 1))) * 16);
+            const uint32_t pc = TL::request_piece(lane, k);
             dma16(base, __umul24((uint32_t)__shfl(q, r, 64), stride) + pc, g0 + k * 1024);
         }
     };
-    auto fragments = [&](bf16x8_t* f) {
-        const char* g = smem + BUF + wave_u * 32 * RB + l32 * RB;
+    auto fragments = [&](bf16x8_t (&f)[2][KSTEPS]) {       // queries l16 and 16 + l16
+        const char* mine = smem + BUF + wave_u * 32 * RB + l16 * RB;
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) f[ks] = *reinterpret_cast<const bf16x8_t*>(g + ((2 * ks + hf) ^ (l32 & (PPR - 1))) * 16);
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks)
+                f[qt][ks] = *reinterpret_cast<const bf16x8_t*>(mine + qt * 16 * RB + ((4 * ks + g) ^ TL::swz(l16)) * 16);
     };
-    bf16x8_t qf[KSTEPS], dof[KSTEPS];
+    bf16x8_t qf[2][KSTEPS], dof[2][KSTEPS];
     lookup_rows(0);
     gather(Q.ptr + ((long long)b * Q.stride_b + (long long)h * Q.stride_h) * 2, (uint32_t)(Q.stride_s * 2));
-    const float lse2 = lse_delta[(long long)bh * 2 * lse_delta_pitch(S) + q];
-    const float ndl = lse_delta[((long long)bh * 2 + 1) * lse_delta_pitch(S) + q];
+    float lse2[2];
+    f32x4_t ndl[2];                            // -delta, the value the sums for dP start from
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        const int qq = __shfl(q, qt * 16 + l16, 64);
+        lse2[qt] = lse_delta[(long long)bh * 2 * lse_delta_pitch(S) + qq];
+        const float d = lse_delta[((long long)bh * 2 + 1) * lse_delta_pitch(S) + qq];
+        ndl[qt] = f32x4_t{d, d, d, d};
+    }
     VMOBA_WAIT_VMCNT(0);
     asm volatile("" ::: "memory");
     fragments(qf);
@@ -240,34 +254,30 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
     for (int i = 0; i < IPW; ++i) { request(0, i, 0); request(0, i, 1); }
     lookup_rows(1);
 
-    f32x16_t dqacc[DT];
+    const f32x4_t zero4 = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t dqacc[CT][2];
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int ct = 0; ct < CT; ++ct) dqacc[ct][0] = dqacc[ct][1] = zero4;
+    uint32_t rlane[TL::NRB], tlane[TL::NTB];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) dqacc[dt][i] = 0.f;
-    uint32_t rlane[TL::NRB], tlane[2][TL::NTB];
+    for (int i = 0; i < TL::NRB; ++i) rlane[i] = TL::row_lane(lane, i);
 #pragma unroll
-    for (int k = 0; k < TL::NRB; ++k) rlane[k] = TL::row_lane(lane, k);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int dt = 0; dt < TL::NTB; ++dt) tlane[t][dt] = TL::tr_lane(lane, t, dt);
+    for (int i = 0; i < TL::NTB; ++i) tlane[i] = TL::tr_lane(lane, i);
 
-    // A 32-key group is a sequence of 2 * KSTEPS + NU matrix instructions: S^T over the k-steps, dP^T over the k-steps
-    // (with P = exp(S - LSE) computed between them), then the third product, first over the keys whose dS is ready
-    // (with the rest of dS computed between them).  Their LDS operands pass through one ring of AHEAD + 1 registers,
-    // fetched AHEAD instructions before use, across the phases and into the next group; fences keep that order, so no
-    // matrix instruction waits a full LDS round trip.
-    constexpr int NU = 2 * DT;                  // matrix instructions of the third product per 32-key group
-    constexpr int NSEQ = 2 * KSTEPS + NU;
+    // A 32-key group is a sequence of units with one LDS operand and two matrix instructions (one per 16 queries) each: S^T over (16 keys,
+    // k-step), dP^T over the same (with P = exp(S - LSE) computed between them, and dS of the first 16 keys), then the third product over the
+    // channel tiles.  The operands pass through one ring of AHEAD + 1 registers, fetched AHEAD units before use, across the phases and into the
+    // next group; fences keep that order, so no matrix instruction waits a full LDS round trip.
+    constexpr int NP = 2 * KSTEPS;              // units of a phase
+    static_assert(NP == CT, "as many units in each phase");
+    constexpr int NSEQ = 3 * NP, VPU = 16 / NP; // VPU: values per unit of the middle phase
     constexpr int AHEAD = 3, RING = AHEAD + 1;
     static_assert(NSEQ % RING == 0, "the second group continues the ring where the first one left it");
-    auto fetch = [&](uint32_t buf, int mt, int n) -> bf16x8_t {     // operand of instruction n of group mt (n past the end: next group)
+    auto fetch = [&](uint32_t buf, int mt, int n) -> bf16x8_t {     // operand of unit n of group mt (n past the end: next group)
         if (n >= NSEQ) { mt += 1; n -= NSEQ; }
-        if (n < KSTEPS) return TL::rows(smem, rlane, buf + mt * HB, n);
-        if (n < 2 * KSTEPS) return TL::rows(smem, rlane, buf + (2 + mt) * HB, n - KSTEPS);
-        const int u = n - 2 * KSTEPS;
-        return TL::transposed(smem, tlane, buf + mt * HB, u / DT, u % DT);
+        if (n < NP) return TL::rows(smem, rlane, buf + mt * HB, n / KSTEPS, n % KSTEPS);
+        if (n < 2 * NP) return TL::rows(smem, rlane, buf + (2 + mt) * HB, (n - NP) / KSTEPS, n % KSTEPS);
+        return TL::transposed(smem, tlane, buf + mt * HB, n - 2 * NP);
     };
     VMOBA_WAIT_VMCNT(0);
     asm volatile("" ::: "memory");
@@ -291,47 +301,53 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
             if (!MASK || mt * 32 < valid) {
-                f32x16_t sacc, dpacc;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) { sacc[i] = 0.f; dpacc[i] = ndl; }        // the sum for dP - delta starts at -delta
-                float ds[16];
-                bf16x8_t dsf;
-                const int vh = valid - mt * 32 - hf;  // MASK: value i belongs to a key of the block when acc_row(i, 0) < vh
-                auto p_value = [&](int i) {           // S^T value -> P^T value, in place
-                    sacc[i] = exp2_raw(fmaf(sacc[i], scale_log2, -lse2));
-                    if (MASK && acc_row(i, 0) >= vh) sacc[i] = 0.f;
+                f32x4_t s[2][2], dp[2][2];            // [16 keys][16 queries]: value i is key 16 * kt + 4 * g + i
+                bf16x8_t dsf[2];
+                const int vh = valid - mt * 32 - 4 * g;       // MASK: value (kt, i) belongs to a key of the block when 16 * kt + i < vh
+                auto p_value = [&](int v) {           // S^T value -> P^T value, in place
+                    const int kt = v >> 3, qt = (v >> 2) & 1, i = v & 3;
+                    float p = exp2_raw(fmaf(s[kt][qt][i], scale_log2, -lse2[qt]));
+                    if (MASK && 16 * kt + i >= vh) p = 0.f;
+                    s[kt][qt][i] = p;
                 };
-                auto ds_value = [&](int i) {
-                    ds[i] = sacc[i] * dpacc[i];
-                    asm volatile("" : "+v"(ds[i]));
+                auto ds_value = [&](int v) {
+                    const int kt = v >> 3, qt = (v >> 2) & 1, i = v & 3;
+                    float d = s[kt][qt][i] * dp[kt][qt][i];
+                    asm volatile("" : "+v"(d));
+                    s[kt][qt][i] = d;
                 };
 #pragma unroll
                 for (int n = 0; n < NSEQ; ++n) {
-                    // the operand AHEAD instructions on (the group after the second one waits for the next chunk)
+                    // the operand AHEAD units on (the group after the second one waits for the next chunk)
                     if (n + AHEAD < NSEQ || mt == 0) op[(n + AHEAD) % RING] = fetch(buf, mt, n + AHEAD);
-                    if (n < KSTEPS) {
-                        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[n % RING], qf[n], sacc, 0, 0, 0);
-                    } else if (n < 2 * KSTEPS) {
-                        const int ks = n - KSTEPS;
-                        dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[n % RING], dof[ks], dpacc, 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
+                    const int m = n % NP, kt = m / KSTEPS, ks = m % KSTEPS;
+                    if (n == 2 * NP) {
 #pragma unroll
-                        for (int v = 0; v < 16 / KSTEPS; ++v) p_value(ks * (16 / KSTEPS) + v);
-                    } else {
-                        const int u = n - 2 * KSTEPS;
-                        if (u == 0) {
+                        for (int v = 8; v < 16; ++v) ds_value(v);
 #pragma unroll
-                            for (int i = 0; i < 8; ++i) ds_value(i);
-                            dsf = pack8(&ds[0]);
-                        }
-                        if (u == DT) dsf = pack8(&ds[8]);
-                        dqacc[u % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[n % RING], dsf, dqacc[u % DT], 0, 0, 0);
-                        if (u < DT) {
-#pragma unroll
-                            for (int v = 0; v < 8 / DT; ++v) ds_value(8 + u * (8 / DT) + v);
+                        for (int qt = 0; qt < 2; ++qt) {
+                            const float d8[8] = {s[0][qt][0], s[0][qt][1], s[0][qt][2], s[0][qt][3], s[1][qt][0], s[1][qt][1], s[1][qt][2], s[1][qt][3]};
+                            dsf[qt] = pack8(d8);
                         }
                     }
-                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt) {
+                        if (n < NP)
+                            s[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[n % RING], qf[qt][ks], ks == 0 ? zero4 : s[kt][qt], 0, 0, 0);
+                        else if (n < 2 * NP)
+                            dp[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[n % RING], dof[qt][ks], ks == 0 ? ndl[qt] : dp[kt][qt], 0, 0, 0);
+                        else
+                            dqacc[m][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[n % RING], dsf[qt], dqacc[m][qt], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (n >= NP && n < 2 * NP) {
+#pragma unroll
+                            for (int v = m * VPU + qt * VPU / 2; v < m * VPU + (qt + 1) * VPU / 2; ++v) {
+                                p_value(v);
+                                if (m >= NP / 2) ds_value(v - 8);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
                 }
             }
         }
@@ -345,13 +361,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
         // the tile's partials are consecutive rows of dQpart (bfloat16): stores of 1 KB runs instead of 16-byte pieces
         char* mine = smem + wave * 32 * OPITCH;                               // this wavefront's rows only: no barrier
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int qt = 0; qt < 2; ++qt) {
                 u32x2_t v;
-                v.x = pack_bf16x2(dqacc[dt][4 * g + 0], dqacc[dt][4 * g + 1]);
-                v.y = pack_bf16x2(dqacc[dt][4 * g + 2], dqacc[dt][4 * g + 3]);
-                *reinterpret_cast<u32x2_t*>(mine + l32 * OPITCH + (dt * 32 + g * 8 + hf * 4) * 2) = v;
+                v.x = pack_bf16x2(dqacc[ct][qt][0], dqacc[ct][qt][1]);
+                v.y = pack_bf16x2(dqacc[ct][qt][2], dqacc[ct][qt][3]);
+                *reinterpret_cast<u32x2_t*>(mine + (qt * 16 + l16) * OPITCH + (ct * 16 + g * 4) * 2) = v;
             }
         char* dst = reinterpret_cast<char*>(dQpart) + (seg + tc.list0) * (long long)(D * 2);
         constexpr int LPR = D * 2 / 16;                                       // lanes per row

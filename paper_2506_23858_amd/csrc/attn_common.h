@@ -288,6 +288,45 @@ struct RowTile {
     }
 };
 
+// The same for v_mfma_f32_16x16x32_bf16 (lane = 16 * g + l16): A operand: lane holds row l16, 8 consecutive k at 8 * g; B operand: column
+// l16, same k; C/D: lane holds column l16, rows 4 * g + i as value i.  Rows are fed in their order: the accumulators of two 16-row
+// tiles, rows 4 * g + i and 16 + 4 * g + i, pack straight into the next product's B operand of 32 rows, and two transpose reads deliver
+// the A operand that goes with it.  (The 16-row instruction does the same work in the same cycles with half the traffic of sums: under the
+// card's power limit a loop of nothing else runs at 2.05 PFLOP/s, 2.0 GHz, against 1.79, 1.75 GHz, of the 32-row one.)
+// Rows lie one after the other, row r's 16-byte piece p at piece position p ^ swz(r).  The LDS serves 256 bytes per cycle: 16 lanes of a
+// row read (eight rows of one piece, the other eight of the next: lanes 0-3, 12-15, 20-23 and 24-27, and so on) have to hit 16 different
+// pieces of 256 bytes, and the 32 lanes of a transposed read (8 rows of two pieces) as well.  So swz leaves the lowest bit alone and is one-to-one
+// in the others over 8 rows (D = 64: over the 4 of either parity, which share no piece positions).
+template <int D>
+struct RowTile16 {
+    static constexpr int RB = 2 * D, PPR = D / 8, RPI = 64 / PPR;
+    static constexpr int HB = 32 * RB;                                 // bytes of 32 rows
+    static constexpr int NPC = 8 / RPI;                                // different requests, see request_piece
+    static constexpr int NRB = D / 32, NTB = D / 16;                   // per-lane addresses of the row and of the transposed reads
+    __device__ static __forceinline__ int swz(int r) { return D == 128 ? (r & 7) << 1 : (r & 6); }
+    // byte offset inside a row that lane `lane` of the request for rows RPI * j ... fetches (j modulo NPC)
+    __device__ static __forceinline__ uint32_t request_piece(int lane, int j) { return (uint32_t)((lane % PPR) ^ swz(RPI * j + lane / PPR)) * 16; }
+    // contraction over the channels: row l16, k-step ks of 32 channels ...
+    __device__ static __forceinline__ uint32_t row_lane(int lane, int ks) {
+        return (uint32_t)((lane & 15) * RB + ((4 * ks + (lane >> 4)) ^ swz(lane & 15)) * 16);
+    }
+    // ... and over the rows: channel tile ct of 16; lane = 16 * g + 4 * e + a asks for four channels of row 4 * g + e
+    __device__ static __forceinline__ uint32_t tr_lane(int lane, int ct) {
+        const int r = lane >> 2, a = lane & 3;
+        return (uint32_t)(r * RB + ((2 * ct + (a >> 1)) ^ swz(r)) * 16 + (a & 1) * 8);
+    }
+    // Operands at byte offset `tile` of `base`; rl = row_lane(., 0 .. NRB - 1), tl = tr_lane(., 0 .. NTB - 1); kt: 16-row half of the 32 rows
+    __device__ static __forceinline__ bf16x8_t rows(const char* base, const uint32_t* rl, uint32_t tile, int kt, int ks) {
+        return *reinterpret_cast<const bf16x8_t*>(base + (rl[ks] + tile) + kt * 16 * RB);
+    }
+    __device__ static __forceinline__ bf16x8_t transposed(const char* base, const uint32_t* tl, uint32_t tile, int ct) {
+        bf16x4_t h[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t*)(base + (tl[ct] + tile) + t * 16 * RB));
+        return __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+};
+
 // 64 lanes x 16 bytes, row `row` of a matrix of `stride` bytes per row (both below 2^24), byte `piece` of it, to LDS lds + IMM.
 template <int IMM>
 __device__ __forceinline__ void dma_row16(const char* base, uint32_t row, uint32_t stride, uint32_t piece, uint32_t lds) {
