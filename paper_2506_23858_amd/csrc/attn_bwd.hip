@@ -1076,7 +1076,7 @@ struct BwdWs {
     int* head_tiles;   // [BH]
     int* kb_start;     // [BH][nb + 1]
     int* kb_order;     // [BH][nb]
-    int4* slot_desc;   // bfloat16: [BH][dkv_slots]
+    int4* slot_desc;   // [BH][dkv_slots], filled for the matrix-core dK/dV kernel (the size does not depend on the type)
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
     char* QD6;         // split kernels: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
     char* KV6;
@@ -1107,7 +1107,7 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int nb, int64_t cap, int e
     w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
     w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
     w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
-    w.slot_desc = (int4*)(p + off);  off += es == 2 ? align_up((size_t)BH * dkv_slots(S, nb, 128, true).slots * 16, 256) : 0;
+    w.slot_desc = (int4*)(p + off);  off += align_up((size_t)BH * dkv_slots(S, nb, 128, true).slots * 16, 256);
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
     w.QD6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
