@@ -755,25 +755,59 @@ __global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ P
 // Eq. 4); BYCOUNT = true: where the descending cumulative COUNT reaches it (a fixed global k).
 // The cut inside one level's bins, by 1024 threads: my_s / my_c = mass and count of bin 1023 - t.  Returns true in the one thread whose
 // bin holds the cut (level 0: or in the last thread when the pool does not reach the target), with the new state in *st.
-struct ScanLds { unsigned long long s[HIST_BINS / 64], c[HIST_BINS / 64]; };
+struct ScanLds { unsigned long long s[HIST_BINS / 64]; unsigned int c[HIST_BINS / 64]; };
+static_assert(HIST_BINS / 64 == 16, "scan_level sums over wavefronts in a row of 16 lanes");
+// Inclusive prefix sums over the 64 lanes, or over each row of 16, by data-parallel-primitive moves: a shuffle is a trip through the LDS,
+// two for 64 bits.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned int moved32(unsigned int x) { return (unsigned int)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long moved64(unsigned long long x) {
+    return (unsigned long long)moved32<CTRL, ROWS>((unsigned int)(x >> 32)) << 32 | moved32<CTRL, ROWS>((unsigned int)x);
+}
+constexpr int ROW_SHR = 0x110, ROW_BCAST15 = 0x142, ROW_BCAST31 = 0x143;
+__device__ __forceinline__ unsigned int row_scan32(unsigned int x) {
+    x += moved32<ROW_SHR + 1, 0xf>(x);
+    x += moved32<ROW_SHR + 2, 0xf>(x);
+    x += moved32<ROW_SHR + 4, 0xf>(x);
+    return x + moved32<ROW_SHR + 8, 0xf>(x);
+}
+__device__ __forceinline__ unsigned long long row_scan64(unsigned long long x) {
+    x += moved64<ROW_SHR + 1, 0xf>(x);
+    x += moved64<ROW_SHR + 2, 0xf>(x);
+    x += moved64<ROW_SHR + 4, 0xf>(x);
+    return x + moved64<ROW_SHR + 8, 0xf>(x);
+}
+__device__ __forceinline__ unsigned int wave_scan32(unsigned int x) {
+    x = row_scan32(x);
+    x += moved32<ROW_BCAST15, 0xa>(x);                   // rows 1 and 3: the last lane of the row before
+    return x + moved32<ROW_BCAST31, 0xc>(x);             // rows 2 and 3: lane 31
+}
+__device__ __forceinline__ unsigned long long wave_scan64(unsigned long long x) {
+    x = row_scan64(x);
+    x += moved64<ROW_BCAST15, 0xa>(x);
+    return x + moved64<ROW_BCAST31, 0xc>(x);
+}
 template <int LEVEL, bool BYCOUNT>
-__device__ __forceinline__ bool scan_level(ScanLds& lds, unsigned long long my_s, unsigned long long my_c, HeadState* st, unsigned long long target,
+__device__ __forceinline__ bool scan_level(ScanLds& lds, unsigned long long my_s, unsigned int my_c, HeadState* st, unsigned long long target,
                                            int fix_shift) {
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    unsigned long long is = my_s, ic = my_c;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long a = __shfl_up(is, off, 64), c = __shfl_up(ic, off, 64);
-        if (lane >= off) { is += a; ic += c; }
-    }
+    unsigned long long is = wave_scan64(my_s);
+    unsigned int ic = wave_scan32(my_c);                 // (a pool holds fewer than 2^31 entries)
     if (lane == 63) { lds.s[wv] = is; lds.c[wv] = ic; }
     __syncthreads();
-    for (int w = 0; w < wv; ++w) { is += lds.s[w]; ic += lds.c[w]; }
+    {   // the wavefronts before this one: lane i of each row of 16 has wavefront i
+        const int i = lane & 15;
+        const unsigned long long a = row_scan64(i < wv ? lds.s[i] : 0ull);
+        const unsigned int c = row_scan32(i < wv ? lds.c[i] : 0u);
+        is += (unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(a >> 32), 15) << 32 | (unsigned int)__builtin_amdgcn_readlane((int)a, 15);
+        ic += (unsigned int)__builtin_amdgcn_readlane((int)c, 15);
+    }
     __syncthreads();                                     // the caller may scan the next level right away
     const unsigned long long need = (LEVEL == 0) ? target : st->need;
-    const unsigned long long cexcl = ic - my_c;
-    const unsigned long long incl = BYCOUNT ? ic : is;
-    const unsigned long long excl = BYCOUNT ? cexcl : is - my_s;
+    const unsigned int cexcl = ic - my_c;
+    const unsigned long long incl = BYCOUNT ? (unsigned long long)ic : is;
+    const unsigned long long excl = BYCOUNT ? (unsigned long long)cexcl : is - my_s;
     if (LEVEL == 0 && t == HIST_BINS - 1 && incl < need) {
         // the whole pool does not reach the target (tau >= 1, or rounding): keep everything
         st->all = 1u;
@@ -798,7 +832,7 @@ __device__ __forceinline__ bool scan_level(ScanLds& lds, unsigned long long my_s
         }
         if (take > my_c) take = my_c;
         if (take < 1) take = 1;
-        st->n_tie = (unsigned)my_c;
+        st->n_tie = my_c;
         st->take = (unsigned)take;
     }
     return true;
@@ -1503,13 +1537,12 @@ __global__ __launch_bounds__(64) void blk_ptr_kernel(const int* __restrict__ row
     block_offsets(row_tot + (long long)blockIdx.x * (nb + 1), blk_ptr, row_ptr, k_out, theta_out, blockIdx.x, nb, S, cap, dev_status, write_k);
 }
 
-// Offsets of both list forms for one head by the NW wavefronts of a workgroup (what wave_scan_kernel and blk_ptr_kernel do).
-template <int NW>
+// Offsets of both list forms for one head by the 16 wavefronts of a workgroup (what wave_scan_kernel and blk_ptr_kernel do).
 __device__ __forceinline__ void head_offsets(int* sTot, int* __restrict__ wcnt, int* __restrict__ wtot, int* __restrict__ blk_ptr, int* __restrict__ row_ptr,
                                              long long* __restrict__ k_out, float* __restrict__ theta_out, int bh, int nb, int S, int n_waves, long long cap,
                                              int* __restrict__ dev_status, int write_k) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int j = wv; j <= nb; j += NW) {
+    for (int j = wv; j <= nb; j += 16) {
         int* col = j < nb ? wcnt + ((long long)bh * nb + j) * n_waves : wtot + (long long)bh * n_waves;
         int carry = 0;
         for (int base = 0; base < n_waves; base += 64) {
@@ -1530,13 +1563,19 @@ __device__ __forceinline__ void head_offsets(int* sTot, int* __restrict__ wcnt, 
 }
 
 // Everything between the scores and the lists -- the three radix levels, tie ranks, mask, list offsets -- for a small pool, one
-// workgroup per head in one launch instead of ten that take 2 to 7 us each whatever their size.  Bound by the latency of its
-// dozen dependent trips to the L2.  Same integers, same results as the kernels above.  Whole selection, 12 heads x 1560 tokens x 20
-// blocks: 57 -> 45 us; 2 heads x 512 x 16 (float32, with the score kernel's smaller share per workgroup): 72 -> 36 us.  The line
-// lies at 2^15 values: from about 6 x 10^4 on (four rounds of rows per wavefront) the separate launches are as fast or faster (at 10^5
-// values 70 against 84 us; with the cut alone in one workgroup 70 as well).
+// workgroup per head in one launch instead of ten that take 2 to 7 us each whatever their size.  Bound by the instructions of one compute
+// unit and a dozen barriers.  A head's values are read once, beside the histogram, and stay in registers for both refinement levels
+// and the mask (32 of the 128 a thread of 1024 may have).  The mask is first one flat run of bits, a comparison per 64 values; a
+// row's words are cut out of it with two reads and a shift.  Same integers, same results as the kernels above.
+// 12 heads x 1560 tokens x 20 blocks: 23.1 -> 16.7 us, 2 heads x 512 x 16: 15.9 -> 9.4 (before: values fetched for every pass, mask bits by
+// LDS atomics, scans by shuffles); with the values kept but the bits still by atomics 22.3 and 14.0.  The line lies at 2^15 values: before,
+// the separate launches were as fast from about 6 x 10^4 on, and more values would not fit the registers.
 constexpr long long SMALL_POOL = 1 << 15;
 constexpr int SMALL_ROWS = 4096, SMALL_WORDS = 4;
+constexpr int SMALL_VALS = (int)(SMALL_POOL / HIST_BINS);
+// (blocks + 1) * (groups of 64 queries) <= pool / 64 + blocks + groups + 1
+constexpr int SMALL_COUNTS = 1024;
+static_assert(SMALL_POOL / 64 + SMALL_WORDS * 32 + SMALL_ROWS / 64 + 1 <= SMALL_COUNTS, "counts of a head must fit the LDS array");
 template <bool BYCOUNT>
 __global__ __launch_bounds__(HIST_BINS) void small_cut_kernel(const float* __restrict__ P, const unsigned int* __restrict__ hist_cnt,
                                                               const unsigned long long* __restrict__ hist_sum, unsigned long long target, int fix_shift,
@@ -1549,47 +1588,45 @@ __global__ __launch_bounds__(HIST_BINS) void small_cut_kernel(const float* __res
     __shared__ ScanLds scan;
     __shared__ HeadState sState;
     __shared__ unsigned long long sPk[HIST_BINS];
-    __shared__ int sTies[SMALL_ROWS];
-    __shared__ MaskLds<SMALL_WORDS> sMask[NW];
+    __shared__ unsigned long long sKeep[SMALL_POOL / 64 + 1], sTie[SMALL_POOL / 64];   // a bit per value: kept, equal to theta
+    __shared__ int sCnt[SMALL_COUNTS];                           // [block, then all blocks][group of 64 queries]
     __shared__ int sTot[SMALL_WORDS * 32 + 1];
     __shared__ int sW[NW];
     const int bh = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int pool = S * nb;
+    const int pool = S * nb, words = (nb + 31) / 32;
     const unsigned int* p = reinterpret_cast<const unsigned int*>(P) + (long long)bh * pool;
-    const bool aligned = (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+    // ---- the head's values: value t + 1024 k in v[k]
+    const long long hi = (long long)bh * HIST_BINS + HIST_BINS - 1 - t;
+    const unsigned long long h_sum = hist_sum[hi];
+    const unsigned int h_cnt = hist_cnt[hi];
+    unsigned int v[SMALL_VALS];
+#pragma unroll
+    for (int k = 0; k < SMALL_VALS; ++k) {
+        const int e = t + k * HIST_BINS;
+        v[k] = ~0u;                                      // matches no prefix
+        if (e < pool) v[k] = p[e];
+    }
+    sPk[t] = 0ull;
     // ---- the cut
     HeadState st = {0, 0, 0, 0, 0, 0};
-    {
-        const long long i = (long long)bh * HIST_BINS + HIST_BINS - 1 - t;
-        if (t == 0) sState = st;
-        __syncthreads();
-        if (scan_level<0, BYCOUNT>(scan, hist_sum[i], hist_cnt[i], &st, target, fix_shift)) sState = st;
-        __syncthreads();
-        st = sState;
-    }
+    if (t == 0) sState = st;
+    __syncthreads();
+    if (scan_level<0, BYCOUNT>(scan, h_sum, h_cnt, &st, target, fix_shift)) sState = st;
+    __syncthreads();
+    st = sState;
     auto refine = [&](auto level) {
         constexpr int LEVEL = decltype(level)::value;
-        sPk[t] = 0ull;
-        __syncthreads();
-        const int n4 = aligned ? pool / 4 : 0;
-        for (int i0 = t; i0 < n4; i0 += 4 * HIST_BINS) {
-            u32x4_t v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const u32x4_t none = {~0u, ~0u, ~0u, ~0u};      // matches no prefix
-                v[k] = i0 + k * HIST_BINS < n4 ? reinterpret_cast<const u32x4_t*>(p)[i0 + k * HIST_BINS] : none;
-            }
+        for (int k0 = 0; k0 < SMALL_VALS; k0 += 4)
+            if (k0 * HIST_BINS < pool)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) refine_add<LEVEL>(sPk, st.prefix, v[k][u]);
-        }
-        for (int i = 4 * n4 + t; i < pool; i += HIST_BINS) refine_add<LEVEL>(sPk, st.prefix, p[i]);
+                for (int k = k0; k < k0 + 4; ++k) refine_add<LEVEL>(sPk, st.prefix, v[k]);
         __syncthreads();
         const int bin = HIST_BINS - 1 - t;
         unsigned long long cnt, sum;
         refine_bin<LEVEL>(sPk[bin], st.prefix, bin, fix_shift, cnt, sum);
-        if (scan_level<LEVEL, BYCOUNT>(scan, sum, cnt, &st, target, fix_shift)) sState = st;
+        sPk[bin] = 0ull;                                 // for the next level; the scan's barriers lie between
+        if (scan_level<LEVEL, BYCOUNT>(scan, sum, (unsigned int)cnt, &st, target, fix_shift)) sState = st;
         __syncthreads();
         st = sState;
     };
@@ -1601,50 +1638,82 @@ __global__ __launch_bounds__(HIST_BINS) void small_cut_kernel(const float* __res
         k_out[bh] = st.all ? (long long)pool : (long long)(st.cnt_above + st.take);
         theta_out[bh] = st.all ? 0.f : __uint_as_float(st.prefix);
     }
-    // ---- ranks of the entries equal to theta, needed when some but not all of them are kept
-    if (!st.all && st.take != st.n_tie) {
-        for (int q = wv; q < S; q += NW) {
-            int c = 0;
-            for (int j0 = 0; j0 < nb; j0 += 64) c += __popcll(__ballot(j0 + lane < nb && p[(long long)q * nb + j0 + lane] == st.prefix));
-            if (lane == 0) sTies[q] = c;
+    // ---- mask bits; of entries equal to theta the first `take`
+    const bool all_ties = st.all || st.take == st.n_tie;
+    const unsigned int least = st.all ? 0u : st.prefix + (all_ties ? 0u : 1u);
+#pragma unroll
+    for (int k0 = 0; k0 < SMALL_VALS; k0 += 4) {
+        if (k0 * HIST_BINS < pool) {
+#pragma unroll
+            for (int k = k0; k < k0 + 4; ++k) {          // (no row's words hold a bit past the pool)
+                const unsigned long long keep = __ballot(v[k] >= least), tie = __ballot(v[k] == st.prefix);
+                if (lane == 0) { sKeep[k * NW + wv] = keep; sTie[k * NW + wv] = tie; }
+            }
         }
+    }
+    __syncthreads();
+    if (!all_ties) {
+        const int n_words = (pool + 63) / 64;            // at most 512: one per thread
+        unsigned long long tie = t < n_words ? sTie[t] : 0ull;
+        const unsigned int incl = wave_scan32((unsigned int)__popcll(tie));
+        if (lane == 63) sW[wv] = (int)incl;
         __syncthreads();
-        constexpr int PER = SMALL_ROWS / HIST_BINS;
-        int v[PER], sum = 0;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            v[e] = t * PER + e < S ? sTies[t * PER + e] : 0;
-            sum += v[e];
+        unsigned int before = incl - (unsigned int)__popcll(tie);
+        for (int w = 0; w < wv; ++w) before += (unsigned int)sW[w];
+        unsigned long long keep = 0ull;
+        for (; tie && before < st.take; ++before) {
+            const unsigned long long low = tie & (0ull - tie);
+            keep |= low;
+            tie ^= low;
         }
-        int incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) sW[wv] = incl;
-        __syncthreads();
-        int run = incl - sum;
-        for (int w = 0; w < wv; ++w) run += sW[w];
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            if (t * PER + e < S) sTies[t * PER + e] = run;
-            run += v[e];
-        }
+        if (keep) sKeep[t] |= keep;
         __syncthreads();
     }
-    // ---- mask and per-wavefront counts, list offsets
-    for (int w = wv; w < n_waves; w += NW)
-        mask_rows<SMALL_WORDS>(sMask[wv], P, st, sTies, mask, wtot, wcnt, bh, w, S, nb, n_waves, own_blk_off, query_pos);
+    // ---- mask words and the counts per block and group of 64 queries (lane = row)
+    for (int w = wv; w < n_waves; w += NW) {
+        const int q = w * 64 + lane;
+        const bool live = q < S;
+        const int own = own_blk_off && live ? block_of_position(own_blk_off, nb, query_pos ? query_pos[q] : q) : -1;
+        const unsigned int* flat = reinterpret_cast<const unsigned int*>(sKeep);
+        int kept = 0;
+        for (int wd = 0; wd < words; ++wd) {
+            const int jn = min(32, nb - wd * 32);
+            unsigned int g = 0u;
+            if (live) {
+                const int at = q * nb + wd * 32;
+                const unsigned long long two = (unsigned long long)flat[(at >> 5) + 1] << 32 | flat[at >> 5];
+                g = (unsigned int)(two >> (at & 31)) & (~0u >> (32 - jn));
+                if (wd == (own >> 5)) g |= 1u << (own & 31);           // own = -1: no word matches
+                mask[((long long)bh * S + q) * words + wd] = g;
+            }
+            int mine = 0;                                              // lane b: the count of block 32 wd + b
+            for (int bit = 0; bit < jn; ++bit) {
+                const int c = __popcll(__ballot((g >> bit) & 1u));
+                kept += c;
+                mine = lane == bit ? c : mine;
+            }
+            if (lane < jn) sCnt[(wd * 32 + lane) * n_waves + w] = mine;
+        }
+        if (lane == 0) sCnt[nb * n_waves + w] = kept;
+    }
     __syncthreads();
-    head_offsets<NW>(sTot, wcnt, wtot, blk_ptr, row_ptr, k_out, theta_out, bh, nb, S, n_waves, cap, dev_status, write_k);
+    // ---- list offsets (what wave_scan_kernel and blk_ptr_kernel do); at most 64 groups of queries
+    for (int j = wv; j <= nb; j += NW) {
+        const int c = lane < n_waves ? sCnt[j * n_waves + lane] : 0;
+        const int incl = (int)wave_scan32((unsigned int)c);
+        int* col = j < nb ? wcnt + ((long long)bh * nb + j) * n_waves : wtot + (long long)bh * n_waves;
+        if (lane < n_waves) col[lane] = incl - c;
+        if (lane == 63) sTot[j] = incl;
+    }
+    __syncthreads();
+    if (wv == 0) block_offsets(sTot, blk_ptr, row_ptr, k_out, theta_out, bh, nb, S, cap, dev_status, write_k);
 }
 
 __global__ __launch_bounds__(1024) void head_offsets_kernel(int* __restrict__ wcnt, int* __restrict__ wtot, int* __restrict__ blk_ptr,
                                                             int* __restrict__ row_ptr, long long* __restrict__ k_out, float* __restrict__ theta_out,
                                                             int nb, int S, int n_waves, long long cap, int* __restrict__ dev_status, int write_k) {
     __shared__ int sTot[VMOBA_MAX_BLOCKS + 1];
-    head_offsets<16>(sTot, wcnt, wtot, blk_ptr, row_ptr, k_out, theta_out, blockIdx.x, nb, S, n_waves, cap, dev_status, write_k);
+    head_offsets(sTot, wcnt, wtot, blk_ptr, row_ptr, k_out, theta_out, blockIdx.x, nb, S, n_waves, cap, dev_status, write_k);
 }
 
 // Workgroup i of n runs on XCD i % 8; this index makes the workgroups of one XCD neighbours in the work list, so runs
