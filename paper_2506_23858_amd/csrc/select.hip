@@ -22,19 +22,23 @@ constexpr int SCAN_THREADS = 1024;
 constexpr int SCAN_ITEMS = 16;
 
 struct HeadState {              // one per (b, h), lives in the workspace
-    unsigned long long need;    // fixed-point mass still missing inside the current bin range
+    unsigned long long need;    // fixed-point mass still missing inside the current bin range; after the last level: the position
+                                // (row * blocks + block) of the last kept entry among those equal to theta, or TIE_RANKS
     unsigned long long cnt_above;  // pool entries strictly above the current bin range
     unsigned int prefix;        // float bits of theta found so far (high bits)
     unsigned int all;           // 1: threshold never reached -> keep every pair
-    unsigned int n_tie;         // entries equal to theta
-    unsigned int take;          // how many of them belong to the top k
+    unsigned int n_tie;         // entries equal to theta (between the last two levels: candidates offered to the list)
+    unsigned int take;          // how many of them belong to the top k (between the last two levels: 1 if a candidate was dropped)
 };
+
+// HeadState::need after the last level when the entries equal to theta have to be ranked row by row
+constexpr unsigned long long TIE_RANKS = ~0ull;
 
 struct SelectWs {               // workspace carve-up (device pointers)
     unsigned int* hist_cnt;         // [3][BH][1024]
     unsigned long long* hist_sum;   // [3][BH][1024]
     HeadState* state;               // [BH]
-    int* ties;                      // [BH][S]   per-row count of entries equal to theta
+    int* ties;                      // [BH][S]   candidates of the last level, then (TIE_RANKS) per-row count of entries equal to theta
     int* tie_base;                  // [BH][S+1] exclusive scan of ties
     int* wtot;                      // [BH][n_waves]  pairs kept by each group of 64 queries, then its exclusive scan
     int* wcnt;                      // [BH][n_blocks][n_waves]
@@ -838,13 +842,48 @@ __device__ __forceinline__ bool scan_level(ScanLds& lds, unsigned long long my_s
     return true;
 }
 
+// At the last level, when some but not all entries equal to theta are kept: the position of the last kept one, which is all that the mask
+// needs to tell them apart.  The entries come out of the candidate list that the second refinement pass left in `cand` (its at most S
+// entries share 22 bits with theta); a list that overflowed, or more than TIE_MAX equal entries, leaves TIE_RANKS.
+// 12 heads x 112 320 tokens x 288 blocks: the two launches that rank them row by row, another pass over P and a scan of the rows by one
+// workgroup per head, took 253 of 3460 us; this end of the last scan adds 9.
+constexpr int TIE_MAX = 512;
+struct TieLds { HeadState st; unsigned long long last; int n; __align__(16) unsigned int pos[TIE_MAX]; };
+__device__ __forceinline__ unsigned long long last_kept_tie(TieLds& lds, const HeadState& st, const unsigned int* __restrict__ p, const int* __restrict__ cand,
+                                                            unsigned int n_cand) {
+    const int t = threadIdx.x;
+    if (t < TIE_MAX) lds.pos[t] = ~0u;                   // after every position
+    if (t == 0) { lds.n = 0; lds.last = TIE_RANKS; }
+    __syncthreads();
+    for (unsigned int i = t; i < n_cand; i += HIST_BINS) {
+        const unsigned int pos = (unsigned int)cand[i];
+        if (p[pos] == st.prefix) {
+            const int at = atomicAdd(&lds.n, 1);         // at most n_tie of them, in any order
+            if (at < TIE_MAX) lds.pos[at] = pos;
+        }
+    }
+    __syncthreads();
+    if (t < lds.n) {
+        const unsigned int mine = lds.pos[t];
+        unsigned int before = 0;
+        for (int i = 0; i < lds.n; i += 4) {
+            const u32x4_t o = *reinterpret_cast<const u32x4_t*>(&lds.pos[i]);
+            before += (o.x < mine) + (o.y < mine) + (o.z < mine) + (o.w < mine);
+        }
+        if (before == st.take - 1u) lds.last = mine;
+    }
+    __syncthreads();
+    return lds.last;
+}
+
 template <int LEVEL, bool BYCOUNT>
 __global__ __launch_bounds__(HIST_BINS) void scan_level_kernel(const unsigned int* __restrict__ hist_cnt,
                                                                const unsigned long long* __restrict__ hist_sum,
                                                                HeadState* __restrict__ state,
                                                                unsigned long long target, int fix_shift,
                                                                long long pool_size, long long* __restrict__ k_out,
-                                                               float* __restrict__ theta_out) {
+                                                               float* __restrict__ theta_out, const float* __restrict__ P,
+                                                               const int* __restrict__ cand, int S) {
     __shared__ ScanLds lds;
     const int bh = blockIdx.x, t = threadIdx.x;
     HeadState st = state[bh];
@@ -853,9 +892,30 @@ __global__ __launch_bounds__(HIST_BINS) void scan_level_kernel(const unsigned in
         return;
     }
     const long long i = (long long)bh * HIST_BINS + HIST_BINS - 1 - t;
-    if (scan_level<LEVEL, BYCOUNT>(lds, hist_sum[i], hist_cnt[i], &st, target, fix_shift)) {
+    const unsigned int n_cand = st.n_tie, dropped = st.take;
+    const bool mine = scan_level<LEVEL, BYCOUNT>(lds, hist_sum[i], hist_cnt[i], &st, target, fix_shift);
+    if (LEVEL < 2) {
+        if (mine) state[bh] = st;
+        return;
+    }
+    __shared__ TieLds ties;
+    if (t == 0) ties.st.n_tie = ties.st.take = 0u;
+    __syncthreads();
+    if (mine) ties.st = st;
+    __syncthreads();
+    st = ties.st;
+    if (st.n_tie == 0u) {                                // no bin holds the cut (values that are no numbers)
+        if (t == 0) state[bh].n_tie = state[bh].take = 0u;
+        return;
+    }
+    unsigned long long last = TIE_RANKS;
+    if (st.take != st.n_tie && !dropped && n_cand <= (unsigned int)S && st.n_tie <= (unsigned int)TIE_MAX)
+        last = last_kept_tie(ties, st, reinterpret_cast<const unsigned int*>(P) + bh * pool_size, cand + (long long)bh * S, n_cand);
+    if (t == 0) {
+        st.need = last;
         state[bh] = st;
-        if (LEVEL == 2) { k_out[bh] = (long long)(st.cnt_above + st.take); theta_out[bh] = __uint_as_float(st.prefix); }
+        k_out[bh] = (long long)(st.cnt_above + st.take);
+        theta_out[bh] = __uint_as_float(st.prefix);
     }
 }
 
@@ -933,10 +993,11 @@ __global__ __launch_bounds__(256) void pool_rescale_kernel(float* __restrict__ P
 // bin, and those, not the pass over P, set the time when thousands of workgroups flush.
 constexpr int REFINE_NT = 1024;
 template <int LEVEL>
-__device__ __forceinline__ void refine_add(unsigned long long* sPk, unsigned int prefix, unsigned int u) {
+__device__ __forceinline__ bool refine_add(unsigned long long* sPk, unsigned int prefix, unsigned int u) {
     constexpr int SHIFT_HI = (LEVEL == 1) ? 20 : 10, SHIFT_LO = (LEVEL == 1) ? 10 : 0;
-    if ((u >> SHIFT_HI) == (prefix >> SHIFT_HI))
-        atomicAdd(&sPk[(u >> SHIFT_LO) & (HIST_BINS - 1)], PK_ONE | (unsigned long long)(u & ((1u << SHIFT_LO) - 1u)));
+    if ((u >> SHIFT_HI) != (prefix >> SHIFT_HI)) return false;
+    atomicAdd(&sPk[(u >> SHIFT_LO) & (HIST_BINS - 1)], PK_ONE | (unsigned long long)(u & ((1u << SHIFT_LO) - 1u)));
+    return true;
 }
 // count and fixed-point mass of a packed bin
 template <int LEVEL>
@@ -949,19 +1010,29 @@ __device__ __forceinline__ void refine_bin(unsigned long long w, unsigned int pr
     const int e = (int)(lead >> 23), sh = e - 150 + fix_shift;
     sum = (cnt && e && sh >= 0) ? (cnt * (unsigned long long)((lead & 0x7fffffu) | 0x800000u) + (w & (PK_ONE - 1))) << sh : 0ull;
 }
+// The second pass also lists the positions of its candidates, in any order, for the end of the last scan (see last_kept_tie): few, since
+// they share 22 bits; REFINE_CAND per workgroup and S per head at most, beyond which they are ranked row by row if need be.
+constexpr int REFINE_CAND = 1024;
 template <int LEVEL>
-__global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __restrict__ P, const HeadState* __restrict__ state,
+__global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __restrict__ P, HeadState* __restrict__ state,
                                                           unsigned int* __restrict__ hist_cnt,
                                                           unsigned long long* __restrict__ hist_sum,
-                                                          long long pool_size, int fix_shift) {
+                                                          long long pool_size, int fix_shift, int* __restrict__ cand, int S) {
     __shared__ unsigned long long sPk[HIST_BINS];
+    __shared__ unsigned int sCand[LEVEL == 2 ? REFINE_CAND : 1], sN, sBase;
     const int bh = blockIdx.y;
     const HeadState st = state[bh];
     if (st.all) return;
     for (int i = threadIdx.x; i < HIST_BINS; i += REFINE_NT) sPk[i] = 0ull;
+    if (threadIdx.x == 0) sN = 0u;
     __syncthreads();
     const unsigned int prefix = st.prefix;
-    auto take = [&](unsigned int u) { refine_add<LEVEL>(sPk, prefix, u); };
+    auto take = [&](unsigned int u, long long pos) {     // (a pool holds fewer than 2^31 entries)
+        if (refine_add<LEVEL>(sPk, prefix, u) && LEVEL == 2) {
+            const unsigned int at = atomicAdd(&sN, 1u);
+            if (at < REFINE_CAND) sCand[at] = (unsigned int)pos;
+        }
+    };
     const u32x4_t* src = reinterpret_cast<const u32x4_t*>(P + (long long)bh * pool_size);
     // 16-byte loads need every head's pool to start on a 16-byte boundary
     const long long n4 = (pool_size % 4 == 0) ? pool_size / 4 : 0;
@@ -976,16 +1047,28 @@ __global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __r
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            take(v[k].x); take(v[k].y); take(v[k].z); take(v[k].w);
+            const long long e = 4 * (i0 + REFINE_NT * k);
+            take(v[k].x, e); take(v[k].y, e + 1); take(v[k].z, e + 2); take(v[k].w, e + 3);
         }
     }
     {
         const unsigned int* s1 = reinterpret_cast<const unsigned int*>(P + (long long)bh * pool_size);
         for (long long i = n4 * 4 + (long long)blockIdx.x * REFINE_NT + threadIdx.x; i < pool_size;
              i += (long long)gridDim.x * REFINE_NT)
-            take(s1[i]);
+            take(s1[i], i);
     }
     __syncthreads();
+    if (LEVEL == 2) {
+        const unsigned int n = sN;
+        if (threadIdx.x == 0 && n) {
+            sBase = atomicAdd(&state[bh].n_tie, min(n, (unsigned int)REFINE_CAND));
+            if (n > REFINE_CAND) atomicOr(&state[bh].take, 1u);
+        }
+        __syncthreads();
+        const unsigned int base = n ? sBase : 0u;
+        for (unsigned int i = threadIdx.x; i < min(n, (unsigned int)REFINE_CAND) && base + i < (unsigned int)S; i += REFINE_NT)
+            cand[(long long)bh * S + base + i] = (int)sCand[i];
+    }
     for (int i = threadIdx.x; i < HIST_BINS; i += REFINE_NT) {
         unsigned long long cnt, sum;
         refine_bin<LEVEL>(sPk[i], prefix, i, fix_shift, cnt, sum);
@@ -998,12 +1081,12 @@ __global__ __launch_bounds__(REFINE_NT) void refine_hist_kernel(const float* __r
 
 // ---------------------------------------------------------------------------------------------
 // Per-row count of entries equal to theta.  Only needed when some but not all of them belong
-// to the top k; otherwise the kernel returns at once.
+// to the top k and they are too many for last_kept_tie; otherwise the kernel returns at once.
 __global__ __launch_bounds__(256) void tie_count_kernel(const float* __restrict__ P, const HeadState* __restrict__ state,
                                                         int* __restrict__ ties, int S, int nb) {
     const int bh = blockIdx.y;
     const HeadState st = state[bh];
-    if (st.all || st.take == st.n_tie) return;
+    if (st.all || st.take == st.n_tie || st.need != TIE_RANKS) return;
     const int lane = threadIdx.x & 63;
     const int gw = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int n_gw = gridDim.x * 4;
@@ -1020,10 +1103,9 @@ __global__ __launch_bounds__(256) void tie_count_kernel(const float* __restrict_
 }
 
 // Exclusive prefix sum of in[bh][0..S) into out[bh][0..S], out[bh][S] = total.  One workgroup
-// per head.  `needs_ties` = 1 makes the launch a no-op for heads that do not need tie ranks.
+// per head; a no-op for heads that do not need tie ranks.
 __global__ __launch_bounds__(SCAN_THREADS) void row_scan_kernel(const int* __restrict__ in, int* __restrict__ out,
-                                                                const HeadState* __restrict__ state, int needs_ties,
-                                                                int S) {
+                                                                const HeadState* __restrict__ state, int S) {
     __shared__ int sW[SCAN_THREADS / 64];
     __shared__ int sCarry;
     // a batch of SCAN_THREADS * SCAN_ITEMS values passes through LDS so that global memory is read and written in whole
@@ -1031,10 +1113,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void row_scan_kernel(const int* __res
     // (a thread's items then start SCAN_ITEMS + 1 words apart: no bank conflicts)
     __shared__ int sBuf[SCAN_THREADS * (SCAN_ITEMS + 1)];
     const int bh = blockIdx.x, t = threadIdx.x;
-    if (needs_ties) {
-        const HeadState st = state[bh];
-        if (st.all || st.take == st.n_tie) return;
-    }
+    const HeadState st = state[bh];
+    if (st.all || st.take == st.n_tie || st.need != TIE_RANKS) return;
     const int* src = in + (long long)bh * S;
     int* dst = out + (long long)bh * (S + 1);
     if (t == 0) sCarry = 0;
@@ -1097,17 +1177,19 @@ __device__ __forceinline__ int block_of_position(const int* __restrict__ blk_off
 }
 
 // The mask words of a wavefront's 64 rows: entries above theta, entries equal to it.
-template <int W>
-struct MaskLds { unsigned int gt[64][W + 1], tie[64][W + 1]; };
+struct MaskLds { unsigned int gt[64][VMOBA_MAX_MASK_WORDS + 1], tie[64][VMOBA_MAX_MASK_WORDS + 1]; };
 // Mask of rows [64 w, 64 w + 64) of head bh by one wavefront, with its LDS of its own (a wavefront's LDS instructions
-// execute in order: no barriers).  W: words per row at most.  tie_base: per row of the head, entries equal to theta in the rows
+// execute in order: no barriers).  tie_base: per row of the head, entries equal to theta in the rows
 // before.  own_blk_off: null, or blk_off when every query also keeps the block it lies in itself; query_pos: null when query q
 // sits at block-order position q, else the position of every query (queries kept in the caller's token order).
-template <int W>
-__device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restrict__ P, const HeadState& st, const int* __restrict__ tie_base,
+__device__ __forceinline__ void mask_rows(MaskLds& lds, const float* __restrict__ P, const HeadState& st, const int* __restrict__ tie_base,
                                           unsigned int* __restrict__ mask, int* __restrict__ wtot, int* __restrict__ wcnt, int bh, int w,
                                           int S, int nb, int n_waves, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
+    constexpr int W = VMOBA_MAX_MASK_WORDS;
     const int lane = threadIdx.x & 63;
+    // entries equal to theta: all kept, kept up to a position of the head's pool, or (rare) kept by rank
+    const bool all_ties = st.take == st.n_tie, ranked = !st.all && !all_ties && st.need == TIE_RANKS;
+    const unsigned int last_tie = all_ties ? ~0u : (unsigned int)st.need;
     const bool active = w < n_waves;             // a surplus wavefront has no rows
     const int q0 = active ? w * 64 : 0;
     const int words = (nb + 31) / 32;
@@ -1122,6 +1204,7 @@ __device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restri
         const unsigned int* tile = reinterpret_cast<const unsigned int*>(P + ((long long)bh * S + q0) * nb);
         const bool aligned = (reinterpret_cast<uintptr_t>(tile) & 15) == 0;      // wave-uniform
         const int n4 = (aligned && nb >= 4) ? n_el / 4 : 0;                      // whole groups of four (a group spans at most two rows)
+        const unsigned int pos0 = (unsigned int)q0 * (unsigned int)nb;           // a pool holds fewer than 2^31 entries
         const float inv_nb = 1.f / (float)nb;
         auto put = [&](unsigned int (*arr)[W + 1], int row, int col, unsigned int bits, int count) {
             // `count` (1..4) bits for columns col, col + 1, ... of `row`, continuing in the next row past column nb - 1
@@ -1159,8 +1242,17 @@ __device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restri
                     if (st.all || v > st.prefix) gt |= 1u << cidx;
                     else if (v == st.prefix) ti |= 1u << cidx;
                 }
+                if (ti) {
+                    if (ranked) {
+                        put(lds.tie, row, col, ti, 4);
+                    } else {
+                        const unsigned int pos = pos0 + (unsigned int)e;
+#pragma unroll
+                        for (int cidx = 0; cidx < 4; ++cidx)
+                            if (pos + cidx <= last_tie) gt |= ti & (1u << cidx);
+                    }
+                }
                 put(lds.gt, row, col, gt, 4);
-                if (ti) put(lds.tie, row, col, ti, 4);
             }
         }
         // what the groups of four did not cover (everything when the run does not start 16-byte aligned)
@@ -1171,7 +1263,8 @@ __device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restri
             const int col = e - row * nb;
             const unsigned int v = tile[e];
             if (st.all || v > st.prefix) put(lds.gt, row, col, 1u, 1);
-            else if (v == st.prefix) put(lds.tie, row, col, 1u, 1);
+            else if (v == st.prefix && ranked) put(lds.tie, row, col, 1u, 1);
+            else if (v == st.prefix && pos0 + (unsigned int)e <= last_tie) put(lds.gt, row, col, 1u, 1);
         }
     }
     asm volatile("" ::: "memory");
@@ -1180,8 +1273,7 @@ __device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restri
     const int q = q0 + lane;
     const bool live = lane < rows;
     if (live) {
-        const bool all_ties = (st.take == st.n_tie);
-        int rank = all_ties ? 0 : tie_base[q];
+        int rank = ranked ? tie_base[q] : 0;
         const int own = own_blk_off ? block_of_position(own_blk_off, nb, query_pos ? query_pos[q] : q) : -1;
 #pragma unroll
         for (int wd = 0; wd < W; ++wd) {
@@ -1189,16 +1281,12 @@ __device__ __forceinline__ void mask_rows(MaskLds<W>& lds, const float* __restri
             if (wd < words) {
                 g = lds.gt[lane][wd];
                 if (wd == (own >> 5)) g |= 1u << (own & 31);       // own = -1: no word matches
-                unsigned int t = lds.tie[lane][wd];
-                if (all_ties) {
-                    g |= t;
-                } else {
-                    while (t) {
-                        const int bpos = __ffs(t) - 1;
-                        t &= t - 1;
-                        if ((unsigned)rank < st.take) g |= 1u << bpos;
-                        ++rank;
-                    }
+                unsigned int t = ranked ? lds.tie[lane][wd] : 0u;
+                while (t) {
+                    const int bpos = __ffs(t) - 1;
+                    t &= t - 1;
+                    if ((unsigned)rank < st.take) g |= 1u << bpos;
+                    ++rank;
                 }
                 mask[((long long)bh * S + q) * words + wd] = g;
             }
@@ -1232,10 +1320,10 @@ __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, 
                                                    int* __restrict__ wtot, int* __restrict__ wcnt,
                                                    int S, int nb, int n_waves, const int* __restrict__ own_blk_off,
                                                    const int* __restrict__ query_pos) {
-    __shared__ MaskLds<VMOBA_MAX_MASK_WORDS> lds[4];
+    __shared__ MaskLds lds[4];
     const int bh = blockIdx.y, wv = threadIdx.x >> 6;
     const HeadState st = state[bh];
-    mask_rows<VMOBA_MAX_MASK_WORDS>(lds[wv], P, st, tie_base + (long long)bh * (S + 1), mask, wtot, wcnt, bh, blockIdx.x * 4 + wv, S, nb, n_waves,
+    mask_rows(lds[wv], P, st, tie_base + (long long)bh * (S + 1), mask, wtot, wcnt, bh, blockIdx.x * 4 + wv, S, nb, n_waves,
                                     own_blk_off, query_pos);
 }
 
@@ -2048,25 +2136,26 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
 #define SCAN_LEVEL(LV, HC, HS)                                                                                        \
     do {                                                                                                              \
         if (mode == VMOBA_GLOBAL_TOPK)                                                                                \
-            scan_level_kernel<LV, true><<<dim3(BH), dim3(HIST_BINS), 0, st>>>(HC, HS, ws.state, target, fix_shift, pool, (long long*)k_out, theta_out); \
+            scan_level_kernel<LV, true><<<dim3(BH), dim3(HIST_BINS), 0, st>>>(HC, HS, ws.state, target, fix_shift, pool, (long long*)k_out, theta_out, P, ws.ties, (int)S); \
         else                                                                                                          \
-            scan_level_kernel<LV, false><<<dim3(BH), dim3(HIST_BINS), 0, st>>>(HC, HS, ws.state, target, fix_shift, pool, (long long*)k_out, theta_out); \
+            scan_level_kernel<LV, false><<<dim3(BH), dim3(HIST_BINS), 0, st>>>(HC, HS, ws.state, target, fix_shift, pool, (long long*)k_out, theta_out, P, ws.ties, (int)S); \
     } while (0)
         SCAN_LEVEL(0, ws.hist_cnt, ws.hist_sum);
         VMOBA_CHECK_LAUNCH();
-        refine_hist_kernel<1><<<dim3(refine_gx, BH), dim3(REFINE_NT), 0, st>>>(P, ws.state, hc1, hs1, pool, fix_shift);
+        refine_hist_kernel<1><<<dim3(refine_gx, BH), dim3(REFINE_NT), 0, st>>>(P, ws.state, hc1, hs1, pool, fix_shift, ws.ties, (int)S);
         VMOBA_CHECK_LAUNCH();
         SCAN_LEVEL(1, hc1, hs1);
         VMOBA_CHECK_LAUNCH();
-        refine_hist_kernel<2><<<dim3(refine_gx, BH), dim3(REFINE_NT), 0, st>>>(P, ws.state, hc2, hs2, pool, fix_shift);
+        refine_hist_kernel<2><<<dim3(refine_gx, BH), dim3(REFINE_NT), 0, st>>>(P, ws.state, hc2, hs2, pool, fix_shift, ws.ties, (int)S);
         VMOBA_CHECK_LAUNCH();
         SCAN_LEVEL(2, hc2, hs2);
         VMOBA_CHECK_LAUNCH();
 #undef SCAN_LEVEL
-        const unsigned row_gx = (unsigned)std::min<int64_t>(ceil_div64(S, 4 * 8), 4096);
+        // seldom anything to do (see last_kept_tie): no more workgroups than fill the chip, since 40 000 that return at once take 11 us
+        const unsigned row_gx = (unsigned)std::min<int64_t>(ceil_div64(S, 4 * 8), std::max(1, 8 * vmoba_num_cus() / BH));
         tie_count_kernel<<<dim3(row_gx, BH), dim3(256), 0, st>>>(P, ws.state, ws.ties, (int)S, n_blocks);
         VMOBA_CHECK_LAUNCH();
-        row_scan_kernel<<<dim3(BH), dim3(SCAN_THREADS), 0, st>>>(ws.ties, ws.tie_base, ws.state, 1, (int)S);
+        row_scan_kernel<<<dim3(BH), dim3(SCAN_THREADS), 0, st>>>(ws.ties, ws.tie_base, ws.state, (int)S);
         VMOBA_CHECK_LAUNCH();
         mask_kernel<<<dim3(wave_gx, BH), dim3(256), 0, st>>>(P, ws.state, ws.tie_base, mask, ws.wtot, ws.wcnt,
                                                             (int)S, n_blocks, n_waves, own_off, query_pos);

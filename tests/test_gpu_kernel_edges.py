@@ -333,3 +333,32 @@ def test_partition_across_workgroup_borders(Hh, D, S, tin, tout):
     back = [torch.empty_like(t) for t in outs]
     vb.vmoba_partition(g, 1, 2, Hh, D, outs, back, idx[0], None, None)
     assert torch.equal(back[0], x.to(tout)) and torch.equal(back[1], y)
+
+
+@pytest.mark.parametrize("S,chunk,rows", [
+    (1024, 16, 8), (1024, 16, 9),     # 512 equal values, the most whose last kept one is looked up, and 576, which are ranked row by row
+    (1024, 16, 20),                   # more candidates than the list of a head holds
+    (1001, 15, 7), (1001, 15, 1),     # pools of 1001 x 67 values: only the first head's is 16-byte aligned
+])
+def test_cut_inside_a_run_of_equal_values(S, chunk, rows):
+    """Some query rows are zero, so all their values are 1 / N_b, and tau puts the cut in the middle of them: the mask holds the k best of the
+    GPU's own P, equal ones by query, then block, with a part of the run kept in every head."""
+    heads, D = 3, 64
+    Q, K, V = (synth.iid_normal(1120 + i, (1, S, heads, D)) for i in range(3))
+    Q[:, 5:5 + rows * (S // rows) - 5:S // rows] = 0.0
+    P = gu.run_gpu(Q, K, V, None, (1, 1, S), (0, 0, 0), chunk, 0.5, torch.float32)["P"]
+    nb = P.shape[-1]
+    equal = P[0, 0, 5, 0]
+    for h in range(heads):
+        assert int((P[0, h] == equal).sum()) == rows * nb
+        tau = (float(P[0, h][P[0, h] > equal].sum(dtype=np.float64)) + 0.5 * rows) / S
+        g = gu.run_gpu(Q, K, V, None, (1, 1, S), (0, 0, 0), chunk, tau, torch.float32)
+        for i in range(heads):
+            p, k = g["P"][0, i].reshape(-1), int(g["k"][0, i])
+            order = np.lexsort((np.arange(p.size), -p))
+            keep = np.zeros(p.size, bool)
+            keep[order[:k]] = True
+            assert np.array_equal(g["mask"][0, i].reshape(-1), keep), (h, i, k)
+            gu.check_lists(g, 0, i)
+        above, kept = int((P[0, h] > equal).sum()), int(g["k"][0, h])
+        assert above < kept < above + rows * nb and abs(kept - above - 0.5 * rows * nb) <= 1
