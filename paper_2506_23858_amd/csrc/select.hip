@@ -1176,155 +1176,97 @@ __device__ __forceinline__ int block_of_position(const int* __restrict__ blk_off
     return lo;
 }
 
-// The mask words of a wavefront's 64 rows: entries above theta, entries equal to it.
-struct MaskLds { unsigned int gt[64][VMOBA_MAX_MASK_WORDS + 1], tie[64][VMOBA_MAX_MASK_WORDS + 1]; };
-// Mask of rows [64 w, 64 w + 64) of head bh by one wavefront, with its LDS of its own (a wavefront's LDS instructions
-// execute in order: no barriers).  tie_base: per row of the head, entries equal to theta in the rows
-// before.  own_blk_off: null, or blk_off when every query also keeps the block it lies in itself; query_pos: null when query q
-// sits at block-order position q, else the position of every query (queries kept in the caller's token order).
-__device__ __forceinline__ void mask_rows(MaskLds& lds, const float* __restrict__ P, const HeadState& st, const int* __restrict__ tie_base,
-                                          unsigned int* __restrict__ mask, int* __restrict__ wtot, int* __restrict__ wcnt, int bh, int w,
-                                          int S, int nb, int n_waves, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
-    constexpr int W = VMOBA_MAX_MASK_WORDS;
-    const int lane = threadIdx.x & 63;
-    // entries equal to theta: all kept, kept up to a position of the head's pool, or (rare) kept by rank
-    const bool all_ties = st.take == st.n_tie, ranked = !st.all && !all_ties && st.need == TIE_RANKS;
-    const unsigned int last_tie = all_ties ? ~0u : (unsigned int)st.need;
-    const bool active = w < n_waves;             // a surplus wavefront has no rows
-    const int q0 = active ? w * 64 : 0;
-    const int words = (nb + 31) / 32;
-    const int rows = active ? min(64, S - q0) : 0;
-    // The wavefront's 64 rows of P are one contiguous run of rows * nb values: it is read flat, 16 bytes per lane and
-    // eight loads in flight, and every lane ORs the bits of its four values into the rows' mask words in LDS (a group
-    // of four can straddle two words or two rows).
-    for (int wd = 0; wd < words; ++wd) { lds.gt[lane][wd] = 0u; lds.tie[lane][wd] = 0u; }
-    asm volatile("" ::: "memory");
-    {
-        const int n_el = rows * nb;
-        const unsigned int* tile = reinterpret_cast<const unsigned int*>(P + ((long long)bh * S + q0) * nb);
-        const bool aligned = (reinterpret_cast<uintptr_t>(tile) & 15) == 0;      // wave-uniform
-        const int n4 = (aligned && nb >= 4) ? n_el / 4 : 0;                      // whole groups of four (a group spans at most two rows)
-        const unsigned int pos0 = (unsigned int)q0 * (unsigned int)nb;           // a pool holds fewer than 2^31 entries
-        const float inv_nb = 1.f / (float)nb;
-        auto put = [&](unsigned int (*arr)[W + 1], int row, int col, unsigned int bits, int count) {
-            // `count` (1..4) bits for columns col, col + 1, ... of `row`, continuing in the next row past column nb - 1
-            const int here = min(count, nb - col);
-            const unsigned int b0 = bits & ((1u << here) - 1u);
-            if (b0) {
-                const unsigned long long v = (unsigned long long)b0 << (col & 31);
-                atomicOr(&arr[row][col >> 5], (unsigned int)v);
-                if (v >> 32) atomicOr(&arr[row][(col >> 5) + 1], (unsigned int)(v >> 32));
-            }
-            const unsigned int b1 = bits >> here;
-            if (b1) atomicOr(&arr[row + 1][0], b1);
-        };
-        for (int k0 = 0; k0 < n4; k0 += 64 * 8) {
-            u32x4_t x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i4 = k0 + u * 64 + lane;
-                const u32x4_t z = {0u, 0u, 0u, 0u};
-                x[u] = i4 < n4 ? reinterpret_cast<const u32x4_t*>(tile)[i4] : z;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i4 = k0 + u * 64 + lane;
-                if (i4 >= n4) continue;
-                const int e = 4 * i4;
-                int row = (int)((float)e * inv_nb);
-                if (row * nb > e) --row;
-                if ((row + 1) * nb <= e) ++row;
-                const int col = e - row * nb;
-                unsigned int gt = 0u, ti = 0u;
-#pragma unroll
-                for (int cidx = 0; cidx < 4; ++cidx) {
-                    const unsigned int v = x[u][cidx];
-                    if (st.all || v > st.prefix) gt |= 1u << cidx;
-                    else if (v == st.prefix) ti |= 1u << cidx;
-                }
-                if (ti) {
-                    if (ranked) {
-                        put(lds.tie, row, col, ti, 4);
-                    } else {
-                        const unsigned int pos = pos0 + (unsigned int)e;
-#pragma unroll
-                        for (int cidx = 0; cidx < 4; ++cidx)
-                            if (pos + cidx <= last_tie) gt |= ti & (1u << cidx);
-                    }
-                }
-                put(lds.gt, row, col, gt, 4);
-            }
-        }
-        // what the groups of four did not cover (everything when the run does not start 16-byte aligned)
-        for (int e = 4 * n4 + lane; e < n_el; e += 64) {
-            int row = (int)((float)e * inv_nb);
-            if (row * nb > e) --row;
-            if ((row + 1) * nb <= e) ++row;
-            const int col = e - row * nb;
-            const unsigned int v = tile[e];
-            if (st.all || v > st.prefix) put(lds.gt, row, col, 1u, 1);
-            else if (v == st.prefix && ranked) put(lds.tie, row, col, 1u, 1);
-            else if (v == st.prefix && pos0 + (unsigned int)e <= last_tie) put(lds.gt, row, col, 1u, 1);
-        }
-    }
-    asm volatile("" ::: "memory");
-    // lane = row
-    unsigned int mw[W];
-    const int q = q0 + lane;
-    const bool live = lane < rows;
-    if (live) {
-        int rank = ranked ? tie_base[q] : 0;
-        const int own = own_blk_off ? block_of_position(own_blk_off, nb, query_pos ? query_pos[q] : q) : -1;
-#pragma unroll
-        for (int wd = 0; wd < W; ++wd) {
-            unsigned int g = 0;
-            if (wd < words) {
-                g = lds.gt[lane][wd];
-                if (wd == (own >> 5)) g |= 1u << (own & 31);       // own = -1: no word matches
-                unsigned int t = ranked ? lds.tie[lane][wd] : 0u;
-                while (t) {
-                    const int bpos = __ffs(t) - 1;
-                    t &= t - 1;
-                    if ((unsigned)rank < st.take) g |= 1u << bpos;
-                    ++rank;
-                }
-                mask[((long long)bh * S + q) * words + wd] = g;
-            }
-            mw[wd] = g;
-        }
-    } else {
-#pragma unroll
-        for (int wd = 0; wd < W; ++wd) mw[wd] = 0;
-    }
-    // per-block count over the 64 rows of this wavefront (word by word, so that a word is one register) and their sum,
-    // the number of pairs these 64 queries keep
-    int kept = 0;
-#pragma unroll
-    for (int wd = 0; wd < W; ++wd) {
-        if (wd * 32 < nb) {
-            const unsigned int word = mw[wd];
-            const int jn = min(32, nb - wd * 32);
-            for (int bit = 0; bit < jn; ++bit) {
-                const int j = wd * 32 + bit;
-                const int c = __popcll(__ballot((word >> bit) & 1u));
-                kept += c;
-                if (lane == 0 && active) wcnt[((long long)bh * nb + j) * n_waves + w] = c;
-            }
-        }
-    }
-    if (lane == 0 && active) wtot[(long long)bh * n_waves + w] = kept;
+// Workgroup i of n runs on XCD i % 8; this index makes the workgroups of one XCD neighbours in the work list, so runs
+// that different workgroups write into the same cache line meet in one L2.
+__device__ __forceinline__ int xcd_contiguous(int i, int n) {
+    const int per = n / 8;
+    return i < per * 8 ? (i % 8) * per + i / 8 : i;
 }
 
+// One mask word per lane (lane = row of the wavefront's 64 queries; blocks 32 wd to 32 wd + jn - 1): how many of the rows keep each block, to
+// wcnt[block][w].  Returns the sum.
+__device__ __forceinline__ int count_word(unsigned int word, int wd, int jn, int* __restrict__ wcnt, long long bh_nb, int n_waves, int w) {
+    const int lane = threadIdx.x & 63;
+    int kept = 0, mine = 0;                      // lane b: the count of block 32 wd + b, so that all of them leave in one store
+    for (int bit = 0; bit < jn; ++bit) {
+        const int c = __popcll(__ballot((word >> bit) & 1u));
+        kept += c;
+        mine = lane == bit ? c : mine;
+    }
+    if (lane < jn) wcnt[(bh_nb + wd * 32 + lane) * n_waves + w] = mine;
+    return kept;
+}
+
+// Mask of 64 rows of P by one wavefront (its LDS instructions execute in order: no barriers).  tie_base: per row of the head, entries equal
+// to theta in the rows before, used for TIE_RANKS.  own_blk_off: null, or blk_off when every query also keeps the block it lies in
+// itself; query_pos: null when query q sits at block-order position q, else the position of every query (queries kept in the caller's
+// token order).
+// Bound by the read of P.  The rows are one contiguous run of values, read flat with 16 loads in flight; a comparison of 64 of them is 64
+// bits of one flat mask in the LDS, from which a row's words are cut with two reads and a shift.  Neighbouring workgroups, whose counts
+// share cache lines, run on one XCD.  12 heads: 32 760 x 84 blocks 38.1 -> 29.2 us, 112 320 x 288, 1.7 GB, 375 -> 354 (375 without the
+// order of the workgroups); 32 x 6601 x 36 13.7 -> 10.9.  Before: 16-byte loads, the bits set by LDS atomics.
+constexpr int MASK_LOADS = 16;
 __global__ __launch_bounds__(256) void mask_kernel(const float* __restrict__ P, const HeadState* __restrict__ state,
                                                    const int* __restrict__ tie_base, unsigned int* __restrict__ mask,
                                                    int* __restrict__ wtot, int* __restrict__ wcnt,
                                                    int S, int nb, int n_waves, const int* __restrict__ own_blk_off,
                                                    const int* __restrict__ query_pos) {
-    __shared__ MaskLds lds[4];
-    const int bh = blockIdx.y, wv = threadIdx.x >> 6;
+    __shared__ unsigned long long sBits[4][VMOBA_MAX_BLOCKS + 1];
+    const int bh = blockIdx.y, lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wv;
+    if (w >= n_waves) return;
     const HeadState st = state[bh];
-    mask_rows(lds[wv], P, st, tie_base + (long long)bh * (S + 1), mask, wtot, wcnt, bh, blockIdx.x * 4 + wv, S, nb, n_waves,
-                                    own_blk_off, query_pos);
+    unsigned long long* bits = sBits[wv];
+    const int q0 = w * 64, words = (nb + 31) / 32, rows = min(64, S - q0), n_el = rows * nb;
+    const unsigned int* tile = reinterpret_cast<const unsigned int*>(P + ((long long)bh * S + q0) * nb);
+    // entries equal to theta: all kept, kept up to a position of the head's pool (last_kept_tie), or (rare) kept by rank
+    const bool whole = st.all || st.take == st.n_tie, ranked = !whole && st.need == TIE_RANKS;
+    const unsigned int least = st.all ? 0u : st.prefix + (whole ? 0u : 1u);
+    const long long last_tie = whole || ranked ? -1 : (long long)st.need - (long long)q0 * nb;      // in this tile
+    unsigned int rank = ranked ? (unsigned int)tie_base[(long long)bh * (S + 1) + q0] : 0u;
+    auto chunk = [&](int e0, auto full) {
+        unsigned int x[MASK_LOADS];
+#pragma unroll
+        for (int u = 0; u < MASK_LOADS; ++u) {
+            const int e = e0 + u * 64 + lane;
+            x[u] = decltype(full)::value || e < n_el ? tile[e] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < MASK_LOADS; ++u) {
+            if (!decltype(full)::value && e0 + u * 64 >= n_el) break;
+            unsigned long long keep = __ballot(x[u] >= least);          // (no row's words hold a bit past the run)
+            if (!whole) {
+                const unsigned long long tie = __ballot(x[u] == st.prefix);
+                if (tie) {
+                    const unsigned int before = __popcll(tie & ((1ull << lane) - 1ull));
+                    const bool in = ranked ? rank + before < st.take : e0 + u * 64 + lane <= last_tie;
+                    keep |= tie & __ballot(in);
+                    rank += __popcll(tie);
+                }
+            }
+            if (lane == 0) bits[(e0 >> 6) + u] = keep;
+        }
+    };
+    int e0 = 0;
+    for (; e0 + 64 * MASK_LOADS <= n_el; e0 += 64 * MASK_LOADS) chunk(e0, std::true_type{});
+    if (e0 < n_el) chunk(e0, std::false_type{});
+    asm volatile("" ::: "memory");
+    // lane = row
+    const int q = q0 + lane;
+    const bool live = lane < rows;
+    const int own = own_blk_off && live ? block_of_position(own_blk_off, nb, query_pos ? query_pos[q] : q) : -1;
+    int kept = 0;
+    for (int wd = 0; wd < words; ++wd) {
+        const int jn = min(32, nb - wd * 32);
+        unsigned int g = 0u;
+        if (live) {
+            const int at = lane * nb + wd * 32, sh = at & 63;
+            g = (unsigned int)(bits[at >> 6] >> sh | bits[(at >> 6) + 1] << 1 << (63 - sh)) & (~0u >> (32 - jn));
+            if (wd == (own >> 5)) g |= 1u << (own & 31);       // own = -1: no word matches
+            mask[((long long)bh * S + q) * words + wd] = g;
+        }
+        kept += count_word(g, wd, jn, wcnt, (long long)bh * nb, n_waves, w);
+    }
+    if (lane == 0) wtot[(long long)bh * n_waves + w] = kept;
 }
 
 // Common end of the per-query selections: lane = row of the wavefront's 64 queries, sKeep[row] its mask words.  Adds the
@@ -1333,35 +1275,21 @@ __device__ __forceinline__ void store_local_mask(const unsigned int (*sKeep)[VMO
                                                  int* __restrict__ wtot, int* __restrict__ wcnt, int bh, int w, int q0, int rows, bool active,
                                                  int S, int nb, int n_waves, const int* __restrict__ own_blk_off, const int* __restrict__ query_pos) {
     const int lane = threadIdx.x & 63, words = (nb + 31) / 32;
-    unsigned int mw[VMOBA_MAX_MASK_WORDS];
     const int q = q0 + lane;
     const bool live = lane < rows;
     const int own = (own_blk_off && live) ? block_of_position(own_blk_off, nb, query_pos ? query_pos[q] : q) : -1;
-#pragma unroll
-    for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {
+    if (!active) return;
+    int kept = 0;
+    for (int wd = 0; wd < words; ++wd) {
         unsigned int g = 0;
-        if (live && wd < words) {
+        if (live) {
             g = sKeep[lane][wd];
             if (wd == (own >> 5)) g |= 1u << (own & 31);
             mask[((long long)bh * S + q) * words + wd] = g;
         }
-        mw[wd] = g;
+        kept += count_word(g, wd, min(32, nb - wd * 32), wcnt, (long long)bh * nb, n_waves, w);
     }
-    int kept = 0;
-#pragma unroll
-    for (int wd = 0; wd < VMOBA_MAX_MASK_WORDS; ++wd) {
-        if (wd * 32 < nb) {
-            const unsigned int word = mw[wd];
-            const int jn = min(32, nb - wd * 32);
-            for (int bit = 0; bit < jn; ++bit) {
-                const int j = wd * 32 + bit;
-                const int c = __popcll(__ballot((word >> bit) & 1u));
-                kept += c;
-                if (lane == 0 && active) wcnt[((long long)bh * nb + j) * n_waves + w] = c;
-            }
-        }
-    }
-    if (lane == 0 && active) wtot[(long long)bh * n_waves + w] = kept;
+    if (lane == 0) wtot[(long long)bh * n_waves + w] = kept;
 }
 
 // Per-query ("local") selection, the block-choice variants of the paper's ablation and of its training-free runs.
@@ -1802,13 +1730,6 @@ __global__ __launch_bounds__(1024) void head_offsets_kernel(int* __restrict__ wc
                                                             int nb, int S, int n_waves, long long cap, int* __restrict__ dev_status, int write_k) {
     __shared__ int sTot[VMOBA_MAX_BLOCKS + 1];
     head_offsets(sTot, wcnt, wtot, blk_ptr, row_ptr, k_out, theta_out, blockIdx.x, nb, S, n_waves, cap, dev_status, write_k);
-}
-
-// Workgroup i of n runs on XCD i % 8; this index makes the workgroups of one XCD neighbours in the work list, so runs
-// that different workgroups write into the same cache line meet in one L2.
-__device__ __forceinline__ int xcd_contiguous(int i, int n) {
-    const int per = n / 8;
-    return i < per * 8 ? (i % 8) * per + i / 8 : i;
 }
 
 // Fill q_idx (block-major), col_idx and pair_pos (query-major).  One wavefront per 64 queries,
