@@ -365,13 +365,13 @@ def test_bf16_many_blocks_per_row(tau):
 
 
 @pytest.mark.parametrize("grid,block,mode,topk", [
-    ((5, 6, 20), (1, 1, 2), 0, 0),       # 300 blocks: a full chunk of 256 and one of 44
+    ((5, 6, 20), (1, 1, 2), 0, 0),       # 300 blocks: chunks of 152 and 148
     ((4, 16, 16), (1, 2, 1), 0, 0),      # 512 blocks, the most the library takes
     ((5, 6, 20), (1, 1, 2), 1, 7),       # per-query top-k over 300 blocks
     ((5, 6, 20), (1, 1, 2), 4, 0),       # pool soft-max over 300 blocks (row statistics from the chunked path)
 ])
 def test_bf16_more_than_256_blocks(grid, block, mode, topk):
-    """Beyond 256 blocks the score kernel runs once per chunk of 256 blocks and a second kernel normalises the rows;
+    """Beyond 256 blocks the score kernel runs once per chunk of at most 188 blocks and a second kernel normalises the rows;
     mask rows have up to 16 words."""
     S = grid[0] * grid[1] * grid[2]
     Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(330 + i, (1, S, 2, 128))) for i in range(4))
@@ -386,6 +386,10 @@ def test_bf16_more_than_256_blocks(grid, block, mode, topk):
     ((3, 7, 18), (1, 1, 2), 64),       # 189 blocks, the most with the pre-split means; D = 64
     ((2, 5, 38), (1, 1, 2), 128),      # 190 blocks: means kept as float32
     ((3, 101, 2), (1, 1, 2), 128),     # 303 blocks: chunked launches with rows of P not aligned
+    ((1, 257, 2), (1, 1, 2), 64),      # 257 blocks: chunks of 132 and 125; D = 64
+    ((4, 47, 4), (1, 1, 2), 128),      # 376 blocks: two chunks of 188, the largest
+    ((1, 13, 58), (1, 1, 2), 128),     # 377 blocks: two chunks of 128 and one of 121
+    ((4, 48, 4), (1, 1, 2), 64),       # 384 blocks: three chunks of 128, aligned; D = 64
     ((1, 7, 10), (1, 1, 2), 128),      # 35 blocks: two tiles, not aligned
     ((3, 7, 10), (1, 1, 2), 64),       # 105 blocks: four tiles, not aligned; D = 64
 ])
