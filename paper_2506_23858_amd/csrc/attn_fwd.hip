@@ -98,7 +98,11 @@ __global__ __launch_bounds__(256) void head_tiles_kernel(const int* __restrict__
 //
 // Keys in place (KVR).  K and V may stay where the caller has them: key position p of the block order is then row
 // kv_rows[p] of both.  The row numbers come by way of LDS, too (global_load_lds_dword): those of group g + 8 are requested
-// in step g, those of a tile's first groups two tiles ahead, and a row request takes its row number from there one step before it is issued.
+// in step g by every wavefront, those of a tile's first groups two tiles ahead, two groups by a wavefront, and a row request takes its row
+// number from there one step before it is issued.  A tile's last steps still request the numbers of groups past its end, into its own
+// ring, and those of the very last step may be on their way while the next tile's first step is worked on.  So that step fills a ring of which
+// no tile in sight nor the tile just ended has a share: four rings, tile t in ring t % 4.  (tests/test_forward_schedule.py plays
+// requests, waits and barriers and finds two requests for the same words that nothing orders, with three rings, and none with four.)
 //
 // NEG: the scores of -Q, for a negative scale (the scale given is its magnitude).
 struct FwdArgs {
@@ -139,9 +143,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
     constexpr int OPITCH = D * 2 + 16;
     constexpr int V0 = NR * SLOT, OUT0 = 2 * NR * SLOT, OUTW = 32 * OPITCH, IDX0 = OUT0 + NW * OUTW, DESC0 = IDX0 + 2 * NW * 64 * 4,
                   TOK0 = DESC0 + NW * 64 * 4;
-    // KVR: row numbers of the key groups of three tiles, rings of 16 groups (a request fills two)
-    constexpr int TOKS = 17 * G;
-    __shared__ __align__(1024) char smem[TOK0 + (KVR ? 3 * TOKS * 4 : 0)];
+    // KVR: row numbers of the key groups of the tile before, of this one and of the next two, rings of 16 groups (a request fills two)
+    constexpr int ROW_RINGS = 4, TOKS = 17 * G;
+    __shared__ __align__(1024) char smem[TOK0 + (KVR ? ROW_RINGS * TOKS * 4 : 0)];
     // requests and stores of a wavefront, always in this order: every step the rows of K and V (KVR: and row numbers); then, in a tile's
     // first step, (KVR: row numbers,) the partial rows and LSE of the tile before, a descriptor, list entries, query rows
     constexpr int N_STEP = KVR ? 3 : 2, N_FIRST = (KVR ? 1 : 0) + D * 2 * 32 / 1024 + 1 + 2 + 32 / RPI;
@@ -277,6 +281,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
     long long out_pair = 0;                // first pair and last entry of the tile before `cur`
     int out_last = -1;                     // -1: there is none
     int par = 0, tp = 0;                   // list-entry ring half and row-number ring of `cur`
+    auto ring_ahead = [&](int tiles) { return (tp + tiles) & (ROW_RINGS - 1); };
     request_entries(cur, 0);
     request_entries(nxt, 1);
     if constexpr (KVR) {
@@ -394,11 +399,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
                     begin_v(nxt);
                 }
                 if constexpr (KVR) {
-                    const int tn = tp == 2 ? 0 : tp + 1;
+                    const int tn = ring_ahead(1);
                     dma_row16<0>(k_base, krow, kss, pc16, lds_rows + r0);
                     dma_row16<V0>(v_base, vrow, vss, pc16, lds_rows + r2);
                     // for the next step (after the last one: group 4 of the next tile or, if that has no more than four, the first of the one behind it)
-                    if (WHICH == LAST && groups_of(nxt) == 4) krow = row_number(0, tp == 0 ? 2 : tp - 1);
+                    if (WHICH == LAST && groups_of(nxt) == 4) krow = row_number(0, ring_ahead(2));
                     else krow = g + 5 < Ge ? row_number(g + 5, tp) : row_number(g + 5 - Ge, tn);
                     vrow = g + 3 < Ge ? row_number(g + 3, tp) : row_number(g + 3 - Ge, tn);
                     // every wavefront by itself: its row numbers then need no barrier and all waits the same count
@@ -468,7 +473,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
     using Last = std::integral_constant<int, LAST>;
     for (;;) {
         step(First{}, sA, sB, pB, pA);
-        if constexpr (KVR) request_first_row_numbers(nn, tp == 0 ? 2 : tp - 1);
+        if constexpr (KVR) request_first_row_numbers(nn, ring_ahead(2));
         if (__builtin_expect(out_last >= 0, 1)) write_partials();
         request_descriptor(f_next);
         request_entries(nn, par);
@@ -503,7 +508,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
         g = 0;
         Ge = groups_of(cur);
         par ^= 1;
-        tp = tp == 2 ? 0 : tp + 1;
+        tp = ring_ahead(1);
     }
     // second product of the last tile's last group
     VMOBA_WAIT_VMCNT(0);                   // (no request may reach LDS that belongs to another workgroup by the kernel's end, either)

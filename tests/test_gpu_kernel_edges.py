@@ -128,6 +128,26 @@ def test_bf16_forward_over_many_tiles(chunk, D):
             gu.check_output(f"bf16-tiles-{chunk}-{D}", "O", g["Op"][0, h], O, torch.bfloat16)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [390, 480, 512])
+def test_bf16_forward_in_place_over_many_long_tiles(chunk, D):
+    """Blocks of 13, 15 and 16 key groups found through kv_rows, each workgroup walking at least three tiles: the row numbers of a tile are requested while
+    two earlier ones are worked on.  Every head gives the bits that rearranged keys give; some against the oracle."""
+    grid, S, heads, tau = (1, 30, 52), 1560, 48, 0.9
+    Q, K, V = (synth.to_bf16_grid(synth.iid_normal(1080 + i, (1, S, heads, D))) for i in range(3))
+    g, r = (gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), chunk, tau, torch.bfloat16, kv_in_place=kv, q_in_place=True) for kv in (True, False))
+    TM, per_cu = (256, 1) if D == 128 else (128, 2)
+    tiles = int((-(-np.diff(g["blk_ptr"]) // TM)).sum())
+    assert tiles >= 3 * per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    assert np.array_equal(g["mask"], r["mask"]) and np.array_equal(g["LSE"], r["LSE"]) and np.array_equal(g["O"], r["O"])
+    for h in (0, 24, 47):
+        q, k, v = (x[0, g["perm"], h].astype(np.float64) for x in (Q, K, V))
+        O, LSE = vo.masked_attention_fwd(q, k, v, g["mask"][0, h], g["blk_off"], 1.0 / math.sqrt(D))
+        live = np.isfinite(LSE)
+        gu.check_output(f"bf16-in-place-{chunk}-{D}", "LSE", g["LSE"][0, h][live], LSE[live], torch.bfloat16)
+        gu.check_output(f"bf16-in-place-{chunk}-{D}", "O", g["Op"][0, h], O, torch.bfloat16)
+
+
 def test_bf16_forward_takes_query_rows_far_apart():
     """Rows of Q 16 MB and more apart (their offsets do not fit 32 bits) give the same bits as rows that are neighbours."""
     grid, S, D, pitch = (1, 8, 40), 320, 128, (1 << 23) + 8
