@@ -62,7 +62,8 @@ __global__ __launch_bounds__(256) void head_tiles_kernel(const int* __restrict__
 // S^T and P live in two register sets that swap roles every step.  A tile's last step computes S^T of the next tile's first group, and the
 // next tile's first step ends the tile's second product: no steps with half of the work missing at a tile's ends.  A tile
 // counts as at least four groups (surplus ones are masked like the keys past a block's end), which is what the look-ahead of the
-// row requests needs.
+// row requests needs.  The value rows of a group without a key are zeros: repeating the block's last row would turn an infinity in it into weight 0
+// times infinity, which is no number.
 //
 // What bounds it: two wavefronts of a SIMD together issue one instruction, scalar ones and waits included, every 4.5 cycles or so, and the clock
 // falls as the rate rises (1.8 GHz here, 2.4 without load).  A step is 150 instructions for 16 matrix instructions (165 before): row
@@ -105,6 +106,7 @@ __global__ __launch_bounds__(256) void head_tiles_kernel(const int* __restrict__
 // requests, waits and barriers and finds two requests for the same words that nothing orders, with three rings, and none with four.)
 //
 // NEG: the scores of -Q, for a negative scale (the scale given is its magnitude).
+__device__ const u32x4_t zero_row[16] = {};        // one row of 128 channels
 struct FwdArgs {
     TensorView Q, K, V;
     const int* q_idx;
@@ -236,6 +238,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
     const int dr = wave * RPI + lane / PPR;
     const uint32_t kss = (uint32_t)(by_value.K.stride_s * 2), vss = (uint32_t)(by_value.V.stride_s * 2);
     const uint32_t k_adv = G * kss, v_adv = G * vss;
+    uint32_t krow = 0, vrow = 0;           // KVR: rows of the next request of K and of V, read from the ring a step before
     const char *k_base, *v_base;
     uint32_t k_off = 0, v_off = 0, k_last = 0, v_last = 0;
     auto begin_k = [&](const FwdTile& t) {
@@ -248,6 +251,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
         v_off = (uint32_t)(t.k0 + dr) * vss + pc16;
         v_last = (uint32_t)(t.k0 + t.L - 1) * vss + pc16;
     };
+    // the next value rows requested, for a group without a key, are zeros (until begin_v)
+    auto zero_v = [&]() {
+        v_base = reinterpret_cast<const char*>(zero_row);
+        v_off = v_last = pc16;
+        vrow = 0;
+    };
     // KVR: row numbers of groups x and x + 1 of tile t into ring `tb` (keys past the block's end repeat its last one)
     auto request_row_numbers = [&](const FwdTile& t, int x, int tb) {
         dma4(reinterpret_cast<const char*>(kv_rows), (uint32_t)(t.k0 + min(x * G + lane, t.L - 1)) << 2,
@@ -257,8 +266,6 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
     auto request_first_row_numbers = [&](const FwdTile& t, int tb) { request_row_numbers(t, 2 * (wave & 3), tb); };
     // KVR: row of K and V that this lane requests of group x of the tile of ring `tb`
     auto row_number = [&](int x, int tb) { return (uint32_t) reinterpret_cast<const int*>(smem + TOK0)[tb * TOKS + (x & 15) * G + dr]; };
-    uint32_t krow = 0, vrow = 0;           // KVR: rows of the next request of K and of V, read from the ring a step before
-
     uint32_t rlane[TL::NRB], tlane[2][TL::NTB];
 #pragma unroll
     for (int k = 0; k < TL::NRB; ++k) rlane[k] = TL::row_lane(lane, k);
@@ -294,9 +301,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
     begin_v(cur);
     static_for<4>([&](auto x) {
         constexpr int X = decltype(x)::value;
+        if constexpr (KVR && X < 2) vrow = row_number(X, 0);
+        if (X == 1 && cur.L <= G) zero_v();
         if constexpr (KVR) {
             dma_row16<X * SLOT>(k_base, row_number(X, 0), kss, pc16, lds_rows);
-            if constexpr (X < 2) dma_row16<V0 + X * SLOT>(v_base, row_number(X, 0), vss, pc16, lds_rows);
+            if constexpr (X < 2) dma_row16<V0 + X * SLOT>(v_base, vrow, vss, pc16, lds_rows);
         } else {
             dma16_advance(k_base, min(k_off, k_last), k_off, k_adv, lds_rows, X * SLOT);
             if constexpr (X < 2) dma16_advance(v_base, min(v_off, v_last), v_off, v_adv, lds_rows, V0 + X * SLOT);
@@ -397,6 +406,11 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
                     if (__builtin_expect(g == Ge - 4, 0)) begin_k(nxt);
                 } else if constexpr (WHICH == BEFORE_LAST) {
                     begin_v(nxt);
+                }
+                if constexpr (WHICH == FIRST || WHICH == SECOND) {
+                    if (__builtin_expect((g + 2) * G >= cur.L, 0)) zero_v();
+                } else if constexpr (WHICH == LAST) {
+                    if (__builtin_expect(nxt.L <= G, 0)) zero_v();
                 }
                 if constexpr (KVR) {
                     const int tn = ring_ahead(1);

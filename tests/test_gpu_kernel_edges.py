@@ -148,6 +148,25 @@ def test_bf16_forward_in_place_over_many_long_tiles(chunk, D):
         gu.check_output(f"bf16-in-place-{chunk}-{D}", "O", g["Op"][0, h], O, torch.bfloat16)
 
 
+@pytest.mark.parametrize("kv_in_place", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("chunk", [32, 64, 96, 128, 160])
+def test_bf16_forward_keeps_an_infinity_of_a_block_of_whole_groups(chunk, D, kv_in_place):
+    """An infinite channel in the last value row of a block of 1 to 5 key groups, without a key missing in the last one: infinite for the queries
+    that keep the block (NaN if it is the last one they keep: the merge meets it again with weight 0), and nothing else changes."""
+    grid, S, heads, channel = (1, 1, 3 * chunk), 3 * chunk, 4, 5
+    Q, K, V = (synth.to_bf16_grid(synth.iid_normal(1090 + i, (1, S, heads, D))) for i in range(3))
+    finite = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), chunk, 0.5, torch.bfloat16, kv_in_place=kv_in_place)
+    V[0, chunk - 1, :, channel] = np.inf
+    g = gu.run_gpu(Q, K, V, None, grid, (0, 0, 0), chunk, 0.5, torch.bfloat16, kv_in_place=kv_in_place)
+    keeps, others = g["mask"][0, :, :, 0], g["mask"][0, :, :, 1:].any(-1)
+    assert np.array_equal(g["mask"], finite["mask"]) and np.array_equal(g["LSE"], finite["LSE"])
+    assert (keeps & others).any() and not keeps.all() and np.all(g["Op"][0, ..., channel][keeps & others] == np.inf)
+    assert not np.isfinite(g["Op"][0, ..., channel][keeps]).any()
+    g["Op"][0, ..., channel][keeps] = finite["Op"][0, ..., channel][keeps]
+    assert np.array_equal(g["Op"], finite["Op"])
+
+
 def test_bf16_forward_takes_query_rows_far_apart():
     """Rows of Q 16 MB and more apart (their offsets do not fit 32 bits) give the same bits as rows that are neighbours."""
     grid, S, D, pitch = (1, 8, 40), 320, 128, (1 << 23) + 8
