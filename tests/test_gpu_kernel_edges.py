@@ -167,6 +167,28 @@ def test_bf16_forward_keeps_an_infinity_of_a_block_of_whole_groups(chunk, D, kv_
     assert np.array_equal(g["Op"], finite["Op"])
 
 
+@pytest.mark.parametrize("kv_in_place", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("grid,block,chunk", [
+    ((1, 8, 50), (0, 0, 0), 1), ((1, 8, 50), (0, 0, 0), 31), ((1, 8, 50), (0, 0, 0), 32), ((1, 8, 50), (0, 0, 0), 33),
+    ((1, 8, 50), (0, 0, 0), 63), ((1, 8, 50), (0, 0, 0), 64),
+    ((5, 9, 9), (4, 8, 8), 0),         # 50 keys on average: one block of 256, others of 64, 32, 8, 4 and 1
+])
+def test_bf16_forward_of_short_blocks(grid, block, chunk, D, kv_in_place):
+    """Calls whose usual block has at most 64 keys skip what groups without a key have to do: blocks of one key, around one and two whole groups, and
+    short ones beside one of eight groups, over many tiles of 64 heads."""
+    S, heads = grid[0] * grid[1] * grid[2], 64
+    Q, K, V = (synth.to_bf16_grid(synth.iid_normal(1100 + i, (1, S, heads, D))) for i in range(3))
+    for scale, tau in ((None, 0.6), (0.5, 0.95)):
+        g = gu.run_gpu(Q, K, V, None, grid, block, chunk, tau, torch.bfloat16, softmax_scale=scale, kv_in_place=kv_in_place)
+        for h in (0, 31, 63):
+            q, k, v = (x[0, g["perm"], h].astype(np.float64) for x in (Q, K, V))
+            O, LSE = vo.masked_attention_fwd(q, k, v, g["mask"][0, h], g["blk_off"], 1.0 / math.sqrt(D) if scale is None else scale)
+            live = np.isfinite(LSE)
+            gu.check_output(f"bf16-short-{chunk}-{D}", "LSE", g["LSE"][0, h][live], LSE[live], torch.bfloat16)
+            gu.check_output(f"bf16-short-{chunk}-{D}", "O", g["Op"][0, h], O, torch.bfloat16)
+
+
 def test_bf16_forward_takes_query_rows_far_apart():
     """Rows of Q 16 MB and more apart (their offsets do not fit 32 bits) give the same bits as rows that are neighbours."""
     grid, S, D, pitch = (1, 8, 40), 320, 128, (1 << 23) + 8
