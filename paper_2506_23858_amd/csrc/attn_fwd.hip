@@ -528,7 +528,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
         if constexpr (SHORT) surplus = (Ge - 1) * G >= cur.L;
         out_pair = cur.pair;
         out_last = cur.count - 1;
-        if (--tiles_left == 0) break;
+        // (SHORT leaves at the loop's end: from here the compiler copies registers whose values nothing uses, and in that form it does so right
+        // behind matrix instructions that may still be writing them)
+        if (!SHORT && --tiles_left == 0) break;
         const u32x4_t d = *reinterpret_cast<const u32x4_t*>(smem + DESC0 + wave * 256);
         cur = nxt;
         nxt = nn;
@@ -539,6 +541,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_fwd_tile_mfma_kernel(Fwd
         Ge = groups_of(cur);
         par ^= 1;
         tp = ring_ahead(1);
+        if (SHORT && --tiles_left == 0) break;
     }
     // second product of the last tile's last group
     VMOBA_WAIT_VMCNT(0);                   // (no request may reach LDS that belongs to another workgroup by the kernel's end, either)
