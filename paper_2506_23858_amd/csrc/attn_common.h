@@ -230,10 +230,11 @@ __device__ __forceinline__ void dma16(const char* base, uint32_t byte_off, uint3
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_addr)
                  : "memory", "m0");
 }
-// The same to lds_addr + lds_off, and next += advance: m0 may not be read right after it was written, so the addition stands between.
+// The same to lds_addr + lds_off, and next += advance: m0 may not be read right after it was written, so the addition stands between, and
+// byte_off, read behind it, may not share next's register (&).
 __device__ __forceinline__ void dma16_advance(const char* base, uint32_t byte_off, uint32_t& next, uint32_t advance, uint32_t lds_addr, uint32_t lds_off) {
     asm volatile("s_add_u32 m0, %3, %4\n\tv_add_u32 %0, %5, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 : "+v"(next) : "v"(byte_off), "s"(base), "s"(lds_addr), "s"(lds_off), "s"(advance) : "memory", "m0", "scc");
+                 : "+&v"(next) : "v"(byte_off), "s"(base), "s"(lds_addr), "s"(lds_off), "s"(advance) : "memory", "m0", "scc");
 }
 // The same from any address per lane.
 __device__ __forceinline__ void dma16_at(const char* src, uint32_t lds_addr) {

@@ -7,6 +7,7 @@ reads, and checks every word: what is read was requested for this purpose and ha
 import os
 import random
 import re
+import subprocess
 
 import pytest
 
@@ -189,3 +190,19 @@ def test_the_check_sees_a_ring_that_is_taken_too_early():
     beside the first eight."""
     assert any("on its way" in f for f in play([390] * 4, 4, 64, True, 3))
     assert not play([256] * 4, 4, 64, True, 3)
+
+
+def test_a_request_that_advances_an_offset_loads_from_the_old_one(tmp_path):
+    """dma16_advance adds before it loads, so the offset loaded from needs a register of its own, also where it is the one that is advanced."""
+    (tmp_path / "k.hip").write_text('''#include "attn_common.h"
+__global__ void k(const char* base, uint32_t* off, uint32_t advance, uint32_t lds) {
+    uint32_t o = off[threadIdx.x];
+    dma16_advance(base, o, o, advance, lds, 0);
+    off[threadIdx.x] = o;
+}''')
+    subprocess.run([build.HIPCC] + [f for f in build.FLAGS if f != "-shared"] + ["--cuda-device-only", "-S", "k.hip", "-o", "k.s"], check=True, cwd=tmp_path,
+                   capture_output=True)
+    asm = (tmp_path / "k.s").read_text()
+    advanced, = re.findall(r"\bs_add_u32 m0, .*\n\s*v_add_u32(?:_e32)? (v\d+),", asm)
+    loaded, = re.findall(r"\bglobal_load_lds_dwordx4 (v\d+),", asm)
+    assert advanced != loaded
