@@ -1071,12 +1071,12 @@ __global__ __launch_bounds__(256) void dq_merge_kernel(const float* __restrict__
 struct BwdWs {
     float* dQpart;     // [BH * cap][D], in the tensors' type
     float* delta;      // LSE * log2(e) and -delta, [BH][2][lse_delta_pitch(S)]
-    int4* tile_desc;   // the flat list of all heads' tiles
-    int* n_tiles;      // its length, then the split kernels' flag
+    int* n_tiles;      // length of the tile list, then the split kernels' flag
     int* head_tiles;   // [BH]
-    int* kb_start;     // [BH][nb + 1]
-    int* kb_order;     // [BH][nb]
-    int4* slot_desc;   // [BH][dkv_slots], filled for the matrix-core dK/dV kernel (the size does not depend on the type)
+    int4* tile_desc;   // the flat list of all heads' tiles
+    int* kb_start;     // float32: [BH][nb + 1]
+    int* kb_order;     // float32: [BH][nb]
+    int4* slot_desc;   // bfloat16: [BH][dkv_slots]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
     char* QD6;         // split kernels: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
     char* KV6;
@@ -1096,18 +1096,27 @@ DkvSlots dkv_slots(int64_t S, int nb, int KPW, bool bf16) {
     return d;
 }
 
+constexpr int BWD_TM = 128;                   // queries per dQ tile
+
 BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int nb, int64_t cap, int es, bool split) {
     BwdWs w;
     char* p = (char*)base;
     size_t off = 0;
     w.dQpart = (float*)(p + off);    off += align_up((size_t)BH * cap * D * es, 256);
     w.delta = (float*)(p + off);     off += align_up((size_t)BH * 2 * (size_t)lse_delta_pitch((int)S) * 4, 256);
-    w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
     w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
-    w.kb_start = (int*)(p + off);    off += align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256);
-    w.kb_order = (int*)(p + off);    off += align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
-    w.slot_desc = (int4*)(p + off);  off += align_up((size_t)BH * dkv_slots(S, nb, 128, true).slots * 16, 256);
+    // The tile list and what the dK/dV kernels find their work by.  The slots of a bfloat16 call lie behind the tiles that there can be and in the
+    // place of the float32 kernels' arrays, so that they need scratch of their own only for calls of many blocks and few pairs.
+    w.tile_desc = (int4*)(p + off);
+    const size_t list = align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256), start = align_up((size_t)BH * (VMOBA_MAX_BLOCKS + 1) * 4, 256),
+                 order = align_up((size_t)BH * VMOBA_MAX_BLOCKS * 4, 256);
+    w.kb_start = (int*)(p + off + list);
+    w.kb_order = (int*)(p + off + list + start);
+    const size_t tiles = align_up((size_t)BH * (cap / BWD_TM + nb) * 16, 256);
+    w.slot_desc = (int4*)(p + off + tiles);
+    off += list + start + order;
+    if (es == 2) off = std::max(off, (size_t)((char*)w.slot_desc - p) + align_up((size_t)BH * dkv_slots(S, nb, 128, true).slots * 16, 256));
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
     w.QD6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
@@ -1164,7 +1173,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     }
 
     // ---- delta, tile list, key runs
-    const int TM = 128;                     // queries per dQ tile
+    const int TM = BWD_TM;
     int* const out_of_range = ws.n_tiles + 1;
     const int KPW = bf16 || split ? 128 : 64;        // keys per dK/dV workgroup
     const DkvSlots dkv = dkv_slots(S, n_blocks, KPW, bf16);

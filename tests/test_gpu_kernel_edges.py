@@ -38,6 +38,15 @@ def test_bf16_backward_kernels_at_tile_edges(chunk, D):
         compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.bfloat16, f"bf16-edges-{chunk}", kv_in_place=kv_in_place)
 
 
+@pytest.mark.parametrize("chunk,topk", [(1, 2), (1, 3), (2, 1), (2, 256)])
+def test_bf16_backward_of_many_blocks_and_few_pairs(chunk, topk):
+    """512 and 256 blocks: the slots of the dK/dV kernel need more room than the tile list leaves, and
+    less.  (Every query keeps two keys at least: of a single one dQ is 0 and dK nothing but rounding.)"""
+    grid, S = (1, 16, 32), 512
+    Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(1140 + i, (1, S, 3, 64))) for i in range(4))
+    compare_layer(Q, K, V, dO, grid, (0, 0, 0), chunk, 0.4, torch.bfloat16, f"slots-{chunk}", mode=1, topk=topk)
+
+
 @pytest.mark.parametrize("mode,topk", [(1, 1), (1, 5), (1, 1000), (2, 0), (0x101, 3)])
 @pytest.mark.parametrize("chunk", [48, 43, 42, 6, 5, 3, 2, 1])
 def test_local_selections_at_column_counts(chunk, mode, topk):

@@ -107,3 +107,15 @@ def test_float32_workspace_holds_split_planes_only_where_they_are_used(op, rows,
     assert 0 <= extra(*small) < 1024
     assert 0 <= extra(*large) - planes * 128 * 12 * 14080 < 1024
     assert 0 <= extra(*huge) < 1024
+
+
+def test_backward_workspace_has_no_slot_table_of_its_own():
+    """Beyond LSE, delta and dO's copy a backward call's scratch does not grow with the rows: float32 reads no slot table, and that of a
+    bfloat16 call finds room in the tile list's place, unless there are many blocks and few pairs."""
+    def size(S, dtype, nb=36, cap=1 << 24):
+        return vb.vmoba_workspace_bytes(vb.OP_ATTN_BWD, 1, 1, S, 128, nb, cap, dtype)
+    S, more = 3 << 20, 128 * 1000
+    for dtype, es in ((vb.VMOBA_F32, 4), (vb.VMOBA_BF16, 2)):
+        assert size(S + more, dtype) - size(S, dtype) == more * (2 * 4 + 128 * es)
+    assert size(1024, vb.VMOBA_F32, 512, 1024) - size(1024, vb.VMOBA_F32, 36, 1024) == 0
+    assert size(1024, vb.VMOBA_BF16, 512, 1024) > size(1024, vb.VMOBA_BF16, 36, 1024)
