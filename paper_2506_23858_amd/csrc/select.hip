@@ -262,11 +262,11 @@ __global__ __launch_bounds__(256) void score_kernel(TensorView Q, const float* _
 // by ~4e-3.  S^T[block, q] = sum over the three terms of Bx[block, :] . Q[q, :], with the query on
 // the MFMA column (= lane % 32), so the soft-max over blocks is a reduction over a lane's own
 // registers plus one exchange with lane ^ 32.  SCORE_NW wavefronts x 32 queries per tile.
-// With more than 128 blocks the three bfloat16 copies no longer fit the LDS; FLY keeps the means there as float32 (row
-// stride D + 4) and splits every operand after its fetch: the same three terms from the same operations, so P is the
+// With more than 189 blocks (192 at 64 channels) the three bfloat16 copies no longer fit the LDS; FLY keeps the means there as
+// float32 (row stride D + 4) and splits every operand after its fetch: the same three terms from the same operations, so P is the
 // same, at the price of vector work per matrix instruction.
-// With more than 256 blocks neither the means nor a query's scores fit: the host then launches the kernel once per
-// chunk of up to 256 blocks with RAW set -- the launch covers blocks [jb0, jb0 + nb) of nb_total and writes the scaled
+// With more than 256 blocks a query's scores no longer fit: the host then launches the kernel once per
+// chunk of at most 188 blocks, whose terms fit, with RAW set -- the launch covers blocks [jb0, jb0 + nb) of nb_total and writes the scaled
 // scores themselves into its columns of P -- and softmax_rows_kernel below turns the rows into P afterwards.
 // wavefronts per workgroup of the matrix-core score kernel (two per SIMD share one copy of the block means in LDS)
 constexpr int SCORE_NW = 8, SCORE_NT = 64 * SCORE_NW, SCORE_QT = 32 * SCORE_NW;
@@ -309,10 +309,10 @@ template <bool FIRST, class T>
 __device__ __forceinline__ T& pick_ref(T& a, T& b) {
     if constexpr (FIRST) return a; else return b;
 }
-// NMT > 0: the number of 32-block tiles is that constant (the launch for up to 128 blocks picks the instantiation), so the
-// loops over tiles carry no run-time tests and only the last tile knows padding blocks; NMT = 0: read from nb.
+// NMT > 0: the number of 32-block tiles is that constant (a launch with terms picks the instantiation), so the
+// loops over tiles carry no run-time tests and only the last tile knows padding blocks; NMT = 0 (FLY): read from nb.
 // TR: the accumulators hold S^T (blocks down a lane's registers, the query on the lane: the soft-max of a row is in-lane,
-// and a lane stores 16-byte runs of its row of P) -- needs rows of P that start 16-byte aligned (N_b a multiple of 4).
+// and a lane stores 16-byte runs of its row of P) -- for rows of P that start 16-byte aligned (N_b a multiple of 4), and FLY.
 // !TR: they hold S (queries down the registers, the block on the lane): a store instruction then writes 128-byte runs of
 // two rows with 4-byte pieces whatever N_b is, and the row maximum and sum take a reduction over 32 lanes.
 template <int D, bool FLY, bool RAW, int NMT, bool TR>
@@ -328,7 +328,8 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
     constexpr int STR = D + 8;                 // LDS row stride in bf16 elements
     constexpr int FSTR = D + 4;                // LDS row stride in float elements (FLY)
     constexpr int KSTEPS = D / 16;
-    constexpr int MAX_MT = NMT > 0 ? NMT : (FLY ? 8 : 4);        // up to 256 / 128 blocks
+    static_assert(FLY == (NMT == 0) && !(FLY && (RAW || !TR)), "one launch with float32 means, or terms of a known number of tiles");
+    constexpr int MAX_MT = FLY ? 8 : NMT;                        // FLY: up to 256 blocks
     extern __shared__ __align__(16) unsigned char smem[];
     const int nb_pad = NMT > 0 ? NMT * 32 : ((nb + 31) & ~31);
     const int n_mt = NMT > 0 ? NMT : nb_pad / 32;
@@ -613,15 +614,15 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
 #pragma unroll
                         for (int g = 0; g < 4; ++g) {
                             const int j0 = mt * 32 + 8 * g + 4 * hf;
-                            if (vec_ok && (tile_full(mt) || 8 * g + 3 < lim)) {
+                            if (tile_full(mt) || 8 * g < lim) {          // (the number of blocks and that of a chunk are multiples of four)
                                 const f32x4_t o = {acc[mt][4 * g] * score_scale, acc[mt][4 * g + 1] * score_scale,
                                                    acc[mt][4 * g + 2] * score_scale, acc[mt][4 * g + 3] * score_scale};
                                 *reinterpret_cast<f32x4_t*>(dst + j0) = o;
-                            } else {
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) if (tile_full(mt) || 8 * g + r < lim) dst[j0 + r] = acc[mt][4 * g + r] * score_scale;
                             }
                         }
+                        // tile by tile: with the products of all tiles before the first store, a launch for 144 blocks of 12 heads x 112 320
+                        // tokens takes 389 us instead of 334
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
@@ -1915,7 +1916,7 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
     const bool pool_softmax = mode == VMOBA_POOL_SOFTMAX_THRESHOLD;
     const bool bf16 = Qp->dtype == VMOBA_BF16;
     // LDS of the score kernel this call launches: bfloat16 queries go to the matrix-core kernel (block means as three
-    // bfloat16 terms up to 128 blocks, as float32 beyond), float32 queries to the plain FMA kernel
+    // bfloat16 terms while they fit, as float32 up to 256 blocks, as terms of a chunk beyond), float32 queries to the plain FMA kernel
     // Beyond 256 blocks several launches write the scaled scores of a chunk of the blocks each: the fewest chunks whose means fit the
     // LDS as terms (188 blocks; every launch reads all queries again), of equal size, a multiple of 4 for the sake of 16-byte stores.
     // 288 blocks, 12 heads x 112 320 tokens: 723 -> 610 us (chunks of 256 and 32, means as float32, split after every fetch)
@@ -1992,31 +1993,31 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
                                                 score_scale, fix_shift, copy_shift, row_stat);            \
     } while (0)
         // rows of P that start 16-byte aligned take the kernel with the query on the lane, others the one with the block there
-#define LAUNCH_SCORE_MFMA(DD, FL, RW, NM, NBC, JB0)                                                       \
+        // (not FLY: eight accumulator tiles leave no registers for the reduction's row values)
+#define LAUNCH_SCORE_MFMA(DD, RW, NM, NBC, JB0)                                                           \
     do {                                                                                                  \
-        /* (193..256 blocks in one launch: eight accumulator tiles leave no registers for the reduction's row values) */ \
-        if ((n_blocks & 3) == 0 || (FL && !RW)) LAUNCH_SCORE_MFMA_T(DD, FL, RW, NM, true, NBC, JB0);      \
-        else LAUNCH_SCORE_MFMA_T(DD, FL, RW, NM, false, NBC, JB0);                                        \
+        if ((n_blocks & 3) == 0) LAUNCH_SCORE_MFMA_T(DD, false, RW, NM, true, NBC, JB0);                  \
+        else LAUNCH_SCORE_MFMA_T(DD, false, RW, NM, false, NBC, JB0);                                     \
     } while (0)
         // the bf16 terms fit: one instantiation per number of 32-block tiles
 #define LAUNCH_SCORE_TILES(DD)                                                                            \
     do {                                                                                                  \
         switch ((n_blocks + 31) / 32) {                                                                   \
-            case 1: LAUNCH_SCORE_MFMA(DD, false, false, 1, n_blocks, 0); break;                           \
-            case 2: LAUNCH_SCORE_MFMA(DD, false, false, 2, n_blocks, 0); break;                           \
-            case 3: LAUNCH_SCORE_MFMA(DD, false, false, 3, n_blocks, 0); break;                           \
-            case 4: LAUNCH_SCORE_MFMA(DD, false, false, 4, n_blocks, 0); break;                           \
-            case 5: LAUNCH_SCORE_MFMA(DD, false, false, 5, n_blocks, 0); break;                           \
-            default: LAUNCH_SCORE_MFMA(DD, false, false, 6, n_blocks, 0); break;                          \
+            case 1: LAUNCH_SCORE_MFMA(DD, false, 1, n_blocks, 0); break;                                  \
+            case 2: LAUNCH_SCORE_MFMA(DD, false, 2, n_blocks, 0); break;                                  \
+            case 3: LAUNCH_SCORE_MFMA(DD, false, 3, n_blocks, 0); break;                                  \
+            case 4: LAUNCH_SCORE_MFMA(DD, false, 4, n_blocks, 0); break;                                  \
+            case 5: LAUNCH_SCORE_MFMA(DD, false, 5, n_blocks, 0); break;                                  \
+            default: LAUNCH_SCORE_MFMA(DD, false, 6, n_blocks, 0); break;                                 \
         }                                                                                                 \
     } while (0)
         // a chunk holds 4 to 6 tiles of 32 blocks
 #define LAUNCH_SCORE_RAW(DD)                                                                              \
     do {                                                                                                  \
         switch ((nbc + 31) / 32) {                                                                        \
-            case 4: LAUNCH_SCORE_MFMA(DD, false, true, 4, nbc, jb0); break;                               \
-            case 5: LAUNCH_SCORE_MFMA(DD, false, true, 5, nbc, jb0); break;                               \
-            case 6: LAUNCH_SCORE_MFMA(DD, false, true, 6, nbc, jb0); break;                               \
+            case 4: LAUNCH_SCORE_MFMA(DD, true, 4, nbc, jb0); break;                                      \
+            case 5: LAUNCH_SCORE_MFMA(DD, true, 5, nbc, jb0); break;                                      \
+            case 6: LAUNCH_SCORE_MFMA(DD, true, 6, nbc, jb0); break;                                      \
             default: return VMOBA_ERR_UNSUPPORTED;                                                        \
         }                                                                                                 \
     } while (0)
@@ -2030,9 +2031,9 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
             }
             softmax_rows_kernel<<<dim3((unsigned)std::max<int64_t>(std::min<int64_t>(ceil_div64(S, 4 * 8), 2048), ceil_div64(S, SOFTMAX_MAX_ROWS)), (unsigned)BH), dim3(256), 0, st>>>(
                 P, score_hist, ws.hist_sum, (int)S, n_blocks, fix_shift, row_stat);
-        } else if (D == 128 && fly) LAUNCH_SCORE_MFMA(128, true, false, 0, n_blocks, 0);
+        } else if (D == 128 && fly) LAUNCH_SCORE_MFMA_T(128, true, false, 0, true, n_blocks, 0);
         else if (D == 128) LAUNCH_SCORE_TILES(128);
-        else if (fly) LAUNCH_SCORE_MFMA(64, true, false, 0, n_blocks, 0);
+        else if (fly) LAUNCH_SCORE_MFMA_T(64, true, false, 0, true, n_blocks, 0);
         else LAUNCH_SCORE_TILES(64);
 #undef LAUNCH_SCORE_RAW
 #undef LAUNCH_SCORE_TILES
