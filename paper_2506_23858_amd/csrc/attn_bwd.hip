@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 //   memory:  rows, LSE and delta of half-chunk hc + 5, list entries of half-chunk hc + 8, straight into LDS.
 // The rows are requested by wavefronts 1 alone: wavefronts 0 have the exponentials and were 200 of 1740 cycles behind at every barrier
 // (now 1650 cycles a step, 1024 of them matrix instructions; the clock is at 1.57 GHz then, 2.4 without load).  -delta is the value the sums for dP
-// start from: 32 additions a step less.  Backward calls of 14 040 tokens x 12 heads x 128 / 2 x 6601 x 16 x 64, with the slot descriptors
+// start from: 32 additions a step less (by itself 0.3 % of a training step).  Backward calls of 14 040 tokens x 12 heads x 128 / 2 x 6601 x 16 x 64, with the slot descriptors
 // and the row-wise output: 737 / 540 -> 720 / 521 us; 480p, 1D / 2D / 3D: -1 / -1 / -2 %.
 //
 // Everything the walk reads goes from global memory to LDS without passing through registers (global_load_lds): rings of
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_mfma_kernel(
 // so what step s requested is visible from step s + 3 on.  The loop holds no other global loads, so the count of
 // the wait is exact.  (Before: staged through registers -- 8 row loads and 8 LDS writes per wavefront and chunk of
 // 64, 32 registers of rows in flight and the copies from and to the accumulator registers that these forced, 7.1 and 8.6
-// instructions per matrix instruction for the two wavefronts of a pair, now 6.0 and 7.7.  480p, 12 heads, 1D / 2D / 3D partition:
+// instructions per matrix instruction for the two wavefronts of a pair, 6.0 and 7.7 then and, with the above, 5.5 and 5.9 now.  480p, 12 heads, 1D / 2D / 3D partition:
 // 2.80 / 2.66 / 2.13 -> 2.62 / 2.46 / 2.00 ms.  Timing variants of this form: without the row requests -5 %, without the
 // barrier as well -11 %, without the operand reads from LDS -13 %: no single limiter.)
 // Rows past the end of the list repeat its last entry; their LSE is +inf (weight 0) and their delta 0, read from a

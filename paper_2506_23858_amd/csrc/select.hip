@@ -2105,7 +2105,9 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
         SCAN_LEVEL(2, hc2, hs2);
         VMOBA_CHECK_LAUNCH();
 #undef SCAN_LEVEL
-        // seldom anything to do (see last_kept_tie): no more workgroups than fill the chip, since 40 000 that return at once take 11 us
+        // seldom anything to do (see last_kept_tie): no more workgroups than fill the chip, since 40 000 that return at once take 11 us.
+        // With 0.14 million equal values a head, cut inside them, a whole selection of 12 heads x 32 760 tokens x 84 blocks takes 289 us (223 without
+        // them), with 1.6 and 16 million 112 320 x 288 takes 3.74 and 5.10 ms (2.91); with up to 4096 workgroups a head all the same to 1 %.
         const unsigned row_gx = (unsigned)std::min<int64_t>(ceil_div64(S, 4 * 8), std::max(1, 8 * vmoba_num_cus() / BH));
         tie_count_kernel<<<dim3(row_gx, BH), dim3(256), 0, st>>>(P, ws.state, ws.ties, (int)S, n_blocks);
         VMOBA_CHECK_LAUNCH();

@@ -14,7 +14,7 @@ from paper_2506_23858_amd import binding as vb
 # ---------------------------------------------------------------------------- tolerances and the error record
 # Acceptance bounds on |GPU - oracle| (the oracle is float64 on the same input bits); tol = 2e-2 (bfloat16) /
 # 1e-4 (float32), the stated max-abs tolerances:
-#   float32, every output      max |err| <= tol, unscaled (measured: <= 2.3e-5 everywhere).
+#   float32, every output      max |err| <= tol, unscaled (measured: <= 3.4e-5 everywhere).
 #   bfloat16 O, dV             every ELEMENT: |err| <= tol * max(1, |ref|) -- the plain max-abs bound on every element
 #                              with |ref| <= 1, relative to the element beyond.  A bfloat16 result of magnitude x carries
 #                              up to x * 2^-9 from its own final rounding (1.6e-2 for 4 <= |x| < 8, 3.1e-2 for 8 <= |x| <
