@@ -274,6 +274,26 @@ def test_f32_split_kernels_on_small_weights():
         assert max(errs) <= 1e-4
 
 
+@pytest.mark.parametrize("power", [11, 20])
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_kernels_on_rows_of_different_magnitudes(power, D):
+    """One row of dO far smaller than the others of its head: 2^-11 of them is still split at the head's scale, 2^-20 hands the call to the float32
+    kernels.  That query's dQ scales along either way; two kinds of kernels differ by up to 1e-6, the others' rows as well."""
+    grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
+    Q, K, V, dO = (synth.iid_normal(1090 + i, (1, S, heads, D)) for i in range(4))
+    small = dO.copy()
+    small[0, 777] *= np.float32(2.0 ** -power)
+    a, b = (gu.run_gpu(Q, K, V, d, grid, (0, 0, 0), 300, 0.4, torch.float32) for d in (dO, small))
+    assert gu.multiplies_split_operands(a["plan"])
+    pos = int(a["inv_perm"][777])
+    kept = a["mask"][0][:, pos].any(-1)
+    assert kept.any()
+    err = relative_error(b["dQp"][0, kept, pos].astype(np.float64) * 2.0 ** power, a["dQp"][0, kept, pos].astype(np.float64))
+    rest = [np.delete(g["dQp"], pos, 2) for g in (b, a)]
+    print("   dQ %.2e, other rows %.2e" % (err, relative_error(rest[0], rest[1].astype(np.float64))), flush=True)
+    assert err <= 1e-6 and relative_error(rest[0], rest[1].astype(np.float64)) <= 1e-6
+
+
 @pytest.mark.parametrize("layout", [{}, {"fused_io": True}, {"q_in_place": True}, {"kv_in_place": True}])
 @pytest.mark.parametrize("D", [64, 128])
 def test_f32_split_kernels_in_every_layout(D, layout):

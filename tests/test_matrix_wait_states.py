@@ -14,7 +14,7 @@ from paper_2506_23858_amd import build, binding as vb
 
 OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(build.HIPCC)), "llvm", "bin", "llvm-objdump")
 OPERAND_WAIT = 2                                          # vector instruction -> operand of a matrix instruction
-RESULT_WAIT = {"32x32x16_bf16": 12, "16x16x32_bf16": 8, "32x32x2_f32": 18}    # matrix instruction (8 / 4 / 16 passes) -> anything else
+RESULT_WAIT = {"32x32x16_bf16": 12, "32x32x16_f16": 12, "16x16x32_bf16": 8, "32x32x2_f32": 18}    # matrix instruction (8 / 4 / 16 passes) -> anything else
 REG = re.compile(r"(?<![\w.])([av])(?:(\d+)|\[(\d+):(\d+)\])(?!\w)")
 
 
