@@ -265,9 +265,7 @@ __global__ __launch_bounds__(256) void score_kernel(TensorView Q, const float* _
 // With more than 189 blocks (192 at 64 channels) the three bfloat16 copies no longer fit the LDS; FLY keeps the means there as
 // float32 (row stride D + 4) and splits every operand after its fetch: the same three terms from the same operations, so P is the
 // same, at the price of vector work per matrix instruction.
-// With more than 256 blocks a query's scores no longer fit: the host then launches the kernel once per
-// chunk of at most 188 blocks, whose terms fit, with RAW set -- the launch covers blocks [jb0, jb0 + nb) of nb_total and writes the scaled
-// scores themselves into its columns of P -- and softmax_rows_kernel below turns the rows into P afterwards.
+// More than 256 blocks: score_long_kernel below.
 // wavefronts per workgroup of the matrix-core score kernel (two per SIMD share one copy of the block means in LDS)
 constexpr int SCORE_NW = 8, SCORE_NT = 64 * SCORE_NW, SCORE_QT = 32 * SCORE_NW;
 // every value of a lane's rows (N_T tiles of 16) into the packed histogram
@@ -315,11 +313,11 @@ __device__ __forceinline__ T& pick_ref(T& a, T& b) {
 // and a lane stores 16-byte runs of its row of P) -- for rows of P that start 16-byte aligned (N_b a multiple of 4), and FLY.
 // !TR: they hold S (queries down the registers, the block on the lane): a store instruction then writes 128-byte runs of
 // two rows with 4-byte pieces whatever N_b is, and the row maximum and sum take a reduction over 32 lanes.
-template <int D, bool FLY, bool RAW, int NMT, bool TR>
+template <int D, bool FLY, int NMT, bool TR>
 __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, const float* __restrict__ Bmean,
                                                          float* __restrict__ P, unsigned int* __restrict__ hist_cnt,
                                                          unsigned long long* __restrict__ hist_sum,
-                                                         int BH, int Hh, int S, int nb, int nb_total, int jb0, float score_scale,
+                                                         int BH, int Hh, int S, int nb, float score_scale,
                                                          int fix_shift, int copy_shift, float2* __restrict__ row_stat) {
     // LDS rows of the bf16 terms are padded by 16 bytes.  Beyond 128 blocks (NMT > 4) only the nb real rows and one row of
     // zeros are kept -- the lanes of the last tile that stand for padding blocks read the zero row -- which is what lets
@@ -328,7 +326,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
     constexpr int STR = D + 8;                 // LDS row stride in bf16 elements
     constexpr int FSTR = D + 4;                // LDS row stride in float elements (FLY)
     constexpr int KSTEPS = D / 16;
-    static_assert(FLY == (NMT == 0) && !(FLY && (RAW || !TR)), "one launch with float32 means, or terms of a known number of tiles");
+    static_assert(FLY == (NMT == 0) && !(FLY && !TR), "one launch with float32 means, or terms of a known number of tiles");
     constexpr int MAX_MT = FLY ? 8 : NMT;                        // FLY: up to 256 blocks
     extern __shared__ __align__(16) unsigned char smem[];
     const int nb_pad = NMT > 0 ? NMT * 32 : ((nb + 31) & ~31);
@@ -347,7 +345,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
     // block means of head bh -> LDS, 16 bytes per lane and four loads in flight per lane (the head's means are one
     // contiguous array); clears the histogram words
     auto load_means = [&](int bh) {
-        const f32x4_t* src4 = reinterpret_cast<const f32x4_t*>(Bmean + ((long long)bh * nb_total + jb0) * D);
+        const f32x4_t* src4 = reinterpret_cast<const f32x4_t*>(Bmean + (long long)bh * nb * D);
         const int n4 = nb * D / 4, n4_pad = (FLY ? nb_pad : n_rows) * D / 4;      // rows past nb are zeros
         for (int i0 = tid; i0 < n4_pad; i0 += 4 * SCORE_NT) {
             f32x4_t x4[4];
@@ -388,7 +386,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
 
     const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const int n_tiles = (S + SCORE_QT - 1) / SCORE_QT;
-    const bool vec_ok = ((nb_total | jb0) & 3) == 0;         // this launch's part of a row of P starts 16-byte aligned
+    const bool vec_ok = (nb & 3) == 0;                       // a row of P starts 16-byte aligned
     // The launch's work is the flat list of (head, query tile) pairs; a workgroup takes one contiguous share of it, so
     // all shares are equal to within one tile whatever the number of heads, and reloads the means when its share
     // crosses into the next head.
@@ -440,7 +438,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
     constexpr bool DEFER = NMT > 0 && NMT <= 3;
     f32x16_t outp_own[MAX_MT] = {};                                  // never touched unless DEFER
     bool pending = false;                                             // this lane's outp holds a query's row not yet counted
-    const bool count = !RAW && hist_cnt != nullptr;
+    const bool count = hist_cnt != nullptr;
     for (int flat = t0; flat < t1; ++flat) {
         const int bh = flat / n_tiles, tile = flat - bh * n_tiles;
         if (bh != cur_bh || since_flush >= flush_every) {              // same decision in every wavefront
@@ -532,22 +530,8 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
         if constexpr (!TR) {
             // accumulator value v of tile mt <-> query row 8*(v>>2) + 4*hf + (v&3) of the wavefront's 32, block 32*mt + l32
             const int q_w = tile * SCORE_QT + wave * 32 + 4 * hf;         // + 8*(v>>2) + (v&3)
-            float* prow = P + ((long long)bh * S + q_w) * nb_total + jb0 + l32;
+            float* prow = P + ((long long)bh * S + q_w) * nb + l32;
             auto col_ok = [&](int mt) { return tile_full(mt) || mt * 32 + l32 < nb; };
-            if constexpr (RAW) {
-                take_next_rows();
-#pragma unroll
-                for (int mt = 0; mt < MAX_MT; ++mt) {
-                    if (mt < n_mt && col_ok(mt)) {
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int dq = 8 * (v >> 2) + (v & 3);
-                            if (q_w + dq < S) prow[(long long)dq * nb_total + mt * 32] = acc[mt][v] * score_scale;
-                        }
-                    }
-                }
-                continue;
-            }
             float mrow[16], den[16];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -594,38 +578,13 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
                         const int dq = 8 * (v >> 2) + (v & 3);
-                        if (q_w + dq < S) prow[(long long)dq * nb_total + mt * 32] = outp[mt][v];
+                        if (q_w + dq < S) prow[(long long)dq * nb + mt * 32] = outp[mt][v];
                     }
                 }
             }
             // padding blocks and rows past the end hold P = 0 and land in bin 0 (see below)
             if constexpr (DEFER) pending = true;
             else if (count) packed_hist_add_rows<MAX_MT>(sPk, copy_shift, hist_copy, acc, n_mt);
-            continue;
-        }
-        if constexpr (RAW) {
-            take_next_rows();
-            if (q < S) {
-                float* dst = P + ((long long)bh * S + q) * nb_total + jb0;
-#pragma unroll
-                for (int mt = 0; mt < MAX_MT; ++mt) {
-                    if (mt < n_mt) {
-                        const int lim = nb - 32 * mt - 4 * hf;
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            const int j0 = mt * 32 + 8 * g + 4 * hf;
-                            if (tile_full(mt) || 8 * g < lim) {          // (the number of blocks and that of a chunk are multiples of four)
-                                const f32x4_t o = {acc[mt][4 * g] * score_scale, acc[mt][4 * g + 1] * score_scale,
-                                                   acc[mt][4 * g + 2] * score_scale, acc[mt][4 * g + 3] * score_scale};
-                                *reinterpret_cast<f32x4_t*>(dst + j0) = o;
-                            }
-                        }
-                        // tile by tile: with the products of all tiles before the first store, a launch for 144 blocks of 12 heads x 112 320
-                        // tokens takes 389 us instead of 334
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-            }
             continue;
         }
         float m = -INFINITY;
@@ -671,7 +630,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
         }
         if (row_stat && q < S && hf == 0) row_stat[(long long)bh * S + q] = make_float2(m, den);
         if (q < S) {
-            float* dst = P + ((long long)bh * S + q) * nb_total + jb0;
+            float* dst = P + ((long long)bh * S + q) * nb;
 #pragma unroll
             for (int mt = 0; mt < MAX_MT; ++mt) {
                 if (mt < n_mt) {
@@ -701,56 +660,178 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
 }
 
 // ---------------------------------------------------------------------------------------------
-// More than 256 blocks: P holds the scaled scores (score_mfma_kernel with RAW); this kernel turns every row into its
-// soft-max in place and takes the first radix level.  One wavefront per row, a lane owns columns lane, lane + 64, ...
-// Bound by the read and write of P; one packed LDS atomic per entry, in two interleaved copies of the words (a count and a sum,
-// two atomics, before): 12 heads x 112 320 tokens x 288 blocks, 3.1 GB, 856 -> 652 us.
-constexpr int SOFTMAX_COPIES = 1;                       // log2 of the histogram's replicas
-constexpr int SOFTMAX_MAX_ROWS = 2048;                  // rows of a workgroup: 2048 x 512 entries, what a packed word can count
-__global__ __launch_bounds__(256) void softmax_rows_kernel(float* __restrict__ P, unsigned int* __restrict__ hist_cnt,
-                                                           unsigned long long* __restrict__ hist_sum, int S, int nb,
-                                                           int fix_shift, float2* __restrict__ row_stat) {
-    constexpr int MAXC = VMOBA_MAX_BLOCKS / 64;
-    __shared__ unsigned long long sPk[HIST_BINS << SOFTMAX_COPIES];
-    const int bh = blockIdx.y;
-    for (int i = threadIdx.x; i < (HIST_BINS << SOFTMAX_COPIES); i += 256) sPk[i] = 0ull;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int copy = lane & ((1 << SOFTMAX_COPIES) - 1);
-    for (int q = blockIdx.x * 4 + wv; q < S; q += gridDim.x * 4) {
-        float* row = P + ((long long)bh * S + q) * nb;
-        float v[MAXC];
-        float m = -INFINITY;
+// More than 256 blocks.  A query's scores stay in the registers, NMT tiles of 32 blocks; what does not fit is the block means in LDS, so
+// they pass through it, 64 blocks at a time in two buffers (split into the same three terms by the threads that bring them: 147 KB per
+// 128 channels, 288 blocks and tile, from the L2).  Accumulators as in score_mfma_kernel without TR: the block on the lane, 16 rows down the registers.
+// The soft-max has the operations, and the sums the order, of one wavefront per row whose lane owns columns lane, lane + 64, ...:
+// den = the two halves' sums over the even and the odd tiles, then lanes 16, 8, 4, 2, 1 apart.
+// NW wavefronts of 32 queries each: 8 while NMT tiles leave two wavefronts per SIMD enough registers (NMT = 9), else 4.
+// Bound by its vector instructions, 48 per value: a quarter expf, then the histogram's word, the quotient, the reductions.  12 heads x 112 320 tokens x 288 blocks
+// (selection 2.98 -> 2.34 ms): 0.74 ms; before, launches for 144 blocks each wrote the scores (0.67) and another normalised them in place (0.68), 4.6 GB instead of
+// 1.55.  Selections of 264 / 300 / 330 / 400 / 512 blocks (8, 8, 12 and 12 heads, 32 to 117 K tokens): 1.15 / 2.41 / 1.87 / 2.83 / 3.03 -> 0.87 / 2.00 / 1.54 / 2.51 / 2.75 ms;
+// 384 blocks of 64 channels 2.49 -> 2.01.  Same bits.  Values below any possible theta left out of the histogram: no gain; expf without its test for an overflow: none.
+constexpr int LONG_KB = 64;                             // blocks per LDS buffer
+constexpr int LONG_COPIES = 2;                          // log2 of the histogram's replicas
+template <int CTRL>
+__device__ __forceinline__ float dpp_ror(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)); }
+template <int D, int NMT, int NW>
+__global__ __launch_bounds__(64 * NW, NW / 4) void score_long_kernel(TensorView Q, const float* __restrict__ Bmean, float* __restrict__ P,
+                                                                     unsigned int* __restrict__ hist_cnt, unsigned long long* __restrict__ hist_sum, int BH, int Hh,
+                                                                     int S, int nb, float score_scale, int fix_shift, float2* __restrict__ row_stat) {
+    constexpr int STR = D + 8, KSTEPS = D / 16, NT = 64 * NW, TQ = 32 * NW, COPIES = LONG_COPIES;
+    constexpr int NCH = (NMT + 1) / 2, TERM = LONG_KB * STR, BUF = 3 * TERM;         // chunks; elements of a term and of a buffer
+    constexpr int NLD = LONG_KB * D / 4 / NT;                                         // 16-byte pieces of means per thread and chunk
+    static_assert(NLD * NT * 4 == LONG_KB * D, "equal shares");
+    extern __shared__ __align__(16) unsigned char smem[];
+    __bf16* sB = reinterpret_cast<__bf16*>(smem);                                     // [2][3][LONG_KB][STR]
+    unsigned long long* sPk = reinterpret_cast<unsigned long long*>(sB + 2 * BUF);    // [HIST_BINS << COPIES]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, hf = lane >> 5, copy = lane & ((1 << COPIES) - 1);
+    const int n_tiles = (S + TQ - 1) / TQ, n_flat = BH * n_tiles;
+    const int t0 = (int)((long long)blockIdx.x * n_flat / gridDim.x), t1 = (int)((long long)(blockIdx.x + 1) * n_flat / gridDim.x);
+    if (t0 >= t1) return;
+    bf16x8_t qf[KSTEPS];
+    auto load_q = [&](int flat) {
+        const int bh = flat / n_tiles, tile = flat - bh * n_tiles, b = bh / Hh, h = bh - b * Hh;
+        const int qc = min(tile * TQ + wave * 32 + l32, S - 1);           // rows past the end recompute the last query; never stored
+        const char* src = Q.ptr + ((long long)b * Q.stride_b + (long long)qc * Q.stride_s + (long long)h * Q.stride_h) * 2;
 #pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            const int j = c * 64 + lane;
-            v[c] = j < nb ? row[j] : -INFINITY;
-            m = fmaxf(m, v[c]);
-        }
+        for (int ks = 0; ks < KSTEPS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_t*>(src + (ks * 16 + hf * 8) * 2);
+    };
+    f32x4_t mean[NLD];
+    auto load_means = [&](int bh, int c) {                                // blocks past the last are zeros
+        const f32x4_t* src = reinterpret_cast<const f32x4_t*>(Bmean + ((long long)bh * nb + c * LONG_KB) * D);
+        const int n4 = (nb - c * LONG_KB) * (D / 4);
+        const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-        float den = 0.f;
+        for (int u = 0; u < NLD; ++u) mean[u] = tid + u * NT < n4 ? src[tid + u * NT] : z;
+    };
+    auto store_means = [&](int buf) {
 #pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            if (c * 64 >= nb) continue;       // the same columns in every lane
-            v[c] = expf(v[c] - m);            // exp(-inf) = 0 past the row's end
-            den += v[c];
-        }
+        for (int u = 0; u < NLD; ++u) {
+            const int i = (tid + u * NT) * 4;
+            __bf16* dst = sB + buf * BUF + i / D * STR + i % D;
+            u32x2_t t[3];
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off, 64);
-        if (row_stat && lane == 0) row_stat[(long long)bh * S + q] = make_float2(m, den);
-#pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            const int j = c * 64 + lane;
-            if (j < nb) {
-                const float p = v[c] / den;
-                row[j] = p;
-                if (hist_cnt) packed_hist_add(sPk, SOFTMAX_COPIES, copy, p);
+            for (int e = 0; e < 2; ++e) {
+                const float x0 = mean[u][2 * e], x1 = mean[u][2 * e + 1];
+                t[0][e] = pack_bf16x2(x0, x1);
+                const float r0 = x0 - bf16lo_to_f32(t[0][e]), r1 = x1 - bf16hi_to_f32(t[0][e]);
+                t[1][e] = pack_bf16x2(r0, r1);
+                t[2][e] = pack_bf16x2(r0 - bf16lo_to_f32(t[1][e]), r1 - bf16hi_to_f32(t[1][e]));
             }
+#pragma unroll
+            for (int x = 0; x < 3; ++x) *reinterpret_cast<u32x2_t*>(dst + x * TERM) = t[x];
+        }
+    };
+    const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int flush_every = max(1, (1 << 20) / (TQ * NMT * 32));          // tiles until a packed histogram word could overflow
+    int cur_bh = t0 / n_tiles, since_flush = 0, buf = 0;
+    for (int i = tid; i < (HIST_BINS << COPIES); i += NT) sPk[i] = 0ull;
+    load_q(t0);
+    load_means(cur_bh, 0);
+    store_means(0);
+    for (int flat = t0; flat < t1; ++flat) {
+        const int bh = flat / n_tiles, tile = flat - bh * n_tiles;
+        if (hist_cnt && (bh != cur_bh || since_flush >= flush_every)) {   // same decision in every wavefront
+            __syncthreads();
+            packed_hist_flush(sPk, COPIES, hist_cnt, hist_sum, cur_bh, fix_shift, tid, NT);
+            __syncthreads();
+            for (int i = tid; i < (HIST_BINS << COPIES); i += NT) sPk[i] = 0ull;
+            since_flush = 0;
+        }
+        cur_bh = bh;
+        ++since_flush;
+        f32x16_t acc[NMT];
+#pragma unroll
+        for (int mt = 0; mt < NMT; ++mt) acc[mt] = zero16;
+        const int next = min(flat + 1, t1 - 1);
+        static_for<NCH>([&](auto cc) __attribute__((always_inline)) {
+            constexpr int c = cc, N = c * 2 + 1 < NMT ? 2 : 1;            // tiles of the chunk
+            __syncthreads();                                              // chunk c is in the LDS; everybody is done with the one before
+            load_means(c + 1 < NCH ? bh : next / n_tiles, c + 1 < NCH ? c + 1 : 0);
+            const __bf16* src = sB + buf * BUF + l32 * STR + hf * 8;
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) {
+                bf16x8_t b[3][N];
+#pragma unroll
+                for (int x = 0; x < 3; ++x)
+#pragma unroll
+                    for (int t = 0; t < N; ++t) b[x][t] = *reinterpret_cast<const bf16x8_t*>(src + x * TERM + t * 32 * STR + ks * 16);
+#pragma unroll
+                for (int x = 0; x < 3; ++x)
+#pragma unroll
+                    for (int t = 0; t < N; ++t) acc[c * 2 + t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[ks], b[x][t], acc[c * 2 + t], 0, 0, 0);
+            }
+            store_means(buf ^ 1);
+            buf ^= 1;
+        });
+        load_q(next);
+        __builtin_amdgcn_sched_barrier(0);
+        // accumulator value v of tile mt <-> query row 8*(v>>2) + 4*hf + (v&3) of the wavefront's 32, block 32*mt + l32
+        const int q_w = tile * TQ + wave * 32 + 4 * hf;
+        float* prow = P + ((long long)bh * S + q_w) * nb + l32;
+        const bool whole = tile * TQ + wave * 32 + 32 <= S;
+        auto col_ok = [&](int mt) { return mt < 8 || mt * 32 + l32 < nb; };           // (more than 256 blocks)
+        auto batch = [&](int v0) __attribute__((always_inline)) {                     // rows of four accumulator values
+            float m[4], den[4], rcp[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float t = -INFINITY;
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) {
+                    float sv = acc[mt][v0 + i] * score_scale;
+                    asm("" : "+v"(sv));                                  // rounded here: not to become a part of sv - m
+                    if (mt >= 8) sv = col_ok(mt) ? sv : -INFINITY;
+                    acc[mt][v0 + i] = sv;
+                    t = fmaxf(t, sv);
+                }
+                m[i] = half32_max(t);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float d[2] = {0.f, 0.f};
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) {
+                    const float e = expf(acc[mt][v0 + i] - m[i]);         // exp(-inf) = 0 past the row's end
+                    acc[mt][v0 + i] = e;
+                    d[mt & 1] += e;
+                }
+                float x = d[0] + d[1];
+                typedef unsigned u2 __attribute__((ext_vector_type(2)));
+                const u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                x = __uint_as_float(r.x) + __uint_as_float(r.y);
+                x += dpp_ror<0x128>(x);
+                x += dpp_ror<0x124>(x);
+                x += dpp_ror<0x122>(x);
+                x += dpp_ror<0x121>(x);
+                den[i] = x;
+                rcp[i] = 1.f / x;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int dq = 2 * v0 + i;                                // = 8 * (v >> 2) + (v & 3)
+                const bool live = whole || q_w + dq < S;
+                if (row_stat && live && l32 == 0) row_stat[(long long)bh * S + q_w + dq] = make_float2(m[i], den[i]);
+#pragma unroll
+                for (int mt = 0; mt < NMT; ++mt) {
+                    // the quotient, correctly rounded: from a correctly rounded reciprocal one correction step is enough
+                    const float e = acc[mt][v0 + i], q0 = e * rcp[i], p = fmaf(fmaf(-q0, den[i], e), rcp[i], q0);
+                    if (live && (mt < 8 || col_ok(mt))) {
+                        prow[(long long)dq * nb + mt * 32] = p;
+                        if (hist_cnt) packed_hist_add(sPk, COPIES, copy, p);
+                    }
+                }
+            }
+        };
+#pragma unroll
+        for (int v0 = 0; v0 < 16; v0 += 4) {
+            batch(v0);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
     __syncthreads();
-    if (hist_cnt) packed_hist_flush(sPk, SOFTMAX_COPIES, hist_cnt, hist_sum, bh, fix_shift, threadIdx.x, 256);
+    if (hist_cnt) packed_hist_flush(sPk, COPIES, hist_cnt, hist_sum, cur_bh, fix_shift, tid, NT);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1840,6 +1921,8 @@ __global__ __launch_bounds__(256) void fill_lists_kernel(const unsigned int* __r
     }
 }
 
+size_t score_long_lds_bytes(int D) { return (size_t)2 * 3 * LONG_KB * (D + 8) * 2 + ((size_t)HIST_BINS * 8 << LONG_COPIES); }
+
 size_t score_lds_bytes(int nb, int D) {
     return (size_t)nb * D * 4 + (size_t)QT * (nb | 1) * 4 + HIST_BINS * 4 + HIST_BINS * 8;
 }
@@ -1848,7 +1931,7 @@ size_t score_lds_bytes(int nb, int D) {
 // compute unit, once per kernel (slot) and device.
 int allow_full_lds(const void* kernel, int slot) {
     static std::mutex mu;
-    static bool done[46][64] = {};
+    static bool done[44][64] = {};
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return VMOBA_ERR_HIP;
     std::lock_guard<std::mutex> lock(mu);
@@ -1916,24 +1999,19 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
     const bool pool_softmax = mode == VMOBA_POOL_SOFTMAX_THRESHOLD;
     const bool bf16 = Qp->dtype == VMOBA_BF16;
     // LDS of the score kernel this call launches: bfloat16 queries go to the matrix-core kernel (block means as three
-    // bfloat16 terms while they fit, as float32 up to 256 blocks, as terms of a chunk beyond), float32 queries to the plain FMA kernel
-    // Beyond 256 blocks several launches write the scaled scores of a chunk of the blocks each: the fewest chunks whose means fit the
-    // LDS as terms (188 blocks; every launch reads all queries again), of equal size, a multiple of 4 for the sake of 16-byte stores.
-    // 288 blocks, 12 heads x 112 320 tokens: 723 -> 610 us (chunks of 256 and 32, means as float32, split after every fetch)
-    const bool chunked = bf16 && n_blocks > 256;
-    const int n_chunks = chunked ? (n_blocks + 187) / 188 : 1;
-    const int chunk = chunked ? ((n_blocks + n_chunks - 1) / n_chunks + 3) & ~3 : n_blocks;
-    const int nb_pad = (chunk + 31) & ~31;
+    // bfloat16 terms while they fit, as float32 up to 256 blocks, 64 blocks' terms at a time beyond), float32 queries to the plain FMA kernel
+    const bool many = bf16 && n_blocks > 256;
+    const int nb_pad = (n_blocks + 31) & ~31;
     // three bf16 terms of the means in LDS while they fit beside one copy of the histogram words and the accumulators fit
     // the registers (D = 128: up to 189 blocks; D = 64: 192), else the means as float32, split after every fetch
-    const size_t lds_terms = (size_t)3 * (nb_pad > 128 ? chunk + 1 : nb_pad) * (D + 8) * 2;
+    const size_t lds_terms = (size_t)3 * (nb_pad > 128 ? n_blocks + 1 : nb_pad) * (D + 8) * 2;
     const bool fly = nb_pad > 192 || lds_terms + (size_t)HIST_BINS * 8 > 160 * 1024;
     const size_t lds_means = fly ? (size_t)nb_pad * (D + 4) * 4 : lds_terms;
     // the first radix level of the matrix-core kernel keeps up to 8 replicas of its 8 KB of histogram words, as many as fit
-    int copy_shift = chunked ? 0 : 3;                       // (a chunk's launch counts nothing)
+    int copy_shift = 3;
     while (copy_shift > 0 && lds_means + ((size_t)HIST_BINS * 8 << copy_shift) > 160 * 1024) --copy_shift;
     const size_t lds_mfma = lds_means + ((size_t)HIST_BINS * 8 << copy_shift);
-    const size_t lds = bf16 ? lds_mfma : score_lds_bytes(n_blocks, D);
+    const size_t lds = many ? score_long_lds_bytes(D) : bf16 ? lds_mfma : score_lds_bytes(n_blocks, D);
     if (lds > 160 * 1024) return VMOBA_ERR_UNSUPPORTED;
     const int BH = B * Hh;
     SelectWs ws = carve(workspace, BH, S, n_blocks);
@@ -1985,57 +2063,56 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
     if (bf16) {
         // one workgroup per compute unit (the LDS holds one), each with an equal share of all (head, query tile) pairs
         dim3 mgrid((unsigned)std::min<int64_t>((int64_t)BH * ceil_div64(S, SCORE_QT), vmoba_num_cus()));
-#define LAUNCH_SCORE_MFMA_T(DD, FL, RW, NM, TRV, NBC, JB0)                                                \
+#define LAUNCH_SCORE_MFMA_T(DD, FL, NM, TRV)                                                              \
     do {                                                                                                  \
-        auto kfn = score_mfma_kernel<DD, FL, RW, NM, TRV>;                                                \
-        if (allow_full_lds((const void*)kfn, (RW ? 34 + (TRV ? 0 : 6) + (DD == 128 ? 0 : 3) + NM - 4 : 2 + (TRV ? 0 : 16) + (DD == 128 ? 0 : 8) + (FL ? 6 : NM - 1))) != VMOBA_OK) return VMOBA_ERR_HIP; \
-        kfn<<<mgrid, dim3(SCORE_NT), lds, st>>>(Qv, Bmean, P, score_hist, ws.hist_sum, BH, Hh, (int)S, NBC, n_blocks, JB0, \
+        auto kfn = score_mfma_kernel<DD, FL, NM, TRV>;                                                    \
+        if (allow_full_lds((const void*)kfn, 2 + (TRV ? 0 : 16) + (DD == 128 ? 0 : 8) + (FL ? 6 : NM - 1)) != VMOBA_OK) return VMOBA_ERR_HIP; \
+        kfn<<<mgrid, dim3(SCORE_NT), lds, st>>>(Qv, Bmean, P, score_hist, ws.hist_sum, BH, Hh, (int)S, n_blocks, \
                                                 score_scale, fix_shift, copy_shift, row_stat);            \
     } while (0)
         // rows of P that start 16-byte aligned take the kernel with the query on the lane, others the one with the block there
         // (not FLY: eight accumulator tiles leave no registers for the reduction's row values)
-#define LAUNCH_SCORE_MFMA(DD, RW, NM, NBC, JB0)                                                           \
+#define LAUNCH_SCORE_MFMA(DD, NM)                                                                         \
     do {                                                                                                  \
-        if ((n_blocks & 3) == 0) LAUNCH_SCORE_MFMA_T(DD, false, RW, NM, true, NBC, JB0);                  \
-        else LAUNCH_SCORE_MFMA_T(DD, false, RW, NM, false, NBC, JB0);                                     \
+        if ((n_blocks & 3) == 0) LAUNCH_SCORE_MFMA_T(DD, false, NM, true);                                \
+        else LAUNCH_SCORE_MFMA_T(DD, false, NM, false);                                                   \
     } while (0)
         // the bf16 terms fit: one instantiation per number of 32-block tiles
 #define LAUNCH_SCORE_TILES(DD)                                                                            \
     do {                                                                                                  \
         switch ((n_blocks + 31) / 32) {                                                                   \
-            case 1: LAUNCH_SCORE_MFMA(DD, false, 1, n_blocks, 0); break;                                  \
-            case 2: LAUNCH_SCORE_MFMA(DD, false, 2, n_blocks, 0); break;                                  \
-            case 3: LAUNCH_SCORE_MFMA(DD, false, 3, n_blocks, 0); break;                                  \
-            case 4: LAUNCH_SCORE_MFMA(DD, false, 4, n_blocks, 0); break;                                  \
-            case 5: LAUNCH_SCORE_MFMA(DD, false, 5, n_blocks, 0); break;                                  \
-            default: LAUNCH_SCORE_MFMA(DD, false, 6, n_blocks, 0); break;                                 \
+            case 1: LAUNCH_SCORE_MFMA(DD, 1); break;                                                      \
+            case 2: LAUNCH_SCORE_MFMA(DD, 2); break;                                                      \
+            case 3: LAUNCH_SCORE_MFMA(DD, 3); break;                                                      \
+            case 4: LAUNCH_SCORE_MFMA(DD, 4); break;                                                      \
+            case 5: LAUNCH_SCORE_MFMA(DD, 5); break;                                                      \
+            default: LAUNCH_SCORE_MFMA(DD, 6); break;                                                     \
         }                                                                                                 \
     } while (0)
-        // a chunk holds 4 to 6 tiles of 32 blocks
-#define LAUNCH_SCORE_RAW(DD)                                                                              \
+#define LAUNCH_SCORE_LONG_T(DD, NM, NW, SLOT)                                                             \
     do {                                                                                                  \
-        switch ((nbc + 31) / 32) {                                                                        \
-            case 4: LAUNCH_SCORE_MFMA(DD, true, 4, nbc, jb0); break;                                      \
-            case 5: LAUNCH_SCORE_MFMA(DD, true, 5, nbc, jb0); break;                                      \
-            case 6: LAUNCH_SCORE_MFMA(DD, true, 6, nbc, jb0); break;                                      \
-            default: return VMOBA_ERR_UNSUPPORTED;                                                        \
-        }                                                                                                 \
+        auto kfn = score_long_kernel<DD, NM, NW>;                                                         \
+        if (allow_full_lds((const void*)kfn, 34 + (DD == 128 ? 0 : 5) + SLOT) != VMOBA_OK) return VMOBA_ERR_HIP; \
+        kfn<<<dim3((unsigned)std::min<int64_t>((int64_t)BH * ceil_div64(S, 32 * NW), vmoba_num_cus())), dim3(64 * NW), lds, st>>>( \
+            Qv, Bmean, P, score_hist, ws.hist_sum, BH, Hh, (int)S, n_blocks, score_scale, fix_shift, row_stat); \
     } while (0)
-        if (chunked) {
-            // more than 256 blocks: scaled scores chunk by chunk, then the soft-max of the rows and the first radix level
-            for (int jb0 = 0; jb0 < n_blocks; jb0 += chunk) {
-                const int nbc = std::min(chunk, n_blocks - jb0);
-                if (D == 128) LAUNCH_SCORE_RAW(128);
-                else LAUNCH_SCORE_RAW(64);
-                VMOBA_CHECK_LAUNCH();
-            }
-            softmax_rows_kernel<<<dim3((unsigned)std::max<int64_t>(std::min<int64_t>(ceil_div64(S, 4 * 8), 2048), ceil_div64(S, SOFTMAX_MAX_ROWS)), (unsigned)BH), dim3(256), 0, st>>>(
-                P, score_hist, ws.hist_sum, (int)S, n_blocks, fix_shift, row_stat);
-        } else if (D == 128 && fly) LAUNCH_SCORE_MFMA_T(128, true, false, 0, true, n_blocks, 0);
+        // more than 256 blocks: instantiations for 9, 10, 12, 14 and 16 tiles of 32 blocks
+#define LAUNCH_SCORE_LONG(DD)                                                                             \
+    do {                                                                                                  \
+        if (n_blocks <= 288) LAUNCH_SCORE_LONG_T(DD, 9, 8, 0);                                            \
+        else if (n_blocks <= 320) LAUNCH_SCORE_LONG_T(DD, 10, 4, 1);                                      \
+        else if (n_blocks <= 384) LAUNCH_SCORE_LONG_T(DD, 12, 4, 2);                                      \
+        else if (n_blocks <= 448) LAUNCH_SCORE_LONG_T(DD, 14, 4, 3);                                      \
+        else LAUNCH_SCORE_LONG_T(DD, 16, 4, 4);                                                           \
+    } while (0)
+        if (many && D == 128) LAUNCH_SCORE_LONG(128);
+        else if (many) LAUNCH_SCORE_LONG(64);
+        else if (D == 128 && fly) LAUNCH_SCORE_MFMA_T(128, true, 0, true);
         else if (D == 128) LAUNCH_SCORE_TILES(128);
-        else if (fly) LAUNCH_SCORE_MFMA_T(64, true, false, 0, true, n_blocks, 0);
+        else if (fly) LAUNCH_SCORE_MFMA_T(64, true, 0, true);
         else LAUNCH_SCORE_TILES(64);
-#undef LAUNCH_SCORE_RAW
+#undef LAUNCH_SCORE_LONG
+#undef LAUNCH_SCORE_LONG_T
 #undef LAUNCH_SCORE_TILES
 #undef LAUNCH_SCORE_MFMA
 #undef LAUNCH_SCORE_MFMA_T

@@ -404,6 +404,35 @@ def test_bf16_block_counts_across_the_score_kernel_variants(grid, block, D):
     assert g["nb"] == g_nb(grid, block)
 
 
+@pytest.mark.parametrize("blocks,D", [(257, 128), (288, 64), (289, 128), (320, 64), (321, 128), (385, 64), (448, 128), (449, 128)])
+def test_bf16_block_counts_across_the_score_kernel_for_many_blocks(blocks, D):
+    """First and last counts of its instantiations (9, 10, 12, 14, 16 tiles of 32 blocks), a last row tile and a last block that are not full."""
+    S = 3 * blocks - 2
+    Q, K, V, dO = (synth.to_bf16_grid(synth.iid_normal(370 + i, (1, S, 2, D))) for i in range(4))
+    g, o = compare_layer(Q, K, V, dO, (1, 1, S), (0, 0, 0), 3, 0.3, torch.bfloat16, f"score-many-{blocks}-{D}")
+    assert g["nb"] == blocks
+
+
+@pytest.mark.parametrize("chunk", [33, 31])
+def test_score_kernel_for_many_blocks_walks_tiles_and_heads(chunk):
+    """More row tiles than compute units, so that a workgroup takes several, of one head and of the next (means of either pass through the LDS): every
+    head's rows have the bits of a call of that head alone."""
+    S, heads, D = 9000, 9 if chunk == 33 else 8, 128
+    Q, K, V = (gu.to_dev(synth.to_bf16_grid(synth.iid_normal(380 + i, (1, S, heads, D))), torch.bfloat16) for i in range(3))
+
+    def probabilities(q, k, v):
+        plan = vb.LayerPlan(1, q.shape[2], D, (1, 90, 100), chunk=chunk, tau=0.3, dtype=torch.bfloat16, need_bwd=False)
+        plan.partition(q, k, v)
+        plan.select()
+        torch.cuda.synchronize()
+        assert plan.nb > 256 and int(plan.dev_status.item()) == 0
+        return plan.P[0].clone()
+    P = probabilities(Q, K, V)
+    assert -(-S // (256 if chunk == 33 else 128)) * heads > torch.cuda.get_device_properties(0).multi_processor_count
+    for h in (0, 3, heads - 1):
+        assert torch.equal(P[h], probabilities(*(x[:, :, h:h + 1].contiguous() for x in (Q, K, V)))[0]), h
+
+
 def g_nb(grid, block):
     return math.prod(-(-a // b) for a, b in zip(grid, block))
 
