@@ -62,24 +62,25 @@ def lib():
     L.vmoba_workspace_bytes.restype = C.c_size_t
     L.vmoba_status_string.argtypes = [C.c_int]
     L.vmoba_status_string.restype = C.c_char_p
+    # (tensor descriptors: pointers to vmoba_tensor, as bytes or ctypes objects)
     L.vmoba_partition.argtypes = [C.POINTER(vmoba_grid), C.c_int, C.c_int, C.c_int, C.c_int, C.c_int,
-                                  C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor), P, P, P, P]
+                                  P, P, P, P, P, P]
     L.vmoba_partition.restype = C.c_int
     L.vmoba_select.argtypes = [C.c_int, C.c_int, C.c_int64, C.c_int, C.c_int32, P,
-                               C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor), C.c_float, C.c_float, C.c_int,
+                               P, P, C.c_float, C.c_float, C.c_int,
                                C.c_int32, P, P, P, P, P, P, P, P, C.c_int64, P, P, P, P, P, P, C.c_size_t, P]
     L.vmoba_select.restype = C.c_int
     L.vmoba_select_static.argtypes = L.vmoba_select.argtypes[:-3] + [P]      # no workspace pointer / size
     L.vmoba_select_static.restype = C.c_int
     L.vmoba_attn_fwd.argtypes = [C.c_int, C.c_int, C.c_int64, C.c_int, C.c_int32, P,
-                                 C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor),
-                                 P, P, P, P, C.c_int64, C.c_float, C.POINTER(vmoba_tensor), P, P, P, P, C.c_size_t, P]
+                                 P, P, P,
+                                 P, P, P, P, C.c_int64, C.c_float, P, P, P, P, P, C.c_size_t, P]
     L.vmoba_attn_fwd.restype = C.c_int
     L.vmoba_attn_bwd.argtypes = [C.c_int, C.c_int, C.c_int64, C.c_int, C.c_int32, P,
-                                 C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor),
-                                 C.POINTER(vmoba_tensor), P, C.POINTER(vmoba_tensor),
+                                 P, P, P,
+                                 P, P, P,
                                  P, P, P, P, C.c_int64, C.c_float,
-                                 C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor), C.POINTER(vmoba_tensor),
+                                 P, P, P,
                                  P, P, P, P, C.c_size_t, P]
     L.vmoba_attn_bwd.restype = C.c_int
     L.vmoba_profile_events.argtypes = [C.c_int, P, P]
@@ -105,8 +106,9 @@ _DTYPE_CODES = {torch.float32: VMOBA_F32, torch.bfloat16: VMOBA_BF16}
 
 
 # A short call is bound by the host: a training step with every tensor in block order describes 30 tensors and passes 50 pointers beside
-# its 15 launches.  So a tensor is asked once for its strides (2.3 -> 1.1 us a descriptor) and addresses are plain integers,
-# which the argument types turn into pointers (0.3 -> 0.1 us).  2 heads x 512 tokens x 64, float32, forward and backward: 118 -> 100 us.
+# its 15 launches.  So a tensor is asked once for its strides, its descriptor is packed as bytes (1.1 -> 0.7 us against a ctypes structure), addresses are
+# plain integers, which the argument types turn into pointers, and the current stream is asked for as a number, not as an
+# object.  2 heads x 512 tokens x 64, float32, forward and backward: 103 -> 82 us (host alone 108 -> 80, half of it the launches).
 def _dtype_code(t: torch.Tensor) -> int:
     code = _DTYPE_CODES.get(t.dtype)
     if code is None:
@@ -121,13 +123,29 @@ def tensor_desc(t: torch.Tensor) -> vmoba_tensor:
     return vmoba_tensor(t.data_ptr(), _dtype_code(t), strides[0], strides[1], strides[2])
 
 
+_pack_desc = struct.Struct("Pi4xqqq").pack        # the fields of vmoba_tensor
+assert struct.calcsize("Pi4xqqq") == C.sizeof(vmoba_tensor)
+
+
+def _desc(t: torch.Tensor) -> bytes:
+    """tensor_desc(t) as the bytes of the structure."""
+    strides = t.stride()
+    assert len(strides) == 4 and strides[3] == 1, "expect a (b, s, h, d) view with contiguous d"
+    code = _DTYPE_CODES.get(t.dtype)
+    return _pack_desc(t.data_ptr(), _dtype_code(t) if code is None else code, strides[0], strides[1], strides[2])
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    return _raw_stream(_device()) if _raw_stream and _device else torch.cuda.current_stream().cuda_stream
 
 
 def make_grid(T, H, W, bt=0, bh=0, bw=0, chunk=0) -> vmoba_grid:
@@ -184,9 +202,7 @@ def vmoba_partition(g, inverse, B, Hh, D, ins, outs, perm, inv_perm, blk_off, st
     """ins / outs: lists of (b, s, h, d) views."""
     n = len(ins)
     assert len(outs) == n
-    arr_in = (vmoba_tensor * max(n, 1))(*[tensor_desc(t) for t in ins])
-    arr_out = (vmoba_tensor * max(n, 1))(*[tensor_desc(t) for t in outs])
-    rc = lib().vmoba_partition(C.byref(g), int(inverse), B, Hh, D, n, arr_in, arr_out,
+    rc = lib().vmoba_partition(C.byref(g), int(inverse), B, Hh, D, n, b"".join(map(_desc, ins)), b"".join(map(_desc, outs)),
                                _ptr(perm), _ptr(inv_perm), _ptr(blk_off), _stream(stream))
     _check("vmoba_partition", rc)
 
@@ -198,12 +214,11 @@ SELECT_OWN_BLOCK = 0x100
 def vmoba_select(B, Hh, S, D, n_blocks, blk_off, Qp, Kp, tau, score_scale, mode, topk, Bmean, P, mask,
                  blk_ptr, q_idx, row_ptr, col_idx, pair_pos, nnz_capacity, k_out, theta_out, dev_status,
                  workspace, stream=None, query_pos=None, kv_rows=None):
-    q, k = tensor_desc(Qp), tensor_desc(Kp)
-    rc = lib().vmoba_select(B, Hh, S, D, n_blocks, _ptr(blk_off), C.byref(q), C.byref(k),
+    rc = lib().vmoba_select(B, Hh, S, D, n_blocks, _ptr(blk_off), _desc(Qp), _desc(Kp),
                             float(tau), float(score_scale), int(mode), int(topk), _ptr(Bmean), _ptr(P), _ptr(mask),
                             _ptr(blk_ptr), _ptr(q_idx), _ptr(row_ptr), _ptr(col_idx), _ptr(pair_pos),
                             int(nnz_capacity), _ptr(k_out), _ptr(theta_out), _ptr(dev_status), _ptr(query_pos),
-                            _ptr(kv_rows), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream))
+                            _ptr(kv_rows), _ptr(workspace), workspace.nbytes, _stream(stream))
     _check("vmoba_select", rc)
 
 
@@ -214,8 +229,7 @@ def vmoba_select_static(B, Hh, S, D, n_blocks, blk_off, Qp, Kp, tau, score_scale
                         blk_ptr, q_idx, row_ptr, col_idx, pair_pos, nnz_capacity, k_out, theta_out, dev_status,
                         stream=None, query_pos=None, kv_rows=None):
     """vmoba_select on the library's static scratch array (no workspace argument, nothing allocated)."""
-    q, k = tensor_desc(Qp), tensor_desc(Kp)
-    rc = lib().vmoba_select_static(B, Hh, S, D, n_blocks, _ptr(blk_off), C.byref(q), C.byref(k),
+    rc = lib().vmoba_select_static(B, Hh, S, D, n_blocks, _ptr(blk_off), _desc(Qp), _desc(Kp),
                                    float(tau), float(score_scale), int(mode), int(topk), _ptr(Bmean), _ptr(P),
                                    _ptr(mask), _ptr(blk_ptr), _ptr(q_idx), _ptr(row_ptr), _ptr(col_idx),
                                    _ptr(pair_pos), int(nnz_capacity), _ptr(k_out), _ptr(theta_out),
@@ -225,24 +239,22 @@ def vmoba_select_static(B, Hh, S, D, n_blocks, blk_off, Qp, Kp, tau, score_scale
 
 def vmoba_attn_fwd(B, Hh, S, D, n_blocks, blk_off, Qp, Kp, Vp, blk_ptr, q_idx, row_ptr, pair_pos,
                    nnz_capacity, softmax_scale, O, LSE, workspace, stream=None, out_rows=None, kv_rows=None):
-    q, k, v, o = tensor_desc(Qp), tensor_desc(Kp), tensor_desc(Vp), tensor_desc(O)
-    rc = lib().vmoba_attn_fwd(B, Hh, S, D, n_blocks, _ptr(blk_off), C.byref(q), C.byref(k), C.byref(v),
+    rc = lib().vmoba_attn_fwd(B, Hh, S, D, n_blocks, _ptr(blk_off), _desc(Qp), _desc(Kp), _desc(Vp),
                               _ptr(blk_ptr), _ptr(q_idx), _ptr(row_ptr), _ptr(pair_pos), int(nnz_capacity),
-                              float(softmax_scale), C.byref(o), _ptr(LSE), _ptr(out_rows), _ptr(kv_rows), _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _stream(stream))
+                              float(softmax_scale), _desc(O), _ptr(LSE), _ptr(out_rows), _ptr(kv_rows), _ptr(workspace),
+                              workspace.nbytes, _stream(stream))
     _check("vmoba_attn_fwd", rc)
 
 
 def vmoba_attn_bwd(B, Hh, S, D, n_blocks, blk_off, Qp, Kp, Vp, O, LSE, dO, blk_ptr, q_idx, row_ptr,
                    pair_pos, nnz_capacity, softmax_scale, dQ, dK, dV, workspace, stream=None, rows=None, key_rows=None,
                    kv_rows=None):
-    d = [tensor_desc(t) for t in (Qp, Kp, Vp, O, dO, dQ, dK, dV)]
-    rc = lib().vmoba_attn_bwd(B, Hh, S, D, n_blocks, _ptr(blk_off), C.byref(d[0]), C.byref(d[1]), C.byref(d[2]),
-                              C.byref(d[3]), _ptr(LSE), C.byref(d[4]), _ptr(blk_ptr), _ptr(q_idx),
+    rc = lib().vmoba_attn_bwd(B, Hh, S, D, n_blocks, _ptr(blk_off), _desc(Qp), _desc(Kp), _desc(Vp),
+                              _desc(O), _ptr(LSE), _desc(dO), _ptr(blk_ptr), _ptr(q_idx),
                               _ptr(row_ptr), _ptr(pair_pos), int(nnz_capacity), float(softmax_scale),
-                              C.byref(d[5]), C.byref(d[6]), C.byref(d[7]), _ptr(rows), _ptr(key_rows), _ptr(kv_rows),
+                              _desc(dQ), _desc(dK), _desc(dV), _ptr(rows), _ptr(key_rows), _ptr(kv_rows),
                               _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _stream(stream))
+                              workspace.nbytes, _stream(stream))
     _check("vmoba_attn_bwd", rc)
 
 
