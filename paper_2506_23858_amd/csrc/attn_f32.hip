@@ -2,7 +2,7 @@
 // v_mfma_f32_32x32x2_f32 (every product and sum in float32; 64 cycles for 4096 FLOP, 157 TFLOP/s on the whole chip).
 //
 // For the calls that the kernels on split operands (attn_split.hip) do not take: small ones (use_split), and those whose tensors hold
-// infinities, NaNs or magnitudes out of the range that two float16 terms hold.
+// infinities, NaNs or magnitudes out of the range that three bfloat16 terms hold.
 //
 // Work decomposition as in the bfloat16 kernels: a tile is up to 128 gathered queries of one key block (forward, dQ), a
 // run is up to 64 keys of one block that meet the block's whole query list (dK/dV).
@@ -335,9 +335,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_f32_kernel(
 //   S = Q . K^T,  dP = dO . V^T,  dV^T += dO^T . P,  dK^T += Q^T . dS
 // The two wavefronts of a key group add their sums through LDS at the end.  64 keys rather than 128: a block's last run is
 // rarely full, and the two query halves keep the LDS traffic of a shared chunk.
-// A run of at most 32 keys would leave kw = 1 idle: there both buffers are filled at a time and wavefronts kw = 1 take the second chunk, with the keys of kw = 0.
-// What a step's requests take is no longer hidden, but a step's 128 matrix instructions of 64 cycles (64 channels) do for two.  2 heads x 512 tokens x 64, blocks of 32 keys met by
-// some 100 queries: 20.0 -> 17.9 us (a third of it is the chain of look-ups before the first row; finding the run without a search changes nothing).
 template <int D>
 __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
     const int* __restrict__ run_if, int parts, TensorView Q, TensorView K, TensorView V, TensorView dO, const float* __restrict__ lse_delta,
@@ -360,8 +357,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
     const int l32 = lane & 31, hf = lane >> 5, kw = wave & 1, qh = wave >> 1;
     const int key0 = ((run_id - ks[lo]) * parts + part) * KPW;
     if (key0 >= L) return;
-    const bool both = L - key0 <= 32;                             // both buffers at a time (uniform over the workgroup)
-    const int kk = key0 + (both ? 0 : kw * 32) + l32;
+    const int kk = key0 + kw * 32 + l32;
     const bool live = kk < L;
     const bool wave_live = kk - l32 < L;                          // any key of this wavefront exists
     const int krow = k0 + min(kk, L - 1);
@@ -402,13 +398,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
             }
         };
         request(0, index_of(0));
-        if (both && n_chunks > 1) request(1, index_of(1));
-        int idx_next = index_of(both ? 2 : 1), idx_after = both ? index_of(3) : 0;
+        int idx_next = index_of(1);
         const TileReads<D> rd(lane);
         auto next_chunk = [&](int c) {
             VMOBA_WAIT_VMCNT(0);
             __syncthreads();
-            if (!both && c + 1 < n_chunks) {
+            if (c + 1 < n_chunks) {
                 request(c + 1, idx_next);
                 idx_next = index_of(c + 2);
             }
@@ -416,51 +411,40 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
         if (!wave_live) {                                         // no key of this wavefront exists: it only moves rows
             for (int c = 0; c < n_chunks; ++c) next_chunk(c);
         } else
-        for (int step = 0; step < n_chunks; step += both ? 2 : 1) {
-            next_chunk(step);
-            const int c = step + (both ? kw : 0);
-            if (c < n_chunks) {
-                const char* tQ = sT[c & 1][0] + qh * HALF;
-                const char* tdO = sT[c & 1][1] + qh * HALF;
-                f32x16_t s = zero16, dp = zero16;
-                two_products_over_channels<D>(rd, tQ, tdO, kf, vf, s, dp);
-                float oa[DT], qa[DT];
-                read_cols<D>(rd, tdO, 0, oa);
-                read_cols<D>(rd, tQ, 0, qa);
-                const int left = cnt - c * QC - qh * 32 - 4 * hf;      // value 4*i + r is query row 8*i + r of this lane half
+        for (int c = 0; c < n_chunks; ++c) {
+            next_chunk(c);
+            const char* tQ = sT[c & 1][0] + qh * HALF;
+            const char* tdO = sT[c & 1][1] + qh * HALF;
+            f32x16_t s = zero16, dp = zero16;
+            two_products_over_channels<D>(rd, tQ, tdO, kf, vf, s, dp);
+            float oa[DT], qa[DT];
+            read_cols<D>(rd, tdO, 0, oa);
+            read_cols<D>(rd, tQ, 0, qa);
+            const int left = cnt - c * QC - qh * 32 - 4 * hf;      // value 4*i + r is query row 8*i + r of this lane half
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(&sLD[c & 1][0][qh * 32 + 8 * i + 4 * hf]);
-                    const f32x4_t d4 = *reinterpret_cast<const f32x4_t*>(&sLD[c & 1][1][qh * 32 + 8 * i + 4 * hf]);
+            for (int i = 0; i < 4; ++i) {
+                const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(&sLD[c & 1][0][qh * 32 + 8 * i + 4 * hf]);
+                const f32x4_t d4 = *reinterpret_cast<const f32x4_t*>(&sLD[c & 1][1][qh * 32 + 8 * i + 4 * hf]);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int v = 4 * i + r;
-                        s[v] = exp2_raw(fmaf(s[v], scale_log2, -l4[r]));
-                        dp[v] = s[v] * (dp[v] + d4[r]);
-                    }
+                for (int r = 0; r < 4; ++r) {
+                    const int v = 4 * i + r;
+                    s[v] = exp2_raw(fmaf(s[v], scale_log2, -l4[r]));
+                    dp[v] = s[v] * (dp[v] + d4[r]);
                 }
-                if (left < 32) {                                      // rows past the end of the list
+            }
+            if (left < 32) {                                      // rows past the end of the list
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        if (8 * (v >> 2) + (v & 3) >= left) { s[v] = 0.f; dp[v] = 0.f; }
-                }
-                product_over_rows<D>(rd, tdO, oa, s, acc[0]);
-                product_over_rows<D>(rd, tQ, qa, dp, acc[1]);
+                for (int v = 0; v < 16; ++v)
+                    if (8 * (v >> 2) + (v & 3) >= left) { s[v] = 0.f; dp[v] = 0.f; }
             }
-            if (both && step + 2 < n_chunks) {
-                __syncthreads();                                  // everybody is done with both
-                request(step + 2, idx_next);
-                if (step + 3 < n_chunks) request(step + 3, idx_after);
-                idx_next = index_of(step + 4);
-                idx_after = index_of(step + 5);
-            }
+            product_over_rows<D>(rd, tdO, oa, s, acc[0]);
+            product_over_rows<D>(rd, tQ, qa, dp, acc[1]);
         }
-        // the second query half's sums join the first's, and those of the second chunks
-        constexpr int SUMS = 2 * DT * 16 * 64;
-        static_assert(3 * SUMS * 4 <= (int)sizeof(sT), "the sums of three wavefronts fit the row buffers");
-        float* red = reinterpret_cast<float*>(&sT[0][0][0]) + (both ? wave - 1 : kw) * SUMS;
+        // the second query half's sums join the first's
+        static_assert(2 * 2 * DT * 16 * 64 * 4 <= (int)sizeof(sT), "the sums of two wavefronts fit the row buffers");
+        float* red = reinterpret_cast<float*>(&sT[0][0][0]) + kw * (2 * DT * 16 * 64);
         __syncthreads();
-        if (both ? wave > 0 : qh == 1) {
+        if (qh == 1) {
 #pragma unroll
             for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -469,19 +453,16 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_f32_kernel(
                     for (int v = 0; v < 16; ++v) red[((x * DT + dt) * 16 + v) * 64 + lane] = acc[x][dt][v];
         }
         __syncthreads();
-        if (both && wave > 0) return;
-        if (qh == 0)
-            for (int w = 0; w < (both ? 3 : 1); ++w) {
-                const float* from = both ? reinterpret_cast<const float*>(&sT[0][0][0]) + w * SUMS : red;
+        if (qh == 0) {
 #pragma unroll
-                for (int x = 0; x < 2; ++x)
+            for (int x = 0; x < 2; ++x)
 #pragma unroll
-                    for (int dt = 0; dt < DT; ++dt)
+                for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) acc[x][dt][v] += from[((x * DT + dt) * 16 + v) * 64 + lane];
-            }
+                    for (int v = 0; v < 16; ++v) acc[x][dt][v] += red[((x * DT + dt) * 16 + v) * 64 + lane];
+        }
     }
-    if (qh == 0 && !(both && kw) && live) {
+    if (qh == 0 && live) {
         const long long kout = rows ? rows[krow] : krow;
         float* pv = reinterpret_cast<float*>(dV.ptr + ((long long)b * dV.stride_b + kout * dV.stride_s + (long long)h * dV.stride_h) * 4);
         float* pk = reinterpret_cast<float*>(dK.ptr + ((long long)b * dK.stride_b + kout * dK.stride_s + (long long)h * dK.stride_h) * 4);

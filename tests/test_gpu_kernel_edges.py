@@ -85,21 +85,6 @@ def check_heads(case, g, Q, K, V, dO, heads, scale=None, dtype=torch.float32, b=
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("chunk,tau", [(32, 0.1), (32, 0.9), (33, 0.5), (70, 0.7)])
-def test_f32_kernels_on_runs_of_few_keys(chunk, tau, D):
-    """Small float32 calls (float32 instruction) whose runs of keys have at most 32 keys, in part or all: there two chunks of 64 queries are met at a time,
-    by lists of one chunk, of an odd number of chunks and of more than two steps."""
-    grid, S, heads = (1, 20, 19), 380, 2
-    Q, K, V, dO = (synth.iid_normal(1100 + i, (1, S, heads, D)) for i in range(4))
-    g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), chunk, tau, torch.float32)
-    assert not gu.multiplies_split_operands(g["plan"])
-    chunks = -(-np.diff(g["blk_ptr"]) // 64)
-    assert tau != 0.9 or chunks.max() > 4
-    assert tau != 0.1 or chunks.min() == 1
-    check_heads(f"f32-few-keys-{chunk}-{tau}-{D}", g, Q, K, V, dO, range(heads))
-
-
-@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("chunk", [31, 33, 97, 129, 300])
 def test_f32_split_kernels_at_tile_edges(chunk, D):
     """float32 calls large enough for the kernels on split operands: blocks that end around a 32-key group and around a run of 128 keys
