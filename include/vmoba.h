@@ -102,7 +102,7 @@ int vmoba_layer_kind(int layer);
 int vmoba_partition_dims(const vmoba_grid* g, int64_t* S, int32_t* n_blocks);
 
 /* Bytes of workspace `op` needs for this geometry.  nnz_capacity is per (batch, head).  Pass the attention calls' own n_blocks
- * and nnz_capacity: for float32 they also decide whether the operands are split into bfloat16 terms, which takes room. */
+ * and nnz_capacity: for float32 they also decide whether the operands are split into 16-bit terms, which takes room. */
 size_t vmoba_workspace_bytes(int op, int B, int Hh, int64_t S, int D, int32_t n_blocks,
                              int64_t nnz_capacity, int dtype);
 
