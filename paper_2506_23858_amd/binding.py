@@ -108,7 +108,7 @@ _DTYPE_CODES = {torch.float32: VMOBA_F32, torch.bfloat16: VMOBA_BF16}
 # A short call is bound by the host: a training step with every tensor in block order describes 30 tensors and passes 50 pointers beside
 # its 15 launches.  So a tensor is asked once for its strides, its descriptor is packed as bytes (1.1 -> 0.7 us against a ctypes structure), addresses are
 # plain integers, which the argument types turn into pointers, and the current stream is asked for as a number, not as an
-# object.  2 heads x 512 tokens x 64, float32, forward and backward: 103 -> 82 us (host alone 108 -> 80, half of it the launches).
+# object.  2 heads x 512 tokens x 64, float32, forward and backward: 104 -> 85 us (host alone 108 -> 80, half of it the launches).
 def _dtype_code(t: torch.Tensor) -> int:
     code = _DTYPE_CODES.get(t.dtype)
     if code is None:
