@@ -196,6 +196,7 @@ void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const int* run_if, int par
 struct SplitTensor { TensorView X; const int* map; char* dst; int pitch; };
 struct SplitTensors { SplitTensor t[4]; };
 static inline int split_scan_chunks(int64_t S) { return (int)(S < 64 * 64 ? (S + 63) / 64 : 64); }
+static inline size_t split_scratch_bytes(int BH, int64_t S, int n) { return (size_t)BH * (16 + (size_t)split_scan_chunks(S) * n * 8); }
 void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const SplitTensors& in, int n, void* scratch, int4** power, int* out_of_range);
 void launch_fwd_tiles_split(int D, dim3 grid, hipStream_t st, const char* Q2, const char* KV4, const int4* power, const int* q_idx, const int4* flat_desc,
                             const int* n_tiles, const int* out_of_range, float* Opart, float* lse_part, int S, long long cap, float scale_log2);
@@ -206,17 +207,15 @@ void launch_dkv_split(int D, dim3 grid, hipStream_t st, const char* QD4, const c
                       const int* blk_ptr, const int* q_idx, const int* kb_start, const int* kb_order, const int* out_of_range, const TensorView& dK,
                       const TensorView& dV, const int* rows, int Hh, int S, int pitch, int nb, long long cap, float scale_log2, float scale, int BH, int slots,
                       int group);
-// float32 calls with enough work -- multiply-adds of one product over all pairs the lists can hold, less for short blocks, whose partial rows set the
-// time -- take the split kernels, if 32-bit offsets reach every split row of a head (with the width that three terms would have, which is what the workspace holds).
-// What they cost beside their products are two passes over the inputs and seven launches in a training step.  Forward and backward go together: weights
-// recomputed by other sums than those of the LSE make dQ's error larger by up to a tenth.  Training step (forward) without / with them, us, one head of 128 channels
-// unless said otherwise: blocks of 300 keys, 600 / 1200 tokens 211 / 139 (93 / 72), 232 / 154 (97 / 76), 8 heads x 4800 1284 / 596 (335 / 225); 128 keys, 640 / 1280 / 2560
-// tokens 143 / 116 (65 / 63), 170 / 134 (71 / 68), 241 / 182 (91 / 94); 64 keys, 1280 / 2560 tokens 164 / 128 (66 / 71), 236 / 173 (96 / 100), 4 heads x 2560 319 / 229 (130 / 120);
-// 32 keys, 4 and 16 heads x 2560 388 / 295 (154 / 150), 1141 / 862 (378 / 379).  So from 128 keys on the line lies as low as has been measured, and below where a
-// forward call alone no longer loses.
+// float32 calls with enough work -- multiply-adds of one product over all pairs the lists can hold -- take the split kernels, if
+// 32-bit offsets reach every split row of a head.  What they cost beside their products is seven passes over the inputs
+// and ten launches in a training step; what they save grows with the pairs and with the length of the blocks (below some 64 keys
+// the partial rows set the time).  Training step (forward) with / without them, us: blocks of 300 keys, work 6.7e7:
+// 207 / 251 (95 / 107), 2.4e9: 421 / 613 (153 / 176); 128 keys, 3.0e8: 210 / 212; 64 keys, 3.0e8: 225 / 228 (98 / 97), 2.4e9: 538 / 570
+// (205 / 217); 32 keys, 3.0e8: 263 / 255, 2.4e9: 880 / 936 (298 / 287).
 static inline bool use_split(int BH, int64_t S, int D, int n_blocks, int64_t cap) {
     const double len = (double)S / n_blocks, work = (double)BH * (double)cap * (double)D * len;
-    return work * (len / 128) * (len / 128) >= (len >= 128 ? 1.2e7 : 2e8) && S < (1 << 24) && (uint64_t)S * 12 * (uint64_t)D < ((uint64_t)1 << 32);
+    return work * (len / 128) * (len / 128) >= 2e8 && S < (1 << 24) && (uint64_t)S * 12 * (uint64_t)D < ((uint64_t)1 << 32);
 }
 // Compute units of the current device (queried once).
 int vmoba_num_cus();

@@ -2,7 +2,7 @@
 // v_mfma_f32_32x32x2_f32 (every product and sum in float32; 64 cycles for 4096 FLOP, 157 TFLOP/s on the whole chip).
 //
 // For the calls that the kernels on split operands (attn_split.hip) do not take: small ones (use_split), and those whose tensors hold
-// infinities, NaNs or magnitudes out of the range that two float16 terms hold.
+// infinities, NaNs or magnitudes out of the range that three bfloat16 terms hold.
 //
 // Work decomposition as in the bfloat16 kernels: a tile is up to 128 gathered queries of one key block (forward, dQ), a
 // run is up to 64 keys of one block that meet the block's whole query list (dK/dV).

@@ -671,7 +671,7 @@ FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool 
     w.n_tiles = (int*)(p + off);     off += 256;
     w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
     w.Q2 = p + off;                  off += split ? align_up((size_t)BH * S * 6 * D, 256) : 0;
-    w.split_scratch = w.Q2 + (size_t)BH * S * 4 * D;              // (at most half a byte per row and head and 48 bytes per head)
+    w.split_scratch = w.Q2 + (size_t)BH * S * 4 * D;              // (at most half a byte per row and head and 36 bytes per head: see split_scratch_bytes)
     w.KV4 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
