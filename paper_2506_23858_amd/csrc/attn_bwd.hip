@@ -1078,9 +1078,8 @@ struct BwdWs {
     int* kb_order;     // float32: [BH][nb]
     int4* slot_desc;   // bfloat16: [BH][dkv_slots]
     char* dO_copy;     // [BH, S, D] block-order copy of dO (used with a row map)
-    char* QD4;         // split kernels: [BH][S][4][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip),
-    char* KV4;         // with room for half as much again behind each
-    char* split_scratch;
+    char* QD6;         // split kernels: [BH][S][6][D], the terms of Q and dO by query id, and those of K and V in block order (see attn_split.hip)
+    char* KV6;
     size_t total;
 };
 
@@ -1119,9 +1118,8 @@ BwdWs carve_bwd(void* base, int BH, int64_t S, int D, int nb, int64_t cap, int e
     off += list + start + order;
     if (es == 2) off = std::max(off, (size_t)((char*)w.slot_desc - p) + align_up((size_t)BH * dkv_slots(S, nb, 128, true).slots * 16, 256));
     w.dO_copy = p + off;             off += align_up((size_t)BH * S * D * es, 256);
-    w.QD4 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
-    w.split_scratch = w.QD4 + (size_t)BH * S * 8 * D;
-    w.KV4 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.QD6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
 }
@@ -1197,10 +1195,11 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         dOv.stride_h = S * D;
         dOv.stride_s = D;
     }
-    int4* split_power = nullptr;
     if (split) {
-        const SplitTensors in = {{{Qv, nullptr, ws.QD4, 8 * D}, {dOv, nullptr, ws.QD4 + 4 * D, 8 * D}, {Kv, kv_rows, ws.KV4, 8 * D}, {Vv, kv_rows, ws.KV4 + 4 * D, 8 * D}}};
-        launch_split_rows(D, BH, Hh, (int)S, st, in, 4, ws.split_scratch, &split_power, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.QD6, 6, 0, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, dOv, nullptr, ws.QD6, 6, 3, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, Kv, kv_rows, ws.KV6, 6, 0, out_of_range);
+        launch_split_rows(D, BH, Hh, (int)S, st, Vv, kv_rows, ws.KV6, 6, 3, out_of_range);
         VMOBA_CHECK_LAUNCH();
     }
     const int pitch = lse_delta_pitch((int)S);
@@ -1210,7 +1209,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
         const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);     // one workgroup per tile
         if (!bf16) {
             if (split)
-                launch_dq_tiles_split(D, grid, st, ws.QD4, ws.KV4, split_power, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, out_of_range, ws.dQpart, (int)S, pitch,
+                launch_dq_tiles_split(D, grid, st, ws.QD6, ws.KV6, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, out_of_range, ws.dQpart, (int)S, pitch,
                                       (long long)nnz_capacity, scale_log2);
             launch_dq_tiles_f32(D, grid, st, split ? out_of_range : nullptr, Qv, Kv, Vv, dOv, ws.delta, q_idx, ws.tile_desc, ws.n_tiles, ws.dQpart, Hh, (int)S,
                                 (long long)nnz_capacity, scale_log2, kv_rows);
@@ -1240,7 +1239,7 @@ extern "C" int vmoba_attn_bwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
 #define DKV_ARGS blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, dKv, dVv, krows, Hh, (int)S, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, kv_rows
         if (!bf16) {
             if (split)
-                launch_dkv_split(D, hgrid, st, ws.QD4, ws.KV4, split_power, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, out_of_range, dKv, dVv, krows,
+                launch_dkv_split(D, hgrid, st, ws.QD6, ws.KV6, ws.delta, blk_off, blk_ptr, q_idx, ws.kb_start, ws.kb_order, out_of_range, dKv, dVv, krows,
                                  Hh, (int)S, pitch, n_blocks, (long long)nnz_capacity, scale_log2, softmax_scale, BH, dkv.slots, dkv.group);
             const int parts = split ? 2 : 1;
             launch_dkv_f32(D, dim3((unsigned)(dkv.grid_x * parts), (unsigned)BH), st, split ? out_of_range : nullptr, parts, Qv, Kv, Vv, dOv, ws.delta, DKV_ARGS);

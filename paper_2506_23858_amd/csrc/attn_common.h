@@ -190,23 +190,16 @@ void launch_dkv_f32(int D, dim3 grid, hipStream_t st, const int* run_if, int par
                     const float* lse_delta, const int* blk_off, const int* blk_ptr, const int* q_idx, const int* kb_start,
                     const int* kb_order, const TensorView& dK, const TensorView& dV, const int* rows, int Hh, int S, int nb, long long cap,
                     float scale_log2, float scale, const int* kv_rows);
-// The same on the float16 matrix instruction, from rows split into two terms each (attn_split.hip).  A tensor to split, and where plane h of its row 0 goes (plane l
-// behind it, rows `pitch` bytes apart, heads S rows); launch_split_rows writes the powers of two the planes are scaled by to scratch ([head][4], in the
-// tensors' order) and what it finds them from behind them.
-struct SplitTensor { TensorView X; const int* map; char* dst; int pitch; };
-struct SplitTensors { SplitTensor t[4]; };
-static inline int split_scan_chunks(int64_t S) { return (int)(S < 64 * 64 ? (S + 63) / 64 : 64); }
-static inline size_t split_scratch_bytes(int BH, int64_t S, int n) { return (size_t)BH * (16 + (size_t)split_scan_chunks(S) * n * 8); }
-void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const SplitTensors& in, int n, void* scratch, int4** power, int* out_of_range);
-void launch_fwd_tiles_split(int D, dim3 grid, hipStream_t st, const char* Q2, const char* KV4, const int4* power, const int* q_idx, const int4* flat_desc,
+// The same on the bfloat16 matrix instruction, from rows split into three terms each (attn_split.hip).
+void launch_split_rows(int D, int BH, int Hh, int S, hipStream_t st, const TensorView& X, const int* map, char* dst, int planes, int plane0, int* out_of_range);
+void launch_fwd_tiles_split(int D, dim3 grid, hipStream_t st, const char* Q3, const char* KV6, const int* q_idx, const int4* flat_desc,
                             const int* n_tiles, const int* out_of_range, float* Opart, float* lse_part, int S, long long cap, float scale_log2);
-void launch_dq_tiles_split(int D, dim3 grid, hipStream_t st, const char* QD4, const char* KV4, const int4* power, const float* lse_delta, const int* q_idx,
+void launch_dq_tiles_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* q_idx,
                            const int4* flat_desc, const int* n_tiles, const int* out_of_range, float* dQpart, int S, int pitch, long long cap,
                            float scale_log2);
-void launch_dkv_split(int D, dim3 grid, hipStream_t st, const char* QD4, const char* KV4, const int4* power, const float* lse_delta, const int* blk_off,
-                      const int* blk_ptr, const int* q_idx, const int* kb_start, const int* kb_order, const int* out_of_range, const TensorView& dK,
-                      const TensorView& dV, const int* rows, int Hh, int S, int pitch, int nb, long long cap, float scale_log2, float scale, int BH, int slots,
-                      int group);
+void launch_dkv_split(int D, dim3 grid, hipStream_t st, const char* QD6, const char* KV6, const float* lse_delta, const int* blk_off, const int* blk_ptr,
+                      const int* q_idx, const int* kb_start, const int* kb_order, const int* out_of_range, const TensorView& dK, const TensorView& dV,
+                      const int* rows, int Hh, int S, int pitch, int nb, long long cap, float scale_log2, float scale, int BH, int slots, int group);
 // float32 calls with enough work -- multiply-adds of one product over all pairs the lists can hold -- take the split kernels, if
 // 32-bit offsets reach every split row of a head.  What they cost beside their products is seven passes over the inputs
 // and ten launches in a training step; what they save grows with the pairs and with the length of the blocks (below some 64 keys

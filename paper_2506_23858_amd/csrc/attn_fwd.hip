@@ -646,9 +646,8 @@ struct FwdWs {
     int4* tile_desc;   // the flat list of all heads' tiles
     int* n_tiles;      // its length, then the split kernels' flag
     int* head_tiles;   // [BH]
-    char* Q2;          // split kernels: [BH][S][2][D], the terms of Q, and [BH][S][4][D], those of K and V in block order (see attn_split.hip),
-    char* KV4;         // with room for half as much again behind each
-    char* split_scratch;
+    char* Q3;          // split kernels: [BH][S][3][D], the terms of Q, and [BH][S][6][D], those of K and V in block order (see attn_split.hip)
+    char* KV6;
     size_t total;
 };
 
@@ -670,9 +669,8 @@ FwdWs carve_fwd(void* base, int BH, int64_t S, int D, int64_t cap, int es, bool 
     w.tile_desc = (int4*)(p + off);  off += align_up((size_t)BH * vmoba_max_tiles(cap, 64) * 16, 256);
     w.n_tiles = (int*)(p + off);     off += 256;
     w.head_tiles = (int*)(p + off);  off += align_up((size_t)BH * 4, 256);
-    w.Q2 = p + off;                  off += split ? align_up((size_t)BH * S * 6 * D, 256) : 0;
-    w.split_scratch = w.Q2 + (size_t)BH * S * 4 * D;              // (at most half a byte per row and head and 36 bytes per head: see split_scratch_bytes)
-    w.KV4 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
+    w.Q3 = p + off;                  off += split ? align_up((size_t)BH * S * 6 * D, 256) : 0;
+    w.KV6 = p + off;                 off += split ? align_up((size_t)BH * S * 12 * D, 256) : 0;
     w.total = off;
     return w;
 }
@@ -741,17 +739,17 @@ extern "C" int vmoba_attn_fwd(int B, int Hh, int64_t S, int D, int32_t n_blocks,
     tile_list_kernel<<<dim3((unsigned)ceil_div64(max_tiles, 256), (unsigned)BH), dim3(256), 0, st>>>(
         blk_ptr, blk_off, head_tiles, ws.tile_desc, ws.n_tiles, split ? ws.n_tiles + 1 : nullptr, BH, n_blocks, TM);
     VMOBA_CHECK_LAUNCH();
-    int4* split_power = nullptr;
     if (split) {
-        const SplitTensors in = {{{Qv, nullptr, ws.Q2, 4 * D}, {Kv, kv_rows, ws.KV4, 8 * D}, {Vv, kv_rows, ws.KV4 + 4 * D, 8 * D}}};
-        launch_split_rows(D, BH, Hh, (int)S, st, in, 3, ws.split_scratch, &split_power, ws.n_tiles + 1);
+        launch_split_rows(D, BH, Hh, (int)S, st, Qv, nullptr, ws.Q3, 3, 0, ws.n_tiles + 1);
+        launch_split_rows(D, BH, Hh, (int)S, st, Kv, kv_rows, ws.KV6, 6, 0, ws.n_tiles + 1);
+        launch_split_rows(D, BH, Hh, (int)S, st, Vv, kv_rows, ws.KV6, 6, 3, ws.n_tiles + 1);
         VMOBA_CHECK_LAUNCH();
     }
     VMOBA_PROFILE_BEGIN(0, st);
     if (!bf16) {
         const dim3 grid = flat_tile_grid(BH, max_tiles, nnz_capacity, TM, n_blocks);
         if (split)
-            launch_fwd_tiles_split(D, grid, st, ws.Q2, ws.KV4, split_power, q_idx, ws.tile_desc, ws.n_tiles, ws.n_tiles + 1, ws.Opart, ws.lse_part, (int)S,
+            launch_fwd_tiles_split(D, grid, st, ws.Q3, ws.KV6, q_idx, ws.tile_desc, ws.n_tiles, ws.n_tiles + 1, ws.Opart, ws.lse_part, (int)S,
                                    (long long)nnz_capacity, scale_log2);
         launch_fwd_tiles_f32(D, grid, st, split ? ws.n_tiles + 1 : nullptr, Qv, Kv, Vv, q_idx, ws.tile_desc, ws.n_tiles,
                              ws.Opart, ws.lse_part, Hh, (long long)nnz_capacity, scale_log2, kv_rows);

@@ -277,8 +277,8 @@ def test_f32_split_kernels_on_small_weights():
 @pytest.mark.parametrize("power", [11, 20])
 @pytest.mark.parametrize("D", [64, 128])
 def test_f32_split_kernels_on_rows_of_different_magnitudes(power, D):
-    """One row of dO far smaller than the others of its head: 2^-11 of them is still split at the head's scale, 2^-20 hands the call to the float32
-    kernels.  That query's dQ scales along either way; two kinds of kernels differ by up to 1e-6, the others' rows as well."""
+    """One row of dO far smaller than the others of its head: that query's dQ scales along, the others' rows stay.  (1e-6: what two kinds of kernels
+    differ by; the test below has one kind and asks for the bits.)"""
     grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
     Q, K, V, dO = (synth.iid_normal(1090 + i, (1, S, heads, D)) for i in range(4))
     small = dO.copy()
@@ -292,6 +292,117 @@ def test_f32_split_kernels_on_rows_of_different_magnitudes(power, D):
     rest = [np.delete(g["dQp"], pos, 2) for g in (b, a)]
     print("   dQ %.2e, other rows %.2e" % (err, relative_error(rest[0], rest[1].astype(np.float64))), flush=True)
     assert err <= 1e-6 and relative_error(rest[0], rest[1].astype(np.float64)) <= 1e-6
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_kernels_on_rows_far_apart_in_magnitude(D):
+    """One row of dO 2^-20 of the others of its head: the call stays on the split kernels -- the other queries' dQ have the bits of the call with ordinary
+    rows, which the sums of the kernels on the float32 instruction do not give -- and that query's dQ scales along exactly."""
+    grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
+    Q, K, V, dO = (synth.iid_normal(1090 + i, (1, S, heads, D)) for i in range(4))
+    small = dO.copy()
+    small[0, 777] *= np.float32(2.0 ** -20)
+    a, b = (gu.run_gpu(Q, K, V, d, grid, (0, 0, 0), 300, 0.4, torch.float32) for d in (dO, small))
+    assert gu.multiplies_split_operands(a["plan"])
+    b["dQ"][0, 777] *= np.float32(2.0 ** 20)
+    assert a["dQ"][0, 777].any() and np.array_equal(a["dQ"], b["dQ"])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_kernels_on_channels_of_different_magnitudes(D):
+    """A channel 2^-24 of the others of its rows, of each tensor in turn: what it alone decides -- a channel of O (of V), dV (of dO), dK (of Q), dQ (of K) --
+    scales along exactly, as float32 sums do, and nothing else changes.  (In the products that would couple it to the rest, the other operand's channel is 0.)"""
+    grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
+    Q, K, V, dO = (synth.iid_normal(1100 + i, (1, S, heads, D)) for i in range(4))
+    dO[..., 5] = V[..., 6] = K[..., 7] = Q[..., 8] = 0.0
+    small = [x.copy() for x in (Q, K, V, dO)]
+    for x, c in zip(small, (7, 8, 5, 6)):
+        x[..., c] *= np.float32(2.0 ** -24)
+    a, b = (gu.run_gpu(*x, grid, (0, 0, 0), 300, 0.4, torch.float32) for x in ((Q, K, V, dO), small))
+    assert gu.multiplies_split_operands(a["plan"]) and np.array_equal(a["mask"], b["mask"])
+    for name, c in (("O", 5), ("dV", 6), ("dK", 7), ("dQ", 8)):
+        b[name][..., c] *= np.float32(2.0 ** 24)
+        err = relative_error(b[name][..., c], a[name][..., c].astype(np.float64))
+        print(f"   {name}: {err:.2e}", flush=True)
+        assert a[name][..., c].any() and np.array_equal(a[name], b[name]), (name, err)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_kernels_on_a_large_value_row(D):
+    """One row of V 2^12 times the others: O and dQ of the queries that do not keep its block have the bits they have without it."""
+    grid, S, heads = (1, 48, 50), 2400, 24 if D == 64 else 8
+    Q, K, V, dO = (synth.iid_normal(1110 + i, (1, S, heads, D)) for i in range(4))
+    large = V.copy()
+    large[0, 777] *= 4096.0
+    a, b = (gu.run_gpu(Q, K, v, dO, grid, (0, 0, 0), 300, 0.4, torch.float32) for v in (V, large))
+    assert gu.multiplies_split_operands(a["plan"])
+    others = ~a["mask"][0, :, :, 777 // 300]                       # (perm is the identity here)
+    assert others.any() and not others.all()
+    for name in ("Op", "dQp"):
+        err = relative_error(b[name][0][others], a[name][0][others].astype(np.float64))
+        print(f"   {name}: {err:.2e}", flush=True)
+        assert np.array_equal(a[name][0][others], b[name][0][others]), (name, err)
+
+
+@pytest.mark.parametrize("heavy", [3, 2397])
+@pytest.mark.parametrize("zero", ["dO", "Q"])
+def test_f32_split_kernels_on_zero_rows(zero, heavy):
+    """A key whose one large weight belongs to a query with a row of zeros in dO (a token that the loss masks), or in Q, and whose other weights are near 2^-36: its
+    dV (its dK) consists of those alone and keeps their relative precision, wherever in the list that query comes.  (Exponents of up to 64 are exact to 2^-18 in
+    float32: 3e-6 of a weight; 1e-5 with the rounding of the LSE.)"""
+    grid, S, heads, D = (1, 48, 50), 2400, 8, 128
+    Q, K, V, dO = (synth.iid_normal(1120 + i, (1, S, heads, D)) for i in range(4))
+    scale, kx = 1.0 / math.sqrt(D), 777
+    Q[..., 0], K[..., 0], Q[..., 1], K[..., 1] = 16.0, 0.0, 0.0, 0.0
+    K[:, kx] = 0.0
+    K[:, kx, :, 0], K[:, kx, :, 1] = -12.0, 16.0
+    if zero == "dO":
+        Q[:, heavy, :, 1] = 19.0
+        dO[:, heavy] = 0.0
+    else:
+        Q[:, heavy] = 0.0
+    g = gu.run_gpu(Q, K, V, dO, grid, (0, 0, 0), 300, 1.0, torch.float32)
+    assert gu.multiplies_split_operands(g["plan"])
+    worst = 0.0
+    for h in (0, heads - 1):
+        q, k, v, d = (x[0, :, h].astype(np.float64) for x in (Q, K, V, dO))
+        O, LSE = vo.masked_attention_fwd(q, k, v, g["mask"][0, h], g["blk_off"], scale)
+        w = np.exp(scale * q @ k[kx] - LSE)
+        rest = np.delete(w, heavy)
+        assert rest.max() < 2.0 ** -32 and w[heavy] > 2.0 ** -12
+        dS = w * (d @ v[kx] - (d * O).sum(1))
+        errs = relative_error(g["dVp"][0, h, kx], w @ d), relative_error(g["dKp"][0, h, kx], scale * dS @ q)
+        print("   dV %.2e dK %.2e" % errs, flush=True)
+        worst = max(worst, errs[0] if zero == "dO" else 0.0, errs[1])
+    assert worst <= 1e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_split_kernels_read_keys_through_their_row_numbers_only(D):
+    """kv_rows may name any row of K and V: their last S rows of 2 S here, behind rows 2^-12 and 2^12 of them.  Same bits as with those rows alone."""
+    grid, S, heads, chunk, tau = (1, 48, 50), 2400, 24 if D == 64 else 8, 300, 0.4
+    Q, K, V, dO = (gu.to_dev(synth.iid_normal(1130 + i, (1, S, heads, D)), torch.float32) for i in range(4))
+    plan = vb.LayerPlan(1, heads, D, grid, (0, 0, 0), chunk, tau, torch.float32, kv_in_place=True)
+    assert gu.multiplies_split_operands(plan)
+    plan.forward(Q, K, V)
+    plan.backward(dO)
+    torch.cuda.synchronize()
+    want = {n: getattr(plan, n).clone() for n in ("O", "LSE", "dQ", "dK", "dV", "mask")}
+    rows = plan.perm + S
+    for power in (-12, 12):
+        wide = [torch.cat([x * 2.0 ** power, x], 1) for x in (K, V)]
+        for n in want:
+            getattr(plan, n).zero_()
+        vb.vmoba_select(1, heads, S, D, plan.nb, plan.blk_off, Q, wide[0], tau, plan.score_scale, plan.mode, 0, plan.Bmean, plan.P, plan.mask, plan.blk_ptr,
+                        plan.q_idx, plan.row_ptr, plan.col_idx, plan.pair_pos, plan.cap, plan.k_out, plan.theta, plan.dev_status, plan.ws_select,
+                        query_pos=plan.inv_perm, kv_rows=rows)
+        lists = (plan.blk_ptr, plan.q_idx, plan.row_ptr, plan.pair_pos, plan.cap, plan.softmax_scale)
+        vb.vmoba_attn_fwd(1, heads, S, D, plan.nb, plan.blk_off, Q, *wide, *lists, plan.O, plan.LSE, plan.ws_attn, kv_rows=rows)
+        vb.vmoba_attn_bwd(1, heads, S, D, plan.nb, plan.blk_off, Q, *wide, plan.O, plan.LSE, dO, *lists, plan.dQ, plan.dK, plan.dV, plan.ws_attn,
+                          key_rows=plan.perm, kv_rows=rows)
+        torch.cuda.synchronize()
+        for n, x in want.items():
+            assert torch.equal(getattr(plan, n), x), (power, n)
 
 
 @pytest.mark.parametrize("layout", [{}, {"fused_io": True}, {"q_in_place": True}, {"kv_in_place": True}])
