@@ -666,10 +666,12 @@ __global__ __launch_bounds__(SCORE_NT) void score_mfma_kernel(TensorView Q, cons
 // The soft-max has the operations, and the sums the order, of one wavefront per row whose lane owns columns lane, lane + 64, ...:
 // den = the two halves' sums over the even and the odd tiles, then lanes 16, 8, 4, 2, 1 apart.
 // NW wavefronts of 32 queries each: 8 while NMT tiles leave two wavefronts per SIMD enough registers (NMT = 9), else 4.
-// Bound by its vector instructions, 48 per value: a quarter expf, then the histogram's word, the quotient, the reductions.  12 heads x 112 320 tokens x 288 blocks
-// (selection 2.98 -> 2.34 ms): 0.74 ms; before, launches for 144 blocks each wrote the scores (0.67) and another normalised them in place (0.68), 4.6 GB instead of
-// 1.55.  Selections of 264 / 300 / 330 / 400 / 512 blocks (8, 8, 12 and 12 heads, 32 to 117 K tokens): 1.15 / 2.41 / 1.87 / 2.83 / 3.03 -> 0.87 / 2.00 / 1.54 / 2.51 / 2.75 ms;
-// 384 blocks of 64 channels 2.49 -> 2.01.  Same bits.  Values below any possible theta left out of the histogram: no gain; expf without its test for an overflow: none.
+// Bound by its vector instructions, 49 per value: a quarter expf, then the histogram's word, the quotient, the reductions.  12 heads x 112 320 tokens x 288 blocks
+// (selection 2.87 -> 2.2 ms): 0.70 ms; before, launches for 144 blocks each wrote the scores (0.67) and another normalised them in place (0.68), 4.6 GB instead of
+// 1.55.  Selections of 128 channels, 8 heads x 33 K tokens x 264 blocks, 8 x 106 K x 300 and 330, 12 x 115 K x 400, 12 x 98 K x 512: 0.49 / 1.99 / 2.34 / 4.24 / 4.43 -> 0.38 / 1.59 / 1.92 /
+// 3.81 / 4.07 ms; of 64, 12 heads x 115 K tokens x 384 and 448 blocks, 98 K x 512: 3.79 / 4.45 / 4.32 -> 3.07 / 3.53 / 3.60.  Same bits.  The gain is smallest where registers do not suffice:
+// 14 tiles of 128 channels and 16 of either spill 23 to 69, beside a wavefront's copies to and from accumulator registers.
+// Values below any possible theta left out of the histogram: no gain; expf without its test for an overflow: none.
 constexpr int LONG_KB = 64;                             // blocks per LDS buffer
 constexpr int LONG_COPIES = 2;                          // log2 of the histogram's replicas
 template <int CTRL>
@@ -805,18 +807,20 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void score_long_kernel(TensorView 
                 x += dpp_ror<0x124>(x);
                 x += dpp_ror<0x122>(x);
                 x += dpp_ror<0x121>(x);
-                den[i] = x;
-                rcp[i] = 1.f / x;
+                den[i] = x * 0x1p64f;
+                rcp[i] = 1.f / x * 0x1p-64f;
+                if constexpr (NMT == 16) __builtin_amdgcn_sched_barrier(0);      // (rows overlapped: five times the scratch accesses at 64 channels)
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int dq = 2 * v0 + i;                                // = 8 * (v >> 2) + (v & 3)
                 const bool live = whole || q_w + dq < S;
-                if (row_stat && live && l32 == 0) row_stat[(long long)bh * S + q_w + dq] = make_float2(m[i], den[i]);
+                if (row_stat && live && l32 == 0) row_stat[(long long)bh * S + q_w + dq] = make_float2(m[i], den[i] * 0x1p-64f);
 #pragma unroll
                 for (int mt = 0; mt < NMT; ++mt) {
-                    // the quotient, correctly rounded: from a correctly rounded reciprocal one correction step is enough
-                    const float e = acc[mt][v0 + i], q0 = e * rcp[i], p = fmaf(fmaf(-q0, den[i], e), rcp[i], q0);
+                    // the quotient, correctly rounded: from a correctly rounded reciprocal one correction step is enough (P. Markstein, IBM J. Res. Dev. 34, 1990)
+                    // if the remainder is exact, hence the 2^64: without it, it is not for exponentials below 2^-102
+                    const float e = acc[mt][v0 + i] * 0x1p64f, q0 = e * rcp[i], p = fmaf(fmaf(-q0, den[i], e), rcp[i], q0);
                     if (live && (mt < 8 || col_ok(mt))) {
                         prow[(long long)dq * nb + mt * 32] = p;
                         if (hist_cnt) packed_hist_add(sPk, COPIES, copy, p);

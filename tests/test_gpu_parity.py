@@ -433,6 +433,36 @@ def test_score_kernel_for_many_blocks_walks_tiles_and_heads(chunk):
         assert torch.equal(P[h], probabilities(*(x[:, :, h:h + 1].contiguous() for x in (Q, K, V)))[0]), h
 
 
+@pytest.mark.parametrize("blocks,D", [(288, 128), (320, 64), (512, 64), (512, 128)])
+def test_score_kernel_for_many_blocks_rounds_small_quotients_correctly(blocks, D):
+    """Scores 72 to 102 below their row's largest, so that probabilities fall below 2^-102 and out of the normal numbers.  Scores are exact, and in head 0 the soft-max
+    denominator is 1: its P is the exponentials themselves.  In the others a second score makes it 1 + exp(-x), and each P has to be the correctly rounded quotient."""
+    S, second, top = blocks, (0.25, 0.5, 0.75, 1.0, 1.5, 2.0, 3.0), blocks // 2
+    heads = len(second) + 1
+    K, Q = np.zeros((1, S, heads, D), np.float32), np.zeros((1, S, heads, D), np.float32)
+    i = np.arange(S)
+    K[0, :, :, 0] = -(72 + (i // 8) % 60 * 0.5)[:, None]
+    K[0, :, :, 1] = -(i % 8 / 16)[:, None]
+    K[0, top, :, :2] = 0.0
+    for h, x in enumerate(second):
+        K[0, top + 1, h + 1, :2] = -x, 0.0
+    Q[..., :2] = 1.0
+    plan = vb.LayerPlan(1, heads, D, (1, 1, S), chunk=1, tau=0.3, score_scale=1.0, need_bwd=False)
+    q, k, v = (gu.to_dev(x, torch.bfloat16) for x in (Q, K, K))
+    plan.partition(q, k, v)
+    plan.select()
+    torch.cuda.synchronize()
+    P = plan.P[0].cpu().numpy()
+    rest = np.ones(blocks, bool)
+    rest[top:top + 2] = False
+    e = P[0][:, rest]
+    assert (e > 0).all() and (e < 2.0 ** -126).any() and (e > 2.0 ** -104).any() and (P[0][:, top] == 1).all()
+    for h, x in enumerate(second):
+        den = np.float32(1 + math.exp(-x))
+        assert (P[h + 1][:, top] == np.float32(1) / den).all()
+        assert np.array_equal(P[h + 1][:, rest].view(np.uint32), (e / den).view(np.uint32)), (x, int((P[h + 1][:, rest] != e / den).sum()))
+
+
 def g_nb(grid, block):
     return math.prod(-(-a // b) for a, b in zip(grid, block))
 
