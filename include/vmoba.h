@@ -28,7 +28,8 @@
  *    (token, head) are contiguous and 16-byte aligned.
  *  - Supported: head dimension D in {64, 128}; dtype float32 or bfloat16 (all tensors of a
  *    call share one dtype); 1 <= n_blocks <= 512 (float32: as long as the score kernel's tile of block means
- *    fits the LDS, n_blocks * (D + 64) * 4 + 12 KB <= 160 KB); bidirectional attention (no causal mask).
+ *    and scores fits the LDS, n_blocks * D * 4 + (n_blocks | 1) * 256 + 12 KB <= 160 KB: 197 blocks of 128 channels,
+ *    295 of 64); bidirectional attention (no causal mask).
  */
 #ifndef VMOBA_H
 #define VMOBA_H

@@ -1931,6 +1931,9 @@ size_t score_lds_bytes(int nb, int D) {
     return (size_t)nb * D * 4 + (size_t)((QT * (nb | 1) + 1) & ~1) * 4 + HIST_BINS * 8 + 4 * QT * 4;
 }
 
+// What vmoba.h limits float32 calls by: score_lds_bytes with 12 KB of histogram, 3 KB more than the kernel takes.
+size_t score_limit_bytes(int nb, int D) { return (size_t)nb * D * 4 + (size_t)QT * (nb | 1) * 4 + 12 * 1024; }
+
 // The score kernels use more dynamic LDS than the default limit: raise a kernel's limit to the whole 160 KB of a
 // compute unit, once per kernel (slot) and device.
 int allow_full_lds(const void* kernel, int slot) {
@@ -2016,7 +2019,7 @@ int select_impl(int B, int Hh, int64_t S, int D, int32_t n_blocks, const int32_t
     while (copy_shift > 0 && lds_means + ((size_t)HIST_BINS * 8 << copy_shift) > 160 * 1024) --copy_shift;
     const size_t lds_mfma = lds_means + ((size_t)HIST_BINS * 8 << copy_shift);
     const size_t lds = many ? score_long_lds_bytes(D) : bf16 ? lds_mfma : score_lds_bytes(n_blocks, D);
-    if (lds > 160 * 1024) return VMOBA_ERR_UNSUPPORTED;
+    if ((bf16 ? lds : score_limit_bytes(n_blocks, D)) > 160 * 1024) return VMOBA_ERR_UNSUPPORTED;
     const int BH = B * Hh;
     SelectWs ws = carve(workspace, BH, S, n_blocks);
     if (workspace_bytes < ws.total) return VMOBA_ERR_WORKSPACE;

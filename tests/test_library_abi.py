@@ -85,6 +85,15 @@ def test_bad_arguments_are_rejected_before_any_launch(L):
     assert vb.status_string(vb.VMOBA_ERR_WORKSPACE) == "workspace too small"
 
 
+@pytest.mark.parametrize("dtype,D,most", [(vb.VMOBA_F32, 128, 197), (vb.VMOBA_F32, 64, 295), (vb.VMOBA_BF16, 128, 512), (vb.VMOBA_BF16, 64, 512)])
+def test_block_limits_of_a_selection(L, dtype, D, most):
+    """The largest number of blocks that vmoba.h names gets as far as the workspace check, one more is refused before it."""
+    dummy, t = C.c_void_p(256), vb.vmoba_tensor(256, dtype, 1024 * D, D, D)
+    tail = [0.25, 0.125, 0, 0] + [dummy] * 8 + [100, dummy, dummy, dummy, None, None, dummy, 16, None]
+    assert [L.vmoba_select(1, 1, 1024, D, nb, dummy, C.byref(t), C.byref(t), *tail) for nb in (most, most + 1)] == [
+        vb.VMOBA_ERR_WORKSPACE, vb.VMOBA_ERR_UNSUPPORTED]
+
+
 def test_workspace_sizes_grow_with_capacity(L):
     a = vb.vmoba_workspace_bytes(vb.OP_ATTN_FWD, 1, 2, 512, 64, 16, 1000, vb.VMOBA_F32)
     b = vb.vmoba_workspace_bytes(vb.OP_ATTN_FWD, 1, 2, 512, 64, 16, 2000, vb.VMOBA_F32)
