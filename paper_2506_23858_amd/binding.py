@@ -116,23 +116,21 @@ def _dtype_code(t: torch.Tensor) -> int:
     return code
 
 
-def tensor_desc(t: torch.Tensor) -> vmoba_tensor:
-    """Descriptor of a 4-D tensor indexed (b, s, h, d) -- any strides with d contiguous."""
-    strides = t.stride()
-    assert len(strides) == 4 and strides[3] == 1, "expect a (b, s, h, d) view with contiguous d"
-    return vmoba_tensor(t.data_ptr(), _dtype_code(t), strides[0], strides[1], strides[2])
-
-
 _pack_desc = struct.Struct("Pi4xqqq").pack        # the fields of vmoba_tensor
 assert struct.calcsize("Pi4xqqq") == C.sizeof(vmoba_tensor)
 
 
 def _desc(t: torch.Tensor) -> bytes:
-    """tensor_desc(t) as the bytes of the structure."""
+    """Descriptor of a 4-D tensor indexed (b, s, h, d) -- any strides with d contiguous -- as the bytes of a vmoba_tensor."""
     strides = t.stride()
     assert len(strides) == 4 and strides[3] == 1, "expect a (b, s, h, d) view with contiguous d"
     code = _DTYPE_CODES.get(t.dtype)
     return _pack_desc(t.data_ptr(), _dtype_code(t) if code is None else code, strides[0], strides[1], strides[2])
+
+
+def tensor_desc(t: torch.Tensor) -> vmoba_tensor:
+    """The same as a ctypes structure, for programs that call the library themselves."""
+    return vmoba_tensor.from_buffer_copy(_desc(t))
 
 
 def _ptr(t):

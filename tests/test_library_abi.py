@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2506_23858_amd import binding as vb
 
@@ -83,6 +84,16 @@ def test_bad_arguments_are_rejected_before_any_launch(L):
     tail_small = [dummy] * 8 + [100, dummy, dummy, dummy, None, None, dummy, 16, None]
     assert L.vmoba_select(*args, 0.25, 0.125, 0, 0, *tail_small) == vb.VMOBA_ERR_WORKSPACE
     assert vb.status_string(vb.VMOBA_ERR_WORKSPACE) == "workspace too small"
+
+
+def test_descriptors_hold_the_tensors_fields():
+    for dtype, code in ((torch.float32, vb.VMOBA_F32), (torch.bfloat16, vb.VMOBA_BF16)):
+        t = torch.empty(2, 5, 3, 4, 64, dtype=dtype)[:, :, 1]
+        d = vb.tensor_desc(t)
+        assert (d.ptr, d.dtype, d.stride_b, d.stride_s, d.stride_h) == (t.data_ptr(), code, 3840, 768, 64)
+        assert bytes(d) == vb._desc(t)
+    with pytest.raises(AssertionError):
+        vb._desc(torch.empty(2, 5, 64, 4).transpose(2, 3))
 
 
 @pytest.mark.parametrize("dtype,D,most", [(vb.VMOBA_F32, 128, 197), (vb.VMOBA_F32, 64, 295), (vb.VMOBA_BF16, 128, 512), (vb.VMOBA_BF16, 64, 512)])
