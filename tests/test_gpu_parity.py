@@ -463,6 +463,30 @@ def test_score_kernel_for_many_blocks_rounds_small_quotients_correctly(blocks, D
         assert np.array_equal(P[h + 1][:, rest].view(np.uint32), (e / den).view(np.uint32)), (x, int((P[h + 1][:, rest] != e / den).sum()))
 
 
+@pytest.mark.parametrize("blocks", [288, 512])
+def test_score_kernel_for_many_blocks_counts_more_than_a_word_holds(blocks):
+    """So many rows of one head for every compute unit that the histogram's words must be emptied on the way (after 2^20 entries of a workgroup): the cut
+    is the one that P itself gives."""
+    D, tau = 64, 0.3
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    rows, tiles = (256, 9) if blocks == 288 else (128, 16)
+    per = -(-(2 ** 20 // (rows * tiles * 32) + 2) * rows * units // blocks)
+    S = per * blocks
+    gen = torch.Generator("cuda").manual_seed(5)
+    Q, K = (torch.randn(1, S, 1, D, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    plan = vb.LayerPlan(1, 1, D, (1, blocks, per), chunk=per, tau=tau, need_bwd=False, q_in_place=True)
+    plan.partition(Q, K, K)
+    plan.select()
+    torch.cuda.synchronize()
+    assert plan.nb == blocks and int(plan.dev_status.item()) == 0
+    P = plan.P.flatten().sort(descending=True)[0]
+    total = P.double().cumsum(0)
+    k = int(plan.k_out.item())
+    assert float(plan.theta.item()) == float(P[k - 1])
+    mass = float(np.float32(tau)) * S                              # (the library sums the values exactly, the reference in float64)
+    assert float(total[k - 2]) < mass + 1e-6 and float(total[k - 1]) >= mass - 1e-6
+
+
 def g_nb(grid, block):
     return math.prod(-(-a // b) for a, b in zip(grid, block))
 
