@@ -103,7 +103,7 @@ int vmoba_layer_kind(int layer);
 int vmoba_partition_dims(const vmoba_grid* g, int64_t* S, int32_t* n_blocks);
 
 /* Bytes of workspace `op` needs for this geometry.  nnz_capacity is per (batch, head).  Pass the attention calls' own n_blocks
- * and nnz_capacity: for float32 they also decide whether the operands are split into 16-bit terms, which takes room. */
+ * and nnz_capacity: for float32 they also decide whether the operands are split into bfloat16 terms, which takes room. */
 size_t vmoba_workspace_bytes(int op, int B, int Hh, int64_t S, int D, int32_t n_blocks,
                              int64_t nnz_capacity, int dtype);
 
@@ -212,7 +212,9 @@ int vmoba_select_static(int B, int Hh, int64_t S, int D, int32_t n_blocks, const
  * Inputs: Q as vmoba_select saw it (block-order Q', or the caller's Q with token ids as query ids), block-order
  * K', V', blk_off, and the lists written by vmoba_select with the same nnz_capacity.  O and LSE are indexed
  * by query id.  Accumulation and soft-max are float32; bfloat16 inputs are multiplied on the
- * matrix cores.
+ * matrix cores.  Larger float32 calls multiply their inputs as three bfloat16 terms each, which hold all their bits;
+ * one value that is not 0 and outside 2^-100 .. 2^26 (infinities and NaNs among them) sends such a call to the slower
+ * float32 instruction.
  *  out_rows  optional int32 [S].  Null: O is written in block order.  Otherwise block-order row q
  *            goes to row out_rows[q] of O: pass the partition's perm and a tensor in the caller's
  *            token order to skip the inverse partition of O.  LSE stays in block order either way.

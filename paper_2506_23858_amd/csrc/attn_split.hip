@@ -21,10 +21,12 @@
 // Work decomposition, orientation and operand plumbing as in the bfloat16 kernels (attn_common.h).
 //
 // Measured on 14 040 tokens x 12 heads x 128 (36 blocks of 390 keys, 785 K kept pairs), float32 instruction -> these: forward
-// 1.45 -> 0.81 ms, dQ 2.3 -> 1.4 ms, dK/dV 3.4 -> 2.2 ms, and 0.27 ms for the seven splitting passes (5.5 TB/s); the whole training step
-// 7.56 -> 4.97 ms.  Matrix pipe: 60 to 65 % of its rate under load; the rest is a quarter of the last runs' keys (dK/dV),
+// 1.45 -> 0.80 ms, dQ 2.3 -> 1.26 ms, dK/dV 3.4 -> 1.86 ms, and 0.27 ms for the seven splitting passes (5.5 TB/s); the whole training step
+// 7.56 -> 4.8 ms.  Matrix pipe: 60 to 65 % of its rate under load; the rest is a quarter of the last runs' keys (dK/dV),
 // the start of a tile with one workgroup per compute unit (dQ), and the soft-max between the products (forward).  Two sums in
 // turn for the six products of a k-step instead of one: no faster, spills in the forward kernel, and larger errors in dK and dV.
+// Two float16 terms, scaled by a power of two per head, and three products take 3.0 ms for the step, but single rows and channels far below a head's
+// largest, and weights far below a key's largest, do not fit five bits of exponent beside it: dV and dK of such a key were wrong by up to 35 %.
 #include "attn_common.h"
 
 namespace {
